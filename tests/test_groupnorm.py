@@ -193,3 +193,54 @@ def test_groupnorm_large_means_do_not_cancel(offset):
     # one ulp of them, relative to a spread of order one
     err = np.abs(y.cpu().double().numpy() - ref).max()
     assert err <= 4 * abs(offset) * 2.0 ** -24 + 1e-5, err
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [
+    # clip_len, n_clips, P, C, groups, dtype
+    (1, 50, 1, 64, 4, "bf16"),        # fewer bites of rows than clips: one workgroup reads, not fifty
+    (1, 300, 7, 512, 8, "f32"),       # more bites than the statistics pass has workgroups, last one partial
+    (16, 5, 401, 320, 32, "bf16"),    # 20.5 MB: plain loads and stores, last bite partial
+    (16, 8, 401, 328, 41, "bf16"),    # 33.7 MB: streaming loads and stores, a lane is a group
+    (7, 9, 211, 640, 32, "f32"),      # 34.0 MB
+])
+def test_groupnorm_walks_cover_every_row(shape):
+    """The passes walk the whole video in interleaved bites of rows (the second one backwards):
+    sizes around the changes of their launch shape, with affine parameters, held to the bars of
+    test_groupnorm_matches_oracle."""
+    clip_len, n_clips, P, C, groups, dtype = shape
+    print(f"[case] groupnorm walk {shape}", flush=True)
+    F = clip_len * n_clips
+    x = synth.make_tensor(F, P, C, 15, "iid", dtype)
+    x = (x.float() + 0.01 * torch.arange(F, dtype=torch.float32)[:, None, None]).to(x.dtype).to(DEV)
+    gen = torch.Generator().manual_seed(16)
+    gamma, beta = torch.randn(C, generator=gen).to(DEV), torch.randn(C, generator=gen).to(DEV)
+    ref, mean, var = oracle.groupnorm(x.cpu().double().numpy(), clip_len, n_clips, groups, eps=1e-5,
+                                      gamma=gamma.cpu().double().numpy(),
+                                      beta=beta.cpu().double().numpy())
+    for in_place in (False, True):
+        y, stats = run_gn(x.clone(), clip_len, n_clips, groups, gamma, beta, in_place=in_place)
+        st = stats.cpu().double().numpy()
+        np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6)
+        np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
+        U.assert_parity(y, ref, "f32_strict" if dtype == "f32" else "bf16", what=f"walk {shape}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_groupnorm_non_finite_values_stay_in_their_group(dtype):
+    clip_len, n_clips, P, C, groups = 4, 3, 11, 80, 4   # 20 channels per group: lanes straddle
+    x = synth.make_tensor(12, P, C, 21, "iid", dtype).to(DEV)
+    clean, _ = run_gn(x.clone(), clip_len, n_clips, groups)
+    for bad in (float("nan"), float("inf")):
+        z = x.clone()
+        z[5, 3, 27] = bad                               # group 1
+        y, stats = run_gn(z, clip_len, n_clips, groups)
+        assert torch.isnan(stats[groups + 1]) and not torch.isnan(stats[groups + 0])
+        assert torch.isnan(y[:, :, 20:40]).all()
+        keep = [c for c in range(C) if not 20 <= c < 40]
+        assert torch.equal(y[:, :, keep], clean[:, :, keep])
+    # a constant group: variance exactly zero
+    y, stats = run_gn(torch.full_like(x, 3.5), clip_len, n_clips, groups, eps=0.25)
+    assert torch.equal(stats, torch.tensor([3.5] * groups + [2.0] * groups, device=DEV))
+    assert not y.any()
