@@ -251,13 +251,15 @@ typedef struct dsattn_conv_desc {
 
 /* The launch the library would make for this shape (host only; for tests and benchmarks). */
 typedef struct dsattn_conv_info {
-    int32_t kernel;        /* 0 = generic vector-ALU kernel, 1 = bf16 MFMA implicit-GEMM kernel */
+    int32_t kernel;        /* 1 = bf16 MFMA implicit-GEMM kernels; 0 = the others: fp32 tensors on the
+                              fp32 matrix instructions (tile_m > 0), or the generic vector-ALU kernel */
     int32_t tile_m;        /* output rows (frame, position) per workgroup, 0 for the generic kernel */
     int32_t tile_n;        /* output channels per workgroup */
     int32_t tile_k;        /* contraction depth per step */
-    int32_t n_blocks;      /* output tiles, counted in units the 8 XCDs share evenly (the matrix-core
-                              kernel is launched with at most one persistent workgroup per compute
-                              unit, which walk them); workgroups launched for the generic kernel */
+    int32_t n_blocks;      /* output tiles, counted in units the 8 XCDs share evenly (the kernels with
+                              tiles of 256 rows are launched with at most one persistent workgroup
+                              per compute unit, which walk them; the others with one workgroup per
+                              tile); workgroups launched for the generic kernel */
     int32_t block_threads;
     int32_t lds_bytes;
     int32_t reserved;
@@ -273,7 +275,8 @@ int dsattn_temporal_conv_info(const dsattn_conv_desc *desc, dsattn_conv_info *in
  *   bias : device, [c_out] fp32, or NULL for none
  *   Y    : device, [F, P, c_out] of out_dtype, 16-byte aligned; must not overlap X
  * Runs on the current device; enqueues one kernel on `stream`; allocates nothing.  bf16 inputs
- * with c_in a multiple of 8 run on the matrix cores, everything else on a plain vector kernel.
+ * with c_in a multiple of 8 and fp32 inputs with c_in a multiple of 4 run on the matrix cores (fp32 on
+ * the fp32 instructions: nothing is rounded to 16 bits), everything else on a plain vector kernel.
  * Errors: EINVAL (bad shape, null or misaligned pointer, overlap), EHIP.
  */
 int dsattn_temporal_conv(const dsattn_conv_desc *desc, const void *X, const void *W,

@@ -25,6 +25,8 @@
 // of stages (the next tile's first stage is loading while the finished tile is stored).  An XCD
 // walks a contiguous run of tiles (all column tiles of a few neighbouring row tiles): the W
 // slabs, and the X rows shared between taps and column tiles, are then served by that XCD's L2.
+// Problems that do not fill the chip with such tiles, and fp32 tensors, run on the kernels of
+// tconv_tile.h; conv_pick() says which.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -514,7 +516,15 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
     }
 }
 
-// Plain vector kernel for every other case (fp32 tensors, c_in not a multiple of 8): one
+}  // namespace
+}  // namespace dsattn
+
+#include "tconv_tile.h"
+
+namespace dsattn {
+namespace {
+
+// Plain vector kernel for every other case (rows that are not whole 16-byte pieces): one
 // thread per output element, output channel fastest.
 template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void tconv_generic_kernel(const Tin *X, const Tin *W,
@@ -537,22 +547,47 @@ __global__ __launch_bounds__(256) void tconv_generic_kernel(const Tin *X, const 
 }
 
 struct ConvVariant {
-    int MI, NJ, WVM, WVN;  // tile = (32 MI WVM) x (32 NJ WVN), WVM x WVN wavefronts
+    int bm, bn, waves;     // tile, wavefronts per workgroup
+    int lds;               // bytes per workgroup
+    int resident;          // persistent workgroups per compute unit; 0: one workgroup per tile
+    bool f32;              // operands
     const void *fn[2];     // bf16 / fp32 output
-    int bm() const { return 32 * MI * WVM; }
-    int bn() const { return 32 * NJ * WVN; }
-    int waves() const { return WVM * WVN; }
 };
-#define DSATTN_CONV_VARIANT(MI, NJ, WVM, WVN)                                    \
-    {MI, NJ, WVM, WVN,                                                           \
-     {(const void *)&tconv_mfma_kernel<MI, NJ, WVM, WVN, false>,                 \
+
+// the two ring slots with the staging gap between them; behind them the bias of each
+// wavefront's 32 NJ channels
+constexpr int conv_lds_bytes(int bm, int bn, int nj, int waves)
+{
+    return kSlots * (bm + bn) * kRow + stage_gap((bm + bn) * kRow, nj, waves) +
+           waves * 32 * nj * (int)sizeof(float);
+}
+
+#define DSATTN_CONV_VARIANT(MI, NJ, WVM, WVN)                                                    \
+    {32 * MI * WVM, 32 * NJ * WVN, WVM * WVN,                                                    \
+     conv_lds_bytes(32 * MI * WVM, 32 * NJ * WVN, NJ, WVM * WVN), 1, false,                      \
+     {(const void *)&tconv_mfma_kernel<MI, NJ, WVM, WVN, false>,                                 \
       (const void *)&tconv_mfma_kernel<MI, NJ, WVM, WVN, true>}}
-// Eight wavefronts (two per SIMD) throughout: one wavefront per SIMD cannot keep the matrix cores
-// busy with 16x16x32 instructions (measured: 1.46 against 2.4 PFLOP/s on idle data).
+#define DSATTN_TILE_VARIANT(MB, NB, WVM, WVN)                                                     \
+    {16 * MB * WVM, 16 * NB * WVN, WVM * WVN, 2 * (16 * MB * WVM + 16 * NB * WVN) * kRow, 0, false, \
+     {(const void *)&tconv_tile_kernel<__bf16, MB, NB, WVM, WVN, false>,                         \
+      (const void *)&tconv_tile_kernel<__bf16, MB, NB, WVM, WVN, true>}}
+#define DSATTN_PIPE_VARIANT(MB, NB, WVM, WVN, S)                                                  \
+    {32 * MB * WVM, 32 * NB * WVN, WVM * WVN, S * (32 * MB * WVM + 32 * NB * WVN) * kRow, 0, false, \
+     {(const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, false>,                              \
+      (const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, true>}}
+// Eight wavefronts (two per SIMD) in the persistent kernels: one wavefront per SIMD cannot keep the
+// matrix cores busy with 16x16x32 instructions (measured: 1.46 against 2.4 PFLOP/s on idle data).
 const ConvVariant kConvVariants[] = {
-    DSATTN_CONV_VARIANT(4, 2, 2, 4),  // 256 x 256
-    DSATTN_CONV_VARIANT(2, 5, 4, 2),  // 256 x 320
+    DSATTN_CONV_VARIANT(4, 2, 2, 4),     // 256 x 256
+    DSATTN_CONV_VARIANT(2, 5, 4, 2),     // 256 x 320
+    DSATTN_TILE_VARIANT(4, 5, 2, 2),     // 128 x 160
+    DSATTN_TILE_VARIANT(2, 4, 4, 2),     // 128 x 128, eight wavefronts
+    DSATTN_PIPE_VARIANT(2, 2, 2, 2, 4),  // 128 x 128, pipelined
+    DSATTN_TILE_VARIANT(2, 2, 2, 2),     // 64 x 64
+    {64, 64, 4, 2 * (64 + 64) * kRow, 0, true,
+     {nullptr, (const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true>}},
 };
+enum { kBig256, kBig320, kTile160, kTile128, kPipe128, kTile64, kTileF32 };  // positions in the table
 
 int conv_validate(const dsattn_conv_desc *d, const char *who)
 {
@@ -576,42 +611,80 @@ int conv_validate(const dsattn_conv_desc *d, const char *who)
     return DSATTN_OK;
 }
 
-// Tile shape: the variant that wastes the fewest output columns, then the fewest output rows.
+int64_t conv_tiles(const ConvVariant &v, int64_t M, int64_t c_out, int groups)
+{
+    return ((M + v.bm - 1) / v.bm) * ((c_out + v.bn - 1) / v.bn) * groups;
+}
+
+// Estimated time in us of a bf16 problem that a round of 256 x 320 tiles does not fill: a start, and
+// per stage what the fullest compute unit takes.  Fitted to sweeps over 256 to 40,960 rows, 320, 640
+// and 1,280 channels, one and three weight sets (measured us at 20 stages, i.e. 1,280 channels):
+//   rows x sets   256 x 320  256 x 256  128 x 160  128 x 128  pipelined  64 x 64
+//     256 x 1       33.0       28.6       18.1       14.2       12.8      < 11.6
+//   2,560 x 1       35.8       32.3       19.8       17.8       14.9       17.2
+//   5,000 x 1       36.1       32.5       27.1       22.7       26.6       28.3
+//   2,560 x 3       37.6       33.9       29.4       37.2       40.0       43.6
+//   5,000 x 3       42.7       62.6       50.9       56.1       67.1       79.2
+double conv_estimate(int variant, int64_t tiles, int64_t stages)
+{
+    const double r1 = (double)((tiles + 255) / 256), r2 = (double)((tiles + 511) / 512);
+    double per_stage = 0.0;
+    switch (variant) {
+    case kBig256: per_stage = 1.45 * r1; break;
+    case kBig320: per_stage = 1.6 * r1; break;
+    case kTile160: per_stage = 0.8 + 0.5 * (r1 - 1.0); break;
+    case kTile128: per_stage = 0.92 * r2; break;
+    case kPipe128: per_stage = 0.55 * r1; break;
+    default: per_stage = 7.5e-4 * (double)std::max<int64_t>(tiles, 350); break;
+    }
+    return 4.0 + per_stage * (double)stages;
+}
+
+// The kernel of a problem; null: the vector kernel.
 const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 1)
 {
-    if (d.io_dtype != DSATTN_BF16 || d.c_in % 8 != 0 || (d.flags & DSATTN_FLAG_FORCE_GENERIC))
-        return nullptr;
+    const bool f32 = d.io_dtype == DSATTN_F32;
+    const int64_t es = f32 ? 4 : 2;
+    // rows are whole 16-byte chunks
+    if (d.c_in * es % 16 != 0 || (d.flags & DSATTN_FLAG_FORCE_GENERIC)) return nullptr;
     // the kernel addresses W, and the rows of X one tile can touch, with 32-bit byte offsets
     const int64_t taps = 2 * (int64_t)d.reach + 1;
-    if (taps * d.c_out * d.c_in * 2 >= ((int64_t)1 << 31)) return nullptr;
-    if ((320 + 2 * (int64_t)d.reach * d.spatial) * d.c_in * 2 >= ((int64_t)1 << 31)) return nullptr;
-    // least multiplied-out area (padding of the last row and column tiles), then the larger
-    // tile (fewer epilogues)
-    const ConvVariant *best = nullptr;
-    double best_area = 0;
-    int64_t best_tiles = 0;
-    for (const ConvVariant &v : kConvVariants) {
-        const int64_t bm = v.bm(), bn = v.bn();
-        const int64_t tm = (M + bm - 1) / bm, tn = (d.c_out + bn - 1) / bn;
-        if (tm * tn * groups > 0x7fffffffLL / 2) continue;
-        const double area = (double)(tm * bm) * (double)(tn * bn);
-        const int64_t tiles = tm * tn;
-        const bool better = !best || area < best_area || (area == best_area && tiles < best_tiles);
-        if (better) {
-            best = &v;
+    if (taps * d.c_out * d.c_in * es >= ((int64_t)1 << 31)) return nullptr;
+    if ((320 + 2 * (int64_t)d.reach * d.spatial) * d.c_in * es >= ((int64_t)1 << 31)) return nullptr;
+    constexpr int64_t kMaxTiles = 0x7fffffffLL / 2;
+    if (f32) {
+        const ConvVariant &v = kConvVariants[kTileF32];
+        return conv_tiles(v, M, d.c_out, groups) <= kMaxTiles ? &v : nullptr;
+    }
+    // Large problems: of the persistent kernels the one with the least multiplied-out area (padding
+    // of the last row and column tiles), then the larger tile (fewer epilogues).
+    int best = -1;
+    int64_t best_area = 0, best_tiles = 0;
+    for (int k : {kBig256, kBig320}) {
+        const ConvVariant &v = kConvVariants[k];
+        const int64_t tiles = conv_tiles(v, M, d.c_out, groups);
+        if (tiles > kMaxTiles) continue;
+        const int64_t area = tiles * v.bm * v.bn;
+        if (best < 0 || area < best_area || (area == best_area && tiles < best_tiles)) {
+            best = k;
             best_area = area;
             best_tiles = tiles;
         }
     }
-    return best;
-}
-
-// the two ring slots with the staging gap between them; behind them the bias of each
-// wavefront's 32 NJ channels
-int conv_lds_bytes(const ConvVariant &v)
-{
-    const int buf = (v.bm() + v.bn()) * kRow;
-    return kSlots * buf + stage_gap(buf, v.NJ, v.waves()) + v.waves() * 32 * v.NJ * (int)sizeof(float);
+    if (best < 0) return nullptr;
+    // Less than one round of them leaves compute units idle: whichever is estimated fastest.
+    if (best_tiles < 256) {
+        const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
+        double best_us = 1e300;
+        for (int k = kBig256; k <= kTile64; ++k) {
+            const double us = conv_estimate(k, conv_tiles(kConvVariants[k], M, d.c_out, groups), stages);
+            if (us < best_us) {
+                best_us = us;
+                best = k;
+            }
+        }
+    }
+    return &kConvVariants[best];
 }
 
 // Compute units of the current device (one persistent workgroup is launched per unit at most).
@@ -659,22 +732,23 @@ hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *
 {
     hipError_t e = hipSuccess;
     if (v) {
-        const void *fn = v->fn[d.out_dtype == DSATTN_F32 ? 1 : 0];
-        const int lds = conv_lds_bytes(*v);
-        // The default cap on dynamic LDS is 64 KB: raised once per kernel and device.  The launch
-        // path only reads a flag (no lock); two threads that both find it clear both set the
-        // attribute, which is harmless.
-        static std::atomic<uint64_t> prepared[sizeof(kConvVariants) / sizeof(kConvVariants[0])][2];
+        // The default cap on dynamic LDS is 64 KB: raised for every variant at the first call on a
+        // device, so that no later call has anything to prepare.  The launch path only reads a flag
+        // (no lock); two threads that both find it clear both set the attributes, which is harmless.
+        static std::atomic<uint64_t> prepared;
         int dev = 0;
         e = hipGetDevice(&dev);  // a thread-local read in the runtime
         if (e != hipSuccess) return e;
-        std::atomic<uint64_t> *mask =
-            dev < 64 ? &prepared[v - kConvVariants][d.out_dtype == DSATTN_F32 ? 1 : 0] : nullptr;
-        if (!mask || !(mask->load(std::memory_order_acquire) >> dev & 1)) {
-            e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            if (mask) mask->fetch_or((uint64_t)1 << dev, std::memory_order_release);
+        if (dev >= 64 || !(prepared.load(std::memory_order_acquire) >> dev & 1)) {
+            for (const ConvVariant &c : kConvVariants)
+                for (const void *f : c.fn) {
+                    if (f) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
+                    if (e != hipSuccess) return e;
+                }
+            if (dev < 64) prepared.fetch_or((uint64_t)1 << dev, std::memory_order_release);
         }
+        const void *fn = v->fn[d.out_dtype == DSATTN_F32 ? 1 : 0];
+        const int64_t es = v->f32 ? 4 : 2;
         ConvArgs a;
         a.X = X;
         for (int g = 0; g < kMaxGroups; ++g) {
@@ -688,19 +762,21 @@ hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *
         a.Cin = d.c_in;
         a.Cout = d.c_out;
         a.n = d.reach;
-        a.KC = (d.c_in + kBK - 1) / kBK;
+        a.KC = (int32_t)((d.c_in * es + kRow - 1) / kRow);
         a.KS = (2 * d.reach + 1) * a.KC;
-        const int64_t bm = v->bm(), bn = v->bn();
+        const int64_t bm = v->bm, bn = v->bn;
         a.tiles_n = (int32_t)((d.c_out + bn - 1) / bn);
         a.tiles_m = (int32_t)((M + bm - 1) / bm);
         a.tiles = a.tiles_m * a.tiles_n * groups;
         a.per_xcd = (a.tiles + kXcds - 1) / kXcds;
-        a.w_bytes = (int32_t)((2 * (int64_t)d.reach + 1) * d.c_out * d.c_in * 2);
+        a.w_bytes = (int32_t)((2 * (int64_t)d.reach + 1) * d.c_out * d.c_in * es);
         void *params[] = {&a};
         // persistent workgroups: one per compute unit at most, the same number on every XCD
-        const int per_xcd_wg = std::min(a.per_xcd, (conv_compute_units(dev) + kXcds - 1) / kXcds);
-        return hipLaunchKernel(fn, dim3((unsigned)(per_xcd_wg * kXcds)), dim3(64 * v->waves()), params,
-                               (size_t)lds, st);
+        const int per_xcd_wg =
+            v->resident ? std::min(a.per_xcd, v->resident * (conv_compute_units(dev) + kXcds - 1) / kXcds)
+                        : a.per_xcd;
+        return hipLaunchKernel(fn, dim3((unsigned)(per_xcd_wg * kXcds)), dim3(64 * v->waves), params,
+                               (size_t)v->lds, st);
     }
     const int64_t total = M * d.c_out;
     const dim3 grid((unsigned)((total + 255) / 256)), block(256);
@@ -750,15 +826,15 @@ int dsattn_temporal_conv_info(const dsattn_conv_desc *desc, dsattn_conv_info *in
     *info = dsattn_conv_info{};
     const ConvVariant *v = conv_pick(d, M);
     if (v) {
-        const int64_t bm = v->bm(), bn = v->bn();
+        const int64_t bm = v->bm, bn = v->bn;
         const int64_t tiles = ((M + bm - 1) / bm) * ((d.c_out + bn - 1) / bn);
-        info->kernel = 1;
+        info->kernel = v->f32 ? 0 : 1;
         info->tile_m = (int32_t)bm;
         info->tile_n = (int32_t)bn;
-        info->tile_k = kBK;
+        info->tile_k = v->f32 ? kBK / 2 : kBK;
         info->n_blocks = (int32_t)(((tiles + kXcds - 1) / kXcds) * kXcds);
-        info->block_threads = 64 * v->waves();
-        info->lds_bytes = conv_lds_bytes(*v);
+        info->block_threads = 64 * v->waves;
+        info->lds_bytes = v->lds;
     } else {
         info->kernel = 0;
         info->tile_n = 1;
@@ -810,15 +886,15 @@ int dsattn_linear_info(const dsattn_linear_desc *desc, dsattn_conv_info *info)
     const ConvVariant *v = conv_pick(d, M, desc->n_out);
     info->block_threads = 256;
     if (v) {
-        info->block_threads = 64 * v->waves();
-        const int64_t bm = v->bm(), bn = v->bn();
+        info->block_threads = 64 * v->waves;
+        const int64_t bm = v->bm, bn = v->bn;
         const int64_t tiles = ((M + bm - 1) / bm) * ((d.c_out + bn - 1) / bn) * desc->n_out;
-        info->kernel = 1;
+        info->kernel = v->f32 ? 0 : 1;
         info->tile_m = (int32_t)bm;
         info->tile_n = (int32_t)bn;
-        info->tile_k = kBK;
+        info->tile_k = v->f32 ? kBK / 2 : kBK;
         info->n_blocks = (int32_t)(((tiles + kXcds - 1) / kXcds) * kXcds);
-        info->lds_bytes = conv_lds_bytes(*v);
+        info->lds_bytes = v->lds;
     } else {
         info->tile_n = 1;
         info->tile_k = 1;

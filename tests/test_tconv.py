@@ -487,3 +487,52 @@ def test_conv_and_linear_in_hip_graph_replays():
         assert torch.equal(y, y_eager), f"replay {rep}: convolution differs from the eager result"
         for t, e in zip(ps, p_eager):
             assert torch.equal(t, e), f"replay {rep}: projection differs from the eager result"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,dtype,tile", [
+    # one to four weight sets, row, column and channel tails of every tile shape the dispatch picks
+    (2487, 1288, 1272, 1, "bf16", (128, 128, 256)),   # one round: the pipelined kernel, 21 stages
+    (2501, 1280, 1276, 3, "bf16", (128, 160, 256)),   # rows of c_out that are not whole 16-byte pieces
+    (5003, 648, 632, 2, "bf16", (128, 128, 512)),
+    (127, 136, 66, 4, "bf16", (64, 64, 256)),
+    (65799, 72, 250, 1, "bf16", (256, 256, 512)),     # more than one round of the large tile
+    (65799, 64, 312, 1, "bf16", (256, 320, 512)),
+    (1, 8, 1, 1, "bf16", (64, 64, 256)),              # a single output
+    (1, 4, 1, 1, "f32", (64, 64, 256)),
+    (65, 36, 70, 3, "f32", (64, 64, 256)),            # c_in not a whole stage, c_out % 4 != 0
+    (193, 644, 128, 1, "f32", (64, 64, 256)),
+])
+def test_linear_tile_shapes_match_oracle(rows, c_in, c_out, n_out, dtype, tile):
+    for out_dtype in (("f32", "bf16") if dtype == "bf16" else ("f32",)):
+        info = linear_case(rows, c_in, c_out, n_out, dtype=dtype, out_dtype=out_dtype)
+        assert (info["tile_m"], info["tile_n"], info["block_threads"]) == tile
+        assert info["kernel"] == (1 if dtype == "bf16" else 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,dtype", [
+    # clip_len, n_clips, P, c_in, c_out, n: rows before the first and after the last frame
+    ((16, 2, 79, 1280, 1280, 1), "bf16"),    # pipelined tile, 60 stages
+    ((16, 3, 7, 72, 60, 2), "bf16"),         # a tile touches every tap's shift
+    ((1, 2, 3, 16, 24, 1), "bf16"),          # two frames, three taps: no interior frame
+    ((16, 3, 7, 68, 60, 2), "f32"),
+    ((16, 2, 41, 320, 130, 1), "f32"),
+    ((3, 1, 2, 4, 4, 3), "f32"),             # the taps reach past both ends from every frame
+])
+def test_conv_small_tiles_match_oracle(shape, dtype):
+    conv_case(*shape, dtype=dtype)
+
+
+@pytest.mark.gpu
+def test_conv_fp32_keeps_fp32_precision():
+    """fp32 tensors stay fp32 throughout: against the oracle the error is that of fp32 sums, three
+    orders below what rounding either operand to bf16 would leave.  Bound: c_in products of unit
+    variance scaled by 1 / sqrt(c_in), each rounding at most 2^-24 of a partial sum below 4, added up
+    as a random walk (factor sqrt(1280) < 40)."""
+    x = synth.make_tensor(300, 1, 1280, 41, "iid", "f32").to(DEV).reshape(300, 1280)
+    w = synth.make_conv_weights(1, 320, 1280, 42, "f32")[0].reshape(320, 1280).to(DEV)
+    y = torch.empty(300, 320, device=DEV)
+    B.dsattn_linear(300, 1280, 320, x, [w], [y], io_dtype=B.DSATTN_F32)
+    ref = oracle.linear(x.cpu().double().numpy(), w.cpu().double().numpy())
+    assert np.abs(y.cpu().double().numpy() - ref).max() <= 40 * 4 * 2.0 ** -24
