@@ -86,13 +86,14 @@ typedef struct dsattn_plan_s dsattn_plan_t; /* opaque; made by dsattn_plan() */
 
 /* What the launch planner decided for dsattn_forward (read-only report). */
 typedef struct dsattn_launch_info {
-    int32_t kernel;          /* 0 = generic vector-ALU kernel, 1 = bf16 MFMA streaming kernel */
+    int32_t kernel;          /* 1 = bf16 MFMA streaming kernel; 0 = any other: 16-query tiles on the
+                                matrix cores (block_threads 256) or the generic vector-ALU kernel */
     int32_t heads_per_wave;  /* MFMA kernel: heads handled by one wavefront */
     int32_t local_tiles;     /* MFMA kernel: 16-key tiles covering the local scope of a query tile */
     int32_t global_tiles;    /* MFMA kernel: 16-key tiles covering the global set */
     int32_t clips_per_task;  /* consecutive 16-frame query tiles walked by one wavefront (whole clips
                                 when clip_len is 16; the generic kernel: 1 clip) */
-    int32_t n_tasks;         /* wavefront tasks = grid size */
+    int32_t n_tasks;         /* wavefront tasks */
     int32_t block_threads;   /* threads per workgroup */
     int32_t lds_bytes;       /* LDS bytes per workgroup */
     int64_t algorithmic_bytes; /* Q + K + V read once, O written once */

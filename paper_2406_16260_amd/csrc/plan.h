@@ -30,6 +30,8 @@ struct dsattn_plan_s {
     // resolved once by the planner for the matrix-core kernel, so that a launch searches nothing
     const void *mfma_fn = nullptr;  // the variant's kernel
     uint64_t gdup = 0;              // bit j: global entry j (< 64) repeats an earlier entry
+
+    const void *tile_fn = nullptr;  // the tile kernel, where the streaming kernel has no variant
 };
 
 namespace dsattn {
@@ -47,6 +49,11 @@ bool generic_supported(const dsattn_plan_t &pl);
 hipError_t generic_prepare(const dsattn_plan_t &pl);  // once per plan, plan's device current
 hipError_t launch_generic(const dsattn_plan_t &pl, const void *Q, const void *K, const void *V,
                           void *O, bool ctx_mode, hipStream_t st);
+
+// Matrix-core attention on 16-query tiles, for what the streaming kernel does not take.
+void tile_attn_plan(dsattn_plan_t &pl);  // sets tile_fn and completes pl.launch if a kernel exists
+hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *K, const void *V,
+                            void *O, bool ctx_mode, hipStream_t st);
 
 // bf16 MFMA streaming kernel. `fill` reports whether a variant exists for the plan's
 // shape; when it does, it completes pl.launch.

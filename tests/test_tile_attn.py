@@ -1,0 +1,138 @@
+"""The matrix-core kernels behind dsattn_forward for what the streaming kernel does not take (fp32
+tensors, clips that are not whole 16-frame tiles, wide local scopes, long global lists): parity with
+the oracle and agreement with the generic kernel, which the flag still selects.
+
+Bars: nothing is rounded to 16 bits on the way (bf16 inputs are exact, weights keep 24 bits), so fp32
+results, from either input type, are held to the fp32 bar of 1e-5; the observed maximum is 1e-6."""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as U
+from paper_2406_16260_amd import binding as B
+from paper_2406_16260_amd import synth
+
+DEV = "cuda:0"
+pytestmark = pytest.mark.gpu
+
+
+def make(F, P, C, dtype, seed=17, gen="iid"):
+    return tuple(synth.make_tensor(F, P, C, seed + t, gen, dtype).to(DEV) for t in range(3))
+
+
+CASES = [
+    # clip_len, n_clips, w, P, h, D, G, options
+    (24, 4, 3, 5, 2, 64, 12, {}),                        # two query tiles, the second half empty
+    (1, 9, 1, 4, 2, 112, 3, {}),                         # a single query per tile
+    (7, 5, 3, 9, 3, 72, 4, {}),                          # D not a multiple of 16
+    (33, 3, 0, 2, 1, 40, 0, {}),                         # no context at all: 33 keys, one in the last tile
+    (16, 1, 0, 3, 1, 8, 0, {}),                          # exactly one key tile (bf16: the streaming kernel's job
+                                                         # at other head sizes)
+    (15, 2, 1, 3, 1, 16, 1, {}),                         # 17 keys
+    (48, 2, 20, 2, 2, 160, 200, {}),                     # 68 to 268 keys, the largest head
+    (14, 5, 6, 3, 2, 128, 20, {"window": 4}),
+    (24, 4, 5, 3, 2, 80, 20, {"window": 0}),             # every local key hidden but one
+    (24, 4, 2, 3, 2, 48, 30, {"dedup": True}),
+    (24, 4, 2, 3, 2, 144, 30, {"dedup": True, "window": 5}),
+    (20, 3, 2, 3, 5, 96, 16, {"bias_global": 2.302585}),
+    (20, 3, 2, 3, 3, 32, 16, {"bias_local": 50.0, "bias_global": -50.0}),
+    (12, 3, 2, 2, 1, 24, 7, {"bias_global": 3e38, "bias_local": -3e38}),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES)
+def test_tile_kernels_match_oracle_and_generic_kernel(case, dtype):
+    clip_len, n_clips, w, P, h, D, G, opts = case
+    print(f"[case] tile {case} {dtype}", flush=True)
+    F = clip_len * n_clips
+    g = np.random.default_rng(5).integers(0, F, size=G).tolist()     # unsorted, with repeats
+    q, k, v = make(F, P, h * D, dtype)
+    opts = dict(opts)
+    dedup = opts.pop("dedup", False)
+    flags = B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0
+    ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=dedup, **opts)
+    for out in (["f32"] if dtype == "f32" else ["f32", "bf16"]):
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, flags=flags, **opts)
+        assert info["kernel"] == 0
+        U.assert_parity(o, ref, "f32_strict" if out == "f32" else "bf16", what=str(case))
+        og, _ = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out,
+                                  flags=flags | B.DSATTN_FLAG_FORCE_GENERIC, **opts)
+        # both within 1e-5 of the same numbers, then at most one rounding apart in bf16
+        bar = 2e-5 if out == "f32" else 2e-5 + 2 * U.bf16_half_ulp(ref).max()
+        assert float((o.double() - og.double()).abs().max()) <= bar
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_peaked_softmax_with_growing_maximum(dtype):
+    """Scores that grow along the list (the running maximum moves at every key tile) and scores that
+    shrink (it never moves again), 100 in size: the accumulated sums are rescaled, not lost."""
+    clip_len, n_clips, P, D = 40, 2, 3, 64
+    F = clip_len * n_clips
+    for sign in (1.0, -1.0):
+        q, k, v = make(F, P, D, dtype)
+        ramp = sign * torch.linspace(0.0, 12.0, F, device=DEV)[:, None, None]
+        q = (q * 0.1 + 1.0).to(q.dtype)
+        k = (k.float() * 0.1 + ramp).to(k.dtype)
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, 6, 1, [79, 0, 40])
+        o, _ = U.library_forward(q, k, v, clip_len, n_clips, 6, 1, [79, 0, 40], out_dtype="f32")
+        # fp32 scores of size 100: an absolute error of up to 64 products' roundings at that size
+        # (2^-24 * 100 each, as a random walk) enters the weights relatively
+        bar = 1e-5 + 8 * 100 * 2.0 ** -24 * float(v.float().abs().max())
+        assert float(np.abs(o.double().cpu().numpy() - ref).max()) <= bar
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_materialised_context_gives_the_same(dtype):
+    for (clip_len, n_clips, w, P, h, D, G, kw) in [(24, 3, 5, 3, 2, 40, 10, {}),
+                                                   (20, 3, 2, 3, 1, 160, 33, {"window": 3})]:
+        F = clip_len * n_clips
+        g = np.random.default_rng(6).integers(0, F, size=G).tolist()
+        q, k, v = make(F, P, h * D, dtype)
+        plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, io_dtype=U.dt_code(dtype), **kw)
+        o1, o2 = torch.empty_like(q), torch.empty_like(q)
+        B.dsattn_forward(plan, q, k, v, o1)
+        ctx = [torch.full((n_clips, plan.lk_max, P, h * D), float("nan"), dtype=q.dtype, device=DEV)
+               for _ in range(2)]
+        B.dsattn_gather_context(plan, k, v, *ctx)
+        B.dsattn_forward_ctx(plan, q, *ctx, o2)
+        torch.cuda.synchronize()
+        assert torch.equal(o1, o2)
+        plan.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_non_finite_values_go_where_the_generic_kernel_puts_them(dtype):
+    clip_len, n_clips, w, P, h, D, g = 24, 3, 2, 3, 2, 40, [5, 70, 33]
+    F = clip_len * n_clips
+    for which, frame, bad in [("v", 10, float("inf")), ("v", 71, float("-inf")), ("v", 33, float("nan")),
+                              ("k", 10, float("inf")), ("k", 70, float("nan")), ("q", 30, float("inf")),
+                              ("q", 30, float("nan")), ("k", 12, float("-inf"))]:
+        t = dict(zip("qkv", make(F, P, h * D, dtype)))
+        t[which][frame, 1, 45] = bad                 # position 1, head 1, channel 5
+        o, _ = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32")
+        og, _ = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32",
+                                  flags=B.DSATTN_FLAG_FORCE_GENERIC)
+        finite = torch.isfinite(og)
+        assert torch.equal(torch.isfinite(o), finite), (which, frame, bad)
+        assert torch.equal(torch.isnan(o), torch.isnan(og)) and torch.equal(o == float("inf"), og == float("inf"))
+        assert float((o - og)[finite].abs().max()) <= 2e-5
+
+
+def test_tile_kernel_in_hip_graph_replays():
+    clip_len, n_clips, w, P, h, D, g = 24, 3, 2, 5, 2, 64, [5, 70, 33]
+    q, k, v = make(72, P, h * D, "bf16")
+    plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g)
+    want, o = torch.empty_like(q), torch.zeros_like(q)
+    B.dsattn_forward(plan, q, k, v, want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.dsattn_forward(plan, q, k, v, o)
+    for _ in range(3):
+        o.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want)
+    plan.close()
