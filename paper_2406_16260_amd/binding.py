@@ -203,6 +203,56 @@ def _stream(stream):
     return int(stream)
 
 
+# The path of an ordinary call, in which every argument is a tensor as it should be: one look at each
+# (element type, count, device, contiguity, in that order) yields its address.  Anything else (a raw
+# address, an array, None, a tensor that is to be refused) gives None and the call takes the general
+# checks below, which accept what may be accepted and say what is wrong with the rest.  Nothing is
+# remembered about a tensor from one call to the next.
+_torch = None
+_DTYPES = {}
+
+
+def _setup_torch():
+    global _torch
+    import torch
+    _DTYPES.update({DSATTN_F32: torch.float32, DSATTN_BF16: torch.bfloat16})
+    _torch = torch
+
+
+def _addr(t, numel, dtype_code, dev):
+    if _torch is None:
+        _setup_torch()
+    if (isinstance(t, _torch.Tensor) and t.dtype is _DTYPES.get(dtype_code) and t.numel() == numel
+            and t.get_device() == dev and t.is_contiguous()):
+        return t.data_ptr()
+    return None
+
+
+def _addr_or_null(t, numel, dtype_code, dev):
+    """For optional tensors: (address or None, whether that is all right)."""
+    if t is None:
+        return None, True
+    p = _addr(t, numel, dtype_code, dev)
+    return p, p is not None
+
+
+def _device_of(t):
+    """The current device if tensor t is on it, else -2 (which no tensor is on)."""
+    if _torch is None:
+        _setup_torch()
+    dev = t.get_device() if isinstance(t, _torch.Tensor) else -1
+    return dev if dev >= 0 and dev == _torch.cuda.current_device() else -2
+
+
+def _raw_stream(stream):
+    """The stream's handle; torch's current stream of the current device for None."""
+    if stream is None:
+        raw = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(_torch.cuda.current_device())
+    return _stream(stream)
+
+
 def _dtype_name(code):
     return "float32" if code == DSATTN_F32 else "bfloat16"
 
@@ -248,6 +298,9 @@ class Plan:
         self.n_global = n_global
         self.device = device
         self._lk_max = None
+        # what every call looks up: the element count of Q, K, V and O
+        self._n = desc.clip_len * desc.n_clips * desc.spatial * desc.heads * desc.head_dim
+        self._dev = device if device >= 0 else -2  # (no tensor is on a host-only plan's device)
 
     def close(self):
         if self.handle:
@@ -332,7 +385,27 @@ def dsattn_plan_launch_info(plan: Plan) -> dict:
     return info.as_dict()
 
 
+def _four(plan, a, b, c, d, nb, out_code):
+    """Addresses of four tensors of a plan: a of Q's size, b and c of nb elements, d of Q's size and
+    the given type; None unless all are as they should be."""
+    n, io, dev = plan._n, plan.desc.io_dtype, plan._dev
+    pa = _addr(a, n, io, dev)
+    pb = _addr(b, nb, io, dev)
+    pc = _addr(c, nb, io, dev)
+    pd = _addr(d, n, out_code, dev)
+    if pa is None or pb is None or pc is None or pd is None:
+        return None
+    return pa, pb, pc, pd
+
+
 def dsattn_gather_context(plan: Plan, K, V, Kctx, Vctx, stream=None):
+    n, io, dev = plan._n, plan.desc.io_dtype, plan._dev
+    nc = plan.desc.n_clips * plan.lk_max * plan.desc.spatial * plan.C
+    ps = _addr(K, n, io, dev), _addr(V, n, io, dev), _addr(Kctx, nc, io, dev), _addr(Vctx, nc, io, dev)
+    if None not in ps:
+        _check((_lib or load()).dsattn_gather_context(plan.handle, *ps, _raw_stream(stream)),
+               "dsattn_gather_context")
+        return
     plan.check("dsattn_gather_context", [plan.frames(K, "K"), plan.frames(V, "V"),
                                          plan.ctx(Kctx, "Kctx"), plan.ctx(Vctx, "Vctx")])
     _check(load().dsattn_gather_context(plan.handle, _ptr(K), _ptr(V), _ptr(Kctx), _ptr(Vctx),
@@ -340,6 +413,10 @@ def dsattn_gather_context(plan: Plan, K, V, Kctx, Vctx, stream=None):
 
 
 def dsattn_forward(plan: Plan, Q, K, V, O, stream=None):
+    ps = _four(plan, Q, K, V, O, plan._n, plan.desc.out_dtype)
+    if ps is not None:
+        _check((_lib or load()).dsattn_forward(plan.handle, *ps, _raw_stream(stream)), "dsattn_forward")
+        return
     plan.check("dsattn_forward", [plan.frames(Q, "Q"), plan.frames(K, "K"), plan.frames(V, "V"),
                                   plan.frames(O, "O", out=True)])
     _check(load().dsattn_forward(plan.handle, _ptr(Q), _ptr(K), _ptr(V), _ptr(O),
@@ -347,6 +424,12 @@ def dsattn_forward(plan: Plan, Q, K, V, O, stream=None):
 
 
 def dsattn_forward_ctx(plan: Plan, Q, Kctx, Vctx, O, stream=None):
+    nc = plan.desc.n_clips * plan.lk_max * plan.desc.spatial * plan.C
+    ps = _four(plan, Q, Kctx, Vctx, O, nc, plan.desc.out_dtype)
+    if ps is not None:
+        _check((_lib or load()).dsattn_forward_ctx(plan.handle, *ps, _raw_stream(stream)),
+               "dsattn_forward_ctx")
+        return
     plan.check("dsattn_forward_ctx", [plan.frames(Q, "Q"), plan.ctx(Kctx, "Kctx"),
                                       plan.ctx(Vctx, "Vctx"), plan.frames(O, "O", out=True)])
     _check(load().dsattn_forward_ctx(plan.handle, _ptr(Q), _ptr(Kctx), _ptr(Vctx), _ptr(O),
@@ -390,6 +473,19 @@ def dsattn_groupnorm(clip_len, n_clips, spatial, channels, groups, X, Y, workspa
                      workspace_bytes, gamma=None, beta=None, stats=None, io_dtype=DSATTN_BF16,
                      eps=1e-5, stream=None):
     desc = DsattnGnDesc(clip_len, n_clips, spatial, channels, groups, io_dtype, float(eps))
+    dev = _device_of(X)
+    n = clip_len * n_clips * spatial * channels
+    px, py = _addr(X, n, io_dtype, dev), _addr(Y, n, io_dtype, dev)
+    pg, okg = _addr_or_null(gamma, channels, DSATTN_F32, dev)
+    pb, okb = _addr_or_null(beta, channels, DSATTN_F32, dev)
+    ps, oks = _addr_or_null(stats, 2 * groups, DSATTN_F32, dev)
+    if (px is not None and py is not None and okg and okb and oks and isinstance(workspace, _torch.Tensor)
+            and workspace.get_device() == dev and workspace.is_contiguous()
+            and workspace.numel() * workspace.element_size() >= workspace_bytes):
+        _check((_lib or load()).dsattn_groupnorm(ctypes.byref(desc), px, pg, pb, py, ps,
+                                                 workspace.data_ptr(), int(workspace_bytes),
+                                                 _raw_stream(stream)), "dsattn_groupnorm")
+        return
     items = _gn_items(desc, X, Y, gamma, beta, stats)
     if hasattr(workspace, "element_size"):
         items.append((workspace, "workspace",
@@ -428,6 +524,14 @@ def dsattn_temporal_conv(clip_len, n_clips, spatial, c_in, c_out, reach, X, W, Y
     desc = DsattnConvDesc(clip_len, n_clips, spatial, c_in, c_out, reach, io_dtype,
                           io_dtype if out_dtype is None else out_dtype, flags)
     rows = clip_len * n_clips * spatial
+    dev = _device_of(X)
+    px, pw = _addr(X, rows * c_in, io_dtype, dev), _addr(W, (2 * reach + 1) * c_out * c_in, io_dtype, dev)
+    py = _addr(Y, rows * c_out, desc.out_dtype, dev)
+    pb, okb = _addr_or_null(bias, c_out, DSATTN_F32, dev)
+    if px is not None and pw is not None and py is not None and okb:
+        _check((_lib or load()).dsattn_temporal_conv(ctypes.byref(desc), px, pw, pb, py,
+                                                     _raw_stream(stream)), "dsattn_temporal_conv")
+        return
     _check_tensors("dsattn_temporal_conv",
                    [(X, "X", rows * c_in, desc.io_dtype),
                     (W, "W", (2 * reach + 1) * c_out * c_in, desc.io_dtype),
@@ -443,6 +547,23 @@ def dsattn_linear_info(rows, c_in, c_out, n_out, io_dtype=DSATTN_BF16, out_dtype
     info = DsattnConvInfo()
     _check(load().dsattn_linear_info(ctypes.byref(desc), ctypes.byref(info)), "dsattn_linear_info")
     return info.as_dict()
+
+
+_ARRAYS = {n: ctypes.c_void_p * n for n in (1, 2, 3, 4)}
+
+
+def _addr_array(items, n, numel, dtype_code, dev, optional=False):
+    """Array of the addresses of n tensors, None unless all are as they should be."""
+    arr = _ARRAYS[n]()
+    for i in range(n):
+        t = items[i]
+        if t is None and optional:
+            continue
+        p = _addr(t, numel, dtype_code, dev)
+        if p is None:
+            return None
+        arr[i] = p
+    return arr
 
 
 def _ptr_array(items, n):
@@ -486,6 +607,18 @@ def dsattn_temporal_layer(plan, X, Ws, workspace, Y, biases=None, stream=None):
     if len(Ws) != 4 or (biases is not None and len(biases) != 4):
         raise ValueError("dsattn_temporal_layer: four weight sets (and four bias entries) expected")
     C = plan.C
+    io, dev = plan.desc.io_dtype, plan._dev
+    px, py = _addr(X, plan._n, io, dev), _addr(Y, plan._n, io, dev)
+    if (px is not None and py is not None and isinstance(workspace, _torch.Tensor)
+            and workspace.element_size() == 1 and workspace.get_device() == dev
+            and workspace.is_contiguous()):
+        w = _addr_array(Ws, 4, C * C, io, dev)
+        b = None if biases is None else _addr_array(biases, 4, C, DSATTN_F32, dev, optional=True)
+        if w is not None and (biases is None or b is not None):
+            _check((_lib or load()).dsattn_temporal_layer(plan.handle, px, w, b, workspace.data_ptr(),
+                                                          workspace.numel(), py, _raw_stream(stream)),
+                   "dsattn_temporal_layer")
+            return
     items = [plan.frames(X, "X"), plan.frames(Y, "Y")]
     for g in range(4):
         items.append((Ws[g], f"W[{g}]", C * C, plan.desc.io_dtype))
