@@ -175,7 +175,9 @@ bool mfma_plan(dsattn_plan_t &pl)
     li.ring_reach = wr;
 
     // everything a launch needs that does not depend on the tensors
-    pl.mfma_fn = var->fn;
+    // (24 tiles: the shortest chunk of the long videos; a clip of a materialised context is a chunk)
+    pl.mfma_fn = m >= 24 && var->fn_sel ? var->fn_sel : var->fn;
+    pl.mfma_ctx_fn = d.clip_len / 16 >= 24 && var->fn_sel ? var->fn_sel : var->fn;
     pl.gdup = 0;  // entries that repeat an earlier one (the kernel takes at most 64 entries)
     for (size_t j = 0; j < pl.global_idx.size() && j < 64; ++j)
         for (size_t jj = 0; jj < j; ++jj)
@@ -192,8 +194,11 @@ bool mfma_plan(dsattn_plan_t &pl)
 // the maximum: plans that share a variant must not lower each other's limit.
 hipError_t mfma_prepare(const dsattn_plan_t &pl)
 {
-    if (!pl.mfma_fn) return hipErrorInvalidValue;
-    return hipFuncSetAttribute(pl.mfma_fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
+    if (!pl.mfma_fn || !pl.mfma_ctx_fn) return hipErrorInvalidValue;
+    const hipError_t e =
+        hipFuncSetAttribute(pl.mfma_fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
+    if (e != hipSuccess || pl.mfma_ctx_fn == pl.mfma_fn) return e;
+    return hipFuncSetAttribute(pl.mfma_ctx_fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
 }
 
 hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, const void *V,
@@ -202,7 +207,8 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
     // the variant and the duplicate mask were resolved by mfma_plan: nothing is searched here
     const dsattn_desc &d = pl.desc;
     const dsattn_launch_info &li = pl.launch;
-    if (!pl.mfma_fn) return hipErrorInvalidValue;
+    const void *fn = ctx_mode ? pl.mfma_ctx_fn : pl.mfma_fn;
+    if (!fn) return hipErrorInvalidValue;
     const int wpb = li.block_threads / 64;
 
     MfmaArgs a;
@@ -239,7 +245,7 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
         return hipErrorInvalidValue;
 
     void *params[] = {&a};
-    return hipLaunchKernel(pl.mfma_fn, dim3((unsigned)(a.BPC * NC)), dim3((unsigned)li.block_threads),
+    return hipLaunchKernel(fn, dim3((unsigned)(a.BPC * NC)), dim3((unsigned)li.block_threads),
                            params, (size_t)li.lds_bytes, st);
 }
 

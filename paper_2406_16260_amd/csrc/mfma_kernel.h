@@ -27,8 +27,7 @@
 // scale folded in), P^T rounded to bf16 and fed straight back as the B operand of  O^T = V^T P^T
 // (16x16x16 bf16 MFMA per key tile, or 16x16x32 per pair of key tiles when both scopes have an even
 // number of tiles).  The denominator is the sum of the rounded weights, taken by one more MFMA
-// with an all-ones A operand.  V^T operands are made from row-major V rows with an MFMA against a
-// 0/1 selector matrix, which is exact.
+// with an all-ones A operand.  V^T operands come out of LDS through gfx950's transposing read.
 // Options of the scopes: the biases of the two scopes' logits enter as one shift of the raw global
 // scores (a softmax sees only their difference); a sliding window |key frame - query frame| <= r
 // on the local scope is a per-lane mask on the local scores; the set-union option drops, per
@@ -78,6 +77,7 @@ struct MfmaVariant {
     int D, HPW, NLT, NGT, WPE;
     bool out_f32;
     const void *fn;
+    const void *fn_sel;  // for long chunks, where there is one
 };
 
 // LDS row stride in bytes for a row of `seg` bf16: padded so that consecutive rows start 4 banks
@@ -145,7 +145,14 @@ struct PvChain<false> {
 
 // WPE = wavefronts per SIMD the register budget is sized for (2: 256 VGPRs, 1: 512); a
 // workgroup is at most 4 * WPE wavefronts so that it fits one compute unit.
-template <int D, int HPW, int NLT, int NGT, int WPE, bool OUT_F32>
+//
+// SEL: V is transposed by an exact product with a 0/1 selector matrix (a matrix instruction, two
+// conversions and half the LDS reads per 16 channels) instead of by gfx950's transposing LDS read.
+// The transposing read is faster wherever arithmetic shows (4 clips, 640 positions, 8 heads of 160: 102
+// -> 95 us; 4 clips, 2,560 positions, 8 heads of 40: 101.5 -> 96; 144 clips, 160 positions, 12 heads of 96: 658 ->
+// 632).  Where memory alone bounds long chunks it is no faster and at some head sizes a little slower (the
+// same with 8 heads of 160: 713 -> 719, 10 of 128: 725 -> 728, 20 of 64: 714 -> 716): those have both kernels.
+template <int D, int HPW, int NLT, int NGT, int WPE, bool OUT_F32, bool SEL>
 __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaArgs a)
 {
     constexpr int SEG = D * HPW;          // bf16 per frame row of this row group
@@ -306,24 +313,35 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
         return __builtin_bit_cast(bf16x8, x);
     };
 
-    // 0/1 selector operands: sel[hf] picks channels 16*hf .. 16*hf+15 of a 32-wide block
-    bf16x8 sel[2];
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            sel[hf][e] = (8 * lg + e == 16 * hf + l16) ? (__bf16)1.0f : (__bf16)0.0f;
-
     // A operands that are all ones (row sums of P^T)
     bf16x8 ones8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones8[e] = (__bf16)1.0f;
     const bf16x4 ones4 = __builtin_shufflevector(ones8, ones8, 0, 1, 2, 3);
 
-    // V^T operand for channels 16*(2kb+hf) .. +15 from the V operand `av` (16 keys x 32 channels):
-    // an exact transpose through the matrix core.  The lane gets keys 4 lg .. 4 lg + 3 of channel
-    // l16: the A operand of the 16x16x16 MFMA, or one half of the A operand of a 16x16x32 MFMA
-    // over a pair of key tiles.
+    // V^T operand for channels 16 dt .. 16 dt + 15 of head `hh` from 16 V rows in LDS: keys 4 lg ..
+    // 4 lg + 3 of channel l16, which is the A operand of the 16x16x16 MFMA, or one half of the A
+    // operand of a 16x16x32 MFMA over a pair of key tiles.  The transposing read of gfx950 does it:
+    // within a group of 16 lanes it hands lane i element i % 4 of the 8 bytes that lanes i / 4, 4 + i / 4,
+    // 8 + i / 4 and 12 + i / 4 point at; lane i points at key 4 lg + i / 4 (`row` = that key's LDS row),
+    // channels 4 (i % 4) .. + 3.  (Past the head's last channel it reads the next head's or the row's
+    // padding: rows of O^T that are not stored.)
+    auto read_vt = [&](const unsigned char *buf, int row, int hh, int dt)
+                       __attribute__((always_inline)) -> bf16x4 {
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4 *)(buf + row * RS + (hh * D + 16 * dt + 4 * (l16 & 3)) * 2));
+        return __builtin_bit_cast(bf16x4, x);
+    };
+    const int vkey = 4 * lg + (l16 >> 2);  // the key of a tile whose row this lane points read_vt at
+    // The same through the matrix core, from the V operand `av` (16 keys x 32 channels): half hf of it
+    bf16x8 sel[SEL ? 2 : 1];
+    if constexpr (SEL) {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                sel[hf][e] = (8 * lg + e == 16 * hf + l16) ? (__bf16)1.0f : (__bf16)0.0f;
+    }
     auto vt_from = [&](const bf16x8 av, int hf) __attribute__((always_inline)) -> bf16x4 {
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
         z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, sel[hf], z, 0, 0, 0);
@@ -424,24 +442,29 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
         wave_sync();
         store_tile(qo, 0, 16, gV);
         wave_sync();
+        auto keep_vt = [&](int hh, int dt, const bf16x4 t) __attribute__((always_inline)) {
+            if (tg < 2 * NGP) {
 #pragma unroll
-        for (int hh = 0; hh < HPW; ++hh)
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb) {
-                const bf16x8 av = read_op32(qo, l16, hh, kb);
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
-                    if (2 * kb + hf < NDT) {
-                        const bf16x4 t = vt_from(av, hf);
-                        if (tg < 2 * NGP) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                vgp[tg / 2][hh][2 * kb + hf][4 * (tg & 1) + e] = t[e];
-                        } else {
-                            vgs[tg - 2 * NGP][hh][2 * kb + hf] = t;
-                        }
-                    }
+                for (int e = 0; e < 4; ++e) vgp[tg / 2][hh][dt][4 * (tg & 1) + e] = t[e];
+            } else {
+                vgs[tg - 2 * NGP][hh][dt] = t;
             }
+        };
+#pragma unroll
+        for (int hh = 0; hh < HPW; ++hh) {
+            if constexpr (SEL) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) {
+                    const bf16x8 av = read_op32(qo, l16, hh, kb);
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf)
+                        if (2 * kb + hf < NDT) keep_vt(hh, 2 * kb + hf, vt_from(av, hf));
+                }
+            } else {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) keep_vt(hh, dt, read_vt(qo, vkey, hh, dt));
+            }
+        }
     }
 
     // weights of local keys past the ring's R rows are cleared after rounding (their scores
@@ -489,10 +512,12 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
         const int chi = min(F, (clip + 1) * a.clip_len + a.wl);
         bool lvalid[NLT][4];
         int arow[NLT];  // ring row this lane feeds as MFMA row l16 of local tile tl (clamped)
+        int vrow[NLT];  // ring row this lane points the transposing read of V at
         const bool interior = 16 * i - w >= clo && 16 * i + 16 + w <= chi;
 #pragma unroll
         for (int tl = 0; tl < NLT; ++tl) {
             arow[tl] = min(16 * tl + l16, R - 1);
+            vrow[tl] = min(16 * tl + vkey, R - 1);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int s = 16 * tl + 4 * lg + e;
@@ -637,36 +662,54 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
                 for (int u = 0; u < NGP; ++u)
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) o[dt] = Chain::mac(vgp[u][hh][dt], ptp[u], o[dt]);
+                if constexpr (SEL) {
 #pragma unroll
-                for (int u = 0; u < NLP; ++u)
+                    for (int u = 0; u < NLP; ++u)
 #pragma unroll
-                    for (int kb = 0; kb < NKB; ++kb) {
-                        const bf16x8 av0 = read_op32(vring, arow[2 * u], hh, kb);
-                        const bf16x8 av1 = read_op32(vring, arow[2 * u + 1], hh, kb);
+                        for (int kb = 0; kb < NKB; ++kb) {
+                            const bf16x8 av0 = read_op32(vring, arow[2 * u], hh, kb);
+                            const bf16x8 av1 = read_op32(vring, arow[2 * u + 1], hh, kb);
 #pragma unroll
-                        for (int hf = 0; hf < 2; ++hf) {
-                            const int dt = 2 * kb + hf;
-                            if (dt < NDT)
-                                o[dt] = Chain::mac(join(vt_from(av0, hf), vt_from(av1, hf)),
-                                                   ptp[NGP + u], o[dt]);
+                            for (int hf = 0; hf < 2; ++hf) {
+                                const int dt = 2 * kb + hf;
+                                if (dt < NDT)
+                                    o[dt] = Chain::mac(join(vt_from(av0, hf), vt_from(av1, hf)),
+                                                       ptp[NGP + u], o[dt]);
+                            }
                         }
-                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < NLP; ++u)
+#pragma unroll
+                        for (int dt = 0; dt < NDT; ++dt)
+                            o[dt] = Chain::mac(join(read_vt(vring, vrow[2 * u], hh, dt),
+                                                    read_vt(vring, vrow[2 * u + 1], hh, dt)),
+                                               ptp[NGP + u], o[dt]);
+                }
             } else {
 #pragma unroll
                 for (int u = 0; u < NGS; ++u)
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) o[dt] = Chain::mac(vgs[u][hh][dt], ptg[u], o[dt]);
+                if constexpr (SEL) {
 #pragma unroll
-                for (int u = 0; u < NLS; ++u)
+                    for (int u = 0; u < NLS; ++u)
 #pragma unroll
-                    for (int kb = 0; kb < NKB; ++kb) {
-                        const bf16x8 av = read_op32(vring, arow[u], hh, kb);
+                        for (int kb = 0; kb < NKB; ++kb) {
+                            const bf16x8 av = read_op32(vring, arow[u], hh, kb);
 #pragma unroll
-                        for (int hf = 0; hf < 2; ++hf) {
-                            const int dt = 2 * kb + hf;
-                            if (dt < NDT) o[dt] = Chain::mac(vt_from(av, hf), ptl[u], o[dt]);
+                            for (int hf = 0; hf < 2; ++hf) {
+                                const int dt = 2 * kb + hf;
+                                if (dt < NDT) o[dt] = Chain::mac(vt_from(av, hf), ptl[u], o[dt]);
+                            }
                         }
-                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < NLS; ++u)
+#pragma unroll
+                        for (int dt = 0; dt < NDT; ++dt)
+                            o[dt] = Chain::mac(read_vt(vring, vrow[u], hh, dt), ptl[u], o[dt]);
+                }
             }
 
             // ---- normalise; lane holds channels 16 dt + 4 lg + {0..3} of query frame l16
@@ -719,10 +762,21 @@ const MfmaVariant *mfma_variants_d64(int *n);
 const MfmaVariant *mfma_variants_d40(int *n);
 const MfmaVariant *mfma_variants_d32(int *n);
 
+template <int D, int HPW, int NLT, int NGT, int WPE, bool OUT_F32>
+const void *mfma_sel_fn()
+{
+    if constexpr ((D == 160 || D == 128 || D == 64) && NGT <= 1 && NLT <= 2)
+        return (const void *)&dsattn_mfma_kernel<D, HPW, NLT, NGT, WPE, OUT_F32, true>;
+    return nullptr;
+}
+
 #define DSATTN_MFMA_VARIANT(D, HPW, NLT, NGT, WPE)                                             \
     {D, HPW, NLT, NGT, WPE, false,                                                             \
-     (const void *)&dsattn_mfma_kernel<D, HPW, NLT, NGT, WPE, false>},                         \
-    {D, HPW, NLT, NGT, WPE, true, (const void *)&dsattn_mfma_kernel<D, HPW, NLT, NGT, WPE, true>}
+     (const void *)&dsattn_mfma_kernel<D, HPW, NLT, NGT, WPE, false, false>,                   \
+     mfma_sel_fn<D, HPW, NLT, NGT, WPE, false>()},                                             \
+    {D, HPW, NLT, NGT, WPE, true,                                                              \
+     (const void *)&dsattn_mfma_kernel<D, HPW, NLT, NGT, WPE, true, false>,                    \
+     mfma_sel_fn<D, HPW, NLT, NGT, WPE, true>()}
 
 // local context 0..16 frames (1 to 3 local key tiles), no or one global key tile
 #define DSATTN_MFMA_SET(D, HPW, WPE)                                                           \

@@ -28,7 +28,8 @@ struct dsattn_plan_s {
     dsattn_launch_info launch;
 
     // resolved once by the planner for the matrix-core kernel, so that a launch searches nothing
-    const void *mfma_fn = nullptr;  // the variant's kernel
+    const void *mfma_fn = nullptr;      // the variant's kernel
+    const void *mfma_ctx_fn = nullptr;  // the same on a materialised context
     uint64_t gdup = 0;              // bit j: global entry j (< 64) repeats an earlier entry
 
     const void *tile_fn = nullptr;  // the tile kernel, where the streaming kernel has no variant

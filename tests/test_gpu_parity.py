@@ -679,3 +679,31 @@ def test_contexts_beyond_the_matrix_core_variants_run_the_generic_kernel():
     assert info["kernel"] == 0
     ref = U.oracle_forward(q, k, v, 16, 4, 2, 4, g, dedup=True)
     U.assert_parity(o, ref, "f32", what="dedup G=94")
+
+
+@pytest.mark.parametrize("D,h,w,G,opts", [
+    (160, 2, 2, 16, {}), (160, 1, 8, 0, {"window": 5}), (128, 2, 3, 7, {"bias_global": 1.0}),
+    (64, 4, 0, 16, {}), (64, 3, 2, 16, {"flags": B.DSATTN_FLAG_DEDUP_GLOBAL}), (160, 2, 0, 9, {}),
+    (96, 2, 2, 16, {}),                      # a head size with one kernel for all chunk lengths
+])
+def test_long_and_short_chunks_run_different_kernels_with_equal_results(D, h, w, G, opts):
+    """Chunks of 24 query tiles and more take the kernel that transposes V through the matrix core,
+    shorter ones the one that reads it transposed from LDS: the same numbers reach the same
+    instructions, so the results are equal bit for bit, and right."""
+    n_clips, P = 30, 3
+    F = 16 * n_clips
+    g = np.random.default_rng(3).integers(0, F, size=G).tolist()
+    announce(f"chunk kernels D={D} h={h} w={w} G={G} {opts}")
+    q, k, v = make(F, P, h * D, 61, "iid", "bf16")
+    for out in ("bf16", "f32"):
+        res = []
+        for m in (24, 23, 30, 5):
+            with U.planner_env(clips_per_task=m):
+                o, info = U.library_forward(q, k, v, 16, n_clips, w, h, g, out_dtype=out, **opts)
+            assert info["kernel"] == 1 and info["clips_per_task"] == m
+            res.append(o)
+        for o in res[1:]:
+            assert torch.equal(o, res[0])
+        kw = {x: y for x, y in opts.items() if x != "flags"}
+        ref = U.oracle_forward(q, k, v, 16, n_clips, w, h, g, dedup="flags" in opts, **kw)
+        U.assert_parity(res[0], ref, out, what=f"D={D}")
