@@ -161,6 +161,15 @@ bool mfma_plan(dsattn_plan_t &pl)
     m = std::max(1, std::min(n_tiles, env_int("DSATTN_CLIPS_PER_TASK", m)));
     const int NC = (n_tiles + m - 1) / m;
     if ((int64_t)RG * NC > 0x7fffffffLL) return false;
+    // A short video whose wavefronts all run at once has nothing to pace: two wavefronts per workgroup
+    // spread over more compute units and start independently.  Measured, one position's heads per
+    // workgroup / two wavefronts: 1 clip, 40 positions, 8 heads of 160 9.1 / 6.6 us; 4 clips, 40 x 8 x 160 10.6 /
+    // 9.7, 160 x 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  From 24 clips on
+    // (35.5 / 36.1), and with four wavefronts and a single clip (8.0 / 8.3), the shared lines of neighbouring
+    // rows count for more.
+    if ((int64_t)RG * NC <= (int64_t)kCus * max_waves_cu && n_tiles <= 16 && wpb > (n_tiles == 1 ? 4 : 2) &&
+        RG % 2 == 0 && !env_int("DSATTN_WAVES_PER_BLOCK", 0))
+        wpb = 2;
 
     dsattn_launch_info &li = pl.launch;
     li.kernel = 1;
