@@ -551,7 +551,7 @@ struct ConvVariant {
     int lds;               // bytes per workgroup
     int resident;          // persistent workgroups per compute unit; 0: one workgroup per tile
     bool f32;              // operands
-    const void *fn[2];     // bf16 / fp32 output
+    const void *fn[2];     // bf16 / fp32 output; fp32 operands: one tap / more
 };
 
 // the two ring slots with the staging gap between them; behind them the bias of each
@@ -585,7 +585,8 @@ const ConvVariant kConvVariants[] = {
     DSATTN_PIPE_VARIANT(2, 2, 2, 2, 4),  // 128 x 128, pipelined
     DSATTN_TILE_VARIANT(2, 2, 2, 2),     // 64 x 64
     {64, 64, 4, 2 * (64 + 64) * kRow, 0, true,
-     {nullptr, (const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true>}},
+     {(const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, false>,
+      (const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, true>}},
 };
 enum { kBig256, kBig320, kTile160, kTile128, kPipe128, kTile64, kTileF32 };  // positions in the table
 
@@ -747,7 +748,7 @@ hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *
                 }
             if (dev < 64) prepared.fetch_or((uint64_t)1 << dev, std::memory_order_release);
         }
-        const void *fn = v->fn[d.out_dtype == DSATTN_F32 ? 1 : 0];
+        const void *fn = v->fn[v->f32 ? d.reach > 0 : d.out_dtype == DSATTN_F32];
         const int64_t es = v->f32 ? 4 : 2;
         ConvArgs a;
         a.X = X;

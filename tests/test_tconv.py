@@ -536,3 +536,19 @@ def test_conv_fp32_keeps_fp32_precision():
     B.dsattn_linear(300, 1280, 320, x, [w], [y], io_dtype=B.DSATTN_F32)
     ref = oracle.linear(x.cpu().double().numpy(), w.cpu().double().numpy())
     assert np.abs(y.cpu().double().numpy() - ref).max() <= 40 * 4 * 2.0 ** -24
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(3, 1, 2, 4, 4, 3), (16, 3, 7, 68, 60, 2), (16, 2, 41, 320, 130, 1)])
+def test_conv_fp32_frames_outside_the_video_add_nothing(shape):
+    """An infinite weight of the outermost taps reaches the frames that have a frame at that tap, and
+    no other: not even as zero times infinity."""
+    clip_len, n_clips, P, c_in, c_out, n = shape
+    announce(f"conv infinite weights {shape}")
+    x = synth.make_tensor(clip_len * n_clips, P, c_in, 45, "iid", "f32").to(DEV)
+    w = synth.make_conv_weights(2 * n + 1, c_out, c_in, 46, "f32")[0].to(DEV)
+    w[0, 1, 2], w[-1, 3, 1] = float("inf"), float("-inf")
+    y = run_conv(x, w, None, clip_len, n_clips, "f32")
+    ref = run_conv(x, w, None, clip_len, n_clips, "f32", flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert torch.isfinite(ref[:n, :, 1]).all() and torch.isfinite(ref[-n:, :, 3]).all()
+    torch.testing.assert_close(y, ref, rtol=TOL_ACC, atol=TOL_ACC)
