@@ -78,7 +78,7 @@ bool mfma_plan(dsattn_plan_t &pl)
     // The set-union option is built into the variants with one global key tile, and into the
     // four-tile variants that run one wavefront per SIMD (head_dim 160 and 128): with that option
     // and four tiles only those are candidates.
-    // With eight tiles it is not built in (the generic kernel takes those).
+    // With eight tiles it is not built in (the 16-query tile kernel takes those).
     if ((d.flags & DSATTN_FLAG_DEDUP_GLOBAL) && NGT == 8) return false;
     const bool need_wpe1 = (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) && NGT == 4;
     const MfmaVariant *var = nullptr;

@@ -2,8 +2,9 @@
 //   * context gather (Section 4.1 context c^i, Section 4.2 Concat(local, global)) as an
 //     index-driven slab copy;
 //   * the generic vector-ALU Dual-scope attention (any dtype, head_dim, clip length), one
-//     wavefront per (clip, position, head); it is the fp32 path and the fallback of the
-//     MFMA kernel, on the original tensors or on a materialised context;
+//     wavefront per (clip, position, head); it takes what the matrix-core kernels do not (rows
+//     that are not whole 16-byte pieces, head_dim above 160, the flag that asks for it), on the
+//     original tensors or on a materialised context;
 //   * a plain copy kernel used as the bandwidth yardstick.
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
