@@ -138,7 +138,8 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
     }
     // The fp32 sums are moved to fp64 every 32 rows: with 256 workgroups a thread may have some five
     // hundred, and one fp32 sum over them rounds more than the shorter sums of eight times as many
-    // workgroups do.  (No slower: 482 us a call at 2,304 x 160 x 1,280 bf16, 486 without.)
+    // workgroups do: 1 / sigma was off by 1.0e-6 at 2,304 x 160 x 1,280 bf16, by 0.7e-7 so.  (No
+    // slower: 482 us a call, 486 without.)
     constexpr int kMove = 8;  // bites
     double sa[VEC] = {}, sq[VEC] = {};
     auto move = [&]() __attribute__((always_inline)) {
