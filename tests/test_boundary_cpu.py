@@ -175,7 +175,8 @@ def plan_info(wl, lv, **kw):
 
 def test_planner_choices_per_level():
     W = synth.WORKLOADS
-    assert plan_info(W["C0"], W["C0"].levels[0])["kernel"] == 0          # fp32: vector-ALU kernel
+    c0 = plan_info(W["C0"], W["C0"].levels[0])            # fp32: the 16-query tile kernel
+    assert (c0["kernel"], c0["variant"], c0["block_threads"]) == (0, -1, 256)
     c3 = plan_info(W["C3"], W["C3"].levels[0])
     assert (c3["kernel"], c3["heads_per_wave"], c3["local_tiles"], c3["global_tiles"]) == (1, 1, 2, 1)
     assert c3["block_threads"] == 512 and c3["lds_bytes"] <= 160 * 1024
@@ -199,9 +200,11 @@ def test_planner_choices_per_level():
 def test_planner_fallbacks_and_overrides(monkeypatch):
     W = synth.WORKLOADS
     lv = W["C3"].levels[0]
-    assert plan_info(W["C3"], lv, flags=B.DSATTN_FLAG_FORCE_GENERIC)["kernel"] == 0
+    i = plan_info(W["C3"], lv, flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert (i["kernel"], i["block_threads"]) == (0, 64)
     monkeypatch.setenv("DSATTN_FORCE_GENERIC", "1")
-    assert plan_info(W["C3"], lv)["kernel"] == 0
+    i = plan_info(W["C3"], lv)
+    assert (i["kernel"], i["block_threads"]) == (0, 64)
     monkeypatch.delenv("DSATTN_FORCE_GENERIC")
     monkeypatch.setenv("DSATTN_CLIPS_PER_TASK", "7")
     monkeypatch.setenv("DSATTN_WAVES_PER_BLOCK", "2")
@@ -210,13 +213,20 @@ def test_planner_fallbacks_and_overrides(monkeypatch):
     assert i["n_tasks"] == 1280 * 21
     monkeypatch.delenv("DSATTN_CLIPS_PER_TASK")
     monkeypatch.delenv("DSATTN_WAVES_PER_BLOCK")
-    # shapes without an MFMA variant run the generic kernel
+    # shapes without a streaming variant run the 16-query tile kernel
     for kw in (dict(clip_len=8), dict(head_dim=48), dict(local_ctx=17), dict(n_global=65)):
         clip_len = kw.get("clip_len", 16)
         g = list(range(kw.get("n_global", 4)))
         plan = B.dsattn_plan(clip_len, 8, kw.get("local_ctx", 2), 4, 2, kw.get("head_dim", 160), g,
                              device=-1)
-        assert B.dsattn_plan_launch_info(plan)["kernel"] == 0, kw
+        i = B.dsattn_plan_launch_info(plan)
+        assert (i["kernel"], i["variant"], i["block_threads"]) == (0, -1, 256), kw
+        plan.close()
+    # and rows that are not whole 16-byte pieces, or heads above 160 channels, the generic kernel
+    for D in (36, 168):
+        plan = B.dsattn_plan(16, 8, 2, 4, 2, D, [0], device=-1)
+        i = B.dsattn_plan_launch_info(plan)
+        assert (i["kernel"], i["variant"], i["block_threads"]) == (0, -1, 64), D
         plan.close()
 
 
@@ -386,7 +396,8 @@ def test_long_clips_with_a_window_run_the_matrix_core_kernel(D, h, clip_len, n_c
     for kw in (dict(window=17), dict(window=None), dict(window=9, n_global=129)):
         g = list(range(kw.get("n_global", 4)))
         plan = B.dsattn_plan(clip_len, n_clips, 8, 160, h, D, g, device=-1, window=kw["window"])
-        assert B.dsattn_plan_launch_info(plan)["kernel"] == 0, kw
+        i = B.dsattn_plan_launch_info(plan)
+        assert (i["kernel"], i["block_threads"]) == (0, 256), kw     # the 16-query tile kernel
         plan.close()
 
 

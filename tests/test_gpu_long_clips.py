@@ -64,10 +64,11 @@ def test_long_clips_without_a_window_where_the_clip_fits_the_ring():
     # the tile on one side), and nothing of the neighbouring clips
     info, *_ = run(32, 4, 0, None, 16, 2, 160, 4, seed=400)
     assert info["ring_reach"] == 16 and info["local_tiles"] == 3
-    # a longer reach than the ring holds runs the vector kernel
-    run(32, 4, 2, None, 16, 2, 160, 2, seed=401, expect_kernel=0)
-    run(288, 2, 8, 17, 0, 2, 160, 2, seed=402, expect_kernel=0)
-    run(24, 4, 2, 2, 4, 2, 160, 2, seed=403, expect_kernel=0)       # not whole tiles
+    # a longer reach than the ring holds runs the 16-query tile kernel
+    for args, seed in (((32, 4, 2, None, 16, 2, 160, 2), 401), ((288, 2, 8, 17, 0, 2, 160, 2), 402),
+                       ((24, 4, 2, 2, 4, 2, 160, 2), 403)):         # (the last: not whole tiles)
+        info, *_ = run(*args, seed=seed, expect_kernel=0)
+        assert info["block_threads"] == 256
 
 
 def test_long_clips_with_scope_biases_union_and_peaked_softmax():

@@ -36,7 +36,8 @@ def test_c0_tiny_fp32():
     ref = U.oracle_forward(q, k, v, wl.clip_len, wl.n_clips, wl.local_ctx, lv.heads, g,
                            scale=1.0 / np.sqrt(8.0))
     U.assert_parity(o, ref, "f32_strict", what="C0")
-    assert info["kernel"] == 0  # fp32 runs the vector-ALU kernel
+    # fp32 runs the 16-query tile kernel on the matrix cores
+    assert info["kernel"] == 0 and info["block_threads"] == 256
 
 
 # ---------------------------------------------------------------- generic kernel, many shapes
@@ -423,7 +424,7 @@ def test_sliding_window_both_kernels(w, r, G):
 
 def test_sliding_window_partition_invariance_on_device():
     # with w >= r the clip partition cannot matter: 2 clips chunked differently, and the fp32
-    # generic kernel with other clip lengths, all agree with banded attention over the video
+    # 16-query tile kernel with other clip lengths, all agree with banded attention over the video
     F, P, h, D, r = 64, 2, 2, 160, 5
     q, k, v = make(F, P, h * D, 37, "iid", "bf16")
     ref = U.oracle_forward(q, k, v, F, 1, 0, h, [], window=r)      # one clip = the whole video
@@ -431,8 +432,9 @@ def test_sliding_window_partition_invariance_on_device():
         o1, i1 = U.library_forward(q, k, v, 16, 4, 5, h, [], out_dtype="f32", window=r)
     with planner_env(clips_per_task=4):
         o2, i2 = U.library_forward(q, k, v, 16, 4, 8, h, [], out_dtype="f32", window=r)
-    o3, i3 = U.library_forward(q, k, v, 8, 8, 6, h, [], out_dtype="f32", window=r)   # generic
-    assert i1["kernel"] == 1 and i2["kernel"] == 1 and i3["kernel"] == 0
+    o3, i3 = U.library_forward(q, k, v, 8, 8, 6, h, [], out_dtype="f32", window=r)   # tile
+    assert i1["kernel"] == 1 and i2["kernel"] == 1
+    assert i3["kernel"] == 0 and i3["block_threads"] == 256
     for o in (o1, o2, o3):
         U.assert_parity(o, ref, "f32", what="window partition invariance")
 
@@ -571,8 +573,8 @@ def test_dedup_global_both_kernels(w, window, g):
 
 
 def test_dedup_global_other_shapes():
-    # fp32 tensors (generic kernel), head_dim 40 with four heads per wavefront, and more than 16
-    # global frames (the option then runs on the generic kernel)
+    # fp32 tensors (16-query tile kernel), head_dim 40 with four heads per wavefront, and more than 16
+    # global frames (the option then runs on the tile kernel)
     q, k, v = make(12, 2, 16, 89, "iid", "f32")
     g = [1, 1, 7, 11]
     ref = U.oracle_forward(q, k, v, 4, 3, 1, 2, g, dedup=True)
@@ -588,7 +590,7 @@ def test_dedup_global_other_shapes():
     g = sorted(set(range(0, 48, 2)))  # 24 global frames
     ref = U.oracle_forward(q, k, v, 16, 3, 3, 8, g, dedup=True)
     o, info = U.library_forward(q, k, v, 16, 3, 3, 8, g, out_dtype="f32", flags=B.DSATTN_FLAG_DEDUP_GLOBAL)
-    assert info["kernel"] == 0
+    assert info["kernel"] == 0 and info["block_threads"] == 256
     U.assert_parity(o, ref, "f32", what="dedup G=24")
 
 
@@ -663,20 +665,20 @@ def test_wide_contexts_on_matrix_cores(D, h, w, G, tiles):
         U.assert_parity(o, ref, od, what=f"wide context D={D} w={w} G={G}")
 
 
-def test_contexts_beyond_the_matrix_core_variants_run_the_generic_kernel():
+def test_contexts_beyond_the_streaming_variants_run_the_tile_kernel():
     q, k, v = make(64, 2, 2 * 160, 1300, "iid", "bf16")
     for D, h, w, G in ((160, 2, 4, 65), (128, 2, 4, 70), (80, 4, 4, 129)):
         g = list(range(G % 64)) + list(range(64)) + ([5] * (G - 64 - G % 64) if G > 64 + G % 64 else [])
         g = (g + [0] * G)[:G]
         o, info = U.library_forward(q, k, v, 16, 4, w, h, g, out_dtype="f32")
-        assert info["kernel"] == 0, (D, G, info)
+        assert info["kernel"] == 0 and info["block_threads"] == 256, (D, G, info)
         ref = U.oracle_forward(q, k, v, 16, 4, w, h, g)
-        U.assert_parity(o, ref, "f32", what=f"generic D={D} G={G}")
+        U.assert_parity(o, ref, "f32", what=f"tile D={D} G={G}")
     # the set union with more than 64 global frames
     g = list(range(64)) + list(range(30))
     o, info = U.library_forward(q, k, v, 16, 4, 2, 4, g, out_dtype="f32",
                                 flags=B.DSATTN_FLAG_DEDUP_GLOBAL)
-    assert info["kernel"] == 0
+    assert info["kernel"] == 0 and info["block_threads"] == 256
     ref = U.oracle_forward(q, k, v, 16, 4, 2, 4, g, dedup=True)
     U.assert_parity(o, ref, "f32", what="dedup G=94")
 

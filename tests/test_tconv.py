@@ -79,11 +79,14 @@ def test_conv_info_tiles_and_counts():
     # no taps beyond the centre: one tap, nothing lost at the ends
     assert B.dsattn_temporal_conv_info(4, 2, 3, 8, 8, 0)["useful_flops"] == 2 * 8 * 3 * 8 * 8
     assert B.dsattn_temporal_conv_info(4, 2, 3, 8, 8, 2)["useful_flops"] == 2 * (5 * 8 - 6) * 3 * 8 * 8
-    # fp32 tensors, channel counts that are not whole 16-byte lanes, and the flag: vector kernel
-    assert B.dsattn_temporal_conv_info(16, 4, 5, 64, 64, 1, io_dtype=B.DSATTN_F32)["kernel"] == 0
-    assert B.dsattn_temporal_conv_info(16, 4, 5, 36, 64, 1)["kernel"] == 0
-    assert B.dsattn_temporal_conv_info(16, 4, 5, 64, 64, 1,
-                                       flags=B.DSATTN_FLAG_FORCE_GENERIC)["kernel"] == 0
+    # fp32 tensors: the fp32 matrix instructions on 64 x 64 tiles
+    i = B.dsattn_temporal_conv_info(16, 4, 5, 64, 64, 1, io_dtype=B.DSATTN_F32)
+    assert (i["kernel"], i["tile_m"], i["tile_n"]) == (0, 64, 64)
+    # channel counts that are not whole 16-byte lanes, and the flag: the vector kernel
+    for kw in (dict(c_in=36), dict(c_in=66, io_dtype=B.DSATTN_F32), dict(flags=B.DSATTN_FLAG_FORCE_GENERIC),
+               dict(io_dtype=B.DSATTN_F32, flags=B.DSATTN_FLAG_FORCE_GENERIC)):
+        i = B.dsattn_temporal_conv_info(16, 4, 5, kw.pop("c_in", 64), 64, 1, **kw)
+        assert (i["kernel"], i["tile_m"]) == (0, 0), kw
     assert B.dsattn_temporal_conv_info(16, 4, 5, 40, 7, 1)["kernel"] == 1
 
 
@@ -265,7 +268,8 @@ def test_linear_info_counts():
     assert tiles <= i["n_blocks"] < tiles + 8
     assert i["useful_flops"] == 2 * 2304 * 160 * 1280 * 1280 * 3
     assert i["algorithmic_bytes"] == 2304 * 160 * 1280 * 2 * 4 + 3 * 1280 * 1280 * 2
-    assert B.dsattn_linear_info(100, 64, 64, 1, io_dtype=B.DSATTN_F32)["kernel"] == 0
+    i = B.dsattn_linear_info(100, 64, 64, 1, io_dtype=B.DSATTN_F32)
+    assert (i["kernel"], i["tile_m"], i["tile_n"]) == (0, 64, 64)
 
 
 def linear_case(rows, c_in, c_out, n_out, dtype="bf16", out_dtype="bf16", flags=0, bias=True, seed=90):
@@ -307,8 +311,10 @@ def test_linear_mfma_matches_oracle(rows, c_in, c_out, n_out):
 
 @pytest.mark.gpu
 def test_linear_other_paths_match_oracle():
-    assert linear_case(50, 12, 9, 3, dtype="f32", out_dtype="f32")["kernel"] == 0
-    assert linear_case(90, 64, 64, 2, flags=B.DSATTN_FLAG_FORCE_GENERIC)["kernel"] == 0
+    i = linear_case(50, 12, 9, 3, dtype="f32", out_dtype="f32")     # fp32 matrix instructions
+    assert (i["kernel"], i["tile_m"]) == (0, 64)
+    i = linear_case(90, 64, 64, 2, flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert (i["kernel"], i["tile_m"]) == (0, 0)
     assert linear_case(300, 128, 128, 3, out_dtype="f32", bias=False)["kernel"] == 1
 
 

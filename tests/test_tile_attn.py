@@ -20,6 +20,18 @@ def make(F, P, C, dtype, seed=17, gen="iid"):
     return tuple(synth.make_tensor(F, P, C, seed + t, gen, dtype).to(DEV) for t in range(3))
 
 
+def assert_tile_kernel(info, clip_len, n_clips, P, h):
+    """The report of a plan that runs the 16-query tile kernel: no streaming variant, a wavefront per
+    query tile, position and head, four to a workgroup."""
+    assert (info["kernel"], info["variant"], info["block_threads"]) == (0, -1, 256), info
+    assert info["n_tasks"] == n_clips * P * h * -(-clip_len // 16), info
+
+
+def assert_generic_kernel(info, n_clips, P, h):
+    assert (info["kernel"], info["variant"], info["block_threads"]) == (0, -1, 64), info
+    assert info["n_tasks"] == n_clips * P * h, info
+
+
 CASES = [
     # clip_len, n_clips, w, P, h, D, G, options
     (24, 4, 3, 5, 2, 64, 12, {}),                        # two query tiles, the second half empty
@@ -54,10 +66,11 @@ def test_tile_kernels_match_oracle_and_generic_kernel(case, dtype):
     ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=dedup, **opts)
     for out in (["f32"] if dtype == "f32" else ["f32", "bf16"]):
         o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, flags=flags, **opts)
-        assert info["kernel"] == 0
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
         U.assert_parity(o, ref, "f32_strict" if out == "f32" else "bf16", what=str(case))
-        og, _ = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out,
+        og, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out,
                                   flags=flags | B.DSATTN_FLAG_FORCE_GENERIC, **opts)
+        assert_generic_kernel(info, n_clips, P, h)
         # both within 1e-5 of the same numbers, then at most one rounding apart in bf16
         bar = 2e-5 if out == "f32" else 2e-5 + 2 * U.bf16_half_ulp(ref).max()
         assert float((o.double() - og.double()).abs().max()) <= bar
@@ -75,7 +88,8 @@ def test_peaked_softmax_with_growing_maximum(dtype):
         q = (q * 0.1 + 1.0).to(q.dtype)
         k = (k.float() * 0.1 + ramp).to(k.dtype)
         ref = U.oracle_forward(q, k, v, clip_len, n_clips, 6, 1, [79, 0, 40])
-        o, _ = U.library_forward(q, k, v, clip_len, n_clips, 6, 1, [79, 0, 40], out_dtype="f32")
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, 6, 1, [79, 0, 40], out_dtype="f32")
+        assert_tile_kernel(info, clip_len, n_clips, P, 1)
         # fp32 scores of size 100: an absolute error of up to 64 products' roundings at that size
         # (2^-24 * 100 each, as a random walk) enters the weights relatively
         bar = 1e-5 + 8 * 100 * 2.0 ** -24 * float(v.float().abs().max())
@@ -90,6 +104,7 @@ def test_materialised_context_gives_the_same(dtype):
         g = np.random.default_rng(6).integers(0, F, size=G).tolist()
         q, k, v = make(F, P, h * D, dtype)
         plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, io_dtype=U.dt_code(dtype), **kw)
+        assert_tile_kernel(B.dsattn_plan_launch_info(plan), clip_len, n_clips, P, h)
         o1, o2 = torch.empty_like(q), torch.empty_like(q)
         B.dsattn_forward(plan, q, k, v, o1)
         ctx = [torch.full((n_clips, plan.lk_max, P, h * D), float("nan"), dtype=q.dtype, device=DEV)
@@ -110,9 +125,11 @@ def test_non_finite_values_go_where_the_generic_kernel_puts_them(dtype):
                               ("q", 30, float("nan")), ("k", 12, float("-inf"))]:
         t = dict(zip("qkv", make(F, P, h * D, dtype)))
         t[which][frame, 1, 45] = bad                 # position 1, head 1, channel 5
-        o, _ = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32")
-        og, _ = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32",
-                                  flags=B.DSATTN_FLAG_FORCE_GENERIC)
+        o, info = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32")
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        og, info = U.library_forward(t["q"], t["k"], t["v"], clip_len, n_clips, w, h, g, out_dtype="f32",
+                                     flags=B.DSATTN_FLAG_FORCE_GENERIC)
+        assert_generic_kernel(info, n_clips, P, h)
         finite = torch.isfinite(og)
         assert torch.equal(torch.isfinite(o), finite), (which, frame, bad)
         assert torch.equal(torch.isnan(o), torch.isnan(og)) and torch.equal(o == float("inf"), og == float("inf"))
@@ -123,6 +140,7 @@ def test_tile_kernel_in_hip_graph_replays():
     clip_len, n_clips, w, P, h, D, g = 24, 3, 2, 5, 2, 64, [5, 70, 33]
     q, k, v = make(72, P, h * D, "bf16")
     plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g)
+    assert_tile_kernel(B.dsattn_plan_launch_info(plan), clip_len, n_clips, P, h)
     want, o = torch.empty_like(q), torch.zeros_like(q)
     B.dsattn_forward(plan, q, k, v, want)
     torch.cuda.synchronize()
