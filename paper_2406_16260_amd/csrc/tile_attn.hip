@@ -33,6 +33,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "plan.h"
 
@@ -58,7 +59,7 @@ struct TileArgs {
     uint32_t per_xcd;  // workgroups per XCD
     uint32_t tasks;
     float sc;          // scale * log2(e)
-    float gb;          // bias of the global keys relative to the local ones, * log2(e)
+    float lb, gb;      // shifts of the local and the global keys' scores, see launch_tile_attn
 };
 
 // The clip's context list: frames [lo, lo + nl), then the global entries; L keys in all.  (Worked
@@ -136,7 +137,7 @@ struct Softmax {
     {
         float mx = -INFINITY, mult = a.sc;
         const bool opts = a.window >= 0 || a.dedup;
-        if (!opts && a.gb == 0.f && 16 * (t0 + nt) <= c.L) {
+        if (!opts && a.lb == 0.f && a.gb == 0.f && 16 * (t0 + nt) <= c.L) {
             // every key counts, as it is
 #pragma unroll
             for (int t = 0; t < KT; ++t)
@@ -157,7 +158,7 @@ struct Softmax {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const bool local = j0 + e < c.nl;
-                    float x = fmaf(s[t][e], a.sc, local ? 0.f : a.gb);
+                    float x = fmaf(s[t][e], a.sc, local ? a.lb : a.gb);
                     bool hidden = j0 + e >= c.L;
                     if (opts) {
                         const int ki = __shfl(info, 4 * lg + e);  // from the key's own lane
@@ -596,8 +597,18 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.tasks = (uint32_t)d.n_clips * d.spatial * d.heads * a.nqt;
     a.per_xcd = (a.tasks + 4 * 8 - 1) / (4 * 8);
     a.sc = pl.scale * kLog2e;
-    // (a softmax sees only the difference of the two biases; 1e38 already hides the lesser scope)
-    a.gb = (float)std::clamp(((double)d.bias_global - d.bias_local) * 1.4426950408889634, -1e38, 1e38);
+    // A softmax sees only the difference of the two biases.  It is taken from the lighter scope's scores:
+    // added to the heavier one's, which are the ones that count, it would take their low bits (a local
+    // bias of -1e4 cost 1e-4 of the result, one of -1e9 all of the scores).  1e38 already hides a scope.
+    const double diff = ((double)d.bias_global - d.bias_local) * 1.4426950408889634;
+    a.lb = (float)std::max(std::min(-diff, 0.0), -1e38);
+    a.gb = (float)std::max(std::min(diff, 0.0), -1e38);
+    // A heavier bias of 2^64 and more swallows the scores beside it in 64 bits too: every key of that
+    // scope weighs the same, as on the vector kernel.
+    if (std::fabs(std::max(d.bias_local, d.bias_global)) >= 0x1p64f) {
+        a.lb = 0.5f * d.bias_local;
+        a.gb = 0.5f * d.bias_global;
+    }
     void *params[] = {&a};
     return hipLaunchKernel(pl.tile_fn, dim3(a.per_xcd * 8), dim3(256), params, 0, st);
 }

@@ -154,3 +154,23 @@ def test_tile_kernel_in_hip_graph_replays():
         torch.cuda.synchronize()
         assert torch.equal(o, want)
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bias", [(-1e3, 0.0), (-1e4, 0.0), (-1e9, 0.0), (-3e38, 0.0), (0.0, -1e9),
+                                  (0.0, 1e9), (1e9, 0.0), (2e9, 1e9), (-3e38, -3e38),
+                                  (-2e38, -3e38)])
+def test_scopes_far_apart_keep_the_heavier_ones_scores(bias, dtype):
+    """A scope damped or switched off by its bias leaves the other scope's scores as they are: the
+    difference of the biases is taken from the lighter scope, never added to the heavier one, where
+    it would drown the scores.  (The last two: beside a bias of 1e38 the oracle's 64 bits hold no score
+    either.)"""
+    clip_len, n_clips, w, P, h, D, G = 24, 3, 2, 3, 2, 64, 12
+    F = clip_len * n_clips
+    g = np.random.default_rng(8).integers(0, F, size=G).tolist()
+    q, k, v = make(F, P, h * D, dtype)
+    kw = dict(bias_local=float(np.float32(bias[0])), bias_global=float(np.float32(bias[1])))
+    ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, **kw)
+    o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32", **kw)
+    assert_tile_kernel(info, clip_len, n_clips, P, h)
+    U.assert_parity(o, ref, "f32_strict", what=f"biases {bias}")
