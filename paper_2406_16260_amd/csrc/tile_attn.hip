@@ -59,7 +59,7 @@ struct TileArgs {
     uint32_t per_xcd;  // workgroups per XCD
     uint32_t tasks;
     float sc;          // scale * log2(e)
-    float lb, gb;      // shifts of the local and the global keys' scores, see launch_tile_attn
+    float lb, gb;      // shifts of the local and the global keys' raw scores, see launch_tile_attn
 };
 
 // The clip's context list: frames [lo, lo + nl), then the global entries; L keys in all.  (Worked
@@ -129,37 +129,30 @@ __device__ __forceinline__ float swap32(float x, bool max)
 template <int KT>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
+    // A shift of the local scores holds from the query's first visible global key on: the set union may
+    // hide them all, and then it is the local scores that count.
+    bool shifted;
+
+    __device__ __forceinline__ explicit Softmax(const TileArgs &a) : shifted(!a.dedup) {}
 
     // scores of key tiles t0 .. t0 + nt - 1 -> weights (unnormalised; those of a tile that is not
     // there are zero); returns the factor for what has been accumulated so far
     __device__ __forceinline__ float step(const TileArgs &a, const Context &c, f32x4 (&s)[KT], int t0,
                                           int nt, int clip, int qt, int lane)
     {
-        float mx = -INFINITY, mult = a.sc;
+        const int l16 = lane & 15, lg = lane >> 4, j0 = 16 * t0 + 4 * lg;
         const bool opts = a.window >= 0 || a.dedup;
-        if (!opts && a.lb == 0.f && a.gb == 0.f && 16 * (t0 + nt) <= c.L) {
-            // every key counts, as it is
-#pragma unroll
-            for (int t = 0; t < KT; ++t)
-                if (t < nt)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[t][e]);
-            mx *= a.sc;
-        } else {
-            mult = 1.f;
-            const int l16 = lane & 15, lg = lane >> 4;
+        if (opts || 16 * (t0 + nt) > c.L) {  // else every key counts
             const int aq = clip * a.clip_len + 16 * qt + l16;
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 if (t >= nt) continue;
-                const int j0 = 16 * (t0 + t) + 4 * lg;
                 int info = 0;
                 if (opts) info = key_info(a, c, 16 * (t0 + t) + l16);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool local = j0 + e < c.nl;
-                    float x = fmaf(s[t][e], a.sc, local ? a.lb : a.gb);
-                    bool hidden = j0 + e >= c.L;
+                    const bool local = j0 + 16 * t + e < c.nl;
+                    bool hidden = j0 + 16 * t + e >= c.L;
                     if (opts) {
                         const int ki = __shfl(info, 4 * lg + e);  // from the key's own lane
                         const int f = ki & 0x3fffffff;
@@ -167,12 +160,35 @@ struct Softmax {
                         const bool seen = (ki >> 30 & 1) || (f >= c.lo && f < c.lo + c.nl && !far);
                         hidden = hidden || (local ? far : a.dedup && seen);
                     }
-                    x = hidden ? -INFINITY : x;
-                    s[t][e] = x;
-                    mx = fmaxf(mx, x);
+                    s[t][e] = hidden ? -INFINITY : s[t][e];
                 }
             }
         }
+        if (a.lb != 0.f || a.gb != 0.f) {
+            if (a.dedup && a.lb != 0.f) {
+                float mg = -INFINITY;
+#pragma unroll
+                for (int t = 0; t < KT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (t < nt && j0 + 16 * t + e >= c.nl) mg = fmaxf(mg, s[t][e]);
+                const bool first = !shifted && swap32(swap16(mg, true), true) > -INFINITY;
+                m += first ? a.lb * a.sc : 0.f;
+                shifted = shifted || first;
+            }
+            const float ls = shifted ? a.lb : 0.f;
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[t][e] += j0 + 16 * t + e < c.nl ? ls : a.gb;
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+            if (t < nt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[t][e]);
+        mx *= a.sc;
         mx = fmaxf(m, swap32(swap16(mx, true), true));
         float alpha = 1.f;
         if (__any(mx > m)) {
@@ -187,7 +203,7 @@ struct Softmax {
             if (t < nt) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], mult, nm));
+                    s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], a.sc, nm));
                     l += s[t][e];
                 }
             } else {
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a
     f32x4 o[NKB][2];
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) o[kb][0] = o[kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<KT> sm;
+    Softmax<KT> sm(a);
 
     const int tiles = (cx.L + 15) / 16;
     bf16x8 kr[KT][NKB], vr[KT][NKB];
@@ -438,7 +454,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
     f32x4 o[NC];  // o[4 b + t]: channel 64 b + W m + t of row m, in block b of width W
 #pragma unroll
     for (int j = 0; j < NC; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<1> sm;
+    Softmax<1> sm(a);
 
     const int tiles = (cx.L + 15) / 16;
     f32x4 kr[NC];
@@ -574,7 +590,6 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
                             bool ctx_mode, hipStream_t st)
 {
     const dsattn_desc &d = pl.desc;
-    constexpr float kLog2e = 1.4426950408889634f;
     TileArgs a;
     a.Q = Q;
     a.K = K;
@@ -596,19 +611,17 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.dedup = (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) ? 1 : 0;
     a.tasks = (uint32_t)d.n_clips * d.spatial * d.heads * a.nqt;
     a.per_xcd = (a.tasks + 4 * 8 - 1) / (4 * 8);
-    a.sc = pl.scale * kLog2e;
     // A softmax sees only the difference of the two biases.  It is taken from the lighter scope's scores:
     // added to the heavier one's, which are the ones that count, it would take their low bits (a local
-    // bias of -1e4 cost 1e-4 of the result, one of -1e9 all of the scores).  1e38 already hides a scope.
-    const double diff = ((double)d.bias_global - d.bias_local) * 1.4426950408889634;
-    a.lb = (float)std::max(std::min(-diff, 0.0), -1e38);
-    a.gb = (float)std::max(std::min(diff, 0.0), -1e38);
-    // A heavier bias of 2^64 and more swallows the scores beside it in 64 bits too: every key of that
-    // scope weighs the same, as on the vector kernel.
-    if (std::fabs(std::max(d.bias_local, d.bias_global)) >= 0x1p64f) {
-        a.lb = 0.5f * d.bias_local;
-        a.gb = 0.5f * d.bias_global;
-    }
+    // bias of -1e4 cost 1e-4 of the result, one of -1e9 all of the scores).  A heavier bias of 2^64 and
+    // more swallows the scores beside it in 64 bits too: every key of that scope weighs the same, as on
+    // the vector kernel.
+    const bool swallows = std::fabs(a.G ? std::max(d.bias_local, d.bias_global) : d.bias_local) >= 0x1p64f;
+    a.sc = swallows ? 1e-30f : pl.scale * 1.4426950408889634f;
+    const double diff = a.G ? ((double)d.bias_global - d.bias_local) * 1.4426950408889634 / a.sc : 0.0;
+    const double hides = 3e38 / std::max(a.sc, 1.f);  // (any scope; times sc it is still finite)
+    a.lb = (float)std::max(std::min(-diff, 0.0), -hides);
+    a.gb = (float)std::max(std::min(diff, 0.0), -hides);
     void *params[] = {&a};
     return hipLaunchKernel(pl.tile_fn, dim3(a.per_xcd * 8), dim3(256), params, 0, st);
 }

@@ -174,3 +174,12 @@ def test_scopes_far_apart_keep_the_heavier_ones_scores(bias, dtype):
     o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32", **kw)
     assert_tile_kernel(info, clip_len, n_clips, P, h)
     U.assert_parity(o, ref, "f32_strict", what=f"biases {bias}")
+    # no global scope at all, and one that the set union hides from every query of the middle clip
+    for g, dedup in (([], False), ([24, 30, 47, 30], True)):
+        # (with the heavier scope hidden, the oracle's 64 bits hold the scores beside -1e9, not -3e38)
+        ro = dict(kw, bias_local=-1e9) if dedup and bias == (-3e38, 0.0) else kw
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=dedup, **ro)
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32",
+                                    flags=B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0, **kw)
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        U.assert_parity(o, ref, "f32_strict", what=f"biases {bias} G={g}")
