@@ -28,8 +28,8 @@
 // (16x16x16 bf16 MFMA per key tile, or 16x16x32 per pair of key tiles when both scopes have an even
 // number of tiles).  The denominator is the sum of the rounded weights, taken by one more MFMA
 // with an all-ones A operand.  V^T operands come out of LDS through gfx950's transposing read.
-// Options of the scopes: the biases of the two scopes' logits enter as one shift of the raw global
-// scores (a softmax sees only their difference); a sliding window |key frame - query frame| <= r
+// Options of the scopes: the difference of the biases of the two scopes' logits (a softmax sees nothing
+// else of them) shifts the raw scores of the lighter scope down; a sliding window |key frame - query frame| <= r
 // on the local scope is a per-lane mask on the local scores; the set-union option drops, per
 // query, the global keys whose frame that query already sees.
 //
@@ -63,8 +63,10 @@ struct MfmaArgs {
     int32_t C;
     int64_t FS;   // frame stride in elements = P * C
     float sc;     // scale * log2(e), > 0
-    float gshift; // (bias_global - bias_local) / scale: the scope biases as a shift of the raw
-                  // global scores (the softmax only sees the difference of the two biases)
+    float lshift, gshift; // shifts of the raw local and global scores: zero for the scope of the heavier
+                  // bias, -|bias_global - bias_local| / scale for the other.  (A shift added to the
+                  // scores that count would take their low bits.)  A query whose global keys the set
+                  // union hides takes its local scores as they are.
     int32_t dedup;   // set union: drop a global entry whose frame the query already sees
     uint64_t gdup;   // bit j: global entry j repeats an earlier global entry
     int64_t cstride; // 0: K and V are [F, P, C].  Otherwise they are materialised contexts
@@ -480,7 +482,7 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
     // four-tile variants that have a whole SIMD's registers (the others have none to spare; the
     // planner does not pick them with that option).
     constexpr bool kDedup = NGT == 1 || (NGT == 4 && WPE == 1);
-    const bool plain_opts = a.window < 0 && a.gshift == 0.f && a.G == 16 * NGT &&
+    const bool plain_opts = a.window < 0 && a.lshift == 0.f && a.gshift == 0.f && a.G == 16 * NGT &&
                             !(kDedup && a.dedup);
 
     // set union: lane j keeps the frame of global entry j
@@ -576,15 +578,17 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
 
             // ---- softmax over keys, per query column (fp32).  The maximum is taken over raw
             // scores (scale > 0), weights are exp2(raw * sc - max * sc); masked keys sit at -inf
-            // and come out as exact zeros.  The scope bias enters as a shift of the global scores.
-            float mx = -INFINITY;
+            // and come out as exact zeros.  The scope biases enter as a shift of one scope's maximum
+            // and exponents.
+            float mg = -INFINITY, ml = -INFINITY;  // global, local
+            float ls = a.lshift;
             if (plain_opts && interior) {
                 // every ring row and every global row is a key; rows past R repeat row R - 1, so
                 // they do not change the maximum, and their weights are cleared below
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[tt][e]);
+                    for (int e = 0; e < 4; ++e) ml = fmaxf(ml, s[tt][e]);
             } else {
                 const bool g_full = a.G == 16 * NGT;  // no partly used global key tile
 #pragma unroll
@@ -592,29 +596,29 @@ __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaA
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         float x = s[tg][e];
-                        if (a.gshift != 0.f) x += a.gshift;
                         if (!g_full && !(16 * tg + 4 * lg + e < a.G)) x = -INFINITY;
                         if (kDedup && a.dedup && ((ghid >> (4 * tg + e)) & 1)) x = -INFINITY;
                         s[tg][e] = x;
-                        mx = fmaxf(mx, x);
+                        mg = fmaxf(mg, x);
                     }
+                if (kDedup && a.dedup && a.lshift != 0.f) ls = colmax(mg) == -INFINITY ? 0.f : ls;
 #pragma unroll
                 for (int tl = 0; tl < NLT; ++tl)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float x = lvalid[tl][e] ? s[NGT + tl][e] : -INFINITY;
                         s[NGT + tl][e] = x;
-                        mx = fmaxf(mx, x);
+                        ml = fmaxf(ml, x);
                     }
             }
-            mx = colmax(mx);
-            const float nm = -mx * a.sc;
+            const float mx = colmax(fmaxf(ml + ls, mg + a.gshift));
+            const float nm = -mx * a.sc, nml = fmaf(ls, a.sc, nm), nmg = fmaf(a.gshift, a.sc, nm);
             // rounded weights of key tile tt (this lane: keys 4 lg + e, query l16)
             auto weights = [&](int tt) __attribute__((always_inline)) -> bf16x4 {
                 bf16x4 pb;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    pb[e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[tt][e], a.sc, nm));  // RNE
+                    pb[e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[tt][e], a.sc, tt < NGT ? nmg : nml));  // RNE
                 if (tt > NGT) {  // a local tile after the first may reach past the ring
                     uint2 u = __builtin_bit_cast(uint2, pb);
                     u.x = pkeep[tt - NGT][0] ? u.x : 0u;

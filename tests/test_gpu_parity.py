@@ -709,3 +709,34 @@ def test_long_and_short_chunks_run_different_kernels_with_equal_results(D, h, w,
         kw = {x: y for x, y in opts.items() if x != "flags"}
         ref = U.oracle_forward(q, k, v, 16, n_clips, w, h, g, dedup="flags" in opts, **kw)
         U.assert_parity(res[0], ref, out, what=f"D={D}")
+
+
+@pytest.mark.parametrize("bias", [(-1e6, 0.0), (-1e9, 0.0), (-3e38, 0.0), (-3e38, 3e38), (0.0, -1e9),
+                                  (0.0, 1e9), (1e9, 0.0), (3e38, -3e38)])
+@pytest.mark.parametrize("clip_len,w,window,D,h,G", [
+    (16, 2, None, 160, 2, 16), (16, 4, None, 40, 4, 40), (48, 4, 5, 80, 2, 7),
+])
+def test_scopes_far_apart_keep_the_heavier_ones_scores(clip_len, w, window, D, h, G, bias):
+    """A scope damped or switched off by its bias leaves the other scope's scores as they are, also
+    where the two biases' difference is more than a float holds."""
+    n_clips, P = 4, 3
+    F = clip_len * n_clips
+    g = np.random.default_rng(8).integers(0, F, size=G).tolist()
+    q, k, v = make(F, P, h * D, 71, "iid", "bf16")
+    kw = dict(bias_local=float(np.float32(bias[0])), bias_global=float(np.float32(bias[1])), window=window)
+    # (the oracle's 64 bits keep the scores beside a bias of 1e9, not beside 3e38; a scope lighter by 1e9
+    # is as absent as one lighter by 3e38)
+    ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, window=window,
+                           bias_local=float(np.clip(bias[0], -1e9, 1e9)),
+                           bias_global=float(np.clip(bias[1], -1e9, 1e9)))
+    o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32", **kw)
+    assert info["kernel"] == 1
+    U.assert_parity(o, ref, "f32", what=f"biases {bias}")
+    # no global scope at all, and one that the set union hides from every query of the second clip
+    kw["bias_local"], kw["bias_global"] = (float(np.clip(b, -1e9, 1e9)) for b in bias)
+    for g, dedup in (([], False), ([clip_len + 7, clip_len + 8] * 2, True)):
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=dedup, **kw)
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32",
+                                    flags=B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0, **kw)
+        assert info["kernel"] == 1
+        U.assert_parity(o, ref, "f32", what=f"biases {bias} G={g}")
