@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "plan.h"
 
@@ -125,8 +126,15 @@ __device__ __forceinline__ float swap32(float x, bool max)
     return max ? fmaxf(y0, y1) : y0 + y1;
 }
 
+// 2^x, and not zero for a finite x (the instruction alone returns zero below -126; 2^100 and more below it
+// is as good as -inf): a weight of zero would make NaN of an infinity in V, which any weight leaves infinite.
+__device__ __forceinline__ float exp2_positive(float x)
+{
+    return __builtin_amdgcn_exp2f(fmaxf(x, fmaf(x, 0x1p-100f, -126.f)));
+}
+
 // The part of the kernel that both types share: masks, running softmax.  KT key tiles per step.
-template <int KT>
+template <int KT, bool POSITIVE>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
     // A shift of the local scores holds from the query's first visible global key on: the set union may
@@ -193,7 +201,7 @@ struct Softmax {
         float alpha = 1.f;
         if (__any(mx > m)) {
             // (no visible key so far: weights of zero, not of exp2(-inf + inf))
-            alpha = mx == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mx);
+            alpha = mx == -INFINITY ? 1.f : POSITIVE ? exp2_positive(m - mx) : __builtin_amdgcn_exp2f(m - mx);
             m = mx;
             l *= alpha;
         }
@@ -203,7 +211,8 @@ struct Softmax {
             if (t < nt) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], a.sc, nm));
+                    const float x = fmaf(s[t][e], a.sc, nm);
+                    s[t][e] = POSITIVE ? exp2_positive(x) : __builtin_amdgcn_exp2f(x);
                     l += s[t][e];
                 }
             } else {
@@ -242,6 +251,63 @@ __device__ __forceinline__ Task task_of(const TileArgs &a)
     return k;
 }
 
+// A bf16 task whose result has a NaN is done again, one query at a time on the vector ALUs: zero times an
+// infinity in V is NaN, a small weight times it is not, and the matrix products have zeros where there is a
+// weight (below 2^-126, and parts of larger ones).  Here a weight is zero only below 2^-149, as on the
+// vector kernel.  (Beside finite values such weights add less than 2^-126 |V|.  Looked for in every step,
+// by the smallest score, they were 1 to 6 % of the kernel; a second pass of its loop with positive parts
+// cost 3 to 5 % by the registers that the two share.)
+template <typename TO>
+__device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, const Context &cx)
+{
+    const int lane = threadIdx.x & 63, D = a.D;
+    const int64_t C = (int64_t)a.h * D, FS = (int64_t)a.P * C;
+    const int64_t rowoff = (int64_t)tk.p * C + (int64_t)tk.g * D;
+    const __bf16 *K = (const __bf16 *)a.K + rowoff, *V = (const __bf16 *)a.V + rowoff;
+    for (int i = 16 * tk.qt; i < min(16 * tk.qt + 16, a.clip_len); ++i) {
+        const int aq = tk.clip * a.clip_len + i;
+        const __bf16 *q = (const __bf16 *)a.Q + (int64_t)aq * FS + rowoff;
+        // raw score of key j, -inf if it does not exist or is hidden
+        auto score = [&](int j) -> float {
+            const __bf16 *k = K + key_row(a, cx, j) * FS;
+            float x = 0.f;
+            for (int d = 0; d < D; ++d) x = fmaf((float)q[d], (float)k[d], x);
+            const int ki = key_info(a, cx, j), f = ki & 0x3fffffff;
+            const bool far = a.window >= 0 && abs(f - aq) > a.window;
+            const bool seen = (ki >> 30 & 1) || (f >= cx.lo && f < cx.lo + cx.nl && !far);
+            return j >= cx.L || (j < cx.nl ? far : a.dedup && seen) ? -INFINITY : x;
+        };
+        float ml = -INFINITY, mg = -INFINITY;
+        for (int j = lane; j < cx.L; j += 64) {
+            const float x = score(j);
+            ml = j < cx.nl ? fmaxf(ml, x) : ml;
+            mg = j < cx.nl ? mg : fmaxf(mg, x);
+        }
+        for (int w = 32; w > 0; w >>= 1) {
+            ml = fmaxf(ml, __shfl_xor(ml, w));
+            mg = fmaxf(mg, __shfl_xor(mg, w));
+        }
+        const float ls = a.dedup && mg == -INFINITY ? 0.f : a.lb;
+        const float m = fmaxf(ml + ls, mg + a.gb) * a.sc;
+        float l = 0.f, o[3] = {0.f, 0.f, 0.f};  // channels lane, lane + 64, lane + 128
+        for (int j0 = 0; j0 < cx.L; j0 += 64) {
+            const int j = j0 + lane;
+            const float w = exp2f(fmaf(score(j) + (j < cx.nl ? ls : a.gb), a.sc, -m));
+            l += w;
+            for (int u = 0; u < min(64, cx.L - j0); ++u) {
+                const float wu = __shfl(w, u);
+                const __bf16 *v = V + key_row(a, cx, j0 + u) * FS;
+                for (int r = 0; r < 3; ++r)
+                    if (lane + 64 * r < D) o[r] = fmaf(wu, (float)v[lane + 64 * r], o[r]);
+            }
+        }
+        for (int w = 32; w > 0; w >>= 1) l += __shfl_xor(l, w);
+        TO *out = (TO *)a.O + (int64_t)aq * FS + rowoff;
+        for (int r = 0; r < 3; ++r)
+            if (lane + 64 * r < D) out[lane + 64 * r] = (TO)(o[r] * (1.0f / l));
+    }
+}
+
 // ---------------------------------------------------------------- bf16
 
 // LDS of one wavefront: the V rows of two key tiles, padded so that the rows spread over the banks
@@ -250,7 +316,7 @@ constexpr int kBf16Tiles = 2;  // key tiles per step
 
 // NKB = ceil(D / 32)
 template <int NKB, bool OUT_F32>
-__global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a)
+__global__ __launch_bounds__(256, NKB == 1 ? 6 : 2) void tile_attn_bf16_kernel(const TileArgs a)
 {
     constexpr int KT = kBf16Tiles;
     constexpr int RS = vrow_bytes(NKB);
@@ -283,7 +349,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a
     f32x4 o[NKB][2];
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) o[kb][0] = o[kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<KT> sm(a);
+    Softmax<KT, false> sm(a);
 
     const int tiles = (cx.L + 15) / 16;
     bf16x8 kr[KT][NKB], vr[KT][NKB];
@@ -338,9 +404,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a
 #pragma unroll
                 for (int u = 0; u < 2; ++u) o[kb][u] *= alpha;
         }
-        // The weights as three bf16 numbers each: 8 bits, the next 8, and the 8 that are left.  A
-        // part is cut off one bit pattern lower, so that none of a positive weight is zero: zero
-        // times an infinity in V would not be what the weight times it is.
+        // The weights as three bf16 numbers each: 8 bits, the next 8, and the 8 that are left.
         u32x4 w[3];
 #pragma unroll
         for (int t = 0; t < KT; ++t)
@@ -349,11 +413,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a
                 float x0 = s[t][e], x1 = s[t][e + 1];
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    uint32_t b0 = __builtin_bit_cast(uint32_t, x0), b1 = __builtin_bit_cast(uint32_t, x1);
-                    if (k < 2) {
-                        b0 = __builtin_elementwise_sub_sat(b0, 1u);
-                        b1 = __builtin_elementwise_sub_sat(b1, 1u);
-                    }
+                    const uint32_t b0 = __builtin_bit_cast(uint32_t, x0), b1 = __builtin_bit_cast(uint32_t, x1);
                     w[k][2 * t + e / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302);  // both high halves
                     x0 -= __builtin_bit_cast(float, b0 & 0xffff0000u);
                     x1 -= __builtin_bit_cast(float, b1 & 0xffff0000u);
@@ -383,6 +443,17 @@ __global__ __launch_bounds__(256, 2) void tile_attn_bf16_kernel(const TileArgs a
             }
     }
 
+    bool nan = false;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            nan = nan || __builtin_isunordered(o[kb][u][0], o[kb][u][1]) ||
+                  __builtin_isunordered(o[kb][u][2], o[kb][u][3]);
+    if (__any(nan)) {
+        vector_task<std::conditional_t<OUT_F32, float, __bf16>>(a, tk, cx);
+        return;
+    }
     const float inv = sm.inverse_sum();
     if (!qok) return;
 #pragma unroll
@@ -419,7 +490,7 @@ struct Floats<1> {
 
 // NF blocks of 64 channels and, with WL = 1, 2 or 4, one of 16 WL channels: 64 NF < D <= 64 NF + 16 WL
 template <int NF, int WL>
-__global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
+__global__ __launch_bounds__(256, NF == 0 && WL == 2 ? 7 : 2) void tile_attn_f32_kernel(const TileArgs a)
 {
     constexpr int NC = 4 * NF + WL;  // 16-byte chunks per lane of a Q or K row; 16-channel tiles of O^T
     using Last = Floats<WL>;
@@ -454,7 +525,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
     f32x4 o[NC];  // o[4 b + t]: channel 64 b + W m + t of row m, in block b of width W
 #pragma unroll
     for (int j = 0; j < NC; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<1> sm(a);
+    Softmax<1, true> sm(a);
 
     const int tiles = (cx.L + 15) / 16;
     f32x4 kr[NC];

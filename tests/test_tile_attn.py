@@ -183,3 +183,70 @@ def test_scopes_far_apart_keep_the_heavier_ones_scores(bias, dtype):
                                     flags=B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0, **kw)
         assert_tile_kernel(info, clip_len, n_clips, P, h)
         U.assert_parity(o, ref, "f32_strict", what=f"biases {bias} G={g}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("clip_len", [3, 40])
+def test_an_infinity_in_v_meets_small_weights(clip_len, dtype):
+    """The smallest weights are not zero beside an infinity: infinite as in the generic kernel, where
+    the weight is subnormal (90 to 102 below the others' scores) or a part of it would be (84).  At 110 the
+    generic kernel's weight is zero, and zero times infinity is NaN; the fp32 tile kernel's never is.
+    Finite values are off by at most 2^-126 of themselves, the weights below the smallest normal number."""
+    n_clips, P, D = 1, 2, 64
+    for below in (84.0, 90.0, 96.0, 102.0, 110.0):
+        q = torch.ones(clip_len, P, D, device=DEV)
+        k = torch.zeros(clip_len, P, D, device=DEV)
+        k[-1] = -below / 8.0
+        for special in (float("inf"), float("-inf"), 1e38, -2e38):
+            v = torch.linspace(-1.0, 1.0, clip_len, device=DEV)[:, None, None].repeat(1, P, D)
+            v[-1, 0, 5] = special
+            t = [x.to(synth.torch_dtype(dtype)) for x in (q, k, v)]
+            o, info = U.library_forward(*t, clip_len, n_clips, 0, 1, [], out_dtype="f32")
+            assert_tile_kernel(info, clip_len, n_clips, P, 1)
+            og, _ = U.library_forward(*t, clip_len, n_clips, 0, 1, [], out_dtype="f32",
+                                      flags=B.DSATTN_FLAG_FORCE_GENERIC)
+            if np.isinf(special):
+                for x, nan in ((o, below > 104.0 and dtype == "bf16"), (og, below > 104.0)):
+                    assert (x[:, 0, 5].isnan() if nan else x[:, 0, 5] == special).all(), (below, special)
+                o[:, 0, 5] = og[:, 0, 5] = 0.0
+            # (the exponent, of size 120 to 160 in base 2, is rounded to 2^-17 of its unit in both kernels)
+            big = 0.0 if np.isinf(special) else abs(special)
+            bar = 2e-5 + big * (2.0 ** -126 + 2 * 2.0 ** -17 * np.exp(-below))
+            assert float((o.double() - og.double()).abs().max()) <= bar, (below, special)
+
+
+@pytest.mark.parametrize("D,h", [(40, 2), (160, 1), (72, 3)])
+@pytest.mark.parametrize("opts", [{}, {"window": 4, "dedup": True}, {"bias_global": 2.0, "dedup": True},
+                                  {"bias_local": 3.0, "window": 0}, {"bias_global": 1e9, "dedup": True}])
+def test_tasks_with_a_nan_are_done_again_with_every_option(opts, D, h):
+    """A NaN in one channel of V sends every bf16 task through the second pass: that channel is NaN, all
+    others are the generic kernel's numbers, on the tensors and on a materialised context."""
+    clip_len, n_clips, w, P = 24, 4, 5, 2
+    F = clip_len * n_clips
+    g = np.random.default_rng(9).integers(0, F, size=80).tolist()
+    opts = dict(opts)
+    flags = B.DSATTN_FLAG_DEDUP_GLOBAL if opts.pop("dedup", False) else 0
+    q, k, v = make(F, P, h * D, "bf16")
+    v[:, :, D - 1] = float("nan")
+    for out in ("f32", "bf16"):
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, flags=flags, **opts)
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        og, _ = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out,
+                                  flags=flags | B.DSATTN_FLAG_FORCE_GENERIC, **opts)
+        assert o[:, :, D - 1].isnan().all() and og[:, :, D - 1].isnan().all()
+        keep = [c for c in range(h * D) if c != D - 1]
+        a, b = o[:, :, keep].double(), og[:, :, keep].double()
+        if opts.get("bias_global") == 1e9:      # (the generic kernel adds the bias to the scores that count)
+            vz = torch.nan_to_num(v)
+            ref = U.oracle_forward(q, k, vz, clip_len, n_clips, w, h, g, dedup=bool(flags), **opts)
+            b = torch.from_numpy(ref).to(DEV)[:, :, keep]
+        bar = 2e-5 + (0 if out == "f32" else 2 * U.bf16_half_ulp(b.cpu().numpy()).max())
+        assert float((a - b).abs().max()) <= bar
+    plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, flags=flags, **opts)
+    ctx = [torch.empty(n_clips, plan.lk_max, P, h * D, dtype=q.dtype, device=DEV) for _ in range(2)]
+    o2 = torch.empty_like(q)
+    B.dsattn_gather_context(plan, k, v, *ctx)
+    B.dsattn_forward_ctx(plan, q, *ctx, o2)
+    torch.cuda.synchronize()
+    plan.close()
+    assert torch.equal(o2[:, :, keep], o[:, :, keep])
