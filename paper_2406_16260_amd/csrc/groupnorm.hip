@@ -27,6 +27,8 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+constexpr int kGnUnroll = 4;  // rows of a bite per row phase of a workgroup
+
 struct GnShape {
     int vec;        // elements per 16-byte lane
     int ch;         // lanes per row = C / vec
@@ -54,14 +56,14 @@ bool gn_shape(const dsattn_gn_desc &d, GnShape &s)
     // whole tensor, at least one per clip, every one with a few rows.
     const int64_t rows_per_clip = (int64_t)d.clip_len * d.spatial;
     const int64_t want = std::max<int64_t>(1, (256 * 8) / d.n_clips);
-    const int64_t max_bpc = std::max<int64_t>(1, rows_per_clip / (4 * s.rpb));
+    const int64_t max_bpc = std::max<int64_t>(1, rows_per_clip / (kGnUnroll * s.rpb));
     s.bpc = (int)std::min<int64_t>(want, max_bpc);
     // One workgroup of about eight wavefronts per compute unit in the statistics pass (256 to 1,024
     // of them and two to eight loads in flight per thread measure the same within 4 %, and fewer
     // leave the finalising kernel less to add up), twice as many in the apply pass: all are resident
     // and walk the tensor together from one end to the other, which both passes rely on.  And no
-    // more than there are bites of 4 * rpb rows: every one reads at least a row.
-    const int64_t bites = (s.rows + 4 * s.rpb - 1) / (4 * s.rpb);
+    // more than there are bites of kGnUnroll * rpb rows: every one reads at least a row.
+    const int64_t bites = (s.rows + kGnUnroll * s.rpb - 1) / (kGnUnroll * s.rpb);
     s.blocks = (int)std::min<int64_t>({(int64_t)d.n_clips * s.bpc, bites, 256});
     s.apply_blocks = (int)std::min<int64_t>(bites, 512);
     return true;
@@ -97,27 +99,39 @@ __device__ inline void gn_add(GnSums &a, double n, double s1, double s2, double 
     a.s2 += s2 + shift * (2.0 * s1 + n * shift);
 }
 
-// Statistics pass: one read of X gives, per workgroup and group, the count, the mean and the
+// What a workgroup reports of a group: mean (two floats) and sum of squared deviations about it.  (The
+// count follows from the workgroup's rows.)
+struct alignas(16) GnPart {
+    float mean, mean_lo;
+    double m2;
+};
+static_assert(sizeof(GnPart) == 16, "");
+
+// Statistics pass: one read of X gives, per workgroup and group, the mean and the
 // sum of squared deviations about that mean of the elements the workgroup saw.  Every thread
-// accumulates sum(x - p) and sum((x - p)^2) about a pilot p of its own (fp32, moved to fp64 every 32
-// rows; the first element it reads: same channel, nearby rows, so the sums stay small and nothing cancels); one
-// thread per group then adds up, in a fixed order, the threads that hold the group's channels
-// about the pilot of the first of them.  Thread (x, y) = (lane of the row, row phase).  A lane's
+// accumulates sum(x - p) and sum((x - p)^2) about a pilot p of its own, the first element it reads, in fp32
+// that moves to fp64 every 32 rows; one thread per group then adds up in fp64, in a fixed order, the
+// threads that hold the group's channels about the pilot of the first of them.  A thread's rows come from
+// the whole video, so its deviations are of the size of the group's spread, however large the mean is:
+// nothing cancels that the spread does not outweigh.  Thread (x, y) = (lane of the row, row phase).  A lane's
 // VEC channels lie in group g0 (the first `split` of them) and, when the lane straddles a
 // boundary, in group g0 + 1.  Means travel as a pair of floats (leading part, remainder), so that
-// a mean much larger than the spread loses nothing.  partial is [workgroup][groups][4].
+// a mean much larger than the spread loses nothing, sums of squared deviations as fp64: the sum over
+// a workgroup's part is beyond fp32 long before a square of it is.  partial is [workgroup][groups] of
+// GnPart.
 //
 // Bound by HBM reads.  All workgroups are resident and take the rows in interleaved bites, so the
 // chip reads the tensor as one linear stream.  (Merging the threads with Chan's update, two fp64
 // divisions per step, kept one thread per group busy for some 4 us at the end of every workgroup.)
 template <typename T>
 __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restrict__ X,
-                                                          float *__restrict__ partial, int ch,
+                                                          GnPart *__restrict__ partial, int ch,
                                                           int cg, int groups, int64_t rows_all)
 {
     constexpr int VEC = sizeof(T) == 2 ? 8 : 4;
-    constexpr int UNR = 4;  // independent row loads in flight per thread
-    extern __shared__ float red[];  // [8][blockDim.y][ch]: (count, pilot, sum, sum of squares) for g0, then g0 + 1
+    constexpr int UNR = kGnUnroll;  // independent row loads in flight per thread
+    // [4][blockDim.y][ch] doubles: sum, sum of squares for g0, then g0 + 1; then [3] floats: rows, pilots
+    extern __shared__ double red[];
     const int lane = threadIdx.x, ry = threadIdx.y, ny = blockDim.y;
     const int g0 = (lane * VEC) / cg;
     const int split = min(VEC, (g0 + 1) * cg - lane * VEC);
@@ -189,55 +203,59 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
         q1 += lo ? 0.0 : sq[i];
     }
     const int t = ry * ch + lane, nt = ny * ch;
-    red[0 * nt + t] = (float)rows * (float)split;
-    red[1 * nt + t] = p0;
-    red[2 * nt + t] = (float)a0;
-    red[3 * nt + t] = (float)q0;
-    red[4 * nt + t] = (float)rows * (float)(VEC - split);
-    red[5 * nt + t] = p1;
-    red[6 * nt + t] = (float)a1;
-    red[7 * nt + t] = (float)q1;
+    float *const redf = (float *)(red + 4 * nt);
+    red[0 * nt + t] = a0;
+    red[1 * nt + t] = q0;
+    red[2 * nt + t] = a1;
+    red[3 * nt + t] = q1;
+    redf[0 * nt + t] = (float)rows;
+    redf[1 * nt + t] = p0;
+    redf[2 * nt + t] = p1;
     __syncthreads();
     for (int g = t; g < groups; g += nt) {
         const int l0 = (g * cg) / VEC, l1 = ((g + 1) * cg - 1) / VEC;
         // (row phase 0 of every workgroup has read at least one row: its pilot is an element)
-        const double P = (l0 * VEC) / cg == g ? red[1 * nt + l0] : red[5 * nt + l0];
+        const double P = (l0 * VEC) / cg == g ? redf[1 * nt + l0] : redf[2 * nt + l0];
         GnSums m = {0.0, 0.0, 0.0};
         for (int y = 0; y < ny; ++y)
             for (int l = l0; l <= l1; ++l) {
-                const int e = y * ch + l, k = (l * VEC) / cg == g ? 0 : 4;
-                const float n = red[k * nt + e];
-                if (n > 0.f)
-                    gn_add(m, n, red[(k + 2) * nt + e], red[(k + 3) * nt + e],
-                           (double)red[(k + 1) * nt + e] - P);
+                const int e = y * ch + l, k = (l * VEC) / cg == g ? 0 : 1;
+                const int s0 = min(VEC, ((l * VEC) / cg + 1) * cg - l * VEC);  // the lane's split
+                const double n = (double)redf[e] * (k ? VEC - s0 : s0);
+                if (n > 0.0)
+                    gn_add(m, n, red[2 * k * nt + e], red[(2 * k + 1) * nt + e],
+                           (double)redf[(1 + k) * nt + e] - P);
             }
-        float *out = partial + ((int64_t)blockIdx.x * groups + g) * 4;
-        const double mean = P + m.s1 / m.n;
+        const double mean = P + m.s1 / m.n, m2 = m.s2 - m.s1 * m.s1 / m.n;
         const float hi = (float)mean;
-        out[0] = (float)m.n;
-        out[1] = hi;
-        out[2] = (float)(mean - (double)hi);
-        const double m2 = m.s2 - m.s1 * m.s1 / m.n;
-        out[3] = (float)(m2 < 0.0 ? 0.0 : m2);  // (a NaN stays one)
+        GnPart part;
+        part.mean = hi;
+        part.mean_lo = (float)(mean - (double)hi);
+        part.m2 = m2 < 0.0 ? 0.0 : m2;  // (a NaN stays one)
+        partial[(int64_t)blockIdx.x * groups + g] = part;
     }
 }
 
 // One workgroup per group adds up the workgroups' moments in fp64, in a fixed order, about the
 // first one's mean: stats[g] = mean, stats[groups + g] = 1 / sqrt(M2 / n + eps) (the biased
 // variance), also to the caller's own array when there is one.
-__global__ __launch_bounds__(256) void gn_finalize_kernel(const float4 *__restrict__ partial,
+__global__ __launch_bounds__(256) void gn_finalize_kernel(const GnPart *__restrict__ partial,
                                                           float *__restrict__ stats,
                                                           float *__restrict__ out, int n_blocks,
-                                                          int groups, float eps)
+                                                          int groups, int cg, int64_t rows_all, int bite,
+                                                          float eps)
 {
     __shared__ double rn[256], rm[256], rq[256];
     const int g = blockIdx.x, t = threadIdx.x;
-    const float4 f = partial[g];
-    const double P = (double)f.y + (double)f.z;
+    const GnPart f = partial[g];
+    const double P = (double)f.mean + (double)f.mean_lo;
+    const int64_t bites = (rows_all + bite - 1) / bite, last = (bites - 1) % n_blocks;
     GnSums m = {0.0, 0.0, 0.0};
     for (int i = t; i < n_blocks; i += 256) {
-        const float4 p = partial[(int64_t)i * groups + g];
-        gn_add(m, p.x, 0.0, p.w, ((double)p.y + (double)p.z) - P);
+        const GnPart p = partial[(int64_t)i * groups + g];
+        // workgroup i took bites i, i + n_blocks, ..; the last one of all may be cut short
+        const int64_t rows = ((bites - 1 - i) / n_blocks + 1) * bite - (i == last ? bites * bite - rows_all : 0);
+        gn_add(m, (double)rows * cg, 0.0, p.m2, ((double)p.mean + (double)p.mean_lo) - P);
     }
     rn[t] = m.n;
     rm[t] = m.s1;
@@ -278,7 +296,7 @@ __global__ __launch_bounds__(1024) void gn_apply_kernel(const uint4 *X, uint4 *Y
                                                         int cg, int groups, int64_t rows_all)
 {
     constexpr int VEC = sizeof(T) == 2 ? 8 : 4;
-    constexpr int UNR = 4;
+    constexpr int UNR = kGnUnroll;
     const int lane = threadIdx.x, ry = threadIdx.y, ny = blockDim.y;
     const int g0 = (lane * VEC) / cg;
     const int split = min(VEC, (g0 + 1) * cg - lane * VEC);
@@ -380,15 +398,16 @@ hipError_t gn_enqueue(const dsattn_gn_desc &d, const GnShape &s, const void *X, 
     float *partial = (float *)workspace;
     float *wstats = partial + 4 * (size_t)d.n_clips * s.bpc * d.groups;
     const dim3 grid(s.blocks), block(s.ch, s.rpb);
-    const size_t lds = 8 * (size_t)s.ch * s.rpb * sizeof(float);
+    const size_t lds = (size_t)s.ch * s.rpb * (4 * sizeof(double) + 3 * sizeof(float));
 
     const bool stream = (size_t)s.rows * s.ch * 16 >= kGnStreamBytes;
 #define DSATTN_GN_RUN(T)                                                                          \
     do {                                                                                          \
         hipLaunchKernelGGL((gn_moments_kernel<T>), grid, block, lds, st, (const uint4 *)X,        \
-                           partial, s.ch, s.cg, d.groups, s.rows);                                \
+                           (GnPart *)partial, s.ch, s.cg, d.groups, s.rows);                      \
         hipLaunchKernelGGL(gn_finalize_kernel, dim3(d.groups), dim3(256), 0, st,                  \
-                           (const float4 *)partial, wstats, stats, s.blocks, d.groups, d.eps);    \
+                           (const GnPart *)partial, wstats, stats, s.blocks, d.groups, s.cg,      \
+                           s.rows, kGnUnroll * s.rpb, d.eps);                                     \
         auto *apply = stream ? &gn_apply_kernel<T, true> : &gn_apply_kernel<T, false>;             \
         hipLaunchKernelGGL(apply, dim3(s.apply_blocks), block, 0, st, (const uint4 *)X, (uint4 *)Y,   \
                            (const float *)wstats, gamma, beta, s.ch, s.cg, d.groups, s.rows);     \

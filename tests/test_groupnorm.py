@@ -262,3 +262,25 @@ def test_groupnorm_long_sums_keep_fp32_statistics():
         xd = x[:, :, g * 10:g * 10 + 10].double()
         want = 1.0 / torch.sqrt(((xd - xd.mean()) ** 2).mean() + 1e-5)
         assert abs(stats[1, g].item() / want.item() - 1.0) <= 4 * 2.0 ** -24
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sigma", [3e17, 1e-21])
+def test_groupnorm_spreads_at_the_ends_of_the_range(sigma, dtype):
+    """Sums of squared deviations beyond fp32's range, and below it, in one workgroup: no single
+    square leaves the range, so the statistics are right.  8,192 elements a workgroup and group, about
+    7e38 and 8e-39 in sum.  Bound at the lower end: 64 squares of 1e-42 are each rounded to a multiple of
+    2^-149, 0.14 % of one; their average is off by less."""
+    clip_len, n_clips, P, C, groups = 16, 16, 64, 512, 4
+    x = synth.make_tensor(clip_len * n_clips, P, C, 33, "iid", "f32")
+    x = (x * sigma).to(synth.torch_dtype(dtype)).to(DEV)
+    eps = 0.0
+    ref, mean, var = oracle.groupnorm(x.cpu().double().numpy(), clip_len, n_clips, groups, eps=eps)
+    y, stats = run_gn(x, clip_len, n_clips, groups, eps=eps)
+    st = stats.cpu().double().numpy()
+    rtol = 3e-6 if sigma > 1 else 1.4e-3
+    np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var), rtol=rtol, atol=0)
+    np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6 * sigma)
+    err = np.abs(y.cpu().double().numpy() - ref)
+    assert (err <= 1e-5 + rtol * np.abs(ref) + (0 if dtype == "f32" else U.bf16_half_ulp(ref))).all()
