@@ -283,9 +283,10 @@ __global__ __launch_bounds__(256) void gn_finalize_kernel(const GnPart *__restri
     }
 }
 
-// Apply pass: y = (x - mean) * (rstd * gamma) + beta, the statistics pass's walk from the other
-// end.  A thread keeps one lane of the row, so its channels' mean, factor and offset are loaded
-// once and stay in registers.  (Fetched anew for every 16 bytes of X, with gamma and beta that was
+// Apply pass: y = (x - mean) * rstd * gamma + beta, the statistics pass's walk from the other
+// end.  A thread keeps one lane of the row, so its channels' mean, factors and offset are loaded
+// once and stay in registers.  (rstd * gamma as one factor, which may leave fp32's range where y does
+// not, is 0.6 % faster: 483 against 486 us a call at 2,304 x 160 x 1,280 bf16.)  (Fetched anew for every 16 bytes of X, with gamma and beta that was
 // 64 bytes of table reads per 16 bytes of tensor and 1,630 us at 2,304 x 160 x 1,280 bf16.)  The walk
 // goes backwards because what the statistics pass read last is still in the 256 MB cache.
 template <typename T, bool STREAM>
@@ -300,12 +301,13 @@ __global__ __launch_bounds__(1024) void gn_apply_kernel(const uint4 *X, uint4 *Y
     const int lane = threadIdx.x, ry = threadIdx.y, ny = blockDim.y;
     const int g0 = (lane * VEC) / cg;
     const int split = min(VEC, (g0 + 1) * cg - lane * VEC);
-    float mu[VEC], sc[VEC], be[VEC];
+    float mu[VEC], rs[VEC], ga[VEC], be[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
         const int c = lane * VEC + k, g = k < split ? g0 : g0 + 1;
         mu[k] = stats[g];
-        sc[k] = stats[groups + g] * (gamma ? gamma[c] : 1.f);
+        rs[k] = stats[groups + g];
+        ga[k] = gamma ? gamma[c] : 1.f;
         be[k] = beta ? beta[c] : 0.f;
     }
     auto load = [&](int64_t i) __attribute__((always_inline)) -> uint4 {
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(1024) void gn_apply_kernel(const uint4 *X, uint4 *Y
         float x[8], y[8];
         unpack(v, x, (T *)nullptr);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) y[k] = fmaf(x[k] - mu[k], sc[k], be[k]);
+        for (int k = 0; k < VEC; ++k) y[k] = fmaf((x[k] - mu[k]) * rs[k], ga[k], be[k]);
         uint4 o;
         if constexpr (sizeof(T) == 2) {
             uint32_t w[4];

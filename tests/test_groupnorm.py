@@ -284,3 +284,24 @@ def test_groupnorm_spreads_at_the_ends_of_the_range(sigma, dtype):
     np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6 * sigma)
     err = np.abs(y.cpu().double().numpy() - ref)
     assert (err <= 1e-5 + rtol * np.abs(ref) + (0 if dtype == "f32" else U.bf16_half_ulp(ref))).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_groupnorm_affine_factors_meet_the_normalised_value(dtype):
+    """gamma multiplies the normalised value: 1 / sigma times gamma alone may leave fp32's range where
+    the result does not (a constant tensor with a large gamma, large values with a small one)."""
+    clip_len, n_clips, P, C, groups = 4, 3, 11, 64, 4
+    gamma = torch.full((C,), 1e37, device=DEV)
+    beta = torch.linspace(-1.0, 1.0, C, device=DEV)
+    x = torch.full((12, P, C), 3.5, dtype=synth.torch_dtype(dtype), device=DEV)
+    y, _ = run_gn(x, clip_len, n_clips, groups, gamma, beta)
+    assert torch.equal(y, beta.to(y.dtype).expand_as(y))
+    x = (synth.make_tensor(12, P, C, 34, "iid", "f32") * 1e17).to(x.dtype).to(DEV)
+    gamma.fill_(3e-26)
+    ref, _, _ = oracle.groupnorm(x.cpu().double().numpy(), clip_len, n_clips, groups, eps=1e-5,
+                                 gamma=gamma.cpu().double().numpy())
+    y, _ = run_gn(x, clip_len, n_clips, groups, gamma)
+    # a few roundings of fp32 (the mean's by its own size), and that of a bf16 result
+    np.testing.assert_allclose(y.cpu().double().numpy(), ref, atol=8 * 2.0 ** -24 * 3e-26,
+                               rtol=8 * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0))
