@@ -644,9 +644,12 @@ const void *f32_fn(int D)
 void tile_attn_plan(dsattn_plan_t &pl)
 {
     const dsattn_desc &d = pl.desc;
-    // tasks are numbered in 31 bits (a plan's frame numbers have 24: room for the flag beside them)
+    // A launch has less than 2^32 threads (64 a task, whole workgroups on every XCD); above, the vector
+    // kernel takes what it can.  (Tasks are numbered in 31 bits; a plan's frame numbers have 24: room for
+    // the flag beside them.)
     const int64_t nqt = (d.clip_len + 15) / 16, units = (int64_t)d.n_clips * d.spatial * d.heads;
-    if (units > 0x7fffffffLL / nqt) return;
+    constexpr int64_t kMaxTasks = (((int64_t)1 << 32) / (8 * 256) - 1) * 32;
+    if (units > kMaxTasks / nqt) return;
     // rows are whole 16-byte chunks
     const bool f32 = d.io_dtype == DSATTN_F32;
     if (d.head_dim % (f32 ? 4 : 8) != 0) return;

@@ -230,6 +230,16 @@ def test_planner_fallbacks_and_overrides(monkeypatch):
         plan.close()
 
 
+def test_tile_kernel_leaves_launches_of_2_to_the_32_threads_to_the_generic_kernel():
+    # a clip of 80 frames is five tasks of 64 threads a position: 67,108,832 tasks are 32 short of 2^26, whose
+    # launch would have 2^32 threads
+    for P, threads in ((13421766, 256), (13421767, 64)):
+        plan = B.dsattn_plan(80, 1, 0, P, 1, 8, [], device=-1)
+        i = B.dsattn_plan_launch_info(plan)
+        plan.close()
+        assert (i["kernel"], i["block_threads"], i["n_tasks"]) == (0, threads, P * (5 if threads == 256 else 1))
+
+
 def test_flags_are_validated_and_dedup_limits_the_planner():
     lib = B.load()
     d = B.DsattnDesc(16, 4, 2, 4, 2, 160, B.DSATTN_BF16, B.DSATTN_BF16, 0.0, 8, 0.0, 0.0, 0)
