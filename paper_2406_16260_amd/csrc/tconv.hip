@@ -654,8 +654,11 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
     if ((320 + 2 * (int64_t)d.reach * d.spatial) * d.c_in * es >= ((int64_t)1 << 31)) return nullptr;
     constexpr int64_t kMaxTiles = 0x7fffffffLL / 2;
     if (f32) {
+        // a workgroup per tile, and a launch has less than 2^32 threads; above, the vector kernel takes what
+        // it can (a few output channels: it has one thread each, a tile 256 for 64 of them)
         const ConvVariant &v = kConvVariants[kTileF32];
-        return conv_tiles(v, M, d.c_out, groups) <= kMaxTiles ? &v : nullptr;
+        constexpr int64_t kMax = ((int64_t)1 << 32) / 256 - kXcds;
+        return conv_tiles(v, M, d.c_out, groups) <= kMax ? &v : nullptr;
     }
     // Large problems: of the persistent kernels the one with the least multiplied-out area (padding
     // of the last row and column tiles), then the larger tile (fewer epilogues).

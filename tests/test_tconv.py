@@ -465,6 +465,14 @@ def test_conv_falls_back_when_offsets_would_not_fit_32_bits():
     assert B.dsattn_temporal_conv_info(16, 4, 40000, 1280, 64, 1)["kernel"] == 1
 
 
+def test_fp32_launches_of_2_to_the_32_threads_fall_back():
+    # 2^24 tiles of 64 rows would be a launch of 2^32 threads; the vector kernel has a thread per output
+    rows = 64 * ((1 << 24) - 8)
+    for r, tile_m in ((rows, 64), (rows + 1, 0)):
+        assert B.dsattn_linear_info(r, 4, 1, 1, io_dtype=B.DSATTN_F32)["tile_m"] == tile_m
+        assert B.dsattn_temporal_conv_info(1, 1, r, 4, 1, 0, io_dtype=B.DSATTN_F32)["tile_m"] == tile_m
+
+
 @pytest.mark.gpu
 def test_conv_and_linear_in_hip_graph_replays():
     """After one eager call on the device (which raises the kernel's LDS limit once), both entry
