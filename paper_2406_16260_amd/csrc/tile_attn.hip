@@ -251,12 +251,29 @@ __device__ __forceinline__ Task task_of(const TileArgs &a)
     return k;
 }
 
-// A bf16 task whose result has a NaN is done again, one query at a time on the vector ALUs: zero times an
-// infinity in V is NaN, a small weight times it is not, and the matrix products have zeros where there is a
-// weight (below 2^-126, and parts of larger ones).  Here a weight is zero only below 2^-149, as on the
+// A bf16 task whose result has a NaN and whose V rows have an infinity is done again, one query at a time
+// on the vector ALUs: zero times an infinity in V is NaN, a small weight times it is not, and the matrix
+// products have zeros where there is a weight (below 2^-126, and parts of larger ones).  Here a weight is zero only below 2^-149, as on the
 // vector kernel.  (Beside finite values such weights add less than 2^-126 |V|.  Looked for in every step,
 // by the smallest score, they were 1 to 6 % of the kernel; a second pass of its loop with positive parts
-// cost 3 to 5 % by the registers that the two share.)
+// cost 3 to 5 % by the registers that the two share.  12 clips of 24 frames x 135 positions, 5 heads of 64: 45 us
+// a single call, 53 with a NaN and no infinity in every head, 870 with infinities in every head; the vector
+// kernel 200.)
+__device__ __forceinline__ bool infinity_in_v(const TileArgs &a, const Task &tk, const Context &cx)
+{
+    const int64_t C = (int64_t)a.h * a.D, FS = (int64_t)a.P * C;
+    const __bf16 *V = (const __bf16 *)a.V + (int64_t)tk.p * C + (int64_t)tk.g * a.D;
+    bool inf = false;
+    for (int j = threadIdx.x & 63; j < cx.L; j += 64) {
+        const __bf16 *v = V + key_row(a, cx, j) * FS;
+        for (int d = 0; d < a.D; d += 8) {
+            const bf16x8 x = *(const bf16x8 *)(v + d);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) inf = inf || __builtin_fabsf((float)x[e]) == INFINITY;
+        }
+    }
+    return __any(inf);
+}
 template <typename TO>
 __device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, const Context &cx)
 {
@@ -271,7 +288,11 @@ __device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, c
         auto score = [&](int j) -> float {
             const __bf16 *k = K + key_row(a, cx, j) * FS;
             float x = 0.f;
-            for (int d = 0; d < D; ++d) x = fmaf((float)q[d], (float)k[d], x);
+            for (int d = 0; d < D; d += 8) {
+                const bf16x8 y = *(const bf16x8 *)(q + d), z = *(const bf16x8 *)(k + d);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x = fmaf((float)y[e], (float)z[e], x);
+            }
             const int ki = key_info(a, cx, j), f = ki & 0x3fffffff;
             const bool far = a.window >= 0 && abs(f - aq) > a.window;
             const bool seen = (ki >> 30 & 1) || (f >= cx.lo && f < cx.lo + cx.nl && !far);
@@ -450,7 +471,7 @@ __global__ __launch_bounds__(256, NKB == 1 ? 6 : 2) void tile_attn_bf16_kernel(c
         for (int u = 0; u < 2; ++u)
             nan = nan || __builtin_isunordered(o[kb][u][0], o[kb][u][1]) ||
                   __builtin_isunordered(o[kb][u][2], o[kb][u][3]);
-    if (__any(nan)) {
+    if (__any(nan) && infinity_in_v(a, tk, cx)) {
         vector_task<std::conditional_t<OUT_F32, float, __bf16>>(a, tk, cx);
         return;
     }

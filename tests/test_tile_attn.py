@@ -218,16 +218,17 @@ def test_an_infinity_in_v_meets_small_weights(clip_len, dtype):
 @pytest.mark.parametrize("D,h", [(40, 2), (160, 1), (72, 3)])
 @pytest.mark.parametrize("opts", [{}, {"window": 4, "dedup": True}, {"bias_global": 2.0, "dedup": True},
                                   {"bias_local": 3.0, "window": 0}, {"bias_global": 1e9, "dedup": True}])
-def test_tasks_with_a_nan_are_done_again_with_every_option(opts, D, h):
-    """A NaN in one channel of V sends every bf16 task through the second pass: that channel is NaN, all
-    others are the generic kernel's numbers, on the tensors and on a materialised context."""
+def test_tasks_with_infinities_are_done_again_with_every_option(opts, D, h):
+    """Infinities of both signs in one channel of V send every bf16 task of their head through the second
+    pass: that channel is NaN, all others are the generic kernel's numbers, on the tensors and on a
+    materialised context."""
     clip_len, n_clips, w, P = 24, 4, 5, 2
     F = clip_len * n_clips
     g = np.random.default_rng(9).integers(0, F, size=80).tolist()
     opts = dict(opts)
     flags = B.DSATTN_FLAG_DEDUP_GLOBAL if opts.pop("dedup", False) else 0
     q, k, v = make(F, P, h * D, "bf16")
-    v[:, :, D - 1] = float("nan")
+    v[0::2, :, D - 1], v[1::2, :, D - 1] = float("inf"), float("-inf")
     for out in ("f32", "bf16"):
         o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, flags=flags, **opts)
         assert_tile_kernel(info, clip_len, n_clips, P, h)
@@ -237,7 +238,8 @@ def test_tasks_with_a_nan_are_done_again_with_every_option(opts, D, h):
         keep = [c for c in range(h * D) if c != D - 1]
         a, b = o[:, :, keep].double(), og[:, :, keep].double()
         if opts.get("bias_global") == 1e9:      # (the generic kernel adds the bias to the scores that count)
-            vz = torch.nan_to_num(v)
+            vz = v.clone()
+            vz[:, :, D - 1] = 0.0
             ref = U.oracle_forward(q, k, vz, clip_len, n_clips, w, h, g, dedup=bool(flags), **opts)
             b = torch.from_numpy(ref).to(DEV)[:, :, keep]
         bar = 2e-5 + (0 if out == "f32" else 2 * U.bf16_half_ulp(b.cpu().numpy()).max())
