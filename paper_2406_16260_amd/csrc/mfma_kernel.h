@@ -152,8 +152,12 @@ struct PvChain<false> {
 // conversions and half the LDS reads per 16 channels) instead of by gfx950's transposing LDS read.
 // The transposing read is faster wherever arithmetic shows (4 clips, 640 positions, 8 heads of 160: 102
 // -> 95 us; 4 clips, 2,560 positions, 8 heads of 40: 101.5 -> 96; 144 clips, 160 positions, 12 heads of 96: 658 ->
-// 632).  Where memory alone bounds long chunks it is no faster and at some head sizes a little slower (the
-// same with 8 heads of 160: 713 -> 719, 10 of 128: 725 -> 728, 20 of 64: 714 -> 716): those have both kernels.
+// 632; chunks of 12 tiles, 320 positions, 8 heads of 160: 503.9 -> 499.6).  On longer chunks memory alone
+// bounds both, and the difference is within 1 % either way.  In 24 runs of the two in turn, selector against
+// transposing read, median and quartiles: 144 clips, 160 positions, 16 global frames, 8 heads of 160 -0.4 % (-0.6
+// to -0.3), 10 of 128 -0.7 % (-0.9 to -0.4), 20 of 64 -0.8 % (-1.0 to -0.5); 96 clips, 256 x 8 x 128 -1.0 % (-1.4
+// to -0.6); without global frames 160 x 8 x 160 +0.1 % (-0.1 to +0.4), with a window +0.3 % (0.0 to +0.5), 640 x 8 x
+// 64 +0.3 % (+0.1 to +0.6).  These three head sizes have both kernels for the first four.
 template <int D, int HPW, int NLT, int NGT, int WPE, bool OUT_F32, bool SEL>
 __global__ __launch_bounds__(256 * WPE, WPE) void dsattn_mfma_kernel(const MfmaArgs a)
 {

@@ -618,14 +618,26 @@ int64_t conv_tiles(const ConvVariant &v, int64_t M, int64_t c_out, int groups)
 }
 
 // Estimated time in us of a bf16 problem that a round of 256 x 320 tiles does not fill: a start, and
-// per stage what the fullest compute unit takes.  Fitted to sweeps over 256 to 40,960 rows, 320, 640
-// and 1,280 channels, one and three weight sets (measured us at 20 stages, i.e. 1,280 channels):
+// per stage what the fullest compute unit takes.  Fitted to sweeps of the projections, 256 to 40,960
+// rows, 320, 640 and 1,280 channels, one and three weight sets (measured us at 20 stages, i.e. 1,280
+// channels):
 //   rows x sets   256 x 320  256 x 256  128 x 160  128 x 128  pipelined  64 x 64
 //     256 x 1       33.0       28.6       18.1       14.2       12.8      < 11.6
 //   2,560 x 1       35.8       32.3       19.8       17.8       14.9       17.2
 //   5,000 x 1       36.1       32.5       27.1       22.7       26.6       28.3
 //   2,560 x 3       37.6       33.9       29.4       37.2       40.0       43.6
 //   5,000 x 3       42.7       62.6       50.9       56.1       67.1       79.2
+// It holds for convolutions too: over 65 of 3 and 5 taps, 320 to 1,280 channels in and out and 256 to
+// 40,960 rows (us below), the kernel it picks is the fastest of the six in 53, and within 14 % in the
+// others, which all take 64 x 64 where the pipelined kernel is faster (few tiles of 60 stages and more).
+// None is slower than the better kernel of 256 rows.
+//   taps, channels, rows   256 x 320  256 x 256  128 x 160  128 x 128  pipelined  64 x 64   picked
+//   3, 640, 2,560             46.7       40.3       25.4       20.6       17.7       14.7   64 x 64
+//   3, 640, 10,240            48.7       45.9       35.4       29.4       34.0       39.8   128 x 128
+//   3, 1,280, 640             87.9       77.5       47.2       44.6       29.3       32.4   64 x 64
+//   3, 1,280, 2,560           88.7       80.5       48.2       45.2       32.8       45.9   pipelined
+//   3, 1,280, 8,192           94.4       85.1       73.5       96.3       94.3      125.5   128 x 160
+//   5, 1,280, 10,240         148.5      134.7      171.5      172.4      195.4      283.9   256 x 256
 double conv_estimate(int variant, int64_t tiles, int64_t stages)
 {
     const double r1 = (double)((tiles + 255) / 256), r2 = (double)((tiles + 511) / 512);
@@ -676,7 +688,9 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
         }
     }
     if (best < 0) return nullptr;
-    // Less than one round of them leaves compute units idle: whichever is estimated fastest.
+    // Less than one round of them leaves compute units idle: whichever is estimated fastest.  (A second
+    // round that is nearly empty does too, and is not asked about: at 258 to 320 tiles of 256 x 320 a smaller
+    // tile is 8 to 20 % faster, 65.2 against 73.7 us at 18,000 x 1,280 x 1,280, from 384 on 1 to 10 %.)
     if (best_tiles < 256) {
         const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
         double best_us = 1e300;

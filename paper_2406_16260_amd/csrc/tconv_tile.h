@@ -17,7 +17,9 @@
 // 640 x 640 takes 77 us where one thread per output took 16,370 us).  Four slots measured the same
 // as two, 128 x 160 tiles up to 1.5 % faster on large problems and 40 % slower on small ones.
 // Small bf16: the stages of a tile are dependent (0.5 to 0.9 us each, 20 of them at 1,280 channels), and
-// from about 12 TB/s on the path from L2 into LDS, which is why the tiles do not shrink further.
+// within a stage the LDS reads: a wavefront's 64 x 64 part reads four 1 KB fragments for four products of
+// 32x32x16, 128 bytes a clock and compute unit, all that the LDS has.  (The path from L2 into LDS alone does
+// 33 TB/s.)
 #pragma once
 
 namespace dsattn {
