@@ -178,9 +178,9 @@ int dsattn_copy_probe(void *dst, const void *src, int64_t bytes, void *stream);
  * of the whole video, which is what the paper's exchange yields (per-clip means -> global mean =
  * mean of the clip means -> per-clip mean squared deviation about the GLOBAL mean -> global
  * variance = mean of those); then  y = (x - mean[g]) / sqrt(var[g] + eps) * gamma[c] + beta[c].
- * Here they are gathered in one pass: every part reports its count, mean and squared deviations
- * about its own mean, and the parts are merged pairwise (Chan et al.), which gives the same
- * global mean and (biased) variance.
+ * Here they are gathered in one pass: every part reports its mean and the squared deviations
+ * about it, and the parts are merged with what their means differ by, which gives the same global
+ * mean and (biased) variance.
  */
 typedef struct dsattn_gn_desc {
     int32_t clip_len;  /* F_clip >= 1 */

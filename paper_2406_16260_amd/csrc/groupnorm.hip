@@ -3,8 +3,8 @@
 // y = (x - mean) * rstd * gamma + beta.  The paper has every device compute its clip's mean,
 // average the means, then compute and average the squared deviations about the global mean: two
 // rounds, because averaging per-clip deviations about per-clip means would be wrong.  The same
-// global mean and variance come out of ONE pass if every part reports (count, mean, sum of squared
-// deviations about its own mean) and the parts are merged with what their means differ by; that
+// global mean and variance come out of ONE pass if every part reports its mean and the sum of squared
+// deviations about it, and the parts are merged with what their means differ by; that
 // is what is done here (one read of X for the statistics instead of two), and between
 // devices it would be one exchange instead of two.
 //

@@ -20,11 +20,11 @@
 // What bounds it: at short context lists HBM and the softmax's vector instructions, about half
 // each.  Tasks are numbered so that one XCD works through consecutive clips of one position: the
 // global frames and the boundary frames that neighbouring clips share are then in its L2, and measured
-// HBM reads are the tensors' own size (1.35 GB for 1.38 GB of Q, K, V at 90 clips of 25 frames x 160
-// positions x 640 channels).  Positions fastest instead: up to 7 % slower.
+// HBM reads are the tensors' own size (1.38 GB of Q, K, V at 90 clips of 25 frames x 160 positions x 640
+// channels; 3.0 TB/s with the vector ALUs busy for 48 % of the time).  Positions fastest instead: up to 7 % slower.
 // Measured (generic kernel before): 12 clips of 24 frames x 135 positions, 5 heads of 64, bf16 35 us
-// (191); 90 clips of 25 x 160, 10 heads of 64, bf16 605 us (3,409; a 5.2 TB/s stream of the four
-// tensors: 355); 384 frames x 640, 8 heads of 80, fp32 687 us (2,644; 484); 2 clips of 288 frames,
+// (191); 90 clips of 25 x 160, 10 heads of 64, bf16 583 us (3,409; a 5.2 TB/s stream of the four
+// tensors: 355); 384 frames x 640, 8 heads of 80, fp32 677 us (2,644; 484); 2 clips of 288 frames,
 // 320 keys a clip, bf16 2.4 ms (602).
 // Variants: V transposed by a 0/1 selector product instead of through LDS, the same time, but an
 // infinity in V reaches the 31 channels beside it; bf16 weights times V on the fp32
