@@ -243,10 +243,10 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
     a.C = pl.C;
     a.FS = (int64_t)d.spatial * pl.C;
     a.sc = pl.scale * 1.4426950408889634f;
-    // (in 64 bits: the difference may be more than a float holds; 1e38 already hides a scope)
+    // (in 64 bits: the difference may be more than a float holds; 3e38 already hides a scope)
     const double diff = a.G ? ((double)d.bias_global - d.bias_local) / pl.scale : 0.0;
-    a.lshift = (float)std::max(std::min(-diff, 0.0), -1e38);
-    a.gshift = (float)std::max(std::min(diff, 0.0), -1e38);
+    a.lshift = (float)std::max(std::min(-diff, 0.0), -3e38);
+    a.gshift = (float)std::max(std::min(diff, 0.0), -3e38);
     a.dedup = (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) ? 1 : 0;
     a.gdup = pl.gdup;
 
