@@ -57,6 +57,18 @@ static void build_ctx_table(dsattn_plan_t &pl)
     }
 }
 
+// The global entries twice: as they are, and marked (bit 30; frames have 24 bits) where an earlier entry
+// has the same frame.
+static void build_global_table(dsattn_plan_t &pl)
+{
+    pl.global_tab = pl.global_idx;
+    std::vector<bool> seen(pl.global_idx.empty() ? 0 : pl.F);
+    for (const int32_t f : pl.global_idx) {
+        pl.global_tab.push_back(f | (seen[f] ? 1 << 30 : 0));
+        seen[f] = true;
+    }
+}
+
 // Launch planner: one decision per U-Net level (P, h, D differ per level, Section 3).
 static void run_planner(dsattn_plan_t &pl)
 {
@@ -137,6 +149,7 @@ int dsattn_plan(const dsattn_desc *desc, const int32_t *global_idx, int32_t n_gl
         pl->window = (d.flags & DSATTN_FLAG_SLIDING_WINDOW) ? d.window : -1;
         pl->global_idx.assign(global_idx, global_idx + n_global);
         build_ctx_table(*pl);
+        build_global_table(*pl);
     } catch (const std::bad_alloc &) {
         delete pl;
         return fail(DSATTN_ENOMEM, "dsattn_plan: host allocation failed");
@@ -153,17 +166,19 @@ int dsattn_plan(const dsattn_desc *desc, const int32_t *global_idx, int32_t n_gl
         }
         const size_t nb_idx = pl->ctx_idx.size() * sizeof(int32_t);
         const size_t nb_len = pl->ctx_len.size() * sizeof(int32_t);
-        const size_t nb_g = std::max<size_t>(1, pl->global_idx.size()) * sizeof(int32_t);
+        const size_t n_tab = pl->global_tab.size();
         e = hipMalloc((void **)&pl->d_ctx_idx, std::max<size_t>(nb_idx, 4));
         if (e == hipSuccess) e = hipMalloc((void **)&pl->d_ctx_len, nb_len);
-        if (e == hipSuccess) e = hipMalloc((void **)&pl->d_global_idx, nb_g);
+        if (e == hipSuccess)
+            e = hipMalloc((void **)&pl->d_global_idx, std::max<size_t>(1, n_tab) * sizeof(int32_t));
         if (e == hipSuccess && nb_idx)
             e = hipMemcpy(pl->d_ctx_idx, pl->ctx_idx.data(), nb_idx, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy(pl->d_ctx_len, pl->ctx_len.data(), nb_len, hipMemcpyHostToDevice);
-        if (e == hipSuccess && !pl->global_idx.empty())
-            e = hipMemcpy(pl->d_global_idx, pl->global_idx.data(),
-                          pl->global_idx.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+        if (e == hipSuccess && n_tab)
+            e = hipMemcpy(pl->d_global_idx, pl->global_tab.data(), n_tab * sizeof(int32_t),
+                          hipMemcpyHostToDevice);
+        pl->d_global_info = pl->d_global_idx + pl->global_idx.size();
         if (e == hipSuccess && pl->launch.kernel == 1)
             e = mfma_prepare(*pl);
         else if (e == hipSuccess && !pl->tile_fn)

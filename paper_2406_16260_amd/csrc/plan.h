@@ -18,12 +18,14 @@ struct dsattn_plan_s {
     int device;      // HIP ordinal or -1
 
     std::vector<int32_t> global_idx;  // host copy, caller order
+    std::vector<int32_t> global_tab;  // host copy of both device tables below
     std::vector<int32_t> ctx_idx;     // host [N][lk_max], -1 padded
     std::vector<int32_t> ctx_len;     // host [N]
 
     int32_t *d_ctx_idx = nullptr;     // device [N][lk_max]
     int32_t *d_ctx_len = nullptr;     // device [N]
-    int32_t *d_global_idx = nullptr;  // device [max(1, n_global)]
+    int32_t *d_global_idx = nullptr;  // device [n_global]
+    int32_t *d_global_info = nullptr; // behind it: the same, bit 30 set where an earlier entry has that frame
 
     dsattn_launch_info launch;
 

@@ -3,29 +3,27 @@
 // longer global lists.  Precision is that of the vector kernel: fp32 softmax, weights kept at 24
 // bits.
 //
-// One wavefront owns 16 query frames of one clip, position and head, and walks the clip's context
-// list in tiles of 16 keys with a running maximum.  With clips of a few dozen frames a key row is
-// used by one to a few wavefronts only, so nothing is shared in LDS and rows are loaded from global
-// memory straight into the operand layout of the matrix instructions.
+// One wavefront owns 16 or 32 query frames of one clip, position and head and walks the clip's context list
+// in tiles of 16 keys with a running maximum.  Rows are fetched with four neighbouring lanes on 64
+// neighbouring bytes and pass through a few KB of wavefront-private LDS into the operand layout.  (Fetched in
+// the operand layout itself, 16 rows to 16 neighbouring lanes, every lane was an access of its own to the
+// first-level cache, which was then busy for the whole of the kernel: 55 accesses a load instruction
+// instead of 14, and 12 clips of 24 frames of 64 global ones, 370 positions, 8 x 160: 530 -> 425 us.)
 //   S^T = K Q^T   keys on M, queries on N.  The lane's 16 bytes are chunk 4 j + lane / 16 of row
 //                 lane % 16, in both operands, so any order of the channels contracts the same:
 //                 one operand of v_mfma_f32_16x16x32_bf16, or four of v_mfma_f32_16x16x4_f32.
 //   O^T = V^T P^T fp32: v_mfma_f32_16x16x4_f32; lane (m, k) loads W consecutive channels 64 b + W m of
 //                 key 4 k + s, the operands of W products, and the weight it holds of that key is the
 //                 other operand as it stands.
-//                 bf16: v_mfma_f32_16x16x32_bf16 over a pair of key tiles; V passes through a few KB
-//                 of wavefront-private LDS for the transposing read, and a weight enters as the sum
+//                 bf16: v_mfma_f32_16x16x32_bf16 over a pair of key tiles; a weight enters as the sum
 //                 of three bf16 numbers (8 bits each: all 24), whose products are exact.
 //
-// What bounds it: at short context lists HBM and the softmax's vector instructions, about half
-// each.  Tasks are numbered so that one XCD works through consecutive clips of one position: the
+// What bounds it: at short context lists HBM and the vector instructions of softmax and splitting, about
+// half each.  Tasks are numbered so that one XCD works through consecutive clips of one position: the
 // global frames and the boundary frames that neighbouring clips share are then in its L2, and measured
-// HBM reads are the tensors' own size (1.38 GB of Q, K, V at 90 clips of 25 frames x 160 positions x 640
-// channels; 3.0 TB/s with the vector ALUs busy for 48 % of the time).  Positions fastest instead: up to 7 % slower.
-// Measured (generic kernel before): 12 clips of 24 frames x 135 positions, 5 heads of 64, bf16 35 us
-// (191); 90 clips of 25 x 160, 10 heads of 64, bf16 583 us (3,409; a 5.2 TB/s stream of the four
-// tensors: 355); 384 frames x 640, 8 heads of 80, fp32 677 us (2,644; 484); 2 clips of 288 frames,
-// 320 keys a clip, bf16 2.4 ms (602).
+// HBM reads are the tensors' own size.  12 clips of 24 frames x 135 positions, 5 x 64, bf16: 25.5 us (32.8
+// with operand-order loads and one query tile a wavefront; 19.4 at the card's copy rate); 2,304 positions
+// x 2 clips of 25, 8 x 80: 158 (200); 3 clips of 24 x 925 positions, 8 x 80, fp32: 188 (220).
 // Variants: V transposed by a 0/1 selector product instead of through LDS, the same time, but an
 // infinity in V reaches the 31 channels beside it; bf16 weights times V on the fp32
 // instructions, 30 % slower; weights split by rounding instead of cutting, 10 % slower.
@@ -51,53 +49,136 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct TileArgs {
     const void *Q, *K, *V;
     void *O;
-    const int32_t *gidx;
+    const int32_t *ginfo;  // global entries: frame, bit 30 where an earlier entry has the same frame
     int32_t N, F, P, h, D, clip_len, lk_max;
     int32_t wl;        // local context width of a clip
-    int32_t nqt;       // query tiles per clip
+    int32_t nqg;       // tasks (groups of query tiles) per clip
     int32_t ctx_mode;  // K and V are materialised contexts [N, lk_max, P, C]
     int32_t G, window, dedup;
     uint32_t per_xcd;  // workgroups per XCD
     uint32_t tasks;
+    uint32_t fsb;      // bytes from a frame to the next one
     float sc;          // scale * log2(e)
     float lb, gb;      // shifts of the local and the global keys' raw scores, see launch_tile_attn
 };
 
-// The clip's context list: frames [lo, lo + nl), then the global entries; L keys in all.  (Worked
-// out here and not read from the plan's table: the first key rows are then asked for at once.)
-// Keys j < run are consecutive rows of K and V, from row0 on.
-struct Context {
-    int lo, nl, L, run;
-    int64_t row0;
+// One wavefront's share: queries [q0, q0 + nq) of one clip, position and head.
+struct Task {
+    int clip, p, g, q0, nq;
+    bool exists;
 };
-__device__ __forceinline__ Context context_of(const TileArgs &a, int clip)
+// (clips of one position are neighbours: numbered the other way round, positions fastest, it
+// measured up to 7 % slower)
+template <int QT>
+__device__ __forceinline__ Task task_of(const TileArgs &a)
+{
+    // XCD x (= workgroup % 8) takes a contiguous run of tasks
+    const uint32_t wg = (blockIdx.x % 8u) * a.per_xcd + blockIdx.x / 8u;
+    // (less than 2^31 tasks: 32-bit divisions, a 64-bit one is some hundred scalar instructions)
+    uint32_t id = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Task k;
+    k.exists = id < a.tasks;
+    id = min(id, a.tasks - 1);
+    uint32_t rest = id / (uint32_t)a.nqg;
+    const int qg = (int)(id - rest * a.nqg);
+    id = rest;
+    rest = id / (uint32_t)a.h;
+    k.g = (int)(id - rest * a.h);
+    k.p = (int)(rest / (uint32_t)a.N);
+    k.clip = (int)(rest - (uint32_t)k.p * a.N);
+    k.q0 = k.clip * a.clip_len + 16 * QT * qg;
+    k.nq = min(16 * QT, a.clip_len - 16 * QT * qg);
+    return k;
+}
+
+// The task's context list: the local frames [lo, lo + nl) that any of its queries sees, then the global
+// entries; L keys in all.  (Worked out here and not read from the plan's table: the first key rows are
+// then asked for at once.)  Rows of K and V are counted from row `base`: local key j is row lrow + j, and
+// global entry i of a materialised context row grow + i.
+struct Context {
+    int lo, nl, L, lrow, grow;
+    int64_t base;
+};
+__device__ __forceinline__ Context context_of(const TileArgs &a, const Task &k)
 {
     Context c;
-    c.lo = max(0, clip * a.clip_len - a.wl);
-    c.nl = min(a.F, (clip + 1) * a.clip_len + a.wl) - c.lo;
+    const int lo = max(0, k.clip * a.clip_len - a.wl), hi = min(a.F, (k.clip + 1) * a.clip_len + a.wl);
+    // under a window, what the task's first and last query see: 383 positions of a clip of 192 frames, 10 x 64,
+    // fp32, with a window of 8 (3 or 4 key tiles instead of 13): 572 -> 177 us
+    c.lo = a.window < 0 ? lo : max(lo, k.q0 - a.window);
+    c.nl = (a.window < 0 ? hi : min(hi, k.q0 + k.nq + a.window)) - c.lo;
     c.L = c.nl + a.G;
-    c.run = a.ctx_mode ? c.L : c.nl;
-    c.row0 = a.ctx_mode ? (int64_t)clip * a.lk_max : (int64_t)c.lo;
+    c.base = a.ctx_mode ? (int64_t)k.clip * a.lk_max : 0;
+    c.lrow = a.ctx_mode ? c.lo - lo : c.lo;
+    c.grow = hi - lo;
     return c;
 }
 
-// row of key j in K and V (keys past the list: the last one's, their weights are zero)
-__device__ __forceinline__ int64_t key_row(const TileArgs &a, const Context &c, int j)
+// The local frames [lo, lo + span) that a query sees.
+struct Visible {
+    int lo;
+    uint32_t span;
+    __device__ __forceinline__ bool sees(int frame) const { return (uint32_t)(frame - lo) < span; }
+};
+__device__ __forceinline__ Visible visible_to(const TileArgs &a, const Context &c, int aq)
 {
-    j = min(j, c.L - 1);
-    return j < c.run ? c.row0 + j : (int64_t)a.gidx[j - c.run];
+    int lo = c.lo, hi = c.lo + c.nl;
+    if (a.window >= 0) {
+        lo = max(lo, aq - a.window);
+        hi = min(hi, aq + a.window + 1);
+    }
+    return {lo, (uint32_t)(hi - lo)};
 }
-// what the masks need to know about key j: its frame and, with the set union, whether it repeats an
-// earlier global entry
-__device__ __forceinline__ int key_info(const TileArgs &a, const Context &c, int j)
+
+// The plan's table of global entries, in LDS as far as it fits (read from memory in the loop, an entry
+// would be waited for behind the rows that are on their way).
+constexpr int kLdsGlobals = 256;
+typedef __attribute__((address_space(3))) const int lds_int;
+struct Globals {
+    const TileArgs &a;
+    lds_int *lds;
+    __device__ __forceinline__ int operator[](int i) const
+    {
+        i = min(max(i, 0), a.G - 1);
+        if (a.G <= kLdsGlobals) return lds[i];
+        return a.ginfo[i];
+    }
+};
+
+// The table's way into LDS: a thread's entry on its way, and all of them there.
+__device__ __forceinline__ bool needs_globals(const TileArgs &a)
+{
+    return a.G > 0 && a.G <= kLdsGlobals && (!a.ctx_mode || a.dedup);
+}
+__device__ __forceinline__ int my_global(const TileArgs &a)
+{
+    return needs_globals(a) ? a.ginfo[min((int)threadIdx.x, a.G - 1)] : 0;
+}
+__device__ __forceinline__ void put_globals(const TileArgs &a, int *lds, int mine)
+{
+    if (!needs_globals(a)) return;
+    lds[threadIdx.x] = mine;
+    __syncthreads();
+}
+
+// row of key j, one of tile t's, in K and V, from the context's base on (keys past the list: the last one's,
+// their weights are zero)
+__device__ __forceinline__ uint32_t key_row(const TileArgs &a, const Context &c, const Globals &g, int t, int j)
 {
     j = min(j, c.L - 1);
-    if (j < c.nl) return c.lo + j;
-    const int frame = a.gidx[j - c.nl];
-    bool dup = false;
-    if (a.dedup)
-        for (int u = 0; u + 1 < a.G; ++u) dup = dup || (u < j - c.nl && a.gidx[u] == frame);
-    return frame | (dup ? 1 << 30 : 0);
+    uint32_t row = (uint32_t)(c.lrow + j);
+    if (16 * t + 16 > c.nl && a.G > 0) {
+        const int i = max(j - c.nl, 0);
+        const uint32_t gr = a.ctx_mode ? (uint32_t)(c.grow + i) : (uint32_t)g[i] & 0x3fffffffu;
+        row = j < c.nl ? row : gr;
+    }
+    return row;
+}
+// The wavefront's position and head of a row: rows are fsb bytes apart.
+template <typename T>
+__device__ __forceinline__ const T *row_ptr(const T *p, uint32_t row, uint32_t fsb)
+{
+    return (const T *)((const unsigned char *)p + (uint64_t)row * fsb);
 }
 
 // Orders LDS accesses of the wavefront's lanes: they execute in issue order, only the compiler has to
@@ -133,69 +214,74 @@ __device__ __forceinline__ float exp2_positive(float x)
     return __builtin_amdgcn_exp2f(fmaxf(x, fmaf(x, 0x1p-100f, -126.f)));
 }
 
-// The part of the kernel that both types share: masks, running softmax.  KT key tiles per step.
-template <int KT, bool POSITIVE>
+// The part of the kernel that both types share: masks, running softmax.  KT key tiles per step.  OPTS: a
+// window, the set union or biases; compiled apart, because the conditions alone, kept in scalar registers
+// and spilled from there, were a third of the loop's instructions (12 clips of 24 frames x 135 positions,
+// 5 x 64: 28.3 -> 25.5 us without them).
+template <int KT, bool POSITIVE, bool OPTS>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
     // A shift of the local scores holds from the query's first visible global key on: the set union may
     // hide them all, and then it is the local scores that count.
-    bool shifted;
+    bool shifted = false;
 
-    __device__ __forceinline__ explicit Softmax(const TileArgs &a) : shifted(!a.dedup) {}
-
-    // scores of key tiles t0 .. t0 + nt - 1 -> weights (unnormalised; those of a tile that is not
-    // there are zero); returns the factor for what has been accumulated so far
-    __device__ __forceinline__ float step(const TileArgs &a, const Context &c, f32x4 (&s)[KT], int t0,
-                                          int nt, int clip, int qt, int lane)
+    // scores of key tiles t0 .. t0 + KT - 1 -> weights (unnormalised; those of keys past the list are zero);
+    // returns the factor for what has been accumulated so far
+    __device__ __forceinline__ float step(const TileArgs &a, const Context &c, const Globals &g, int aq,
+                                          f32x4 (&s)[KT], int t0, int lane)
     {
-        const int l16 = lane & 15, lg = lane >> 4, j0 = 16 * t0 + 4 * lg;
-        const bool opts = a.window >= 0 || a.dedup;
-        if (opts || 16 * (t0 + nt) > c.L) {  // else every key counts
-            const int aq = clip * a.clip_len + 16 * qt + l16;
+        const int lg = lane >> 4, j0 = 16 * t0 + 4 * lg;
+        if (OPTS && (a.window >= 0 || a.dedup)) {
+            const Visible vis = visible_to(a, c, aq);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                if (t >= nt) continue;
-                int info = 0;
-                if (opts) info = key_info(a, c, 16 * (t0 + t) + l16);
+                const bool globals = 16 * (t0 + t) + 16 > c.nl;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool local = j0 + 16 * t + e < c.nl;
-                    bool hidden = j0 + 16 * t + e >= c.L;
-                    if (opts) {
-                        const int ki = __shfl(info, 4 * lg + e);  // from the key's own lane
-                        const int f = ki & 0x3fffffff;
-                        const bool far = a.window >= 0 && abs(f - aq) > a.window;
-                        const bool seen = (ki >> 30 & 1) || (f >= c.lo && f < c.lo + c.nl && !far);
-                        hidden = hidden || (local ? far : a.dedup && seen);
+                    const int j = j0 + 16 * t + e;
+                    bool hidden = !vis.sees(c.lo + j);
+                    if (globals) {
+                        const int ki = a.dedup ? g[j - c.nl] : 0;
+                        const bool seen = a.dedup && ((ki >> 30 & 1) || vis.sees(ki & 0x3fffffff));
+                        hidden = j < c.nl ? hidden : seen || j >= c.L;
                     }
                     s[t][e] = hidden ? -INFINITY : s[t][e];
                 }
             }
+        } else if (16 * (t0 + KT) > c.L) {  // else every key counts
+            int left = c.L - j0;
+            asm volatile("" : "+v"(left));  // (or the comparisons are made in every step)
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[t][e] = 16 * t + e >= left ? -INFINITY : s[t][e];
         }
-        if (a.lb != 0.f || a.gb != 0.f) {
+        if (OPTS && (a.lb != 0.f || a.gb != 0.f)) {
             if (a.dedup && a.lb != 0.f) {
                 float mg = -INFINITY;
 #pragma unroll
                 for (int t = 0; t < KT; ++t)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (t < nt && j0 + 16 * t + e >= c.nl) mg = fmaxf(mg, s[t][e]);
+                        if (j0 + 16 * t + e >= c.nl) mg = fmaxf(mg, s[t][e]);
                 const bool first = !shifted && swap32(swap16(mg, true), true) > -INFINITY;
                 m += first ? a.lb * a.sc : 0.f;
                 shifted = shifted || first;
             }
-            const float ls = shifted ? a.lb : 0.f;
+            const float ls = shifted || !a.dedup ? a.lb : 0.f;
 #pragma unroll
-            for (int t = 0; t < KT; ++t)
+            for (int t = 0; t < KT; ++t) {
+                const bool globals = 16 * (t0 + t) + 16 > c.nl;
+                if (!globals && ls == 0.f) continue;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s[t][e] += j0 + 16 * t + e < c.nl ? ls : a.gb;
+                for (int e = 0; e < 4; ++e) s[t][e] += !globals || j0 + 16 * t + e < c.nl ? ls : a.gb;
+            }
         }
         float mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < KT; ++t)
-            if (t < nt)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[t][e]);
+            for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[t][e]);
         mx *= a.sc;
         mx = fmaxf(m, swap32(swap16(mx, true), true));
         float alpha = 1.f;
@@ -207,18 +293,13 @@ struct Softmax {
         }
         const float nm = m == -INFINITY ? 0.f : -m;
 #pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            if (t < nt) {
+        for (int t = 0; t < KT; ++t)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float x = fmaf(s[t][e], a.sc, nm);
-                    s[t][e] = POSITIVE ? exp2_positive(x) : __builtin_amdgcn_exp2f(x);
-                    l += s[t][e];
-                }
-            } else {
-                s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < 4; ++e) {
+                const float x = fmaf(s[t][e], a.sc, nm);
+                s[t][e] = POSITIVE ? exp2_positive(x) : __builtin_amdgcn_exp2f(x);
+                l += s[t][e];
             }
-        }
         return alpha;
     }
     __device__ __forceinline__ float inverse_sum() const
@@ -226,30 +307,6 @@ struct Softmax {
         return 1.0f / swap32(swap16(l, false), false);
     }
 };
-
-// (clips of one position are neighbours: numbered the other way round, positions fastest, it
-// measured up to 7 % slower)
-struct Task {
-    int clip, p, g, qt;
-    bool exists;
-};
-__device__ __forceinline__ Task task_of(const TileArgs &a)
-{
-    // XCD x (= workgroup % 8) takes a contiguous run of tasks
-    const uint32_t wg = (blockIdx.x % 8u) * a.per_xcd + blockIdx.x / 8u;
-    // (less than 2^31 tasks: 32-bit divisions, a 64-bit one is some hundred scalar instructions)
-    uint32_t id = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    Task k;
-    k.exists = id < a.tasks;
-    uint32_t rest = id / (uint32_t)a.nqt;
-    k.qt = (int)(id - rest * a.nqt);
-    id = rest;
-    rest = id / (uint32_t)a.h;
-    k.g = (int)(id - rest * a.h);
-    k.p = (int)(rest / (uint32_t)a.N);
-    k.clip = (int)(rest - (uint32_t)k.p * a.N);
-    return k;
-}
 
 // A bf16 task whose result has a NaN and whose V rows have an infinity is done again, one query at a time
 // on the vector ALUs: zero times an infinity in V is NaN, a small weight times it is not, and the matrix
@@ -259,13 +316,13 @@ __device__ __forceinline__ Task task_of(const TileArgs &a)
 // cost 3 to 5 % by the registers that the two share.  12 clips of 24 frames x 135 positions, 5 heads of 64: 45 us
 // a single call, 53 with a NaN and no infinity in every head, 870 with infinities in every head; the vector
 // kernel 200.)
-__device__ __forceinline__ bool infinity_in_v(const TileArgs &a, const Task &tk, const Context &cx)
+__device__ __forceinline__ bool infinity_in_v(const TileArgs &a, const Task &tk, const Context &cx, const Globals &gl)
 {
     const int64_t C = (int64_t)a.h * a.D, FS = (int64_t)a.P * C;
-    const __bf16 *V = (const __bf16 *)a.V + (int64_t)tk.p * C + (int64_t)tk.g * a.D;
+    const __bf16 *V = (const __bf16 *)a.V + cx.base * FS + (int64_t)tk.p * C + (int64_t)tk.g * a.D;
     bool inf = false;
     for (int j = threadIdx.x & 63; j < cx.L; j += 64) {
-        const __bf16 *v = V + key_row(a, cx, j) * FS;
+        const __bf16 *v = row_ptr(V, key_row(a, cx, gl, j >> 4, j), a.fsb);
         for (int d = 0; d < a.D; d += 8) {
             const bf16x8 x = *(const bf16x8 *)(v + d);
 #pragma unroll
@@ -275,28 +332,29 @@ __device__ __forceinline__ bool infinity_in_v(const TileArgs &a, const Task &tk,
     return __any(inf);
 }
 template <typename TO>
-__device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, const Context &cx)
+__device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, const Context &cx, const Globals &gl,
+                                           int from, int to)
 {
     const int lane = threadIdx.x & 63, D = a.D;
     const int64_t C = (int64_t)a.h * D, FS = (int64_t)a.P * C;
     const int64_t rowoff = (int64_t)tk.p * C + (int64_t)tk.g * D;
-    const __bf16 *K = (const __bf16 *)a.K + rowoff, *V = (const __bf16 *)a.V + rowoff;
-    for (int i = 16 * tk.qt; i < min(16 * tk.qt + 16, a.clip_len); ++i) {
-        const int aq = tk.clip * a.clip_len + i;
+    const __bf16 *K = (const __bf16 *)a.K + cx.base * FS + rowoff, *V = (const __bf16 *)a.V + cx.base * FS + rowoff;
+    for (int aq = from; aq < to; ++aq) {
+        const Visible vis = visible_to(a, cx, aq);
         const __bf16 *q = (const __bf16 *)a.Q + (int64_t)aq * FS + rowoff;
         // raw score of key j, -inf if it does not exist or is hidden
         auto score = [&](int j) -> float {
-            const __bf16 *k = K + key_row(a, cx, j) * FS;
+            const __bf16 *k = row_ptr(K, key_row(a, cx, gl, j >> 4, j), a.fsb);
             float x = 0.f;
             for (int d = 0; d < D; d += 8) {
                 const bf16x8 y = *(const bf16x8 *)(q + d), z = *(const bf16x8 *)(k + d);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x = fmaf((float)y[e], (float)z[e], x);
             }
-            const int ki = key_info(a, cx, j), f = ki & 0x3fffffff;
-            const bool far = a.window >= 0 && abs(f - aq) > a.window;
-            const bool seen = (ki >> 30 & 1) || (f >= cx.lo && f < cx.lo + cx.nl && !far);
-            return j >= cx.L || (j < cx.nl ? far : a.dedup && seen) ? -INFINITY : x;
+            if (j >= cx.L) return -INFINITY;
+            if (j < cx.nl) return vis.sees(cx.lo + j) ? x : -INFINITY;
+            const int ki = a.dedup ? gl[j - cx.nl] : 0;
+            return a.dedup && ((ki >> 30 & 1) || vis.sees(ki & 0x3fffffff)) ? -INFINITY : x;
         };
         float ml = -INFINITY, mg = -INFINITY;
         for (int j = lane; j < cx.L; j += 64) {
@@ -317,7 +375,7 @@ __device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, c
             l += w;
             for (int u = 0; u < min(64, cx.L - j0); ++u) {
                 const float wu = __shfl(w, u);
-                const __bf16 *v = V + key_row(a, cx, j0 + u) * FS;
+                const __bf16 *v = row_ptr(V, key_row(a, cx, gl, (j0 + u) >> 4, j0 + u), a.fsb);
                 for (int r = 0; r < 3; ++r)
                     if (lane + 64 * r < D) o[r] = fmaf(wu, (float)v[lane + 64 * r], o[r]);
             }
@@ -335,328 +393,530 @@ __device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, c
 constexpr int vrow_bytes(int NKB) { return 64 * NKB + 16; }
 constexpr int kBf16Tiles = 2;  // key tiles per step
 
-// NKB = ceil(D / 32)
-template <int NKB, bool OUT_F32>
-__global__ __launch_bounds__(256, NKB == 1 ? 6 : 2) void tile_attn_bf16_kernel(const TileArgs a)
+// NKB = ceil(D / 32); FULL: D = 32 NKB.  QT query tiles share every key row that is fetched.
+template <int NKB, bool FULL, int QT, bool OPTS, bool OUT_F32>
+__global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf16_kernel(const TileArgs a)
 {
     constexpr int KT = kBf16Tiles;
     constexpr int RS = vrow_bytes(NKB);
     __shared__ __attribute__((aligned(16))) unsigned char smem[4 * KT * 16 * RS];
-    const Task tk = task_of(a);
-    if (!tk.exists) return;
+    __shared__ int gtab[kLdsGlobals];
+    const int ginfo = my_global(a);
+    const Globals gl{a, (lds_int *)gtab};
+    const Task tk = task_of<QT>(a);  // (without a task: the last one's rows, up to the barrier)
     const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
     unsigned char *vs = smem + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (KT * 16 * RS);
     const int D = a.D;
     const int64_t C = (int64_t)a.h * D, FS = (int64_t)a.P * C;
     const int64_t rowoff = (int64_t)tk.p * C + (int64_t)tk.g * D;
-    const int q0 = tk.qt * 16 + l16;
-    const bool qok = q0 < a.clip_len;
-    const int aq = tk.clip * a.clip_len + min(q0, a.clip_len - 1);
-    const Context cx = context_of(a, tk.clip);
+    const Context cx = context_of(a, tk);
 
-    // chunks 4 kb + lg of a row (zeros past the head; the others' lanes all exist)
-    const bool last_ok = 32 * (NKB - 1) + 8 * lg < D;
-    auto load_chunks = [&](const __bf16 *p, bool ok, bf16x8(&r)[NKB]) __attribute__((always_inline)) {
+    // Rows are fetched four lanes to a row, 64 neighbouring bytes: lane l has chunks 4 kb + l % 4 of row l / 4
+    // (past the head: nothing).
+    const int lr = lane >> 2, lc = lane & 3;
+    const bool last_ok = FULL || 32 * (NKB - 1) + 8 * lc < D;
+    auto load_chunks = [&](const __bf16 *p, bf16x8(&r)[NKB]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-            r[kb] = bf16x8{};
-            if (ok && (kb + 1 < NKB || last_ok)) r[kb] = *(const bf16x8 *)(p + 32 * kb);
-        }
+        for (int kb = 0; kb + 1 < NKB; ++kb) r[kb] = *(const bf16x8 *)(p + 32 * kb);
+        if (last_ok) r[NKB - 1] = *(const bf16x8 *)(p + 32 * (NKB - 1));
     };
-    const int64_t laneoff = rowoff + 8 * lg;
-    bf16x8 q[NKB];
-    load_chunks((const __bf16 *)a.Q + (int64_t)aq * FS + laneoff, true, q);
-
-    f32x4 o[NKB][2];
+    const int64_t laneoff = rowoff + 8 * lc;
+    // and written to rows 16 t + .. of the wavefront's LDS (past the head, whatever the register holds: to the
+    // row's padding; those chunks stay zero)
+    const int put_at = lr * RS + 16 * lc, put_last = lr * RS + (last_ok ? 64 * (NKB - 1) + 16 * lc : 64 * NKB);
+    auto put_rows = [&](int t, const bf16x8(&r)[NKB]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) o[kb][0] = o[kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<KT, false> sm(a);
+        for (int kb = 0; kb < NKB; ++kb)
+            *(bf16x8 *)(vs + 16 * t * RS + (FULL || kb + 1 < NKB ? put_at + 64 * kb : put_last)) = r[kb];
+    };
+    if constexpr (!FULL) {
+        for (int i = lane; i < KT * RS; i += 64) *(bf16x8 *)(vs + 16 * i) = bf16x8{};
+        wave_lds_sync();
+    }
+    // chunk 4 kb + lane / 16 of row lane % 16 from there: an operand of the matrix instructions
+    auto fragment = [&](int t, int kb) __attribute__((always_inline)) {
+        return *(const bf16x8 *)(vs + (16 * t + l16) * RS + 64 * kb + 16 * lg);
+    };
 
     const int tiles = (cx.L + 15) / 16;
+    const __bf16 *Kw = (const __bf16 *)a.K + cx.base * FS + laneoff, *Vw = (const __bf16 *)a.V + cx.base * FS + laneoff;
     bf16x8 kr[KT][NKB], vr[KT][NKB];
-    // this lane's row of the first tile of consecutive rows
-    const int64_t run0 = (cx.row0 + l16) * FS + laneoff;
-    // (rows of V past the list are zeros: their weights are, and zero times an infinity is not)
-    auto load_tiles = [&](int t0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const int j = 16 * (t0 + t) + l16;
-            if (16 * (t0 + t) + 16 <= cx.run) {
-                const int64_t at = run0 + (int64_t)(16 * (t0 + t)) * FS;
-                load_chunks((const __bf16 *)a.K + at, true, kr[t]);
-                load_chunks((const __bf16 *)a.V + at, true, vr[t]);
-            } else if (t0 + t < tiles) {
-                const int64_t at = key_row(a, cx, j) * FS + laneoff;
-                load_chunks((const __bf16 *)a.K + at, true, kr[t]);
-                load_chunks((const __bf16 *)a.V + at, j < cx.L, vr[t]);
-            } else {
-#pragma unroll
-                for (int kb = 0; kb < NKB; ++kb) vr[t][kb] = bf16x8{};
-            }
-        }
+    auto load_tile = [&](int t, int t0) __attribute__((always_inline)) {
+        const uint32_t row = key_row(a, cx, gl, t0 + t, 16 * (t0 + t) + lr);
+        load_chunks(row_ptr(Kw, row, a.fsb), kr[t]);
+        load_chunks(row_ptr(Vw, row, a.fsb), vr[t]);
     };
-    load_tiles(0);
+    bf16x8 q[QT][NKB];
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        const int aq = tk.q0 + min(16 * u + lr, tk.nq - 1);
+        load_chunks(row_ptr((const __bf16 *)a.Q + laneoff, aq, a.fsb), q[u]);
+    }
+    // (the first rows, where they need no table, are asked for before it is waited for)
+    const bool early = 16 * KT <= cx.nl;
+    if (early) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t) load_tile(t, 0);
+    }
+    put_globals(a, gtab, ginfo);
+    if (!tk.exists) return;
+    if (!early) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t) load_tile(t, 0);
+    }
+    static_assert(QT <= KT, "the query rows fit");
+#pragma unroll
+    for (int u = 0; u < QT; ++u) put_rows(u, q[u]);
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < QT; ++u)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) q[u][kb] = fragment(u, kb);
+    wave_lds_sync();
+
+    f32x4 o[QT][NKB][2];
+#pragma unroll
+    for (int u = 0; u < QT; ++u)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) o[u][kb][0] = o[u][kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Softmax<KT, false, OPTS> sm[QT];
+
     for (int t0 = 0; t0 < tiles; t0 += KT) {
-        const int nt = min(KT, tiles - t0);
-        f32x4 s[KT];
+        f32x4 s[QT][KT];
+        // K through LDS, then V in its place; the next rows are asked for in the registers that this frees.
+        // (A second tile that is not there is the list's last key over and over, and masked.)
+#pragma unroll
+        for (int t = 0; t < KT; ++t) put_rows(t, kr[t]);
+        wave_lds_sync();
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
-            s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (t >= nt) continue;
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-                s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[t][kb], q[kb], s[t], 0, 0, 0);
-        }
-        // V through LDS, for the transposing read below; the next rows are asked for in the registers
-        // that this frees
-        wave_lds_sync();
+            for (int u = 0; u < QT; ++u) s[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < KT; ++t)
+            for (int kb = 0; kb < NKB; ++kb) {
+                const bf16x8 k = fragment(t, kb);
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-                *(bf16x8 *)(vs + (16 * t + l16) * RS + 64 * kb + 16 * lg) = vr[t][kb];
-        wave_lds_sync();
-        load_tiles(t0 + KT);
-
-        const float alpha = sm.step(a, cx, s, t0, nt, tk.clip, tk.qt, lane);
-        if (__any(alpha != 1.f)) {
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) o[kb][u] *= alpha;
-        }
-        // The weights as three bf16 numbers each: 8 bits, the next 8, and the 8 that are left.
-        u32x4 w[3];
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; e += 2) {
-                float x0 = s[t][e], x1 = s[t][e + 1];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const uint32_t b0 = __builtin_bit_cast(uint32_t, x0), b1 = __builtin_bit_cast(uint32_t, x1);
-                    w[k][2 * t + e / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302);  // both high halves
-                    x0 -= __builtin_bit_cast(float, b0 & 0xffff0000u);
-                    x1 -= __builtin_bit_cast(float, b1 & 0xffff0000u);
-                }
+                for (int u = 0; u < QT; ++u)
+                    s[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k, q[u][kb], s[u][t], 0, 0, 0);
             }
-        // V^T: within a group of 16 lanes the transposing read hands lane i element i % 4 of the 8
-        // bytes that lanes i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4 point at.  Lane i points at key
-        // 4 lg + i / 4, channels 8 (i % 4) + 4 u .. of the block, and so gets keys 4 lg .. 4 lg + 3 of
-        // channel 8 (i / 4) + 4 u + i % 4: the operand's layout, with the channels permuted so that a
-        // lane ends up with eight neighbouring channels of its query.
+        }
+        wave_lds_sync();
+        // (rows of V past the list are zeros: their weights are, and zero times an infinity is not)
+        if (16 * (t0 + KT) > cx.L) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+                    vr[t][kb] = 16 * (t0 + t) + lr < cx.L ? vr[t][kb] : bf16x8{};
+        }
+#pragma unroll
+        for (int t = 0; t < KT; ++t) put_rows(t, vr[t]);
+        wave_lds_sync();
+        if (t0 + KT < tiles) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t) load_tile(t, t0 + KT);
+        }
+
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            if (u > 0 && 16 * u >= tk.nq) break;
+            const float alpha = sm[u].step(a, cx, gl, tk.q0 + min(16 * u + l16, tk.nq - 1), s[u], t0, lane);
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) o[u][kb][x] *= alpha;
+            }
+            // The weights as three bf16 numbers each: 8 bits, the next 8, and the 8 that are left.
+            u32x4 w[3];
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    float x0 = s[u][t][e], x1 = s[u][t][e + 1];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const uint32_t b0 = __builtin_bit_cast(uint32_t, x0), b1 = __builtin_bit_cast(uint32_t, x1);
+                        w[k][2 * t + e / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302);  // both high halves
+                        x0 -= __builtin_bit_cast(float, b0 & 0xffff0000u);
+                        x1 -= __builtin_bit_cast(float, b1 & 0xffff0000u);
+                    }
+                }
+            // V^T: within a group of 16 lanes the transposing read hands lane i element i % 4 of the 8
+            // bytes that lanes i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4 point at.  Lane i points at key
+            // 4 lg + i / 4, channels 8 (i % 4) + 4 x .. of the block, and so gets keys 4 lg .. 4 lg + 3 of
+            // channel 8 (i / 4) + 4 x + i % 4: the operand's layout, with the channels permuted so that a
+            // lane ends up with eight neighbouring channels of its query.  (Read again for the second query
+            // tile: kept, they would cost a quarter of the wavefronts.)
+            wave_lds_sync();
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    s16x4 r[KT];
+#pragma unroll
+                    for (int t = 0; t < KT; ++t)
+                        r[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                            (__attribute__((address_space(3))) s16x4 *)(vs + (16 * t + 4 * lg + (l16 >> 2)) * RS +
+                                                                        64 * kb + 16 * (l16 & 3) + 8 * x));
+                    const bf16x8 v = __builtin_bit_cast(
+                        bf16x8, __builtin_shufflevector(r[0], r[1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        o[u][kb][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            v, __builtin_bit_cast(bf16x8, w[k]), o[u][kb][x], 0, 0, 0);
+                }
+        }
+    }
+
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        if (16 * u >= tk.nq) break;
+        bool nan = false;
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                s16x4 x[KT];
+            for (int x = 0; x < 2; ++x)
+                nan = nan || __builtin_isunordered(o[u][kb][x][0], o[u][kb][x][1]) ||
+                      __builtin_isunordered(o[u][kb][x][2], o[u][kb][x][3]);
+        if (__any(nan) && infinity_in_v(a, tk, cx, gl)) {
+            vector_task<std::conditional_t<OUT_F32, float, __bf16>>(a, tk, cx, gl, tk.q0 + 16 * u,
+                                                                   tk.q0 + min(16 * u + 16, tk.nq));
+            continue;
+        }
+        const float inv = sm[u].inverse_sum();
+        // out as whole rows too: the lane's eight channels of its query go through LDS
+        constexpr int OS = OUT_F32 ? 2 * RS : RS;
+        wave_lds_sync();
 #pragma unroll
-                for (int t = 0; t < KT; ++t)
-                    x[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) s16x4 *)(vs + (16 * t + 4 * lg + (l16 >> 2)) * RS +
-                                                                    64 * kb + 16 * (l16 & 3) + 8 * u));
-                const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5,
-                                                                                   6, 7));
+        for (int kb = 0; kb < NKB; ++kb) {
+            if constexpr (OUT_F32) {
+                *(f32x4 *)(vs + l16 * OS + 128 * kb + 32 * lg) = o[u][kb][0] * inv;
+                *(f32x4 *)(vs + l16 * OS + 128 * kb + 32 * lg + 16) = o[u][kb][1] * inv;
+            } else {
+                bf16x8 y;
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    o[kb][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, __builtin_bit_cast(bf16x8, w[k]),
-                                                                      o[kb][u], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) {
+                    y[e] = (__bf16)(o[u][kb][0][e] * inv);
+                    y[4 + e] = (__bf16)(o[u][kb][1][e] * inv);
+                }
+                *(bf16x8 *)(vs + l16 * OS + 64 * kb + 16 * lg) = y;
             }
-    }
-
-    bool nan = false;
+        }
+        wave_lds_sync();
+        if (16 * u + lr >= tk.nq) continue;
+        const int64_t row = (int64_t)(tk.q0 + 16 * u + lr) * FS + rowoff;
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            nan = nan || __builtin_isunordered(o[kb][u][0], o[kb][u][1]) ||
-                  __builtin_isunordered(o[kb][u][2], o[kb][u][3]);
-    if (__any(nan) && infinity_in_v(a, tk, cx)) {
-        vector_task<std::conditional_t<OUT_F32, float, __bf16>>(a, tk, cx);
-        return;
-    }
-    const float inv = sm.inverse_sum();
-    if (!qok) return;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-        if (kb == NKB - 1 && !last_ok) break;
-        const int64_t at = (int64_t)aq * FS + rowoff + 32 * kb + 8 * lg;
-        if constexpr (OUT_F32) {
-            *(f32x4 *)((float *)a.O + at) = o[kb][0] * inv;
-            *(f32x4 *)((float *)a.O + at + 4) = o[kb][1] * inv;
-        } else {
-            bf16x8 y;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                y[e] = (__bf16)(o[kb][0][e] * inv);
-                y[4 + e] = (__bf16)(o[kb][1][e] * inv);
-            }
-            *(bf16x8 *)((__bf16 *)a.O + at) = y;
+        for (int kb = 0; kb < (OUT_F32 ? 2 : 1) * NKB; ++kb) {
+            const int c = (OUT_F32 ? 4 : 8) * (4 * kb + lc);  // the lane's first channel
+            if (FULL || c < D)
+                *(u32x4 *)((unsigned char *)a.O + (row + c) * (OUT_F32 ? 4 : 2)) =
+                    *(const u32x4 *)(vs + lr * OS + 64 * kb + 16 * lc);
         }
     }
 }
 
 // ---------------------------------------------------------------- fp32
 
-template <int W>
-struct Floats {
-    typedef float type __attribute__((ext_vector_type(W)));
-    static __device__ __forceinline__ float get(const type &x, int t) { return x[t]; }
-};
-template <>
-struct Floats<1> {
-    typedef float type;
-    static __device__ __forceinline__ float get(const type &x, int) { return x; }
-};
-
-// NF blocks of 64 channels and, with WL = 1, 2 or 4, one of 16 WL channels: 64 NF < D <= 64 NF + 16 WL
-template <int NF, int WL>
-__global__ __launch_bounds__(256, NF == 0 && WL == 2 ? 7 : 2) void tile_attn_f32_kernel(const TileArgs a)
+// NC = ceil(D / 16): 16-byte chunks per lane of a Q or K row, 16-channel tiles of O^T; FULL: D = 16 NC.  QT
+// query tiles share every key row that is fetched.
+template <int NC, bool FULL, int QT, bool OPTS>
+__global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
 {
-    constexpr int NC = 4 * NF + WL;  // 16-byte chunks per lane of a Q or K row; 16-channel tiles of O^T
-    using Last = Floats<WL>;
-
-    const Task tk = task_of(a);
-    if (!tk.exists) return;
+    // A row of V, and of O, is NF blocks of 64 channels, then one of 32, then one of 16: lane m has W consecutive
+    // channels of a block of 16 W.
+    constexpr int NF = NC / 4, N2 = NC / 2 % 2, N1 = NC % 2;
+    constexpr int C2 = 64 * NF, C1 = C2 + 32 * N2;  // where the last two start
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    // LDS of one wavefront: the rows of a key tile (or of a query tile), padded
+    constexpr int RS = 64 * NC + 16;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[4 * 16 * RS];
+    __shared__ int gtab[kLdsGlobals];
+    const int ginfo = my_global(a);
+    const Globals gl{a, (lds_int *)gtab};
+    const Task tk = task_of<QT>(a);  // (without a task: the last one's rows, up to the barrier)
     const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+    unsigned char *ks = smem + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (16 * RS);
     const int D = a.D;
     const int64_t C = (int64_t)a.h * D, FS = (int64_t)a.P * C;
     const int64_t rowoff = (int64_t)tk.p * C + (int64_t)tk.g * D;
-    const int q0 = tk.qt * 16 + l16;
-    const bool qok = q0 < a.clip_len;
-    const int aq = tk.clip * a.clip_len + min(q0, a.clip_len - 1);
-    const Context cx = context_of(a, tk.clip);
+    const Context cx = context_of(a, tk);
 
-    // chunks 4 j + lg of a row of Q or K (zeros past the head)
+    // Rows of Q and K are fetched four lanes to a row: lane l has chunks 4 j + l % 4 of row l / 4 (past the
+    // head: nothing) ...
+    const int lr = lane >> 2, lc = lane & 3;
+    const bool last_ok = FULL || 16 * (NC - 1) + 4 * lc < D;
     auto load_chunks = [&](const float *p, f32x4(&r)[NC]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            if (j < 4 * NF) {  // (every lane's chunk exists)
-                r[j] = *(const f32x4 *)(p + 16 * j);
-            } else {
-                r[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (16 * j + 4 * lg < D) r[j] = *(const f32x4 *)(p + 16 * j);
-            }
-        }
+        for (int j = 0; j + 1 < NC; ++j) r[j] = *(const f32x4 *)(p + 16 * j);
+        if (last_ok) r[NC - 1] = *(const f32x4 *)(p + 16 * (NC - 1));
     };
-    const int64_t laneoff = rowoff + 4 * lg;
-    f32x4 q[NC];
-    load_chunks((const float *)a.Q + (int64_t)aq * FS + laneoff, q);
-
-    f32x4 o[NC];  // o[4 b + t]: channel 64 b + W m + t of row m, in block b of width W
+    const int64_t laneoff = rowoff + 4 * lc;
+    // ... and pass through LDS (past the head, whatever the register holds: to the row's padding; those chunks
+    // stay zero): an operand is chunk 4 j + lane / 16 of row lane % 16
+    const int put_at = lr * RS + 16 * lc, put_last = lr * RS + (last_ok ? 64 * (NC - 1) + 16 * lc : 64 * NC);
+    auto put_rows = [&](const f32x4(&r)[NC]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < NC; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<1, true> sm(a);
+        for (int j = 0; j < NC; ++j)
+            *(f32x4 *)(ks + (FULL || j + 1 < NC ? put_at + 64 * j : put_last)) = r[j];
+    };
+    if constexpr (!FULL) {
+        for (int i = lane; i < RS; i += 64) *(f32x4 *)(ks + 16 * i) = f32x4{};
+        wave_lds_sync();
+    }
+    auto fragment = [&](int j) __attribute__((always_inline)) {
+        return *(const f32x4 *)(ks + l16 * RS + 64 * j + 16 * lg);
+    };
 
     const int tiles = (cx.L + 15) / 16;
     f32x4 kr[NC];
-    f32x4 vf[4][NF ? NF : 1];    // [s: key 4 lg + s][block]
-    typename Last::type vl[4];
-    auto load_k = [&](int t) __attribute__((always_inline)) {
-        const int j = 16 * t + l16;
-        const int64_t row = 16 * t + 16 <= cx.run ? cx.row0 + j : key_row(a, cx, j);
-        load_chunks((const float *)a.K + row * FS + laneoff, kr);
+    f32x4 vf[4][NF ? NF : 1];  // [s: key 4 lg + s][block]
+    f32x2 v2[4];
+    float v1[4];
+    const float *Kw = (const float *)a.K + cx.base * FS + laneoff;
+    // (only the last block may reach past the head; channels there: any, those of the result are not stored)
+    const float *Vw = (const float *)a.V + cx.base * FS + rowoff;
+    auto channel = [&](int base, int w, bool last) __attribute__((always_inline)) {
+        return FULL || !last || base + w * l16 < D ? base + w * l16 : 0;
     };
-    // (rows past the list are zeros: their weights are, and zero times an infinity is not)
+    const int cf = channel(0, 4, false), cl = channel(C2 - 64, 4, true);  // (of the first blocks and of the last one)
+    const int c2 = channel(C2, 2, !N1), c1 = channel(C1, 1, true);
+    auto load_k = [&](int t) __attribute__((always_inline)) {
+        load_chunks(row_ptr(Kw, key_row(a, cx, gl, t, 16 * t + lr), a.fsb), kr);
+    };
     auto load_v = [&](int t) __attribute__((always_inline)) {
-        const bool run = 16 * t + 16 <= cx.run;
-        const int c = 64 * NF + WL * l16;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const int j = 16 * t + 4 * lg + s;
-            const bool ok = run || j < cx.L;
-            const float *p = (const float *)a.V + (run ? cx.row0 + j : key_row(a, cx, j)) * FS + rowoff;
-#pragma unroll
-            for (int b = 0; b < NF; ++b) {
-                vf[s][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (ok) vf[s][b] = *(const f32x4 *)(p + 64 * b + 4 * l16);
-            }
-            vl[s] = typename Last::type{};
-            if (ok && c < D) vl[s] = *(const typename Last::type *)(p + c);
-        }
-    };
-    load_k(0);
-    load_v(0);
-    for (int t = 0; t < tiles; ++t) {
-        // (two chains: an instruction of one covers the latency of the other's)
-        f32x4 s2[2] = {};
-#pragma unroll
-        for (int j = 0; j < NC; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                s2[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j][e], q[j][e], s2[e & 1], 0, 0, 0);
-        f32x4 s[1] = {s2[0] + s2[1]};
-        if (t + 1 < tiles) load_k(t + 1);  // (K's registers are free again)
-
-        const float alpha = sm.step(a, cx, s, t, 1, tk.clip, tk.qt, lane);
-        if (__any(alpha != 1.f)) {
-#pragma unroll
-            for (int j = 0; j < NC; ++j) o[j] *= alpha;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
+            const uint32_t row = key_row(a, cx, gl, t, 16 * t + 4 * lg + s);
 #pragma unroll
             for (int b = 0; b < NF; ++b)
+                vf[s][b] = *(const f32x4 *)(row_ptr(Vw, row, a.fsb) +
+                                            (FULL || N2 || N1 || b + 1 < NF ? cf + 64 * b : cl));
+            if constexpr (N2) v2[s] = *(const f32x2 *)(row_ptr(Vw, row, a.fsb) + c2);
+            if constexpr (N1) v1[s] = row_ptr(Vw, row, a.fsb)[c1];
+        }
+    };
+    f32x4 q[QT][NC];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    o[4 * b + u] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][b][u], s[0][e], o[4 * b + u], 0, 0, 0);
+    for (int u = 0; u < QT; ++u) {
+        const int aq = tk.q0 + min(16 * u + lr, tk.nq - 1);
+        load_chunks(row_ptr((const float *)a.Q + laneoff, aq, a.fsb), q[u]);
+    }
+    // (rows that need no table are asked for before it is waited for)
+    if (16 <= cx.nl) {
+        load_k(0);
+        load_v(0);
+    }
+    put_globals(a, gtab, ginfo);
+    if (!tk.exists) return;
+    if (16 > cx.nl) {
+        load_k(0);
+        load_v(0);
+    }
 #pragma unroll
-            for (int u = 0; u < WL; ++u)
-                o[4 * NF + u] =
-                    __builtin_amdgcn_mfma_f32_16x16x4f32(Last::get(vl[e], u), s[0][e], o[4 * NF + u], 0, 0, 0);
+    for (int u = 0; u < QT; ++u) {
+        wave_lds_sync();
+        put_rows(q[u]);
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < NC; ++j) q[u][j] = fragment(j);
+    }
+
+    f32x4 o[QT][NC];  // o[4 b + t]: channel 64 b + W m + t of row m, in block b of width W
+#pragma unroll
+    for (int u = 0; u < QT; ++u)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) o[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Softmax<1, true, OPTS> sm[QT];
+
+    for (int t = 0; t < tiles; ++t) {
+        wave_lds_sync();
+        put_rows(kr);
+        wave_lds_sync();
+        if (t + 1 < tiles) load_k(t + 1);  // (K's registers are free again)
+        // (rows of V past the list are zeros: their weights are, and zero times an infinity is not)
+        if (16 * t + 16 > cx.L) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bool ok = 16 * t + 4 * lg + s < cx.L;
+#pragma unroll
+                for (int b = 0; b < NF; ++b) vf[s][b] = ok ? vf[s][b] : f32x4{};
+                if constexpr (N2) v2[s] = ok ? v2[s] : f32x2{};
+                if constexpr (N1) v1[s] = ok ? v1[s] : 0.f;
+            }
+        }
+        // (two chains a query tile: an instruction of one covers the latency of the other's)
+        f32x4 s2[QT][2] = {};
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const f32x4 k = fragment(j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+                    s2[u][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[e], q[u][j][e], s2[u][e & 1], 0, 0, 0);
+        }
+
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            if (u > 0 && 16 * u >= tk.nq) break;
+            f32x4 s[1] = {s2[u][0] + s2[u][1]};
+            const float alpha = sm[u].step(a, cx, gl, tk.q0 + min(16 * u + l16, tk.nq - 1), s, t, lane);
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j) o[u][j] *= alpha;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                for (int b = 0; b < NF; ++b)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        o[u][4 * b + x] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][b][x], s[0][e], o[u][4 * b + x], 0, 0, 0);
+                if constexpr (N2)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        o[u][4 * NF + x] =
+                            __builtin_amdgcn_mfma_f32_16x16x4f32(v2[e][x], s[0][e], o[u][4 * NF + x], 0, 0, 0);
+                if constexpr (N1)
+                    o[u][NC - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(v1[e], s[0][e], o[u][NC - 1], 0, 0, 0);
+            }
         }
         if (t + 1 < tiles) load_v(t + 1);
     }
 
-    const float inv = sm.inverse_sum();
-    if (!qok) return;
-    float *op = (float *)a.O + (int64_t)aq * FS + rowoff;
 #pragma unroll
-    for (int b = 0; b <= NF; ++b) {
-        const int W = b < NF ? 4 : WL;
-        // the lane's 4 W channels 64 b + W (4 lg + e) + t are contiguous, D a multiple of four
+    for (int u = 0; u < QT; ++u) {
+        if (16 * u >= tk.nq) break;
+        const float inv = sm[u].inverse_sum();
+        wave_lds_sync();
+        // a block's channels W (4 lg + e) + t of query lane % 16, 4 W contiguous ones, are element e of its tile t
+        auto put_block = [&](int W, int first, int channel0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < W; ++u) {
-            const int c = 64 * b + 4 * W * lg + 4 * u;
-            f32x4 y;
+            for (int x = 0; x < W; ++x) {
+                f32x4 y;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) y[x] = o[4 * b + (4 * u + x) % W][(4 * u + x) / W] * inv;
-            if (c < D) *(f32x4 *)(op + c) = y;
-        }
+                for (int z = 0; z < 4; ++z) y[z] = o[u][first + (4 * x + z) % W][(4 * x + z) / W] * inv;
+                *(f32x4 *)(ks + l16 * RS + 4 * (channel0 + 4 * W * lg + 4 * x)) = y;
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < NF; ++b) put_block(4, 4 * b, 64 * b);
+        if constexpr (N2) put_block(2, 4 * NF, C2);
+        if constexpr (N1) put_block(1, NC - 1, C1);
+        wave_lds_sync();
+        if (16 * u + lr >= tk.nq) continue;
+        float *op = (float *)a.O + (int64_t)(tk.q0 + 16 * u + lr) * FS + laneoff;
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+            if (FULL || 16 * j + 4 * lc < D) *(f32x4 *)(op + 16 * j) = *(const f32x4 *)(ks + lr * RS + 64 * j + 16 * lc);
     }
 }
 
-const void *bf16_fn(int D, bool out_f32)
+// Two query tiles per wavefront share the rows that are fetched, and cost registers: taken where as many
+// wavefronts but one or none still fit.  6 clips of 24 / 32 frames, us with one tile a wavefront and with two, bf16:
+// head_dim 32 120 -> 108 / 96 -> 89, 40 156 -> 130 / 120 -> 108, 64 102 -> 92 / 87 -> 87, 80 110 -> 111 / 94 -> 101,
+// 96 93 -> 100 / 85 -> 92, 128 (25 frames of 32 global ones) 116 -> 104, 160 108 -> 113; fp32: 32 119 -> 111, 64 110 -> 103,
+// 80 108 -> 117, 96 114 -> 113 / 108 -> 110, 128 121 -> 111, 160 spills.  Of 48 frames the second wavefront has only one
+// tile: fp32 118 -> 122 at 64, bf16 103 -> 116 at 128, level at 32 to 64.  Options cost registers too: 157 -> 183 at 128
+// with the set union.
+constexpr bool two_query_tiles(bool f32, int blocks)
 {
-#define DSATTN_TILE_BF16(NKB)                                              \
-    case NKB:                                                              \
-        return out_f32 ? (const void *)&tile_attn_bf16_kernel<NKB, true>   \
-                       : (const void *)&tile_attn_bf16_kernel<NKB, false>;
-    switch ((D + 31) / 32) {
-        DSATTN_TILE_BF16(1)
-        DSATTN_TILE_BF16(2)
-        DSATTN_TILE_BF16(3)
-        DSATTN_TILE_BF16(4)
-        DSATTN_TILE_BF16(5)
+    return f32 ? blocks <= 4 || blocks == 7 || blocks == 8 : blocks <= 2 || blocks == 4;
+}
+
+template <int NKB, bool FULL, bool OUT_F32>
+const void *bf16_fn(int qt, bool opts)
+{
+    if constexpr (two_query_tiles(false, NKB))
+        if (qt == 2) return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 2, false, OUT_F32>;
+    return opts ? (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, true, OUT_F32>
+                : (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, false, OUT_F32>;
+}
+template <int NKB>
+const void *bf16_fn(int D, int qt, bool opts, bool out_f32)
+{
+    if (D == 32 * NKB) return out_f32 ? bf16_fn<NKB, true, true>(qt, opts) : bf16_fn<NKB, true, false>(qt, opts);
+    return out_f32 ? bf16_fn<NKB, false, true>(qt, opts) : bf16_fn<NKB, false, false>(qt, opts);
+}
+template <int NC, bool FULL>
+const void *f32_fn(int qt, bool opts)
+{
+    if constexpr (two_query_tiles(true, NC))
+        if (qt == 2) return (const void *)&tile_attn_f32_kernel<NC, FULL, 2, false>;
+    return opts ? (const void *)&tile_attn_f32_kernel<NC, FULL, 1, true>
+                : (const void *)&tile_attn_f32_kernel<NC, FULL, 1, false>;
+}
+template <int NC>
+const void *f32_fn(int D, int qt, bool opts)
+{
+    return D == 16 * NC ? f32_fn<NC, true>(qt, opts) : f32_fn<NC, false>(qt, opts);
+}
+
+const void *tile_fn(const dsattn_desc &d, int qt, bool opts)
+{
+    const bool out_f32 = d.out_dtype == DSATTN_F32;
+    const int D = d.head_dim;
+    if (d.io_dtype == DSATTN_BF16) switch ((D + 31) / 32) {
+        case 1: return bf16_fn<1>(D, qt, opts, out_f32);
+        case 2: return bf16_fn<2>(D, qt, opts, out_f32);
+        case 3: return bf16_fn<3>(D, qt, opts, out_f32);
+        case 4: return bf16_fn<4>(D, qt, opts, out_f32);
+        case 5: return bf16_fn<5>(D, qt, opts, out_f32);
+        default: return nullptr;
+        }
+    switch ((D + 15) / 16) {
+    case 1: return f32_fn<1>(D, qt, opts);
+    case 2: return f32_fn<2>(D, qt, opts);
+    case 3: return f32_fn<3>(D, qt, opts);
+    case 4: return f32_fn<4>(D, qt, opts);
+    case 5: return f32_fn<5>(D, qt, opts);
+    case 6: return f32_fn<6>(D, qt, opts);
+    case 7: return f32_fn<7>(D, qt, opts);
+    case 8: return f32_fn<8>(D, qt, opts);
+    case 9: return f32_fn<9>(D, qt, opts);
+    case 10: return f32_fn<10>(D, qt, opts);
     default: return nullptr;
     }
-#undef DSATTN_TILE_BF16
 }
 
-const void *f32_fn(int D)
+// Query tiles per wavefront.
+int query_tiles(const dsattn_desc &d, bool opts)
 {
-    const struct {
-        int max;
-        const void *fn;
-    } table[] = {
-        {16, (const void *)&tile_attn_f32_kernel<0, 1>},  {32, (const void *)&tile_attn_f32_kernel<0, 2>},
-        {64, (const void *)&tile_attn_f32_kernel<0, 4>},  {80, (const void *)&tile_attn_f32_kernel<1, 1>},
-        {96, (const void *)&tile_attn_f32_kernel<1, 2>},  {128, (const void *)&tile_attn_f32_kernel<1, 4>},
-        {144, (const void *)&tile_attn_f32_kernel<2, 1>}, {160, (const void *)&tile_attn_f32_kernel<2, 2>},
-    };
-    for (const auto &t : table)
-        if (D <= t.max) return t.fn;
-    return nullptr;
+    const bool f32 = d.io_dtype == DSATTN_F32;
+    const int nqt = (d.clip_len + 15) / 16, blocks = f32 ? (d.head_dim + 15) / 16 : (d.head_dim + 31) / 32;
+    // (a few thousand tiles are one round of wavefronts either way, and half as long with a tile each)
+    const bool round = (int64_t)d.n_clips * d.spatial * d.heads * nqt >= 4096;
+    return round && !opts && two_query_tiles(f32, blocks) && nqt > 1 && (nqt != 3 || (!f32 && blocks <= 2)) ? 2 : 1;
+}
+
+// What the scopes' biases take from the local and the global keys' raw scores; returns the factor of the
+// scores in the exponent.
+// A softmax sees only the difference of the two biases.  It is taken from the lighter scope's scores:
+// added to the heavier one's, which are the ones that count, it would take their low bits (a local
+// bias of -1e4 cost 1e-4 of the result, one of -1e9 all of the scores).  A heavier bias of 2^64 and
+// more swallows the scores beside it in 64 bits too: every key of that scope weighs the same, as on
+// the vector kernel.
+float bias_shifts(const dsattn_plan_t &pl, float &lb, float &gb)
+{
+    const dsattn_desc &d = pl.desc;
+    const bool globals = !pl.global_idx.empty();
+    const bool swallows = std::fabs(globals ? std::max(d.bias_local, d.bias_global) : d.bias_local) >= 0x1p64f;
+    const float sc = swallows ? 1e-30f : pl.scale * 1.4426950408889634f;
+    const double diff = globals ? ((double)d.bias_global - d.bias_local) * 1.4426950408889634 / sc : 0.0;
+    const double hides = 3e38 / std::max(sc, 1.f);  // (any scope; times sc it is still finite)
+    lb = (float)std::max(std::min(-diff, 0.0), -hides);
+    gb = (float)std::max(std::min(diff, 0.0), -hides);
+    return sc;
+}
+
+// Whether a plan needs the kernels with options.
+bool has_opts(const dsattn_plan_t &pl)
+{
+    float lb, gb;
+    bias_shifts(pl, lb, gb);
+    return pl.window >= 0 || (pl.desc.flags & DSATTN_FLAG_DEDUP_GLOBAL) || lb != 0.f || gb != 0.f;
 }
 
 }  // namespace
@@ -674,7 +934,9 @@ void tile_attn_plan(dsattn_plan_t &pl)
     // rows are whole 16-byte chunks
     const bool f32 = d.io_dtype == DSATTN_F32;
     if (d.head_dim % (f32 ? 4 : 8) != 0) return;
-    pl.tile_fn = f32 ? f32_fn(d.head_dim) : bf16_fn(d.head_dim, d.out_dtype == DSATTN_F32);
+    // a frame's bytes are counted in 32 bits
+    if ((int64_t)d.spatial * pl.C * (f32 ? 4 : 2) > 0xffffffffLL) return;
+    pl.tile_fn = tile_fn(d, query_tiles(d, has_opts(pl)), has_opts(pl));
     if (!pl.tile_fn) return;
     pl.launch.n_tasks = (int32_t)(units * nqt);
     pl.launch.block_threads = 256;
@@ -690,7 +952,7 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.K = K;
     a.V = V;
     a.O = O;
-    a.gidx = pl.d_global_idx;
+    a.ginfo = pl.d_global_info;
     a.N = d.n_clips;
     a.F = pl.F;
     a.wl = d.local_ctx;
@@ -699,24 +961,16 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.D = d.head_dim;
     a.clip_len = d.clip_len;
     a.lk_max = pl.lk_max;
-    a.nqt = (d.clip_len + 15) / 16;
+    const int per_wave = 16 * query_tiles(d, has_opts(pl));
+    a.nqg = (d.clip_len + per_wave - 1) / per_wave;
     a.ctx_mode = ctx_mode ? 1 : 0;
     a.G = (int32_t)pl.global_idx.size();
-    a.window = pl.window;
-    a.dedup = (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) ? 1 : 0;
-    a.tasks = (uint32_t)d.n_clips * d.spatial * d.heads * a.nqt;
+    a.window = std::min(pl.window, pl.F);
+    a.dedup = a.G > 0 && (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) ? 1 : 0;
+    a.tasks = (uint32_t)d.n_clips * d.spatial * d.heads * a.nqg;
     a.per_xcd = (a.tasks + 4 * 8 - 1) / (4 * 8);
-    // A softmax sees only the difference of the two biases.  It is taken from the lighter scope's scores:
-    // added to the heavier one's, which are the ones that count, it would take their low bits (a local
-    // bias of -1e4 cost 1e-4 of the result, one of -1e9 all of the scores).  A heavier bias of 2^64 and
-    // more swallows the scores beside it in 64 bits too: every key of that scope weighs the same, as on
-    // the vector kernel.
-    const bool swallows = std::fabs(a.G ? std::max(d.bias_local, d.bias_global) : d.bias_local) >= 0x1p64f;
-    a.sc = swallows ? 1e-30f : pl.scale * 1.4426950408889634f;
-    const double diff = a.G ? ((double)d.bias_global - d.bias_local) * 1.4426950408889634 / a.sc : 0.0;
-    const double hides = 3e38 / std::max(a.sc, 1.f);  // (any scope; times sc it is still finite)
-    a.lb = (float)std::max(std::min(-diff, 0.0), -hides);
-    a.gb = (float)std::max(std::min(diff, 0.0), -hides);
+    a.fsb = (uint32_t)((int64_t)d.spatial * pl.C * (d.io_dtype == DSATTN_F32 ? 4 : 2));
+    a.sc = bias_shifts(pl, a.lb, a.gb);
     void *params[] = {&a};
     return hipLaunchKernel(pl.tile_fn, dim3(a.per_xcd * 8), dim3(256), params, 0, st);
 }

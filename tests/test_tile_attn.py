@@ -252,3 +252,73 @@ def test_tasks_with_infinities_are_done_again_with_every_option(opts, D, h):
     torch.cuda.synchronize()
     plan.close()
     assert torch.equal(o2[:, :, keep], o[:, :, keep])
+
+
+BRANCHES = [
+    # clip_len, n_clips, w, P, h, D, G, options: clips that fill no query tile
+    (8, 5, 6, 3, 2, 64, 4, {}),
+    (5, 7, 3, 2, 2, 40, 9, {"window": 2, "dedup": True}),
+    (3, 11, 9, 2, 1, 96, 5, {"bias_global": 1.5}),
+    (2, 3, 1, 2, 1, 16, 0, {"bias_local": 1.0}),
+    # more global entries than the table in LDS holds, and exactly as many
+    (24, 12, 2, 1, 1, 32, 257, {"dedup": True}),
+    (24, 12, 2, 1, 1, 160, 256, {"bias_local": -1.0, "dedup": True}),
+    (40, 8, 2, 1, 1, 64, 300, {}),
+    # two query tiles per wavefront (from 4,096 tiles on): the second nearly empty, full, absent from the last
+    # wavefront
+    (17, 8, 2, 131, 2, 32, 5, {}),
+    (32, 8, 1, 129, 2, 128, 16, {}),
+    (48, 5, 0, 139, 2, 64, 3, {}),
+    (80, 4, 5, 103, 2, 104, 7, {}),
+    # a window that hides most of a long clip
+    (100, 2, 12, 2, 1, 72, 11, {"window": 3, "dedup": True}),
+    (100, 2, 12, 2, 1, 136, 0, {"window": 40}),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", BRANCHES)
+def test_tile_kernel_branches_match_oracle_on_both_sources(case, dtype):
+    """The forms that the launch chooses between, on the tensors and on a materialised context."""
+    clip_len, n_clips, w, P, h, D, G, opts = case
+    print(f"[case] tile branch {case} {dtype}", flush=True)
+    F = clip_len * n_clips
+    g = np.random.default_rng(15).integers(0, F, size=G).tolist()
+    q, k, v = make(F, P, h * D, dtype, seed=23)
+    opts = dict(opts)
+    dedup = opts.pop("dedup", False)
+    ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=dedup, **opts)
+    plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, io_dtype=U.dt_code(dtype), out_dtype=B.DSATTN_F32,
+                         flags=B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0, **opts)
+    assert_tile_kernel(B.dsattn_plan_launch_info(plan), clip_len, n_clips, P, h)
+    o1 = torch.full((F, P, h * D), float("nan"), device=DEV)
+    o2 = o1.clone()
+    B.dsattn_forward(plan, q, k, v, o1)
+    ctx = [torch.full((n_clips, plan.lk_max, P, h * D), float("nan"), dtype=q.dtype, device=DEV) for _ in range(2)]
+    B.dsattn_gather_context(plan, k, v, *ctx)
+    B.dsattn_forward_ctx(plan, q, *ctx, o2)
+    torch.cuda.synchronize()
+    plan.close()
+    U.assert_parity(o1, ref, "f32_strict", what=f"{case} on the tensors")
+    assert torch.equal(o1, o2)
+
+
+@pytest.mark.parametrize("D", list(range(4, 161, 12)))
+def test_every_fp32_row_shape(D):
+    """Blocks of 64, 32 and 16 channels, the last one full or not."""
+    q, k, v = make(40, 2, 2 * D, "f32", seed=31)
+    ref = U.oracle_forward(q, k, v, 20, 2, 3, 2, [39, 3])
+    o, info = U.library_forward(q, k, v, 20, 2, 3, 2, [39, 3], out_dtype="f32")
+    assert_tile_kernel(info, 20, 2, 2, 2)
+    U.assert_parity(o, ref, "f32_strict", what=f"D={D}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_scores_of_minus_infinity_in_the_first_tiles(dtype):
+    """Keys whose scores are -inf have no weight, also where they fill the first step."""
+    q, k, v = make(40, 2, 64, dtype, seed=37)
+    q = (q.abs() + 0.1).to(q.dtype)
+    k[:32, 1, 5] = float("-inf")
+    o, _ = U.library_forward(q, k, v, 40, 1, 0, 1, [], out_dtype="f32")
+    og, _ = U.library_forward(q, k, v, 40, 1, 0, 1, [], out_dtype="f32", flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert torch.isfinite(og).all() and float((o - og).abs().max()) <= 2e-5
