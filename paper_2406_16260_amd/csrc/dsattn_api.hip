@@ -266,14 +266,10 @@ int dsattn_gather_context(const dsattn_plan_t *plan, const void *K, const void *
     DeviceGuard g(plan->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "dsattn_gather_context: hipSetDevice");
     hipStream_t st = (hipStream_t)stream;
-    if (K) {
-        hipError_t e = launch_gather(*plan, K, Kctx, st);
-        if (e != hipSuccess) return hip_fail(e, "dsattn_gather_context: launch (K)");
-    }
-    if (V) {
-        hipError_t e = launch_gather(*plan, V, Vctx, st);
-        if (e != hipSuccess) return hip_fail(e, "dsattn_gather_context: launch (V)");
-    }
+    const void *src[2] = {K ? K : V, V};
+    void *dst[2] = {K ? Kctx : Vctx, Vctx};
+    const hipError_t e = launch_gather(*plan, K && V ? 2 : 1, src, dst, st);
+    if (e != hipSuccess) return hip_fail(e, "dsattn_gather_context: launch");
     return DSATTN_OK;
 }
 

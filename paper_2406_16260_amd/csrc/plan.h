@@ -43,7 +43,8 @@ namespace dsattn {
 int fail(int code, const char *fmt, ...);
 
 // Launchers; each validates nothing (the API layer has) and returns a hipError_t.
-hipError_t launch_gather(const dsattn_plan_t &pl, const void *X, void *Xctx, hipStream_t st);
+// (gathers n = 1 or 2 tensors)
+hipError_t launch_gather(const dsattn_plan_t &pl, int n, const void *const *X, void *const *Xctx, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, int64_t bytes, hipStream_t st);
 
 // Generic vector-ALU attention. ctx_mode = false: K/V are [F,P,C] and keys are
