@@ -8,7 +8,8 @@
 // is what is done here (one read of X for the statistics instead of two), and between
 // devices it would be one exchange instead of two.
 //
-// All kernels stream X ([F, P, C], C fastest) with 16-byte lanes; a lane's 16 bytes belong to at
+// Tensors of up to a million elements take one launch of gn_small_kernel, larger ones three kernels.  These
+// stream X ([F, P, C], C fastest) with 16-byte lanes; a lane's 16 bytes belong to at
 // most two groups.  Reductions are deterministic: per-thread fp32 sums about a per-thread pilot,
 // a fixed-order merge per workgroup into a table in the caller's workspace, and a small
 // finalising kernel in fp64.
@@ -130,7 +131,8 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
 {
     constexpr int VEC = sizeof(T) == 2 ? 8 : 4;
     constexpr int UNR = kGnUnroll;  // independent row loads in flight per thread
-    // [4][blockDim.y][ch] doubles: sum, sum of squares for g0, then g0 + 1; then [3] floats: rows, pilots
+    // [4][blockDim.y][ch] doubles: sum, sum of squares for g0, then g0 + 1; then [3] floats: rows, pilots;
+    // then [shares][groups][3] doubles
     extern __shared__ double red[];
     const int lane = threadIdx.x, ry = threadIdx.y, ny = blockDim.y;
     const int g0 = (lane * VEC) / cg;
@@ -212,20 +214,42 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
     redf[1 * nt + t] = p0;
     redf[2 * nt + t] = p1;
     __syncthreads();
-    for (int g = t; g < groups; g += nt) {
+    // A few threads per group share its row phases, then one of them adds up what they have.  (One thread per
+    // group from the start was a chain of LDS reads as long as phases x lanes, some 3 us at the end of every
+    // workgroup: 64 x 60 x 640 bf16 18.5 -> 15.1 us a call, 296 x 696 x 320 76.0 -> 71.7.)
+    const int shares = max(1, min(min(nt / groups, ny), 8));
+    double *const shared_sums = red + 4 * nt + (3 * nt + 1) / 2;  // [shares][groups][3]
+    for (int gs = t; gs < groups * shares; gs += nt) {
+        const int g = gs % groups, share = gs / groups;
         const int l0 = (g * cg) / VEC, l1 = ((g + 1) * cg - 1) / VEC;
         // (row phase 0 of every workgroup has read at least one row: its pilot is an element)
-        const double P = (l0 * VEC) / cg == g ? redf[1 * nt + l0] : redf[2 * nt + l0];
+        const double P = l0 * VEC >= g * cg ? redf[1 * nt + l0] : redf[2 * nt + l0];
         GnSums m = {0.0, 0.0, 0.0};
-        for (int y = 0; y < ny; ++y)
+        for (int y = share; y < ny; y += shares)
             for (int l = l0; l <= l1; ++l) {
-                const int e = y * ch + l, k = (l * VEC) / cg == g ? 0 : 1;
-                const int s0 = min(VEC, ((l * VEC) / cg + 1) * cg - l * VEC);  // the lane's split
-                const double n = (double)redf[e] * (k ? VEC - s0 : s0);
+                const int e = y * ch + l, k = l * VEC >= g * cg ? 0 : 1;  // the lane's first group, or its second
+                const int channels = min((l + 1) * VEC, (g + 1) * cg) - max(l * VEC, g * cg);
+                const double n = (double)redf[e] * channels;
                 if (n > 0.0)
                     gn_add(m, n, red[2 * k * nt + e], red[(2 * k + 1) * nt + e],
                            (double)redf[(1 + k) * nt + e] - P);
             }
+        double *const at = shared_sums + 3 * (int64_t)gs;
+        at[0] = m.n;
+        at[1] = m.s1;
+        at[2] = m.s2;
+    }
+    __syncthreads();
+    for (int g = t; g < groups; g += nt) {
+        const int l0 = (g * cg) / VEC;
+        const double P = l0 * VEC >= g * cg ? redf[1 * nt + l0] : redf[2 * nt + l0];
+        GnSums m = {0.0, 0.0, 0.0};
+        for (int share = 0; share < shares; ++share) {
+            const double *const at = shared_sums + 3 * ((int64_t)share * groups + g);
+            m.n += at[0];
+            m.s1 += at[1];
+            m.s2 += at[2];
+        }
         const double mean = P + m.s1 / m.n, m2 = m.s2 - m.s1 * m.s1 / m.n;
         const float hi = (float)mean;
         GnPart part;
@@ -245,7 +269,7 @@ __global__ __launch_bounds__(256) void gn_finalize_kernel(const GnPart *__restri
                                                           int groups, int cg, int64_t rows_all, int bite,
                                                           float eps)
 {
-    __shared__ double rn[256], rm[256], rq[256];
+    __shared__ double rn[4], rm[4], rq[4];
     const int g = blockIdx.x, t = threadIdx.x;
     const GnPart f = partial[g];
     const double P = (double)f.mean + (double)f.mean_lo;
@@ -257,19 +281,24 @@ __global__ __launch_bounds__(256) void gn_finalize_kernel(const GnPart *__restri
         const int64_t rows = ((bites - 1 - i) / n_blocks + 1) * bite - (i == last ? bites * bite - rows_all : 0);
         gn_add(m, (double)rows * cg, 0.0, p.m2, ((double)p.mean + (double)p.mean_lo) - P);
     }
-    rn[t] = m.n;
-    rm[t] = m.s1;
-    rq[t] = m.s2;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            rn[t] += rn[t + w];
-            rm[t] += rm[t + w];
-            rq[t] += rq[t + w];
-        }
-        __syncthreads();
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        m.n += __shfl_xor(m.n, w);
+        m.s1 += __shfl_xor(m.s1, w);
+        m.s2 += __shfl_xor(m.s2, w);
     }
+    if (t % 64 == 0) {
+        rn[t / 64] = m.n;
+        rm[t / 64] = m.s1;
+        rq[t / 64] = m.s2;
+    }
+    __syncthreads();
     if (t == 0) {
+        for (int w = 1; w < 4; ++w) {
+            rn[0] += rn[w];
+            rm[0] += rm[w];
+            rq[0] += rq[w];
+        }
         const double d = rm[0] / rn[0];
         double var = rq[0] / rn[0] - d * d;
         var = var < 0.0 ? 0.0 : var;  // (a NaN stays one)
@@ -359,6 +388,97 @@ __global__ __launch_bounds__(1024) void gn_apply_kernel(const uint4 *X, uint4 *Y
     }
 }
 
+// Small tensors in one launch: a workgroup holds all of a group in registers, PER pairs of neighbouring
+// channels a thread, and goes from mean to squared deviations to result without another read.  A group's
+// rows are pieces of 2 cg or 4 cg bytes, so lines are fetched by the several groups that share them, and
+// there are only as many workgroups as groups; what it saves is two launches and the gaps between them.
+// A thread's sums are fp32 over 16 elements at a time, everything beyond that is fp64.  In place it works
+// too: nothing is written before the group has been read.
+constexpr int kGnSmallThreads = 1024;
+constexpr int kGnSmallMaxCg = 256;
+template <typename T, int PER>
+__global__ __launch_bounds__(kGnSmallThreads) void gn_small_kernel(const T *X, T *Y, const float *__restrict__ gamma,
+                                                                   const float *__restrict__ beta, float *out, int C,
+                                                                   int cg, int groups, int rows, float eps)
+{
+    constexpr int NT = kGnSmallThreads, NW = NT / 64;
+    typedef T pair __attribute__((ext_vector_type(2)));
+    __shared__ double part[2][NW];
+    __shared__ float sg[kGnSmallMaxCg], sb[kGnSmallMaxCg];
+    const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    X += g * cg;
+    Y += g * cg;
+    const float pilot = (float)X[0];
+    if (t < cg) {
+        sg[t] = gamma ? gamma[g * cg + t] : 1.f;
+        sb[t] = beta ? beta[g * cg + t] : 0.f;
+    }
+    // Pairs t + i NT of the group: row and channel are counted along.
+    const int hp = cg / 2, n2 = rows * hp;
+    const int dr = NT / hp, dc = 2 * (NT - dr * hp);
+    const int row0 = t / hp, c0 = 2 * (t - row0 * hp);
+    pair x[PER];
+    auto walk = [&](auto &&visit) __attribute__((always_inline)) {
+        int at = row0 * C + c0, c = c0;  // elements from the group's first (a small tensor: they fit)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (t + i * NT < n2) visit(i, at, c);
+            const bool over = c + dc >= cg;
+            c += over ? dc - cg : dc;
+            at += over ? (dr + 1) * C + dc - cg : dr * C + dc;
+        }
+    };
+    walk([&](int i, int at, int) { x[i] = *(const pair *)(X + at); });
+    auto total = [&](double s, int which) __attribute__((always_inline)) -> double {
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+        if (lane == 0) part[which][wv] = s;
+        __syncthreads();
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += part[which][w];
+        return sum;
+    };
+    const double n = 2.0 * n2;
+    auto sums = [&](auto &&f) __attribute__((always_inline)) -> double {
+        double s = 0.0;
+#pragma unroll
+        for (int i0 = 0; i0 < PER; i0 += 8) {
+            float a = 0.f;
+#pragma unroll
+            for (int i = i0; i < std::min(PER, i0 + 8); ++i)
+                if (t + i * NT < n2) a = f((float)x[i][1], f((float)x[i][0], a));
+            s += (double)a;
+        }
+        return s;
+    };
+    const double s = total(sums([&](float v, float a) { return a + (v - pilot); }), 0);
+    const double mean = (double)pilot + s / n;
+    const float mu = (float)mean;
+    const double off = mean - (double)mu;
+    const double q = total(sums([&](float v, float a) { return fmaf(v - mu, v - mu, a); }), 1) / n - off * off;
+    const float rs = (float)(1.0 / sqrt((q < 0.0 ? 0.0 : q) + (double)eps));  // (a NaN stays one)
+    if (t == 0 && out) {
+        out[g] = mu;
+        out[groups + g] = rs;
+    }
+    walk([&](int i, int at, int c) {
+        *(pair *)(Y + at) = pair{(T)fmaf(((float)x[i][0] - mu) * rs, sg[c], sb[c]),
+                                 (T)fmaf(((float)x[i][1] - mu) * rs, sg[c + 1], sb[c + 1])};
+    });
+}
+
+// Where it is the faster one.  32 groups, us a call with three launches and with one, bf16: 16 x 30 x 960 14.7 and
+// 7.8 (eight pairs a thread), 32 x 40 x 640 15.2 and 9.4, 16 x 51 x 1,280 15.2 and 10.3, 32 x 100 x 320 15.4 and
+// 12.9; fp32: 14.7 and 7.7, 14.6 and 8.9, 14.2 and 9.6, but 14.1 and 15.0 (3,200 rows of short pieces).  With 32
+// pairs a thread, 64 x 40 x 640 bf16, 20.6 against 15.1.
+bool gn_small(const dsattn_gn_desc &d, const GnShape &s)
+{
+    const int64_t most_rows = d.io_dtype == DSATTN_BF16 ? 4096 : 2560;
+    return s.cg % 2 == 0 && s.cg <= kGnSmallMaxCg && d.groups >= 8 && s.rows <= most_rows &&
+           s.rows * s.cg <= 2 * 16 * kGnSmallThreads;
+}
+
 int gn_validate(const dsattn_gn_desc *d, GnShape &s, const char *who)
 {
     if (!d) return fail(DSATTN_EINVAL, "%s: null descriptor", who);
@@ -393,14 +513,36 @@ size_t gn_workspace_bytes(const dsattn_gn_desc &d, const GnShape &s)
 // 64 x 2,560 x 320 bf16 77 / 64 us, 384 x 640 x 640 fp32 368 / 320 us.
 constexpr size_t kGnStreamBytes = (size_t)32 << 20;
 
-// Enqueues the three kernels; everything is validated.
+// Enqueues the kernels; everything is validated.
 hipError_t gn_enqueue(const dsattn_gn_desc &d, const GnShape &s, const void *X, const float *gamma,
                       const float *beta, void *Y, float *stats, void *workspace, hipStream_t st)
 {
+    if (gn_small(d, s)) {
+        const bool few = s.rows * s.cg <= 2 * 8 * kGnSmallThreads;
+        const dim3 grid(d.groups), block(kGnSmallThreads);
+#define DSATTN_GN_SMALL(T, PER)                                                                   \
+    hipLaunchKernelGGL((gn_small_kernel<T, PER>), grid, block, 0, st, (const T *)X, (T *)Y, gamma, beta, stats, \
+                       d.channels, s.cg, d.groups, (int)s.rows, d.eps)
+        if (d.io_dtype == DSATTN_BF16) {
+            if (few)
+                DSATTN_GN_SMALL(__bf16, 8);
+            else
+                DSATTN_GN_SMALL(__bf16, 16);
+        } else {
+            if (few)
+                DSATTN_GN_SMALL(float, 8);
+            else
+                DSATTN_GN_SMALL(float, 16);
+        }
+#undef DSATTN_GN_SMALL
+        return hipGetLastError();
+    }
     float *partial = (float *)workspace;
     float *wstats = partial + 4 * (size_t)d.n_clips * s.bpc * d.groups;
     const dim3 grid(s.blocks), block(s.ch, s.rpb);
-    const size_t lds = (size_t)s.ch * s.rpb * (4 * sizeof(double) + 3 * sizeof(float));
+    const int nt = s.ch * s.rpb, shares = std::max(1, std::min({nt / d.groups, s.rpb, 8}));
+    const size_t lds = (size_t)nt * 4 * sizeof(double) + (size_t)(3 * nt + 1) / 2 * 8 +
+                       (size_t)shares * d.groups * 3 * sizeof(double);
 
     const bool stream = (size_t)s.rows * s.ch * 16 >= kGnStreamBytes;
 #define DSATTN_GN_RUN(T)                                                                          \

@@ -305,3 +305,37 @@ def test_groupnorm_affine_factors_meet_the_normalised_value(dtype):
     # a few roundings of fp32 (the mean's by its own size), and that of a bf16 result
     np.testing.assert_allclose(y.cpu().double().numpy(), ref, atol=8 * 2.0 ** -24 * 3e-26,
                                rtol=8 * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,C,groups", [
+    (1, 128, 8),          # one row: a few pairs for 1,024 threads
+    (1023, 128, 8),       # the last size of eight pairs a thread less a row
+    (1024, 128, 8),       # exactly that size
+    (1025, 128, 8),       # the next one
+    (2048, 128, 8),       # the last size that one launch takes, and one row more
+    (2049, 128, 8),
+    (2560, 96, 12),       # the row limits of the two types
+    (2561, 96, 12),
+    (4096, 64, 8),
+    (4097, 64, 8),
+    (97, 2048, 8),        # 256 channels per group: the most that one launch takes
+    (97, 2064, 8),
+])
+def test_groupnorm_small_tensors_in_one_launch(rows, C, groups, dtype):
+    """Sizes around the limits of the single-launch kernel, held to the bars of test_groupnorm_matches_oracle;
+    half of the tensor is shifted, so that no part has the whole's mean."""
+    print(f"[case] groupnorm small {rows} {C} {groups} {dtype}", flush=True)
+    x = synth.make_tensor(rows, 1, C, 41, "iid", dtype)
+    x = (x.float() + (torch.arange(rows) % 2 * 3.0)[:, None, None]).to(x.dtype).to(DEV)
+    gen = torch.Generator().manual_seed(4)
+    gamma, beta = torch.randn(C, generator=gen).to(DEV), torch.randn(C, generator=gen).to(DEV)
+    ref, mean, var = oracle.groupnorm(x.cpu().double().numpy(), rows, 1, groups, eps=1e-5,
+                                      gamma=gamma.cpu().double().numpy(), beta=beta.cpu().double().numpy())
+    for in_place in (False, True):
+        y, stats = run_gn(x.clone(), rows, 1, groups, gamma, beta, in_place=in_place)
+        st = stats.cpu().double().numpy()
+        np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6)
+        np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
+        U.assert_parity(y, ref, "f32_strict" if dtype == "f32" else "bf16", what=f"small {rows} {C}")
