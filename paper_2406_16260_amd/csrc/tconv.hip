@@ -580,15 +580,17 @@ constexpr int conv_lds_bytes(int bm, int bn, int nj, int waves)
 const ConvVariant kConvVariants[] = {
     DSATTN_CONV_VARIANT(4, 2, 2, 4),     // 256 x 256
     DSATTN_CONV_VARIANT(2, 5, 4, 2),     // 256 x 320
+    DSATTN_CONV_VARIANT(2, 3, 4, 2),     // 256 x 192
     DSATTN_TILE_VARIANT(4, 5, 2, 2),     // 128 x 160
     DSATTN_TILE_VARIANT(2, 4, 4, 2),     // 128 x 128, eight wavefronts
     DSATTN_PIPE_VARIANT(2, 2, 2, 2, 4),  // 128 x 128, pipelined
+    DSATTN_PIPE_VARIANT(2, 1, 2, 2, 6),  // 128 x 64, pipelined
     DSATTN_TILE_VARIANT(2, 2, 2, 2),     // 64 x 64
     {64, 64, 4, 2 * (64 + 64) * kRow, 0, true,
      {(const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, false>,
       (const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, true>}},
 };
-enum { kBig256, kBig320, kTile160, kTile128, kPipe128, kTile64, kTileF32 };  // positions in the table
+enum { kBig256, kBig320, kBig192, kTile160, kTile128, kPipe128, kPipe64, kTile64, kTileF32 };  // positions in the table
 
 int conv_validate(const dsattn_conv_desc *d, const char *who)
 {
@@ -617,40 +619,48 @@ int64_t conv_tiles(const ConvVariant &v, int64_t M, int64_t c_out, int groups)
     return ((M + v.bm - 1) / v.bm) * ((c_out + v.bn - 1) / v.bn) * groups;
 }
 
-// Estimated time in us of a bf16 problem that a round of 256 x 320 tiles does not fill: a start, and
-// per stage what the fullest compute unit takes.  Fitted to sweeps of the projections, 256 to 40,960
-// rows, 320, 640 and 1,280 channels, one and three weight sets (measured us at 20 stages, i.e. 1,280
-// channels):
-//   rows x sets   256 x 320  256 x 256  128 x 160  128 x 128  pipelined  64 x 64
-//     256 x 1       33.0       28.6       18.1       14.2       12.8      < 11.6
-//   2,560 x 1       35.8       32.3       19.8       17.8       14.9       17.2
-//   5,000 x 1       36.1       32.5       27.1       22.7       26.6       28.3
-//   2,560 x 3       37.6       33.9       29.4       37.2       40.0       43.6
-//   5,000 x 3       42.7       62.6       50.9       56.1       67.1       79.2
-// It holds for convolutions too: over 65 of 3 and 5 taps, 320 to 1,280 channels in and out and 256 to
-// 40,960 rows (us below), the kernel it picks is the fastest of the six in 53, and within 14 % in the
-// others, which all take 64 x 64 where the pipelined kernel is faster (few tiles of 60 stages and more).
-// None is slower than the better kernel of 256 rows.
-//   taps, channels, rows   256 x 320  256 x 256  128 x 160  128 x 128  pipelined  64 x 64   picked
-//   3, 640, 2,560             46.7       40.3       25.4       20.6       17.7       14.7   64 x 64
-//   3, 640, 10,240            48.7       45.9       35.4       29.4       34.0       39.8   128 x 128
-//   3, 1,280, 640             87.9       77.5       47.2       44.6       29.3       32.4   64 x 64
-//   3, 1,280, 2,560           88.7       80.5       48.2       45.2       32.8       45.9   pipelined
-//   3, 1,280, 8,192           94.4       85.1       73.5       96.3       94.3      125.5   128 x 160
-//   5, 1,280, 10,240         148.5      134.7      171.5      172.4      195.4      283.9   256 x 256
-double conv_estimate(int variant, int64_t tiles, int64_t stages)
+// Estimated time in us of a bf16 problem of a few rounds of tiles: a start, and per round the stages of a tile
+// and what its start and end cost.  Of the kernels with two workgroups on a compute unit a round is 512 tiles,
+// the last one, of up to 256, a shorter one.  Fitted to 137 projections and convolutions of 1 to 5 taps, 500 to
+// 60,000 rows, 128 to 1,280 channels, one and three weight sets, three sets of tensors in rotation (weights come
+// from beyond the L2, as a model's do); over these the kernel that the rule below picks is 1.4 % behind the fastest
+// of the eight on average and 9 % at most but for one (64 x 64 for 3,000 x 1,024 x 1,024, 12.0 against 13.8 us), and 5 %
+// faster on average than without the 128 x 64 and 256 x 192 tiles.  With its weights in the L2 a convolution of few
+// tiles may be faster on 64 x 64 (544 x 640 x 640, 3 taps, 10.8 against 13.0 us, but 16.9 against 13.2 from beyond it).
+// Measured us (rows x c_in x c_out, taps x sets):
+//                                256 x 320  256 x 192  128 x 160  128 x 128  pipelined  128 x 64  64 x 64
+//     1,104 x   960 x   320, 3      78.5               38.0       31.1      29.0      17.5      23.8
+//     2,400 x   640 x   640, 3      56.9               27.3       22.2      21.3      13.6      17.2
+//     2,560 x 1,280 x   640, 5     172.4               81.3       66.5      60.0      34.0      49.3
+//     6,400 x 1,280 x   320, 3     107.0               50.1       41.0      38.1      23.3      31.0
+//     1,728 x   320 x   320, 3      29.9               15.5       11.2      12.7       8.6       7.1
+//     1,280 x 1,280 x 1,280, 1      41.9       25.7     20.5       17.9      16.0      11.7      13.1
+//     2,560 x 1,280 x 1,280, 1      42.4       26.0     20.6       18.0      16.6      19.9      16.5
+//     2,560 x 1,280 x 1,280, 1 x 3  43.3       27.6     27.5       35.6      43.5      46.5      41.6
+//     7,072 x 1,024 x 1,024, 1 x 3  66.8       44.5     52.9       47.8      71.9      83.6      64.9
+//     7,200 x 1,280 x 1,280, 3     107.7               65.7       92.8     108.4     106.3     112.9
+double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
 {
-    const double r1 = (double)((tiles + 255) / 256), r2 = (double)((tiles + 511) / 512);
-    double per_stage = 0.0;
+    const double st = (double)stages;
+    const int64_t full = tiles / 512, rest = tiles - 512 * full;
+    auto whole = [&](double per_stage, double ends) {  // one workgroup on a compute unit
+        return 3.0 + (double)((tiles + 255) / 256) * (per_stage * st + ends);
+    };
+    auto paired = [&](double one, double one_ends, double two, double two_ends, double full_round, double full_ends) {
+        return 3.0 + (double)full * (full_round * st + full_ends) +
+               (rest > 256 ? two * st + two_ends : rest > 0 ? one * st + one_ends : 0.0);
+    };
     switch (variant) {
-    case kBig256: per_stage = 1.45 * r1; break;
-    case kBig320: per_stage = 1.6 * r1; break;
-    case kTile160: per_stage = 0.8 + 0.5 * (r1 - 1.0); break;
-    case kTile128: per_stage = 0.92 * r2; break;
-    case kPipe128: per_stage = 0.55 * r1; break;
-    default: per_stage = 7.5e-4 * (double)std::max<int64_t>(tiles, 350); break;
+    case kBig256: return whole(1.22, 5.0);
+    case kBig320: return whole(1.55, 6.0);
+    case kBig192: return whole(1.03, 4.8);
+    case kTile160: return paired(0.75, 2.5, 0.955, 5.0, 1.12, 4.0);
+    case kTile128: return paired(0.61, 2.9, 0.74, 2.6, 0.87, 1.4);
+    case kPipe128: return whole(0.54, 2.6);
+    case kPipe64: return whole(0.2625, 3.4);
+    default:  // 64 x 64, several to a unit; its two slots do not cover the latency of weights beyond the L2
+        return 4.0 + 1.3e-3 * (double)tiles + st * std::max(small_w ? 0.2 : 0.455, 8.2e-4 * (double)tiles);
     }
-    return 4.0 + per_stage * (double)stages;
 }
 
 // The kernel of a problem; null: the vector kernel.
@@ -672,8 +682,15 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
         constexpr int64_t kMax = ((int64_t)1 << 32) / 256 - kXcds;
         return conv_tiles(v, M, d.c_out, groups) <= kMax ? &v : nullptr;
     }
+    // Up to 128 output channels: the large tiles would multiply out at least as many again.  270,816 x 128 x 128 from
+    // HBM, one set 46.4 us on 256 x 256 tiles, 38.2 on 256 x 128, 35.2 on these; three sets 103.5, 87.4, 77.8.
+    // (A launch has less than 2^32 threads.)
+    const int64_t tiles128 = conv_tiles(kConvVariants[kTile128], M, d.c_out, groups);
+    const bool narrow = d.c_out > 64 && d.c_out <= 128 && tiles128 <= ((int64_t)1 << 32) / 512 - kXcds;
     // Large problems: of the persistent kernels the one with the least multiplied-out area (padding
-    // of the last row and column tiles), then the larger tile (fewer epilogues).
+    // of the last row and column tiles), then the larger tile (fewer epilogues).  (256 x 192 tiles, which
+    // multiply out a tenth less for 576 channels, take more energy a flop: layers of 128,000 and 259,328 rows, 487
+    // and 985 us without them, 543 and 1,099 with.)
     int best = -1;
     int64_t best_area = 0, best_tiles = 0;
     for (int k : {kBig256, kBig320}) {
@@ -688,19 +705,23 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
         }
     }
     if (best < 0) return nullptr;
-    // Less than one round of them leaves compute units idle: whichever is estimated fastest.  (A second
-    // round that is nearly empty does too, and is not asked about: at 258 to 320 tiles of 256 x 320 a smaller
-    // tile is 8 to 20 % faster, 65.2 against 73.7 us at 18,000 x 1,280 x 1,280, from 384 on 1 to 10 %.)
-    if (best_tiles < 256) {
-        const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
+    // Less than one round of them leaves compute units idle: whichever is estimated fastest.  So does a second
+    // round that is nearly empty: whichever is estimated a tenth faster.  (The fit has no problems of fewer than
+    // four stages there, and from one and a half rounds on memory and power decide.)
+    const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
+    if (best_tiles < 256 || (best_tiles < 384 && stages >= 4)) {
+        const bool small_w = taps * d.c_out * d.c_in * es <= (int64_t)1 << 20;
         double best_us = 1e300;
+        if (best_tiles >= 256) best_us = 0.9 * conv_estimate(best, best_tiles, stages, small_w);
         for (int k = kBig256; k <= kTile64; ++k) {
-            const double us = conv_estimate(k, conv_tiles(kConvVariants[k], M, d.c_out, groups), stages);
+            const double us = conv_estimate(k, conv_tiles(kConvVariants[k], M, d.c_out, groups), stages, small_w);
             if (us < best_us) {
                 best_us = us;
                 best = k;
             }
         }
+    } else if (narrow) {
+        best = kTile128;
     }
     return &kConvVariants[best];
 }

@@ -11,7 +11,9 @@
 // l % 16, chunk 4 kk + l / 16 of the stage: one operand of v_mfma_f32_16x16x32_bf16, or element s of
 // it the operand of the s-th of four v_mfma_f32_16x16x4_f32 (which channels an instruction
 // contracts is free as long as both operands agree).
-// tconv_pipe_kernel: one workgroup per compute unit, software-pipelined, for problems of one round.
+// tconv_pipe_kernel: one workgroup per compute unit, software-pipelined, for problems of one round; with
+// 128 x 64 tiles and six slots for those of few tiles and many stages, where the latency of weights from
+// beyond the L2 is what a stage takes (6,400 x 1,280 x 320, 3 taps: 31.0 us with two slots of 64 x 64, 23.3).
 //
 // What bounds them.  fp32: the fp32 matrix rate (157 TFLOP/s; 40,000 x 1,280 x 1,280 reaches 131, 10,240 x
 // 640 x 640 takes 77 us where one thread per output took 16,370 us).  Four slots measured the same

@@ -566,3 +566,24 @@ def test_conv_fp32_frames_outside_the_video_add_nothing(shape):
     ref = run_conv(x, w, None, clip_len, n_clips, "f32", flags=B.DSATTN_FLAG_FORCE_GENERIC)
     assert torch.isfinite(ref[:n, :, 1]).all() and torch.isfinite(ref[-n:, :, 3]).all()
     torch.testing.assert_close(y, ref, rtol=TOL_ACC, atol=TOL_ACC)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", [
+    (1283, 1288, 1272, 1, (128, 64, 256)),    # the pipelined 128 x 64 tile: 21 stages in six slots, tails everywhere
+    (129, 8200, 68, 2, (128, 64, 256)),       # a second row tile of one row, c_out not whole 16-byte pieces
+    (7041, 584, 570, 3, (256, 192, 512)),     # the 256 x 192 tile, less than a round
+    (98500, 72, 126, 1, (128, 128, 512)),     # few output channels: small tiles for a large problem
+    (98500, 64, 128, 2, (128, 128, 512)),
+])
+def test_linear_tiles_for_few_tiles_and_few_channels(rows, c_in, c_out, n_out, tile):
+    for out_dtype in ("f32", "bf16"):
+        info = linear_case(rows, c_in, c_out, n_out, dtype="bf16", out_dtype=out_dtype)
+        assert (info["kernel"], info["tile_m"], info["tile_n"], info["block_threads"]) == (1,) + tile
+
+
+@pytest.mark.gpu
+def test_conv_on_the_pipelined_narrow_tile():
+    """60 stages, rows before the first and after the last frame."""
+    assert B.dsattn_temporal_conv_info(16, 2, 41, 1280, 320, 1)["tile_n"] == 64
+    conv_case(16, 2, 41, 1280, 320, 1, dtype="bf16")
