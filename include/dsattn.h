@@ -253,7 +253,7 @@ typedef struct dsattn_conv_desc {
 /* The launch the library would make for this shape (host only; for tests and benchmarks). */
 typedef struct dsattn_conv_info {
     int32_t kernel;        /* 1 = bf16 MFMA implicit-GEMM kernels; 0 = the others: fp32 tensors on the
-                              fp32 matrix instructions (tile_m > 0), or the generic vector-ALU kernel */
+                              matrix cores (tile_m > 0), or the generic vector-ALU kernel */
     int32_t tile_m;        /* output rows (frame, position) per workgroup, 0 for the generic kernel */
     int32_t tile_n;        /* output channels per workgroup */
     int32_t tile_k;        /* contraction depth per step */
@@ -277,7 +277,8 @@ int dsattn_temporal_conv_info(const dsattn_conv_desc *desc, dsattn_conv_info *in
  *   Y    : device, [F, P, c_out] of out_dtype, 16-byte aligned; must not overlap X
  * Runs on the current device; enqueues one kernel on `stream`; allocates nothing.  bf16 inputs
  * with c_in a multiple of 8 and fp32 inputs with c_in a multiple of 4 run on the matrix cores (fp32 on
- * the fp32 instructions: nothing is rounded to 16 bits), everything else on a plain vector kernel.
+ * the fp32 instructions, or split into three bf16 numbers each, which add up to it: nothing is rounded to 16
+ * bits), everything else on a plain vector kernel.
  * Errors: EINVAL (bad shape, null or misaligned pointer, overlap), EHIP.
  */
 int dsattn_temporal_conv(const dsattn_conv_desc *desc, const void *X, const void *W,

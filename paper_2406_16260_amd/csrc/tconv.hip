@@ -46,6 +46,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 64;       // contraction depth per stage (bf16 elements)
 constexpr int kRow = 128;     // bytes of one LDS row: the 64 channels of a stage = one cache line
@@ -520,6 +521,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
 }  // namespace dsattn
 
 #include "tconv_tile.h"
+#include "tconv_split.h"
 
 namespace dsattn {
 namespace {
@@ -575,6 +577,9 @@ constexpr int conv_lds_bytes(int bm, int bn, int nj, int waves)
     {32 * MB * WVM, 32 * NB * WVN, WVM * WVN, S * (32 * MB * WVM + 32 * NB * WVN) * kRow, 0, false, \
      {(const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, false>,                              \
       (const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, true>}}
+#define DSATTN_SPLIT_VARIANT(MB)                                                                  \
+    {32 * MB, 32 * MB, 4, 3 * 64 * MB * 64, 0, true,                                              \
+     {(const void *)&tconv_split_kernel<MB>, (const void *)&tconv_split_kernel<MB>}}
 // Eight wavefronts (two per SIMD) in the persistent kernels: one wavefront per SIMD cannot keep the
 // matrix cores busy with 16x16x32 instructions (measured: 1.46 against 2.4 PFLOP/s on idle data).
 const ConvVariant kConvVariants[] = {
@@ -589,8 +594,10 @@ const ConvVariant kConvVariants[] = {
     {64, 64, 4, 2 * (64 + 64) * kRow, 0, true,
      {(const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, false>,
       (const void *)&tconv_tile_kernel<float, 2, 2, 2, 2, true, true>}},
+    DSATTN_SPLIT_VARIANT(2),             // fp32 on the bf16 instructions: 64 x 64
+    DSATTN_SPLIT_VARIANT(4),             // 128 x 128
 };
-enum { kBig256, kBig320, kBig192, kTile160, kTile128, kPipe128, kPipe64, kTile64, kTileF32 };  // positions in the table
+enum { kBig256, kBig320, kBig192, kTile160, kTile128, kPipe128, kPipe64, kTile64, kTileF32, kSplit64, kSplit128 };  // positions in the table
 
 int conv_validate(const dsattn_conv_desc *d, const char *who)
 {
@@ -663,6 +670,28 @@ double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
     }
 }
 
+// The same for fp32, of the kernel on the fp32 instructions and of those on the bf16 instructions.  Measured us,
+// 64 x 64 fp32, 64 x 64 and 128 x 128 split:
+//    1,600 x   640 x   640, 3 taps     41.4   49.1  107.0    (one workgroup on a compute unit)
+//      900 x 1,280 x 1,280, 1          48.0   42.1   73.1
+//   11,856 x   320 x   320, 1 x 3      63.9   57.4   58.6
+//    6,400 x   320 x   320, 3          37.0   33.4   56.4
+//   10,240 x   640 x   640, 1          76.7   65.0   54.0
+//   10,240 x   640 x   640, 1 x 3     201.1  172.4  141.7
+//    7,152 x 1,024 x 1,024, 1 x 3     348.7  310.9  251.2
+double conv_f32_estimate(int variant, int64_t tiles, int64_t stages)
+{
+    const double st = (double)stages, n = (double)tiles;
+    const int64_t full = tiles / 512, rest = tiles - 512 * full;
+    switch (variant) {
+    case kTileF32: return 4.0 + st * std::max(tiles <= 256 ? 0.66 : 1.1, 2.35e-3 * n);
+    case kSplit64: return 4.0 + st * std::max(tiles <= 256 ? 0.82 : 0.98, 2.0e-3 * n);
+    default:
+        return 3.0 + (double)full * (2.65 * st + 4.0) +
+               (rest > 256 ? 2.45 * st + 3.0 : rest > 0 ? 1.78 * st + 2.0 : 0.0);
+    }
+}
+
 // The kernel of a problem; null: the vector kernel.
 const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 1)
 {
@@ -675,12 +704,22 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
     if (taps * d.c_out * d.c_in * es >= ((int64_t)1 << 31)) return nullptr;
     if ((320 + 2 * (int64_t)d.reach * d.spatial) * d.c_in * es >= ((int64_t)1 << 31)) return nullptr;
     constexpr int64_t kMaxTiles = 0x7fffffffLL / 2;
+    const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
     if (f32) {
         // a workgroup per tile, and a launch has less than 2^32 threads; above, the vector kernel takes what
         // it can (a few output channels: it has one thread each, a tile 256 for 64 of them)
-        const ConvVariant &v = kConvVariants[kTileF32];
         constexpr int64_t kMax = ((int64_t)1 << 32) / 256 - kXcds;
-        return conv_tiles(v, M, d.c_out, groups) <= kMax ? &v : nullptr;
+        if (conv_tiles(kConvVariants[kTileF32], M, d.c_out, groups) > kMax) return nullptr;
+        int best = kTileF32;
+        double best_us = 1e300;
+        for (int k : {kTileF32, kSplit64, kSplit128}) {
+            const double us = conv_f32_estimate(k, conv_tiles(kConvVariants[k], M, d.c_out, groups), stages);
+            if (us < best_us) {
+                best_us = us;
+                best = k;
+            }
+        }
+        return &kConvVariants[best];
     }
     // Up to 128 output channels: the large tiles would multiply out at least as many again.  270,816 x 128 x 128 from
     // HBM, one set 46.4 us on 256 x 256 tiles, 38.2 on 256 x 128, 35.2 on these; three sets 103.5, 87.4, 77.8.
@@ -708,7 +747,6 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
     // Less than one round of them leaves compute units idle: whichever is estimated fastest.  So does a second
     // round that is nearly empty: whichever is estimated a tenth faster.  (The fit has no problems of fewer than
     // four stages there, and from one and a half rounds on memory and power decide.)
-    const int64_t stages = taps * ((d.c_in * es + kRow - 1) / kRow);
     if (best_tiles < 256 || (best_tiles < 384 && stages >= 4)) {
         const bool small_w = taps * d.c_out * d.c_in * es <= (int64_t)1 << 20;
         double best_us = 1e300;

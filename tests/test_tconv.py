@@ -587,3 +587,79 @@ def test_conv_on_the_pipelined_narrow_tile():
     """60 stages, rows before the first and after the last frame."""
     assert B.dsattn_temporal_conv_info(16, 2, 41, 1280, 320, 1)["tile_n"] == 64
     conv_case(16, 2, 41, 1280, 320, 1, dtype="bf16")
+
+
+# Shapes that run on the fp32 kernels with split operands: 64 x 64 and 128 x 128 tiles, with tails in rows, columns
+# and channels, rows of c_out that are whole 16-byte pieces and not.
+SPLIT = [(3000, 100, 130, 2, 64), (3001, 132, 192, 2, 64), (12900, 36, 634, 1, 128), (12801, 64, 640, 1, 128)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", SPLIT)
+def test_fp32_split_kernels_match_oracle(rows, c_in, c_out, n_out, tile):
+    for bias in (True, False):
+        info = linear_case(rows, c_in, c_out, n_out, dtype="f32", out_dtype="f32", bias=bias)
+        assert (info["kernel"], info["tile_m"], info["tile_n"]) == (0, tile, tile)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,tile", [((16, 20, 41, 36, 132, 1), 64), ((16, 4, 201, 68, 640, 2), 128),
+                                        ((1, 300, 43, 40, 140, 1), 64)])
+def test_fp32_split_convolutions_match_oracle(shape, tile):
+    """Rows before the first and after the last frame; infinite weights of the outermost taps reach only the
+    frames that have a frame at that tap."""
+    clip_len, n_clips, P, c_in, c_out, n = shape
+    assert B.dsattn_temporal_conv_info(*shape, io_dtype=B.DSATTN_F32)["tile_m"] == tile
+    conv_case(*shape, dtype="f32")
+    x = synth.make_tensor(clip_len * n_clips, P, c_in, 45, "iid", "f32").to(DEV)
+    w = synth.make_conv_weights(2 * n + 1, c_out, c_in, 46, "f32")[0].to(DEV)
+    w[0, 1, 2], w[-1, 3, 1] = float("inf"), float("-inf")
+    y = run_conv(x, w, None, clip_len, n_clips, "f32")
+    ref = run_conv(x, w, None, clip_len, n_clips, "f32", flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert torch.isfinite(ref[:n, :, 1]).all() and torch.isfinite(ref[-n:, :, 3]).all()
+    torch.testing.assert_close(y, ref, rtol=TOL_ACC, atol=TOL_ACC)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", SPLIT)
+def test_fp32_split_kernels_at_the_ends_of_the_range(rows, c_in, c_out, n_out, tile):
+    """Infinities, NaN and numbers beyond the largest bf16 number give what the vector kernel gives, and so do
+    numbers whose smaller parts would not be there: the error is fp32's at every magnitude."""
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    X = torch.randn(rows, c_in, device=DEV, generator=gen)
+    W = [torch.randn(c_out, c_in, device=DEV, generator=gen) / 8 for _ in range(n_out)]
+    X[5, 3], X[70, 1], X[200, 0], X[rows - 1, 2] = float("inf"), float("-inf"), float("nan"), 3.4e38
+    X[300] *= 1e-36
+    X[301] *= 1e-41
+    X[302] = 0.0
+    W[0][7, 2], W[-1][c_out - 1, 4] = float("inf"), -3.4e38
+    X[::17, 4] = 0.0                                    # (zero times a weight of -3.4e38 is zero)
+    res = []
+    for flags in (0, B.DSATTN_FLAG_FORCE_GENERIC):
+        Y = [torch.full((rows, c_out), 7.0, device=DEV) for _ in range(n_out)]
+        B.dsattn_linear(rows, c_in, c_out, X, W, Y, io_dtype=B.DSATTN_F32, flags=flags)
+        torch.cuda.synchronize()
+        res.append(torch.stack(Y))
+    y, ref = res
+    assert torch.equal(y.isnan(), ref.isnan())
+    assert torch.equal(torch.where(y.isinf(), y, 0.0), torch.where(ref.isinf(), ref, 0.0))
+    ok = ref.isfinite()
+    # (c_in roundings of partial sums that are at most the sum of the products' sizes, in both kernels)
+    size = torch.stack([X.abs().double().nan_to_num(posinf=0.0) @ w.abs().double().nan_to_num(posinf=0.0).t()
+                        for w in W])
+    bar = 2 * c_in * (2.0 ** -24 * size + 2.0 ** -149)
+    assert ((y.double() - ref.double()).abs()[ok] <= bar[ok]).all()
+
+
+@pytest.mark.gpu
+def test_fp32_split_is_no_less_precise_than_fp32_sums():
+    """Against 64 bits, 2-norm: fp32 sums of 640 products of the vector kernel's order are off by 1e-6 relatively,
+    those on the fp32 instructions by 4.5e-7; the split kernel has to stay below the latter."""
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    X = torch.randn(10240, 640, device=DEV, generator=gen)
+    W = torch.randn(640, 640, device=DEV, generator=gen) / 640 ** 0.5
+    Y = torch.empty(10240, 640, device=DEV)
+    B.dsattn_linear(10240, 640, 640, X, [W], [Y], io_dtype=B.DSATTN_F32)
+    assert B.dsattn_linear_info(10240, 640, 640, 1, io_dtype=B.DSATTN_F32)["tile_m"] == 128
+    ref = X.double() @ W.double().t()
+    assert float((Y.double() - ref).norm() / ref.norm()) <= 3e-7
