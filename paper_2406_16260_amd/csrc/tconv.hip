@@ -630,22 +630,22 @@ int64_t conv_tiles(const ConvVariant &v, int64_t M, int64_t c_out, int groups)
 // and what its start and end cost.  Of the kernels with two workgroups on a compute unit a round is 512 tiles,
 // the last one, of up to 256, a shorter one.  Fitted to 137 projections and convolutions of 1 to 5 taps, 500 to
 // 60,000 rows, 128 to 1,280 channels, one and three weight sets, three sets of tensors in rotation (weights come
-// from beyond the L2, as a model's do); over these the kernel that the rule below picks is 1.4 % behind the fastest
-// of the eight on average and 9 % at most but for one (64 x 64 for 3,000 x 1,024 x 1,024, 12.0 against 13.8 us), and 5 %
-// faster on average than without the 128 x 64 and 256 x 192 tiles.  With its weights in the L2 a convolution of few
-// tiles may be faster on 64 x 64 (544 x 640 x 640, 3 taps, 10.8 against 13.0 us, but 16.9 against 13.2 from beyond it).
-// Measured us (rows x c_in x c_out, taps x sets):
-//                                256 x 320  256 x 192  128 x 160  128 x 128  pipelined  128 x 64  64 x 64
-//     1,104 x   960 x   320, 3      78.5               38.0       31.1      29.0      17.5      23.8
-//     2,400 x   640 x   640, 3      56.9               27.3       22.2      21.3      13.6      17.2
-//     2,560 x 1,280 x   640, 5     172.4               81.3       66.5      60.0      34.0      49.3
-//     6,400 x 1,280 x   320, 3     107.0               50.1       41.0      38.1      23.3      31.0
-//     1,728 x   320 x   320, 3      29.9               15.5       11.2      12.7       8.6       7.1
-//     1,280 x 1,280 x 1,280, 1      41.9       25.7     20.5       17.9      16.0      11.7      13.1
-//     2,560 x 1,280 x 1,280, 1      42.4       26.0     20.6       18.0      16.6      19.9      16.5
-//     2,560 x 1,280 x 1,280, 1 x 3  43.3       27.6     27.5       35.6      43.5      46.5      41.6
-//     7,072 x 1,024 x 1,024, 1 x 3  66.8       44.5     52.9       47.8      71.9      83.6      64.9
-//     7,200 x 1,280 x 1,280, 3     107.7               65.7       92.8     108.4     106.3     112.9
+// from beyond the L2, as a model's do).  Over 45 others, drawn from 1,400 to 120,000 rows and 320 to 1,280 channels,
+// the kernel that the rule below picks is 2.0 % behind the fastest of the eight on average, 17 % in one case
+// (68,864 x 960 x 320, 5 taps, 1.05 rounds: 251 against 215 us) and 9 % at most in the others.  With its weights in
+// the L2 a convolution of few tiles may be faster on 64 x 64 (544 x 640 x 640, 3 taps, 10.8 against 13.0 us, but 16.9
+// against 13.2 from beyond it).  Measured us (rows x c_in x c_out, taps x sets):
+//                                256 x 256  256 x 320  256 x 192  128 x 160  128 x 128  pipelined  128 x 64  64 x 64
+//     1,104 x   960 x   320, 3         59.0       67.0       51.0       34.7       31.5       22.4      17.2     23.6
+//     2,400 x   640 x   640, 3         42.1       47.7       36.4       24.9       22.4       16.8      13.5     17.0
+//     2,560 x 1,280 x   640, 5        123.5      141.4      107.9       73.3       68.5       44.9      33.4     49.1
+//     6,400 x 1,280 x   320, 3         75.7       87.2       66.5       46.0       40.8       28.9      22.6     30.7
+//     1,728 x   320 x   320, 3         22.7       26.4       19.1       14.4       11.1       10.3       8.6      6.9
+//     1,280 x 1,280 x 1,280, 1         30.5       34.6       26.5       19.0       17.9       13.3      11.3     12.9
+//     2,560 x 1,280 x 1,280, 1         30.9       35.0       26.8       19.2       18.0       13.7      19.6     16.4
+//     2,560 x 1,280 x 1,280, 1 x 3     32.0       35.9       28.0       27.0       35.5       36.5      45.7     41.1
+//     7,072 x 1,024 x 1,024, 1 x 3     51.6       57.5       45.0       50.0       47.0       59.2      81.3     64.0
+//     7,200 x 1,280 x 1,280, 3         78.3       89.2       68.1       67.2       93.4       89.9     105.6    113.0
 double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
 {
     const double st = (double)stages;
@@ -659,11 +659,11 @@ double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
     };
     switch (variant) {
     case kBig256: return whole(1.22, 5.0);
-    case kBig320: return whole(1.55, 6.0);
+    case kBig320: return whole(1.37, 6.0);
     case kBig192: return whole(1.03, 4.8);
     case kTile160: return paired(0.75, 2.5, 0.955, 5.0, 1.12, 4.0);
     case kTile128: return paired(0.61, 2.9, 0.74, 2.6, 0.87, 1.4);
-    case kPipe128: return whole(0.54, 2.6);
+    case kPipe128: return whole(0.43, 2.3);
     case kPipe64: return whole(0.2625, 3.4);
     default:  // 64 x 64, several to a unit; its two slots do not cover the latency of weights beyond the L2
         return 4.0 + 1.3e-3 * (double)tiles + st * std::max(small_w ? 0.2 : 0.455, 8.2e-4 * (double)tiles);

@@ -293,6 +293,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
     constexpr int BM = 32 * MB * WVM, BN = 32 * NB * WVN;
     constexpr int GA = BM / 8 / NW, GB = BN / 8 / NW;
     static_assert(GA * 8 * NW == BM && GB * 8 * NW == BN, "the wavefronts share the loads evenly");
+    static_assert(GA % 2 == 0 && GB % 2 == 0, "a load's group is even or odd for all wavefronts");
     constexpr int NL = GA + GB;
     constexpr int ABYTES = BM * kRow, BUF = (BM + BN) * kRow;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -325,8 +326,13 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
                     bias[j][q][e] = gbias[min(cbase + 32 * j + 8 * q + 4 * (lane >> 5) + e, a.Cout - 1)];
     }
 
+    // Chunks are swizzled by row / 2 here: the 16 lanes that a 16-byte LDS read serves together are rows 0 - 3,
+    // 12 - 15, 20 - 23 and 24 - 27 of a fragment of 32 rows (or the other 16), and rows alternate between the two
+    // halves of the banks, so row / 2 % 8 is what tells those of one half apart.  (By row % 8 every read was a
+    // two-way conflict, half of all LDS cycles: 2,560 x 1,280 x 1,280 on 128 x 128 tiles 16.6 us, 13.9 so.)
     const int lr = lane >> 3;
-    const int lc = (lane & 7) ^ lr;
+    // the chunk a lane fetches of a row of an even 8-row group; of an odd one it is the other half's
+    const int lc = (lane & 7) ^ (lr >> 1);
     const int rowbytes = a.Cin * 2;
     constexpr uint32_t kOob = 0xfffffff0u;
     const int64_t rb = max((int64_t)0, m0 - (int64_t)a.n * a.P);
@@ -338,21 +344,22 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
     int xoff[GA], woff[GB];  // byte offset of this lane's row and chunk within the tile's rows
 #pragma unroll
     for (int l = 0; l < GA; ++l) {
-        xoff[l] = (wv * (8 * GA) + lr + 8 * l) * rowbytes + lc * 16;
+        xoff[l] = (wv * (8 * GA) + lr + 8 * l) * rowbytes + (lc ^ (l & 1) << 2) * 16;
         asm volatile("" : "+v"(xoff[l]));
     }
 #pragma unroll
     for (int l = 0; l < GB; ++l) {
-        woff[l] = (wv * (8 * GB) + lr + 8 * l) * rowbytes + lc * 16;
+        woff[l] = (wv * (8 * GB) + lr + 8 * l) * rowbytes + (lc ^ (l & 1) << 2) * 16;
         asm volatile("" : "+v"(woff[l]));
     }
     const int taps = 2 * a.n + 1;
     int su_kc = 0, su_t = 0, su_slot = 0, su_ks = 0;
-    bool ld_live = false;
+    bool ld_live[2] = {false, false};  // of even and odd groups
     uint32_t ld_xs = 0, ld_ws = 0;
     unsigned char *ld_as = smem, *ld_bs = smem;
     auto stage_setup = [&]() __attribute__((always_inline)) {
-        ld_live = su_ks < a.KS && su_kc * kBK + lc * 8 < a.Cin;
+        ld_live[0] = su_ks < a.KS && su_kc * kBK + lc * 8 < a.Cin;
+        ld_live[1] = su_ks < a.KS && su_kc * kBK + (lc ^ 4) * 8 < a.Cin;
         const int64_t mshift = m0 + (int64_t)(su_t - a.n) * a.P;
         ld_xs = (uint32_t)((int)(mshift - rb) * rowbytes + su_kc * kRow);
         ld_ws = (uint32_t)((su_t * a.Cout + n0) * rowbytes + su_kc * kRow);
@@ -369,11 +376,11 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
         if (l < GA)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 xres, (__attribute__((address_space(3))) void *)(ld_as + l * 1024), 16,
-                ld_live ? (uint32_t)xoff[l] + ld_xs : kOob, 0, 0, 0);
+                ld_live[l & 1] ? (uint32_t)xoff[l] + ld_xs : kOob, 0, 0, 0);
         else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 wres, (__attribute__((address_space(3))) void *)(ld_bs + (l - GA) * 1024), 16,
-                ld_live ? (uint32_t)woff[l - GA] + ld_ws : kOob, 0, 0, 0);
+                ld_live[(l - GA) & 1] ? (uint32_t)woff[l - GA] + ld_ws : kOob, 0, 0, 0);
     };
 
     f32x16 acc[MB][NB];
@@ -387,7 +394,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
     // fragment of 16 channels kq: lane l is row l % 32, chunk 2 kq + l / 32
     int koff[4];
 #pragma unroll
-    for (int kq = 0; kq < 4; ++kq) koff[kq] = (((2 * kq) | (lane >> 5)) ^ (lane & 7)) * 16;
+    for (int kq = 0; kq < 4; ++kq) koff[kq] = (((2 * kq) | (lane >> 5)) ^ (lane >> 1 & 7)) * 16;
     const int abase = (wm * 32 * MB + (lane & 31)) * kRow;
     const int bbase = ABYTES + (wn * 32 * NB + (lane & 31)) * kRow;
     constexpr int NF = MB + NB;
