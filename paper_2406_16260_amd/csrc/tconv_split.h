@@ -14,7 +14,7 @@
 // What bounds it: the vector instructions of the splitting, beside the matrix instructions: a stage of 128 x 128 takes
 // 2.5 us with two workgroups on a compute unit, 1.3 of which the matrix cores are busy.  7,152 x 1,024 x 1,024
 // 84 us = 178 TFLOP/s of fp32 products, 120 us on the fp32 instructions (whose peak is 157 TFLOP/s); 10,240 x 640 x 640
-// three sets 142 against 201 us.
+// three sets 142 against 201 us, one 52 against 77.
 #pragma once
 
 namespace dsattn {
@@ -108,9 +108,21 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
     const unsigned char *fa = smem + (wm * 16 * MB + l16) * 64 + sw;
     const unsigned char *fb = smem + (B + wn * 16 * MB + l16) * 64 + sw;
 
+    // Of wavefronts that share a SIMD the one that splits goes first: until it is done its workgroup multiplies
+    // nothing, while matrix instructions that wait a few cycles cost only those.  In a single round (two workgroups
+    // of 128 x 128 on a compute unit, four of 64 x 64) and where the last one is more than half full; else the
+    // workgroups do better drawn apart, so that the first to end make room.  us, without and with: 10,240 x 640 x 640 (400 tiles of 128 x 128)
+    // 54.6 and 51.6, 3,328 x 1,280 x 1,280, three sets (780) 198 and 184, 2,560 x 1,280 x 1,280 (800 of 64 x 64)
+    // 71.2 and 62.4; but 5,120 x 640 x 640, three sets (600 of 128 x 128) 87.3 and 90.1, 10,240 rows of them (1,200)
+    // 138 and 145, 3,360 x 1,280 x 1,280 (1,060 of 64 x 64) 2 % of a layer slower.
+    constexpr int kRound = MB == 4 ? 512 : 1024;
+    const bool first = a.tiles <= kRound || (a.tiles - 1) % kRound >= kRound / 2;
+
     load_stage();
     for (int ks = 0; ks < a.KS; ++ks) {
+        if (first) __builtin_amdgcn_s_setprio(1);
         put_stage();
+        __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         if (ks + 1 < a.KS) load_stage();
         bf16x8 x[3][MB];
