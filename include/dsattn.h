@@ -277,8 +277,8 @@ int dsattn_temporal_conv_info(const dsattn_conv_desc *desc, dsattn_conv_info *in
  *   Y    : device, [F, P, c_out] of out_dtype, 16-byte aligned; must not overlap X
  * Runs on the current device; enqueues one kernel on `stream`; allocates nothing.  bf16 inputs
  * with c_in a multiple of 8 and fp32 inputs with c_in a multiple of 4 run on the matrix cores (fp32 on
- * the fp32 instructions, or split into three bf16 numbers each, which add up to it: nothing is rounded to 16
- * bits), everything else on a plain vector kernel.
+ * the fp32 instructions, or split into three bf16 numbers each, which add up to it, or a tile is done again in
+ * fp32: nothing is rounded to 16 bits), everything else on a plain vector kernel.
  * Errors: EINVAL (bad shape, null or misaligned pointer, overlap), EHIP.
  */
 int dsattn_temporal_conv(const dsattn_conv_desc *desc, const void *X, const void *W,

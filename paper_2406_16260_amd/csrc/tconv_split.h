@@ -1,5 +1,5 @@
-// fp32 projections and convolutions on the bf16 matrix instructions: every fp32 number is the sum of three
-// bf16 numbers (24 bits in 8 + 8 + 8), products of bf16 numbers are exact in fp32, and of the nine products of two
+// fp32 projections and convolutions on the bf16 matrix instructions: an fp32 number is the sum of three
+// bf16 numbers (24 bits in 8 + 8 + 8; where one is too small for that, its tile is done again in fp32), products of bf16 numbers are exact in fp32, and of the nine products of two
 // numbers the six of 2^-16 and more are summed in fp32; the three that are left out are below 2^-25 of the
 // largest.  Errors against 64 bits are a third of those of the fp32 instructions, whose sums are rounded after
 // every fourth channel instead of every 32nd (2-norm, relative, 128 to 3,840 products a sum: 0.65e-7 to 3.8e-7 against
@@ -28,6 +28,7 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
     constexpr int PLANE = 2 * B * 64;      // bytes of a plane: B rows of X, then B rows of W, 32 channels each
     constexpr int NLD = 2 * B * 8 / 256;   // 16-byte pieces per thread and stage
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int incomplete[4];  // a wavefront has met an operand that is not the sum of its parts
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
     const int tile = (int)(blockIdx.x % kXcds) * a.per_xcd + (int)(blockIdx.x / kXcds);
@@ -75,7 +76,9 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
         su_t = su_t + 1 == taps ? 0 : su_t + 1;
         su_kc += su_t == 0 ? 1 : 0;
     };
-    // a piece is four channels: 8 bytes of chunk lc / 2 in every plane
+    // a piece is four channels: 8 bytes of chunk lc / 2 in every plane.  `lost`: bits of third parts that no bf16
+    // number has
+    uint32_t lost = 0;
     auto put_stage = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int l = 0; l < NLD; ++l) {
@@ -86,7 +89,11 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
             for (int p = 0; p < 3; ++p) {
                 bf16x4 h;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = (__bf16)x[e];  // nearest even
+                for (int e = 0; e < 4; ++e) {
+                    const float r = x[e];  // (a bit_cast of x[e] itself would be element 0's)
+                    h[e] = (__bf16)r;      // nearest even
+                    if (p == 2) lost |= __builtin_bit_cast(uint32_t, r) & 0xffffu;
+                }
                 *(bf16x4 *)(at + p * PLANE) = h;
                 const u32x2 w = __builtin_bit_cast(u32x2, h);
                 x[0] -= __builtin_bit_cast(float, w[0] << 16);
@@ -123,6 +130,10 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
         if (first) __builtin_amdgcn_s_setprio(1);
         put_stage();
         __builtin_amdgcn_s_setprio(0);
+        if (ks + 1 == a.KS) {  // (read behind the loop's last barrier)
+            const bool any = __any(lost != 0);
+            if (lane == 0) incomplete[wv] = any;
+        }
         __syncthreads();
         if (ks + 1 < a.KS) load_stage();
         bf16x8 x[3][MB];
@@ -150,23 +161,21 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
         __syncthreads();
     }
 
-    // Lane l holds channels 4 (l / 16) + e of row l % 16 of every 16 x 16 block.  Infinities, NaN and numbers whose
-    // leading part rounds to an infinity leave NaN or an infinity here, and numbers so small that their last parts
-    // are not there leave results as small: such a wavefront's part is done again as the vector kernel does it.
+    // Lane l holds channels 4 (l / 16) + e of row l % 16 of every 16 x 16 block.
     const int64_t mrow0 = m0 + wm * 16 * MB;
     const int cbase = n0 + wn * 16 * MB;
-    bool again = false;
+    bool again = (incomplete[0] | incomplete[1] | incomplete[2] | incomplete[3]) != 0;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
             big[i][j] += small[i][j];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float y = __builtin_fabsf(big[i][j][e]);
-                again = again || !(y < INFINITY) || (y < 0x1p-90f && y != 0.f);
-            }
+            for (int e = 0; e < 4; ++e) again = again || !(__builtin_fabsf(big[i][j][e]) < INFINITY);
         }
+    // Operands that are not the sum of their parts (the smallest part of a number below 2^-110 may be below bf16's
+    // last bit, 2^-133) and results that are not finite (the parts of an infinity, of a NaN, or of a number whose
+    // leading part rounds to an infinity): done again as the vector kernel does it.
     if (__any(again)) {
         for (int r = 0; r < 16 * MB; ++r)
             for (int c = lane; c < 16 * MB; c += 64) {

@@ -652,6 +652,49 @@ def test_fp32_split_kernels_at_the_ends_of_the_range(rows, c_in, c_out, n_out, t
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", SPLIT)
+@pytest.mark.parametrize("small,large", [(4e-41, 1e30), (1.77e-38, 2.0 ** 40), (1.2e-37, 1e9), (2.0 ** -115, 2.0 ** 60),
+                                         (2.0 ** -120, 2.0 ** 60), (2.0 ** -126, 2.0 ** 100), (1e-41, 1.0)])
+def test_fp32_split_kernels_with_operands_whose_parts_run_out(small, large, rows, c_in, c_out, n_out, tile):
+    """A bf16 part cannot be below 2^-133: an operand near the smallest normal number, or below it, is not the sum of
+    three, however large its result is.  All of one operand that small, or a single row or element of it in a tile
+    of ordinary ones, in X and in W.  2-norm of what is small, against 64 bits: a rounding of 2^-24 of the partial sum at each of
+    c_in steps adds up to sqrt(c_in) 2^-24 as a random walk, twice that is allowed; two parts of 16 bits in all
+    would be off by 2^-18.  (A result below 2^-126 is a multiple of 2^-149.)"""
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    X0 = torch.randn(rows, c_in, device=DEV, generator=gen)
+    W0 = [torch.randn(c_out, c_in, device=DEV, generator=gen) for _ in range(n_out)]
+    row, col = rows - 70, c_out - 3
+    for which in ("X", "W", "row of X", "row of W", 0, 1, 2, 3):
+        announce(f"split small operands {small} {large} {which} {rows} {c_in} {c_out} {n_out}")
+        X, W = X0.clone(), [w.clone() for w in W0]
+        if which == "W":
+            X.mul_(large)
+            [w.mul_(small) for w in W]
+        elif which == "row of W":
+            X.mul_(large)
+            W[-1][col] *= small
+        else:
+            [w.mul_(large) for w in W]
+            if which == "X":
+                X.mul_(small)
+            elif which == "row of X":
+                X[row] *= small
+            else:                                           # a single element, in every place of a load
+                keep = float(X[row, c_in - 8 + which]) * small
+                X[row] = 0.0
+                X[row, c_in - 8 + which] = keep
+        Y = [torch.full((rows, c_out), 7.0, device=DEV) for _ in range(n_out)]
+        B.dsattn_linear(rows, c_in, c_out, X, W, Y, io_dtype=B.DSATTN_F32)
+        torch.cuda.synchronize()
+        y = Y[-1].double()
+        ref = X.double() @ W[-1].double().t()
+        for a, b in ((y[row], ref[row]), (y[:, col], ref[:, col])):
+            bar = 2 * c_in ** 0.5 * 2.0 ** -24 * b.norm() + c_in * 2.0 ** -149 * b.numel() ** 0.5
+            assert float((a - b).norm()) <= float(bar), (which, float((a - b).norm() / b.norm()))
+
+
+@pytest.mark.gpu
 def test_fp32_split_is_no_less_precise_than_fp32_sums():
     """Against 64 bits, 2-norm: fp32 sums of 640 products of the vector kernel's order are off by 1e-6 relatively,
     those on the fp32 instructions by 4.5e-7; the split kernel has to stay below the latter."""
