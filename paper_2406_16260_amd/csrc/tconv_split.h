@@ -1,9 +1,9 @@
 // fp32 projections and convolutions on the bf16 matrix instructions: an fp32 number is the sum of three
-// bf16 numbers (24 bits in 8 + 8 + 8; where one is too small for that, its tile is done again in fp32), products of bf16 numbers are exact in fp32, and of the nine products of two
-// numbers the six of 2^-16 and more are summed in fp32; the three that are left out are below 2^-25 of the
-// largest.  Errors against 64 bits are a third of those of the fp32 instructions, whose sums are rounded after
-// every fourth channel instead of every 32nd (2-norm, relative, 128 to 3,840 products a sum: 0.65e-7 to 3.8e-7 against
-// 2.0e-7 to 1.1e-6).
+// bf16 numbers (24 bits in 8 + 8 + 8; where one is too small for that, its tile is done again in fp32), products
+// of bf16 numbers are exact in fp32, and of the nine products of two numbers the six of 2^-16 and more are summed
+// in fp32; the three that are left out are below 2^-25 of the largest.  Errors against 64 bits are a third of
+// those of the fp32 instructions, whose sums are rounded after every fourth channel instead of every 32nd (2-norm,
+// relative, 128 to 3,840 products a sum: 0.65e-7 to 3.8e-7 against 2.0e-7 to 1.1e-6).
 //
 // Same implicit GEMM and tiles as the other kernels (rows m = f * P + p, taps as row offsets of X, stages of 32
 // channels of one tap, taps innermost, tiles numbered group, row, column).  A stage's rows come into registers
@@ -175,24 +175,49 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
         }
     // Operands that are not the sum of their parts (the smallest part of a number below 2^-110 may be below bf16's
     // last bit, 2^-133) and results that are not finite (the parts of an infinity, of a NaN, or of a number whose
-    // leading part rounds to an infinity): done again as the vector kernel does it.
+    // leading part rounds to an infinity): done again on the fp32 instructions, operands from memory as the
+    // instructions take them: lane l has row l % 16, channels 4 (l / 16) .. of every 16, one of them an instruction.
+    // (10,240 x 640 x 640, 52.6 us: 102 with a NaN in X, a wavefront's part of one row of tiles, 157 with one in every
+    // row; one thread an output, as on the vector kernel, 3,640 and 9,630.  On the fp32 kernel 77.)
     if (__any(again)) {
-        for (int r = 0; r < 16 * MB; ++r)
-            for (int c = lane; c < 16 * MB; c += 64) {
-                const int64_t m = mrow0 + r;
-                const int co = cbase + c;
-                if (m >= a.M || co >= a.Cout) continue;
-                float y = gbias ? gbias[co] : 0.f;
-                for (int tap = 0; tap < taps; ++tap) {
-                    const int64_t ms = m + (int64_t)(tap - a.n) * a.P;
-                    if (ms < 0 || ms >= a.M) continue;
-                    const float *px = (const float *)a.X + ms * a.Cin;
-                    const float *pw = (const float *)a.W[grp] + ((int64_t)tap * a.Cout + co) * a.Cin;
-                    for (int ci = 0; ci < a.Cin; ++ci) y = fmaf(pw[ci], px[ci], y);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j) big[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int tap = 0; tap < taps; ++tap) {
+            const int64_t ms = mrow0 + l16 + (int64_t)(tap - a.n) * a.P;  // X's row for the lane's first one
+            const uint32_t xs = (uint32_t)((int)(ms - rb) * rowbytes + 16 * lg);
+            const uint32_t ws = (uint32_t)((tap * a.Cout + cbase + l16) * rowbytes + 16 * lg);
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < MB; ++j) small[i][j] = big[i][j];
+            for (int c = 0; c < a.Cin; c += 16) {
+                const bool live = c + 4 * lg < a.Cin;
+                f32x4 xf[MB], wf[MB];
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    const uint32_t at = (uint32_t)(16 * i * rowbytes + 4 * c);
+                    xf[i] = __builtin_bit_cast(
+                        f32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, live ? xs + at : kOob, 0, 0));
+                    wf[i] = __builtin_bit_cast(
+                        f32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, live ? ws + at : kOob, 0, 0));
                 }
-                gY[m * a.Cout + co] = y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j)
+#pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            big[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[j][e], xf[i][e], big[i][j], 0, 0, 0);
             }
-        return;
+            // (a frame outside the video adds nothing, not even its zeros times an infinite weight)
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+                if (ms + 16 * i < 0 || ms + 16 * i >= a.M)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j) big[i][j] = small[i][j];
+        }
     }
     f32x4 bias[MB] = {};
     if (gbias) {

@@ -695,6 +695,26 @@ def test_fp32_split_kernels_with_operands_whose_parts_run_out(small, large, rows
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(16, 20, 41, 36, 132, 1), (16, 4, 201, 68, 640, 2), (1, 300, 43, 40, 140, 1)])
+def test_fp32_split_convolutions_done_again(shape):
+    """Tiles of small operands, with rows before the first and after the last frame and infinite weights of the
+    outermost taps, against the vector kernel: two fp32 sums of as many products, each off by a random walk of
+    2^-24 a step."""
+    clip_len, n_clips, P, c_in, c_out, n = shape
+    announce(f"conv done again {shape}")
+    x = synth.make_tensor(clip_len * n_clips, P, c_in, 48, "iid", "f32").to(DEV) * 1e-37
+    w = synth.make_conv_weights(2 * n + 1, c_out, c_in, 49, "f32")[0].to(DEV) * 1e9
+    w[0, 1, 2], w[-1, 3, 1] = float("inf"), float("-inf")
+    y = run_conv(x, w, None, clip_len, n_clips, "f32")
+    ref = run_conv(x, w, None, clip_len, n_clips, "f32", flags=B.DSATTN_FLAG_FORCE_GENERIC)
+    assert torch.isfinite(ref[:n, :, 1]).all() and torch.isfinite(ref[-n:, :, 3]).all()
+    ok = ref.isfinite()
+    assert torch.equal(y.isfinite(), ok) and torch.equal(y[~ok], ref[~ok])
+    a, b = y[ok].double(), ref[ok].double()
+    assert float((a - b).norm()) <= 4 * ((2 * n + 1) * c_in) ** 0.5 * 2.0 ** -24 * float(b.norm())
+
+
+@pytest.mark.gpu
 def test_fp32_split_is_no_less_precise_than_fp32_sums():
     """Against 64 bits, 2-norm: fp32 sums of 640 products of the vector kernel's order are off by 1e-6 relatively,
     those on the fp32 instructions by 4.5e-7; the split kernel has to stay below the latter."""
