@@ -628,30 +628,30 @@ int64_t conv_tiles(const ConvVariant &v, int64_t M, int64_t c_out, int groups)
 
 // Estimated time in us of a bf16 problem of a few rounds of tiles: a start, and per round the stages of a tile
 // and what its start and end cost.  Of the kernels with two workgroups on a compute unit a round is 512 tiles,
-// the last one, of up to 256, a shorter one.  Fitted to 137 projections and convolutions of 1 to 5 taps, 500 to
-// 60,000 rows, 128 to 1,280 channels, one and three weight sets, three sets of tensors in rotation (weights come
-// from beyond the L2, as a model's do).  Over 45 others, drawn from 1,400 to 120,000 rows and 320 to 1,280 channels,
-// the kernel that the rule below picks is 2.0 % behind the fastest of the eight on average, 17 % in one case
-// (68,864 x 960 x 320, 5 taps, 1.05 rounds: 251 against 215 us) and 9 % at most in the others.  With its weights in
-// the L2 a convolution of few tiles may be faster on 64 x 64 (544 x 640 x 640, 3 taps, 10.8 against 13.0 us, but 16.9
-// against 13.2 from beyond it).  Measured us (rows x c_in x c_out, taps x sets):
+// the last one, of up to 256, a shorter one; of the 64 x 64 kernel a stage takes as long as the most tiles on a unit
+// make it.  Fitted to 186 convolutions of 3 and 5 taps, 256 to 29,000 rows, 128 to 1,280 channels, and 25 larger
+// projections, each with three sets of tensors in rotation and with enough weights to come from beyond the L2s.  Of those
+// the kernel that the rule below picks is 0.4 % behind the fastest of the eight on average with three sets (a line
+// through the 64 x 64 kernel's stages, and one round's stage time in all: 1.2 %; 11,200 to 12,320 rows of 320 output
+// channels up to 13 %) and 0.8 % from beyond the L2s.  Measured us, three sets (rows x c_in x c_out, taps x sets):
 //                                256 x 256  256 x 320  256 x 192  128 x 160  128 x 128  pipelined  128 x 64  64 x 64
-//     1,104 x   960 x   320, 3         59.0       67.0       51.0       34.7       31.5       22.4      17.2     23.6
-//     2,400 x   640 x   640, 3         42.1       47.7       36.4       24.9       22.4       16.8      13.5     17.0
-//     2,560 x 1,280 x   640, 5        123.5      141.4      107.9       73.3       68.5       44.9      33.4     49.1
-//     6,400 x 1,280 x   320, 3         75.7       87.2       66.5       46.0       40.8       28.9      22.6     30.7
-//     1,728 x   320 x   320, 3         22.7       26.4       19.1       14.4       11.1       10.3       8.6      6.9
-//     1,280 x 1,280 x 1,280, 1         30.5       34.6       26.5       19.0       17.9       13.3      11.3     12.9
-//     2,560 x 1,280 x 1,280, 1         30.9       35.0       26.8       19.2       18.0       13.7      19.6     16.4
-//     2,560 x 1,280 x 1,280, 1 x 3     32.0       35.9       28.0       27.0       35.5       36.5      45.7     41.1
-//     7,072 x 1,024 x 1,024, 1 x 3     51.6       57.5       45.0       50.0       47.0       59.2      81.3     64.0
-//     7,200 x 1,280 x 1,280, 3         78.3       89.2       68.1       67.2       93.4       89.9     105.6    113.0
+//       256 x   320 x   640, 3          23.7       27.1       19.4       14.6       11.2       10.6        8.6      6.8
+//     4,000 x   320 x   320, 3          24.6       27.6       20.4       14.8       11.9       10.9        9.1      8.9
+//    12,320 x   320 x   320, 3          26.0       28.5       21.8       15.8       16.2       21.6       16.9     14.8
+//    13,328 x   320 x   320, 3          25.9       28.4       21.8       15.8       16.2       21.2       23.4     19.2
+//     1,200 x   960 x   320, 3          60.0       68.2       51.6       35.0       32.0       22.8       17.5     23.7
+//    12,320 x   960 x   320, 3          60.4       67.9       51.7       36.6       36.6       47.0       37.3     34.5
+//    16,000 x 1,280 x   320, 5         126.0      140.2      108.7       77.9       84.5       96.6      101.6    112.1
+//     4,160 x   640 x   640, 3          43.2       48.3       37.0       25.7       22.8       18.1       25.4     18.7
+//     3,952 x 1,280 x   640, 3          78.3       88.5       67.1       45.9       42.3       29.4       43.2     32.5
+//     3,536 x 1,280 x 1,280, 1 x 3       35.5       38.6       52.6       41.8       41.2       54.7       67.0     56.6
+//     4,496 x 1,280 x 1,280, 3          78.9       88.5       67.4       61.0       50.2       62.3       69.2     74.0
 double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
 {
     const double st = (double)stages;
-    const int64_t full = tiles / 512, rest = tiles - 512 * full;
+    const int64_t full = tiles / 512, rest = tiles - 512 * full, rounds = (tiles + 255) / 256;
     auto whole = [&](double per_stage, double ends) {  // one workgroup on a compute unit
-        return 3.0 + (double)((tiles + 255) / 256) * (per_stage * st + ends);
+        return 3.0 + (double)rounds * (per_stage * st + ends);
     };
     auto paired = [&](double one, double one_ends, double two, double two_ends, double full_round, double full_ends) {
         return 3.0 + (double)full * (full_round * st + full_ends) +
@@ -661,12 +661,16 @@ double conv_estimate(int variant, int64_t tiles, int64_t stages, bool small_w)
     case kBig256: return whole(1.22, 5.0);
     case kBig320: return whole(1.37, 6.0);
     case kBig192: return whole(1.03, 4.8);
-    case kTile160: return paired(0.75, 2.5, 0.955, 5.0, 1.12, 4.0);
-    case kTile128: return paired(0.61, 2.9, 0.74, 2.6, 0.87, 1.4);
-    case kPipe128: return whole(0.43, 2.3);
-    case kPipe64: return whole(0.2625, 3.4);
-    default:  // 64 x 64, several to a unit; its two slots do not cover the latency of weights beyond the L2
-        return 4.0 + 1.3e-3 * (double)tiles + st * std::max(small_w ? 0.2 : 0.455, 8.2e-4 * (double)tiles);
+    case kTile160: return paired(0.70, 2.5, 0.93, 4.5, 1.12, 4.0);
+    case kTile128: return paired(0.61, 2.9, 0.74 + 4e-4 * (double)std::max<int64_t>(0, rest - 280), 2.6, 0.87, 1.4);
+    case kPipe128: return whole(rounds > 1 ? 0.43 : 0.383 + 3.4e-4 * (double)tiles, 2.3);
+    case kPipe64: return rounds > 1 ? whole(0.314, 2.1) : whole(0.2625, 3.4);
+    default: {  // 64 x 64; its two slots do not cover the latency of weights beyond the L2
+        static const double warm[] = {0.2, 0.3, 0.41, 0.61}, cold[] = {0.455, 0.455, 0.5, 0.67};
+        const double stage = rounds > 4 ? std::max(small_w ? 1.0 : 1.05, 8.2e-4 * (double)tiles)
+                                        : (small_w ? warm : cold)[rounds - 1];
+        return 4.0 + 1.3e-3 * (double)tiles + st * stage;
+    }
     }
 }
 
@@ -748,7 +752,12 @@ const ConvVariant *conv_pick(const dsattn_conv_desc &d, int64_t M, int groups = 
     // round that is nearly empty: whichever is estimated a tenth faster.  (The fit has no problems of fewer than
     // four stages there, and from one and a half rounds on memory and power decide.)
     if (best_tiles < 256 || (best_tiles < 384 && stages >= 4)) {
-        const bool small_w = taps * d.c_out * d.c_in * es <= (int64_t)1 << 20;
+        // weights that three sets of tensors keep in an XCD's L2: all of them, or the column tiles that an XCD has
+        // (320 x 320 x 640, 3 taps, 7 of 10 column tiles, 0.8 MB: 6.9 us on 64 x 64, 8.6 on 128 x 64; 320 x 640 x 320,
+        // 4 of 5, 0.94 MB: 14.5 and 12.9)
+        const int64_t w_bytes = taps * d.c_out * d.c_in * es, tiles_n = (d.c_out + 63) / 64;
+        const int64_t xcd_n = std::min(tiles_n, (conv_tiles(kConvVariants[kTile64], M, d.c_out, groups) + kXcds - 1) / kXcds);
+        const bool small_w = w_bytes <= (int64_t)1 << 20 || w_bytes / tiles_n * xcd_n <= (int64_t)7 << 17;
         double best_us = 1e300;
         if (best_tiles >= 256) best_us = 0.9 * conv_estimate(best, best_tiles, stages, small_w);
         for (int k = kBig256; k <= kTile64; ++k) {

@@ -582,6 +582,21 @@ def test_linear_tiles_for_few_tiles_and_few_channels(rows, c_in, c_out, n_out, t
         assert (info["kernel"], info["tile_m"], info["tile_n"], info["block_threads"]) == (1,) + tile
 
 
+@pytest.mark.parametrize("shape,tile", [
+    # clip_len, n_clips, P, c_in, c_out, n: the fastest of the eight kernels where they were timed, by 5 % and more
+    ((16, 1, 500, 320, 320, 1), (64, 64)),      # three 64 x 64 tiles on a compute unit, 11.0 us; 11.6 on 128 x 128
+    ((16, 1, 770, 320, 320, 1), (64, 64)),      # four, 14.8; 15.8 on 128 x 160, 16.2 on 128 x 128
+    ((16, 1, 833, 320, 320, 1), (128, 160)),    # 15.8; five 64 x 64 tiles 19.2
+    ((16, 1, 770, 640, 320, 1), (64, 64)),      # 24.8; 26.7 on 128 x 64
+    ((16, 1, 1000, 1280, 320, 2), (128, 160)),  # 77.9; 84.5 on 128 x 128
+    ((16, 1, 16, 320, 640, 1), (64, 64)),       # an XCD has half of the weights, 6.8; 8.6 on 128 x 64
+    ((16, 1, 26, 640, 640, 1), (128, 64)),      # 13.0; 16.9 on 64 x 64
+])
+def test_conv_tile_choice_where_several_are_near(shape, tile):
+    info = B.dsattn_temporal_conv_info(*shape)
+    assert (info["tile_m"], info["tile_n"]) == tile
+
+
 @pytest.mark.gpu
 def test_conv_on_the_pipelined_narrow_tile():
     """60 stages, rows before the first and after the last frame."""
