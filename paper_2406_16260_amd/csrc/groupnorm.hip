@@ -132,7 +132,7 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
     constexpr int VEC = sizeof(T) == 2 ? 8 : 4;
     constexpr int UNR = kGnUnroll;  // independent row loads in flight per thread
     // [4][blockDim.y][ch] doubles: sum, sum of squares for g0, then g0 + 1; then [3] floats: rows, pilots;
-    // then [shares][groups][3] doubles
+    // then, of more than one share, [shares][groups][3] doubles
     extern __shared__ double red[];
     const int lane = threadIdx.x, ry = threadIdx.y, ny = blockDim.y;
     const int g0 = (lane * VEC) / cg;
@@ -217,13 +217,27 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
     // A few threads per group share its row phases, then one of them adds up what they have.  (One thread per
     // group from the start was a chain of LDS reads as long as phases x lanes, some 3 us at the end of every
     // workgroup: 64 x 60 x 640 bf16 18.5 -> 15.1 us a call, 296 x 696 x 320 76.0 -> 71.7.)
+    // (One share, where a thread has a group to itself: no table, which many groups would have no room for.)
     const int shares = max(1, min(min(nt / groups, ny), 8));
-    double *const shared_sums = red + 4 * nt + (3 * nt + 1) / 2;  // [shares][groups][3]
+    double *const shared_sums = red + 4 * nt + (3 * nt + 1) / 2;  // [shares][groups][3], of more than one share
+    auto first_pilot = [&](int g) __attribute__((always_inline)) -> double {
+        // (row phase 0 of every workgroup has read at least one row: its pilot is an element)
+        const int l0 = (g * cg) / VEC;
+        return l0 * VEC >= g * cg ? redf[1 * nt + l0] : redf[2 * nt + l0];
+    };
+    auto report = [&](int g, const GnSums &m) __attribute__((always_inline)) {
+        const double mean = first_pilot(g) + m.s1 / m.n, m2 = m.s2 - m.s1 * m.s1 / m.n;
+        const float hi = (float)mean;
+        GnPart part;
+        part.mean = hi;
+        part.mean_lo = (float)(mean - (double)hi);
+        part.m2 = m2 < 0.0 ? 0.0 : m2;  // (a NaN stays one)
+        partial[(int64_t)blockIdx.x * groups + g] = part;
+    };
     for (int gs = t; gs < groups * shares; gs += nt) {
         const int g = gs % groups, share = gs / groups;
         const int l0 = (g * cg) / VEC, l1 = ((g + 1) * cg - 1) / VEC;
-        // (row phase 0 of every workgroup has read at least one row: its pilot is an element)
-        const double P = l0 * VEC >= g * cg ? redf[1 * nt + l0] : redf[2 * nt + l0];
+        const double P = first_pilot(g);
         GnSums m = {0.0, 0.0, 0.0};
         for (int y = share; y < ny; y += shares)
             for (int l = l0; l <= l1; ++l) {
@@ -234,15 +248,18 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
                     gn_add(m, n, red[2 * k * nt + e], red[(2 * k + 1) * nt + e],
                            (double)redf[(1 + k) * nt + e] - P);
             }
+        if (shares == 1) {
+            report(g, m);
+            continue;
+        }
         double *const at = shared_sums + 3 * (int64_t)gs;
         at[0] = m.n;
         at[1] = m.s1;
         at[2] = m.s2;
     }
+    if (shares == 1) return;
     __syncthreads();
     for (int g = t; g < groups; g += nt) {
-        const int l0 = (g * cg) / VEC;
-        const double P = l0 * VEC >= g * cg ? redf[1 * nt + l0] : redf[2 * nt + l0];
         GnSums m = {0.0, 0.0, 0.0};
         for (int share = 0; share < shares; ++share) {
             const double *const at = shared_sums + 3 * ((int64_t)share * groups + g);
@@ -250,13 +267,7 @@ __global__ __launch_bounds__(1024) void gn_moments_kernel(const uint4 *__restric
             m.s1 += at[1];
             m.s2 += at[2];
         }
-        const double mean = P + m.s1 / m.n, m2 = m.s2 - m.s1 * m.s1 / m.n;
-        const float hi = (float)mean;
-        GnPart part;
-        part.mean = hi;
-        part.mean_lo = (float)(mean - (double)hi);
-        part.m2 = m2 < 0.0 ? 0.0 : m2;  // (a NaN stays one)
-        partial[(int64_t)blockIdx.x * groups + g] = part;
+        report(g, m);
     }
 }
 
@@ -541,8 +552,9 @@ hipError_t gn_enqueue(const dsattn_gn_desc &d, const GnShape &s, const void *X, 
     float *wstats = partial + 4 * (size_t)d.n_clips * s.bpc * d.groups;
     const dim3 grid(s.blocks), block(s.ch, s.rpb);
     const int nt = s.ch * s.rpb, shares = std::max(1, std::min({nt / d.groups, s.rpb, 8}));
+    // (at most 45,056 bytes: more than one share takes several row phases, and then there are 512 threads at most)
     const size_t lds = (size_t)nt * 4 * sizeof(double) + (size_t)(3 * nt + 1) / 2 * 8 +
-                       (size_t)shares * d.groups * 3 * sizeof(double);
+                       (shares > 1 ? (size_t)shares * d.groups * 3 * sizeof(double) : 0);
 
     const bool stream = (size_t)s.rows * s.ch * 16 >= kGnStreamBytes;
 #define DSATTN_GN_RUN(T)                                                                          \

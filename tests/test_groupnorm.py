@@ -339,3 +339,19 @@ def test_groupnorm_small_tensors_in_one_launch(rows, C, groups, dtype):
         np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6)
         np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
         U.assert_parity(y, ref, "f32_strict" if dtype == "f32" else "bf16", what=f"small {rows} {C}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,C,groups,dtype", [(4097, 8192, 1024, "bf16"), (2561, 4096, 1024, "f32"),
+                                                 (4099, 7936, 992, "bf16")])
+def test_groupnorm_as_many_groups_as_lanes(rows, C, groups, dtype):
+    """A group per lane at the widest rows, in three launches: the statistics pass's LDS is at its largest.  Held to
+    the bars of test_groupnorm_matches_oracle."""
+    print(f"[case] groupnorm many groups {rows} {C} {groups} {dtype}", flush=True)
+    x = synth.make_tensor(rows, 1, C, 43, "iid", dtype)
+    ref, mean, var = oracle.groupnorm(x.double().numpy(), rows, 1, groups, eps=1e-5)
+    y, stats = run_gn(x.to(DEV), rows, 1, groups)
+    st = stats.cpu().double().numpy()
+    np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6)
+    np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
+    U.assert_parity(y, ref, "f32_strict" if dtype == "f32" else "bf16", what=f"many groups {rows} {C}")
