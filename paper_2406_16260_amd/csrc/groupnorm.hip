@@ -403,8 +403,9 @@ __global__ __launch_bounds__(1024) void gn_apply_kernel(const uint4 *X, uint4 *Y
 // channels a thread, and goes from mean to squared deviations to result without another read.  A group's
 // rows are pieces of 2 cg or 4 cg bytes, so lines are fetched by the several groups that share them, and
 // there are only as many workgroups as groups; what it saves is two launches and the gaps between them.
-// A thread's sums are fp32 over 16 elements at a time, everything beyond that is fp64.  In place it works
-// too: nothing is written before the group has been read.
+// A thread's sums are fp32 over 16 elements at a time about its own first element (an outlier rounds the sums of
+// one thread, not of all), everything beyond that is fp64.  In place it works too: nothing is written before the
+// group has been read.
 constexpr int kGnSmallThreads = 1024;
 constexpr int kGnSmallMaxCg = 256;
 template <typename T, int PER>
@@ -419,7 +420,6 @@ __global__ __launch_bounds__(kGnSmallThreads) void gn_small_kernel(const T *X, T
     const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     X += g * cg;
     Y += g * cg;
-    const float pilot = (float)X[0];
     if (t < cg) {
         sg[t] = gamma ? gamma[g * cg + t] : 1.f;
         sb[t] = beta ? beta[g * cg + t] : 0.f;
@@ -450,7 +450,8 @@ __global__ __launch_bounds__(kGnSmallThreads) void gn_small_kernel(const T *X, T
         for (int w = 0; w < NW; ++w) sum += part[which][w];
         return sum;
     };
-    const double n = 2.0 * n2;
+    const double n = 2.0 * n2, mine = t < n2 ? 2.0 * ((n2 - 1 - t) / NT + 1) : 0.0;
+    const float pilot = t < n2 ? (float)x[0][0] : 0.f;
     auto sums = [&](auto &&f) __attribute__((always_inline)) -> double {
         double s = 0.0;
 #pragma unroll
@@ -463,8 +464,8 @@ __global__ __launch_bounds__(kGnSmallThreads) void gn_small_kernel(const T *X, T
         }
         return s;
     };
-    const double s = total(sums([&](float v, float a) { return a + (v - pilot); }), 0);
-    const double mean = (double)pilot + s / n;
+    const double s = sums([&](float v, float a) { return a + (v - pilot); });
+    const double mean = total(s + mine * (double)pilot, 0) / n;
     const float mu = (float)mean;
     const double off = mean - (double)mu;
     const double q = total(sums([&](float v, float a) { return fmaf(v - mu, v - mu, a); }), 1) / n - off * off;

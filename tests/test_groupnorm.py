@@ -355,3 +355,27 @@ def test_groupnorm_as_many_groups_as_lanes(rows, C, groups, dtype):
     np.testing.assert_allclose(st[:groups], mean, rtol=0, atol=2e-6)
     np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
     U.assert_parity(y, ref, "f32_strict" if dtype == "f32" else "bf16", what=f"many groups {rows} {C}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("outlier", [1e5, -3e12])
+@pytest.mark.parametrize("rows,C,groups", [(1024, 256, 8), (300, 320, 32), (5000, 256, 8)])
+def test_groupnorm_one_outlier_rounds_few_sums(rows, C, groups, outlier, dtype):
+    """An element far from all others, first or in the middle of its group.  Only the fp32 sums of the one thread that
+    takes it as its pilot, or adds it, are rounded at its size.  In one launch they are 16 elements: deviations off by
+    2^-24 of it and sums of up to 16 of them by 2^-24 of 1 to 16 times it, 152 times 2^-24 at the most; in three launches
+    32 rows of 8, as a random walk sqrt(256) times about 10.  (About one pilot for all elements: off by 2^-24 of it in
+    each, 2.8e-4 of the mean's 3 with 1e5 among 32,768; the bar is 5e-5 there.)"""
+    for at in (0, rows * C // groups // 2):
+        print(f"[case] groupnorm outlier {rows} {C} {groups} {outlier} {at} {dtype}", flush=True)
+        cg = C // groups
+        x = synth.make_tensor(rows, 1, C, 44, "iid", dtype)
+        for g in range(groups):
+            x[at // cg, 0, g * cg + at % cg] = outlier
+        _, mean, var = oracle.groupnorm(x.double().numpy(), rows, 1, groups, eps=1e-5)
+        _, stats = run_gn(x.to(DEV), rows, 1, groups)
+        st = stats.cpu().double().numpy()
+        n = rows * cg
+        np.testing.assert_allclose(st[:groups], mean, rtol=2.0 ** -23, atol=256 * abs(outlier) * 2.0 ** -24 / n)
+        np.testing.assert_allclose(st[groups:], 1.0 / np.sqrt(var + 1e-5), rtol=3e-6, atol=0)
