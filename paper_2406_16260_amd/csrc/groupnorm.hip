@@ -8,7 +8,8 @@
 // is what is done here (one read of X for the statistics instead of two), and between
 // devices it would be one exchange instead of two.
 //
-// Tensors of up to a million elements take one launch of gn_small_kernel, larger ones three kernels.  These
+// Tensors of up to 32,768 elements a group (a million with 32 groups; gn_small() has the other limits) take one
+// launch of gn_small_kernel, larger ones three kernels.  These
 // stream X ([F, P, C], C fastest) with 16-byte lanes; a lane's 16 bytes belong to at
 // most two groups.  Reductions are deterministic: per-thread fp32 sums about a per-thread pilot,
 // a fixed-order merge per workgroup into a table in the caller's workspace, and a small
@@ -484,11 +485,18 @@ __global__ __launch_bounds__(kGnSmallThreads) void gn_small_kernel(const T *X, T
 // 7.8 (eight pairs a thread), 32 x 40 x 640 15.2 and 9.4, 16 x 51 x 1,280 15.2 and 10.3, 32 x 100 x 320 15.4 and
 // 12.9; fp32: 14.7 and 7.7, 14.6 and 8.9, 14.2 and 9.6, but 14.1 and 15.0 (3,200 rows of short pieces).  With 32
 // pairs a thread, 64 x 40 x 640 bf16, 20.6 against 15.1.
+// Many groups: a piece of a row is an access of its own however short it is, and the pieces of all groups count.  bf16,
+// rows x channels / groups: 1,200 x 2,560 / 320 (384,000 pieces) 20.0 and 16.8, 2,560 x 1,024 / 128 (328,000) 16.4 and
+// 14.8, 4,096 x 1,024 / 128 (524,000) 17.5 and 20.1, 2,000 x 2,560 / 320 (640,000) 20.7 and 25.1, 4,096 x 8,192 /
+// 1,024 (4,194,000) 49.6 and 135; fp32, eight channels a group: 896 x 3,200 / 400 (358,000) 17.4 and 12.8, 2,560 x
+// 2,048 / 256 (655,000) 19.7 and 21.0; four: 256 x 4,096 / 1,024 (262,000) 16.0 and 16.0, 640 x 2,048 / 512 (328,000)
+// 14.7 and 14.1, 1,200 x 1,280 / 320 (384,000) 15.8 and 16.0, 640 x 3,200 / 800 (512,000) 18.2 and 21.4.
 bool gn_small(const dsattn_gn_desc &d, const GnShape &s)
 {
     const int64_t most_rows = d.io_dtype == DSATTN_BF16 ? 4096 : 2560;
+    const int64_t most_pieces = s.cg < 8 ? 2 << 17 : 3 << 17;
     return s.cg % 2 == 0 && s.cg <= kGnSmallMaxCg && d.groups >= 8 && s.rows <= most_rows &&
-           s.rows * s.cg <= 2 * 16 * kGnSmallThreads;
+           s.rows * s.cg <= 2 * 16 * kGnSmallThreads && s.rows * d.groups <= most_pieces;
 }
 
 int gn_validate(const dsattn_gn_desc *d, GnShape &s, const char *who)
