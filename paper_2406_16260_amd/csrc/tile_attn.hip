@@ -15,8 +15,8 @@
 //   O^T = V^T P^T fp32: v_mfma_f32_16x16x4_f32; lane (m, k) loads W consecutive channels 64 b + W m of
 //                 key 4 k + s, the operands of W products, and the weight it holds of that key is the
 //                 other operand as it stands.
-//                 bf16: v_mfma_f32_16x16x32_bf16 over a pair of key tiles; a weight enters as the sum
-//                 of three bf16 numbers (8 bits each: all 24), whose products are exact.
+//                 bf16: v_mfma_f32_16x16x32_bf16 over a pair of key tiles (an odd one: 16x16x16); a weight
+//                 enters as the sum of three bf16 numbers (8 bits each: all 24), whose products are exact.
 //
 // What bounds it: at short context lists HBM and the vector instructions of softmax and splitting, about
 // half each.  Tasks are numbered so that one XCD works through consecutive clips of one position: the
@@ -45,6 +45,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 struct TileArgs {
     const void *Q, *K, *V;
@@ -218,7 +219,7 @@ __device__ __forceinline__ float exp2_positive(float x)
 // window, the set union or biases; compiled apart, because the conditions alone, kept in scalar registers
 // and spilled from there, were a third of the loop's instructions (12 clips of 24 frames x 135 positions,
 // 5 x 64: 28.3 -> 25.5 us without them).
-template <int KT, bool POSITIVE, bool OPTS>
+template <bool POSITIVE, bool OPTS>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
     // A shift of the local scores holds from the query's first visible global key on: the set union may
@@ -227,6 +228,7 @@ struct Softmax {
 
     // scores of key tiles t0 .. t0 + KT - 1 -> weights (unnormalised; those of keys past the list are zero);
     // returns the factor for what has been accumulated so far
+    template <int KT>
     __device__ __forceinline__ float step(const TileArgs &a, const Context &c, const Globals &g, int aq,
                                           f32x4 (&s)[KT], int t0, int lane)
     {
@@ -393,9 +395,16 @@ __device__ __forceinline__ void vector_task(const TileArgs &a, const Task &tk, c
 constexpr int vrow_bytes(int NKB) { return 64 * NKB + 16; }
 constexpr int kBf16Tiles = 2;  // key tiles per step
 
+// Wavefronts per SIMD that the kernel's registers have to leave room for: as many as the loop over pairs alone leaves.
+// (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80.)
+constexpr int bf16_waves(int NKB, bool FULL, int QT, bool OPTS)
+{
+    return QT == 2 ? 2 : NKB == 1 ? 6 : NKB == 2 && FULL && !OPTS ? 5 : NKB == 3 && !OPTS ? 4 : 2;
+}
+
 // NKB = ceil(D / 32); FULL: D = 32 NKB.  QT query tiles share every key row that is fetched.
 template <int NKB, bool FULL, int QT, bool OPTS, bool OUT_F32>
-__global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf16_kernel(const TileArgs a)
+__global__ __launch_bounds__(256, bf16_waves(NKB, FULL, QT, OPTS)) void tile_attn_bf16_kernel(const TileArgs a)
 {
     constexpr int KT = kBf16Tiles;
     constexpr int RS = vrow_bytes(NKB);
@@ -453,17 +462,15 @@ __global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf
         load_chunks(row_ptr((const __bf16 *)a.Q + laneoff, aq, a.fsb), q[u]);
     }
     // (the first rows, where they need no table, are asked for before it is waited for)
-    const bool early = 16 * KT <= cx.nl;
-    if (early) {
-#pragma unroll
-        for (int t = 0; t < KT; ++t) load_tile(t, 0);
-    }
+    const bool odd = tiles & 1, early = 16 * (odd ? 1 : KT) <= cx.nl;
+    auto load_first = [&]() __attribute__((always_inline)) {
+        load_tile(0, 0);
+        if (!odd) load_tile(1, 0);
+    };
+    if (early) load_first();
     put_globals(a, gtab, ginfo);
     if (!tk.exists) return;
-    if (!early) {
-#pragma unroll
-        for (int t = 0; t < KT; ++t) load_tile(t, 0);
-    }
+    if (!early) load_first();
     static_assert(QT <= KT, "the query rows fit");
 #pragma unroll
     for (int u = 0; u < QT; ++u) put_rows(u, q[u]);
@@ -479,12 +486,12 @@ __global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf
     for (int u = 0; u < QT; ++u)
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) o[u][kb][0] = o[u][kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<KT, false, OPTS> sm[QT];
+    Softmax<false, OPTS> sm[QT];
 
-    for (int t0 = 0; t0 < tiles; t0 += KT) {
+    auto key_tiles = [&](auto n, int t0) __attribute__((always_inline)) {
+        constexpr int KT = decltype(n)::value;  // of them in this step
         f32x4 s[QT][KT];
         // K through LDS, then V in its place; the next rows are asked for in the registers that this frees.
-        // (A second tile that is not there is the list's last key over and over, and masked.)
 #pragma unroll
         for (int t = 0; t < KT; ++t) put_rows(t, kr[t]);
         wave_lds_sync();
@@ -514,7 +521,7 @@ __global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf
         wave_lds_sync();
         if (t0 + KT < tiles) {
 #pragma unroll
-            for (int t = 0; t < KT; ++t) load_tile(t, t0 + KT);
+            for (int t = 0; t < kBf16Tiles; ++t) load_tile(t, t0 + KT);
         }
 
 #pragma unroll
@@ -528,7 +535,7 @@ __global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf
                     for (int x = 0; x < 2; ++x) o[u][kb][x] *= alpha;
             }
             // The weights as three bf16 numbers each: 8 bits, the next 8, and the 8 that are left.
-            u32x4 w[3];
+            uint32_t w[3][2 * KT];
 #pragma unroll
             for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -559,15 +566,28 @@ __global__ __launch_bounds__(256, NKB == 1 && QT == 1 ? 5 : 2) void tile_attn_bf
                         r[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                             (__attribute__((address_space(3))) s16x4 *)(vs + (16 * t + 4 * lg + (l16 >> 2)) * RS +
                                                                         64 * kb + 16 * (l16 & 3) + 8 * x));
-                    const bf16x8 v = __builtin_bit_cast(
-                        bf16x8, __builtin_shufflevector(r[0], r[1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        o[u][kb][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            v, __builtin_bit_cast(bf16x8, w[k]), o[u][kb][x], 0, 0, 0);
+                    for (int k = 0; k < 3; ++k) {
+                        if constexpr (KT == 2) {
+                            const u32x4 wk = {w[k][0], w[k][1], w[k][2], w[k][3]};
+                            o[u][kb][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, __builtin_shufflevector(r[0], r[1], 0, 1, 2, 3, 4, 5, 6, 7)),
+                                __builtin_bit_cast(bf16x8, wk), o[u][kb][x], 0, 0, 0);
+                        } else {
+                            const u32x2 wk = {w[k][0], w[k][1]};
+                            o[u][kb][x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                                r[0], __builtin_bit_cast(s16x4, wk), o[u][kb][x], 0, 0, 0);
+                        }
+                    }
                 }
         }
-    }
+    };
+    // An odd tile goes alone, and first: behind the pairs it cost them two to four registers, and in some forms a
+    // wavefront.  (Half of a pair whose other half is the last key over and over, and alone: 4 clips of 24 frames of
+    // 12 global ones, 162 positions, 8 x 160, three tiles, 51.4 and 46.6 us; 24 clips of 4 frames, 325 positions,
+    // 8 x 80, one tile, 75.7 and 62.8.)
+    if (odd) key_tiles(std::integral_constant<int, 1>{}, 0);
+    for (int t0 = odd; t0 < tiles; t0 += KT) key_tiles(std::integral_constant<int, KT>{}, t0);
 
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
@@ -727,7 +747,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
     for (int u = 0; u < QT; ++u)
 #pragma unroll
         for (int j = 0; j < NC; ++j) o[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Softmax<1, true, OPTS> sm[QT];
+    Softmax<true, OPTS> sm[QT];
 
     for (int t = 0; t < tiles; ++t) {
         wave_lds_sync();

@@ -273,6 +273,17 @@ BRANCHES = [
     # a window that hides most of a long clip
     (100, 2, 12, 2, 1, 72, 11, {"window": 3, "dedup": True}),
     (100, 2, 12, 2, 1, 136, 0, {"window": 40}),
+    # one to five key tiles, the last one full and of one key; odd and even in one launch
+    (4, 3, 0, 2, 2, 64, 12, {}),
+    (4, 3, 0, 2, 2, 64, 13, {"bias_global": -1.0}),
+    (4, 8, 0, 3, 1, 160, 28, {"dedup": True}),
+    (4, 8, 0, 3, 1, 160, 29, {}),
+    (24, 4, 0, 2, 1, 80, 24, {}),
+    (24, 4, 0, 2, 1, 80, 25, {"window": 5}),
+    (8, 5, 4, 2, 1, 128, 17, {"bias_local": 1.0}),
+    (40, 3, 12, 2, 1, 40, 9, {"window": 7, "dedup": True}),
+    (24, 12, 2, 100, 2, 64, 20, {}),
+    (24, 12, 2, 100, 2, 40, 21, {}),
 ]
 
 
