@@ -578,7 +578,7 @@ constexpr int conv_lds_bytes(int bm, int bn, int nj, int waves)
      {(const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, false>,                              \
       (const void *)&tconv_pipe_kernel<MB, NB, WVM, WVN, S, true>}}
 #define DSATTN_SPLIT_VARIANT(MB)                                                                  \
-    {32 * MB, 32 * MB, 4, 3 * 64 * MB * 64, 0, true,                                              \
+    {32 * MB, 32 * MB, 4, 3 * 64 * MB * 64 + 16, 0, true,                                              \
      {(const void *)&tconv_split_kernel<MB>, (const void *)&tconv_split_kernel<MB>}}
 // Eight wavefronts (two per SIMD) in the persistent kernels: one wavefront per SIMD cannot keep the
 // matrix cores busy with 16x16x32 instructions (measured: 1.46 against 2.4 PFLOP/s on idle data).

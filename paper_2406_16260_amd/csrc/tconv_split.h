@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256, 2) void tconv_split_kernel(const ConvArgs a)
     constexpr int PLANE = 2 * B * 64;      // bytes of a plane: B rows of X, then B rows of W, 32 channels each
     constexpr int NLD = 2 * B * 8 / 256;   // 16-byte pieces per thread and stage
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ int incomplete[4];  // a wavefront has met an operand that is not the sum of its parts
+    int *incomplete = (int *)(smem + 3 * PLANE);  // a wavefront has met an operand that is not the sum of its parts
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
     const int tile = (int)(blockIdx.x % kXcds) * a.per_xcd + (int)(blockIdx.x / kXcds);

@@ -638,6 +638,9 @@ __global__ __launch_bounds__(256, bf16_waves(NKB, FULL, QT, OPTS)) void tile_att
 
 // ---------------------------------------------------------------- fp32
 
+// LDS of one wavefront: the rows of a key tile (or of a query tile), padded
+constexpr int krow_bytes(int NC) { return 64 * NC + 16; }
+
 // NC = ceil(D / 16): 16-byte chunks per lane of a Q or K row, 16-channel tiles of O^T; FULL: D = 16 NC.  QT
 // query tiles share every key row that is fetched.
 template <int NC, bool FULL, int QT, bool OPTS>
@@ -648,8 +651,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
     constexpr int NF = NC / 4, N2 = NC / 2 % 2, N1 = NC % 2;
     constexpr int C2 = 64 * NF, C1 = C2 + 32 * N2;  // where the last two start
     typedef float f32x2 __attribute__((ext_vector_type(2)));
-    // LDS of one wavefront: the rows of a key tile (or of a query tile), padded
-    constexpr int RS = 64 * NC + 16;
+    constexpr int RS = krow_bytes(NC);
     __shared__ __attribute__((aligned(16))) unsigned char smem[4 * 16 * RS];
     __shared__ int gtab[kLdsGlobals];
     const int ginfo = my_global(a);
@@ -956,11 +958,14 @@ void tile_attn_plan(dsattn_plan_t &pl)
     if (d.head_dim % (f32 ? 4 : 8) != 0) return;
     // a frame's bytes are counted in 32 bits
     if ((int64_t)d.spatial * pl.C * (f32 ? 4 : 2) > 0xffffffffLL) return;
-    pl.tile_fn = tile_fn(d, query_tiles(d, has_opts(pl)), has_opts(pl));
+    const int qt = query_tiles(d, has_opts(pl));
+    pl.tile_fn = tile_fn(d, qt, has_opts(pl));
     if (!pl.tile_fn) return;
-    pl.launch.n_tasks = (int32_t)(units * nqt);
+    pl.launch.n_tasks = (int32_t)(units * ((nqt + qt - 1) / qt));
     pl.launch.block_threads = 256;
-    pl.launch.lds_bytes = f32 ? 0 : 4 * kBf16Tiles * 16 * vrow_bytes((d.head_dim + 31) / 32);
+    pl.launch.lds_bytes = (f32 ? 4 * 16 * krow_bytes((d.head_dim + 15) / 16)
+                               : 4 * kBf16Tiles * 16 * vrow_bytes((d.head_dim + 31) / 32)) +
+                          kLdsGlobals * (int)sizeof(int32_t);
 }
 
 hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *K, const void *V, void *O,

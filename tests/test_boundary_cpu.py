@@ -230,14 +230,29 @@ def test_planner_fallbacks_and_overrides(monkeypatch):
         plan.close()
 
 
+@pytest.mark.parametrize("io,D,positions,tasks,lds", [
+    # 24 frames, 12 clips, 5 heads: two query tiles a clip, a wavefront each or, from 4,096 tiles on, one for both
+    (B.DSATTN_BF16, 64, 34, 2, 4 * 32 * (128 + 16) + 1024),
+    (B.DSATTN_BF16, 64, 35, 1, 4 * 32 * (128 + 16) + 1024),
+    (B.DSATTN_BF16, 80, 35, 2, 4 * 32 * (192 + 16) + 1024),
+    (B.DSATTN_F32, 64, 35, 1, 4 * 16 * (256 + 16) + 1024),
+    (B.DSATTN_F32, 160, 35, 2, 4 * 16 * (640 + 16) + 1024),
+])
+def test_tile_kernel_reports_its_tasks_and_lds(io, D, positions, tasks, lds):
+    plan = B.dsattn_plan(24, 12, 3, positions, 5, D, [0, 5], io_dtype=io, device=-1)
+    i = B.dsattn_plan_launch_info(plan)
+    plan.close()
+    assert (i["block_threads"], i["n_tasks"], i["lds_bytes"]) == (256, 12 * positions * 5 * tasks, lds)
+
+
 def test_tile_kernel_leaves_launches_of_2_to_the_32_threads_to_the_generic_kernel():
-    # a clip of 80 frames is five tasks of 64 threads a position: 67,108,832 tasks are 32 short of 2^26, whose
-    # launch would have 2^32 threads
+    # a clip of 80 frames is five query tiles a position: with 64 threads each 67,108,832 are 32 short of 2^26, whose
+    # launch would have 2^32 threads.  (Two to a wavefront they are three tasks.)
     for P, threads in ((13421766, 256), (13421767, 64)):
         plan = B.dsattn_plan(80, 1, 0, P, 1, 8, [], device=-1)
         i = B.dsattn_plan_launch_info(plan)
         plan.close()
-        assert (i["kernel"], i["block_threads"], i["n_tasks"]) == (0, threads, P * (5 if threads == 256 else 1))
+        assert (i["kernel"], i["block_threads"], i["n_tasks"]) == (0, threads, P * (3 if threads == 256 else 1))
 
 
 def test_flags_are_validated_and_dedup_limits_the_planner():
