@@ -58,7 +58,7 @@ struct TileArgs {
     int32_t G, window, dedup;
     uint32_t per_xcd;  // workgroups per XCD
     uint32_t tasks;
-    uint32_t fsb;      // bytes from a frame to the next one
+    uint32_t fsb;      // from a frame to the next one, in units of 16 bytes
     float sc;          // scale * log2(e)
     float lb, gb;      // shifts of the local and the global keys' raw scores, see launch_tile_attn
 };
@@ -175,11 +175,11 @@ __device__ __forceinline__ uint32_t key_row(const TileArgs &a, const Context &c,
     }
     return row;
 }
-// The wavefront's position and head of a row: rows are fsb bytes apart.
+// The wavefront's position and head of a row: rows are 16 fsb bytes apart.
 template <typename T>
 __device__ __forceinline__ const T *row_ptr(const T *p, uint32_t row, uint32_t fsb)
 {
-    return (const T *)((const unsigned char *)p + (uint64_t)row * fsb);
+    return (const T *)((const unsigned char *)p + ((uint64_t)row * fsb << 4));
 }
 
 // Orders LDS accesses of the wavefront's lanes: they execute in issue order, only the compiler has to
@@ -956,8 +956,8 @@ void tile_attn_plan(dsattn_plan_t &pl)
     // rows are whole 16-byte chunks
     const bool f32 = d.io_dtype == DSATTN_F32;
     if (d.head_dim % (f32 ? 4 : 8) != 0) return;
-    // a frame's bytes are counted in 32 bits
-    if ((int64_t)d.spatial * pl.C * (f32 ? 4 : 2) > 0xffffffffLL) return;
+    // a frame's 16-byte pieces are counted in 32 bits
+    if ((int64_t)d.spatial * pl.C * (f32 ? 4 : 2) / 16 > 0xffffffffLL) return;
     const int qt = query_tiles(d, has_opts(pl));
     pl.tile_fn = tile_fn(d, qt, has_opts(pl));
     if (!pl.tile_fn) return;
@@ -994,7 +994,7 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.dedup = a.G > 0 && (d.flags & DSATTN_FLAG_DEDUP_GLOBAL) ? 1 : 0;
     a.tasks = (uint32_t)d.n_clips * d.spatial * d.heads * a.nqg;
     a.per_xcd = (a.tasks + 4 * 8 - 1) / (4 * 8);
-    a.fsb = (uint32_t)((int64_t)d.spatial * pl.C * (d.io_dtype == DSATTN_F32 ? 4 : 2));
+    a.fsb = (uint32_t)((int64_t)d.spatial * pl.C * (d.io_dtype == DSATTN_F32 ? 4 : 2) / 16);
     a.sc = bias_shifts(pl, a.lb, a.gb);
     void *params[] = {&a};
     return hipLaunchKernel(pl.tile_fn, dim3(a.per_xcd * 8), dim3(256), params, 0, st);

@@ -45,6 +45,25 @@ def test_attention_on_tensors_beyond_4_gib():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("dtype,P,h,D", [("bf16", 2100003, 8, 128), ("f32", 1050001, 16, 64)])
+def test_tile_attention_on_frames_beyond_4_gib(dtype, P, h, D):
+    """One frame is more than 4 GiB: rows are further apart than 32 bits of bytes."""
+    F, w, g = 3, 1, [2]
+    C = h * D
+    assert P * C * (2 if dtype == "bf16" else 4) > GIB4
+    print(f"[case] large frames {F} x {P} x {C} {dtype}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(340)
+    q, k, v = (torch.empty(F, P, C, dtype=synth.torch_dtype(dtype), device=DEV).normal_(generator=gen) for _ in range(3))
+    o, info = U.library_forward(q, k, v, 1, F, w, h, g, out_dtype=dtype)
+    assert info["block_threads"] == 256                     # the tile kernel, not the generic one
+    pos = [0, 1, P // 2, P - 2, P - 1]
+    ref = U.oracle_forward(q, k, v, 1, F, w, h, g, positions=pos)
+    U.assert_parity(o, ref, "bf16" if dtype == "bf16" else "f32_strict", positions=pos, what="large frames")
+    assert torch.isfinite(o[:, ::1001]).all()
+    del q, k, v, o
+    torch.cuda.empty_cache()
+
+
 def test_gather_of_a_context_beyond_4_gib_bit_exact():
     # the largest level: the materialised context of one tensor is 144 x 88 x 2,560 x 320 bf16 = 19 GiB
     wl = synth.WORKLOADS["C4"]
