@@ -836,13 +836,9 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
     }
 }
 
-// Two query tiles per wavefront share the rows that are fetched, and cost registers: taken where as many
-// wavefronts but one or none still fit.  6 clips of 24 / 32 frames, us with one tile a wavefront and with two, bf16:
-// head_dim 32 120 -> 108 / 96 -> 89, 40 156 -> 130 / 120 -> 108, 64 102 -> 92 / 87 -> 87, 80 110 -> 111 / 94 -> 101,
-// 96 93 -> 100 / 85 -> 92, 128 (25 frames of 32 global ones) 116 -> 104, 160 108 -> 113; fp32: 32 119 -> 111, 64 110 -> 103,
-// 80 108 -> 117, 96 114 -> 113 / 108 -> 110, 128 121 -> 111, 160 spills.  Of 48 frames the second wavefront has only one
-// tile: fp32 118 -> 122 at 64, bf16 103 -> 116 at 128, level at 32 to 64.  Options cost registers too: 157 -> 183 at 128
-// with the set union.
+// Head sizes with kernels of two query tiles per wavefront; query_tiles() says when they are taken.  They share the rows
+// that are fetched and cost registers; others, 6 clips of 24 frames, 1.2 x 10^7 elements, us with one and with two: bf16
+// head_dim 80 26.2 and 29.3, 96 22.0 and 25.8; fp32 80 58.4 and 67.0, 96 61.4 and 63.2, 144 67.4 and 72.3, 160 spills.
 constexpr bool two_query_tiles(bool f32, int blocks)
 {
     return f32 ? blocks <= 4 || blocks == 7 || blocks == 8 : blocks <= 2 || blocks == 4;
@@ -903,14 +899,29 @@ const void *tile_fn(const dsattn_desc &d, int qt, bool opts)
     }
 }
 
-// Query tiles per wavefront.
+// Query tiles per wavefront.  Two are faster where there are so many wavefronts that the registers they cost, one to three
+// wavefronts a SIMD, leave enough rounds.  Time with one over time with two, clips of 24 and of 32 frames (40: not whole
+// blocks of 32 channels, the kernel of one tile has four wavefronts a SIMD where that of 64 has five):
+//                   bf16 16, 32          40          64    104, 128  fp32 16 - 48          64    104, 112         128
+//      5,000 tiles                     1.07  0.94, 1.00  0.89, 0.99                1.00, 1.04  0.88, 0.98  0.99, 1.17
+//      9,000         0.89, 0.93        1.02  0.94, 0.94  0.99, 1.00    1.00, 1.05  1.03, 1.03  0.92, 1.03  1.03, 1.02
+//     16,000         0.97, 1.00  1.08, 1.01  0.92, 0.93  1.09, 1.03    0.99, 1.08  1.06, 1.05  1.00, 0.96  0.98, 0.98
+//     31,000         0.95, 1.03  1.08, 1.11  1.03, 1.01  1.06, 1.06    1.05, 1.12  1.05, 1.02  1.00, 0.98  0.97, 0.97
+//     62,000         1.00, 1.11  1.15, 1.13  1.05, 1.04                1.08, 1.13  1.07, 1.06
+//    125,000 and up  1.06, 1.12  1.18, 1.18  1.08, 1.11  1.09, 1.13    1.08, 1.19  1.09, 1.10  1.05, 1.05  1.03, 1.04
+// Clips of three query tiles leave the second wavefront one: 48 frames 0.85 to 1.00, but 40 from 37,000 tiles on 1.01 to
+// 1.04.  Options cost registers too: 157 us with one, 183 with two at 128 with the set union.
 int query_tiles(const dsattn_desc &d, bool opts)
 {
     const bool f32 = d.io_dtype == DSATTN_F32;
     const int nqt = (d.clip_len + 15) / 16, blocks = f32 ? (d.head_dim + 15) / 16 : (d.head_dim + 31) / 32;
-    // (a few thousand tiles are one round of wavefronts either way, and half as long with a tile each)
-    const bool round = (int64_t)d.n_clips * d.spatial * d.heads * nqt >= 4096;
-    return round && !opts && two_query_tiles(f32, blocks) && nqt > 1 && (nqt != 3 || (!f32 && blocks <= 2)) ? 2 : 1;
+    if (opts || nqt == 1 || !two_query_tiles(f32, blocks)) return 1;
+    const bool part = !f32 && blocks == 2 && d.head_dim % 32 != 0;
+    if (nqt == 3 && !part) return 1;
+    const int64_t tiles = (int64_t)d.n_clips * d.spatial * d.heads * nqt;
+    const int64_t from = f32 ? (blocks == 7 ? 65536 : 4096)
+                             : nqt == 3 ? 36864 : blocks == 1 ? 40960 : blocks == 2 && !part ? 24576 : 12288;
+    return tiles >= from ? 2 : 1;
 }
 
 // What the scopes' biases take from the local and the global keys' raw scores; returns the factor of the

@@ -231,12 +231,15 @@ def test_planner_fallbacks_and_overrides(monkeypatch):
 
 
 @pytest.mark.parametrize("io,D,positions,tasks,lds", [
-    # 24 frames, 12 clips, 5 heads: two query tiles a clip, a wavefront each or, from 4,096 tiles on, one for both
-    (B.DSATTN_BF16, 64, 34, 2, 4 * 32 * (128 + 16) + 1024),
-    (B.DSATTN_BF16, 64, 35, 1, 4 * 32 * (128 + 16) + 1024),
-    (B.DSATTN_BF16, 80, 35, 2, 4 * 32 * (192 + 16) + 1024),
+    # 24 frames, 12 clips, 5 heads: two query tiles a clip, a wavefront each or, where there are enough, one for both
+    (B.DSATTN_BF16, 64, 204, 2, 4 * 32 * (128 + 16) + 1024),
+    (B.DSATTN_BF16, 64, 205, 1, 4 * 32 * (128 + 16) + 1024),
+    (B.DSATTN_BF16, 40, 103, 1, 4 * 32 * (128 + 16) + 1024),
+    (B.DSATTN_BF16, 80, 500, 2, 4 * 32 * (192 + 16) + 1024),
+    (B.DSATTN_F32, 64, 34, 2, 4 * 16 * (256 + 16) + 1024),
     (B.DSATTN_F32, 64, 35, 1, 4 * 16 * (256 + 16) + 1024),
-    (B.DSATTN_F32, 160, 35, 2, 4 * 16 * (640 + 16) + 1024),
+    (B.DSATTN_F32, 112, 500, 2, 4 * 16 * (448 + 16) + 1024),
+    (B.DSATTN_F32, 160, 500, 2, 4 * 16 * (640 + 16) + 1024),
 ])
 def test_tile_kernel_reports_its_tasks_and_lds(io, D, positions, tasks, lds):
     plan = B.dsattn_plan(24, 12, 3, positions, 5, D, [0, 5], io_dtype=io, device=-1)
