@@ -91,8 +91,8 @@ static void run_planner(dsattn_plan_t &pl)
     li.n_tasks = tasks <= 0x7fffffffLL ? (int32_t)tasks : 0;  // 0: too many for one launch
     li.lds_bytes = (int32_t)((pl.lk_max + d.head_dim) * sizeof(float));
     // on the matrix cores, within the same limits, where a tile kernel exists: faster at every size
-    // measured (24-frame clips of 135 positions, 5 heads of 64, bf16: 35 against 191 us; 384 frames x 640
-    // positions, 8 heads of 80, fp32: 677 against 2,644 us), level only where a call is all launch
+    // measured (24-frame clips of 135 positions, 5 heads of 64, bf16: 25 against 191 us; 384 frames x 640
+    // positions, 8 heads of 80, fp32: 586 against 2,644 us), level only where a call is all launch
     if (!force_generic) tile_attn_plan(pl);
 }
 

@@ -8,13 +8,14 @@
 // Same implicit GEMM and tiles as the other kernels (rows m = f * P + p, taps as row offsets of X, stages of 32
 // channels of one tap, taps innermost, tiles numbered group, row, column).  A stage's rows come into registers
 // while the stage before is multiplied out, are split there and written to LDS as three planes of 64-byte rows;
-// 16-byte chunks are XOR-swizzled by row / 4, which keeps the operand reads free of bank conflicts.  Two
-// workgroups share a compute unit: one splits while the other multiplies.
+// 16-byte chunks are XOR-swizzled by row / 4 (of the 16 lanes that a read serves together two and two still share their
+// banks).  Two workgroups share a compute unit: one splits while the other multiplies.
 //
-// What bounds it: the vector instructions of the splitting, beside the matrix instructions: a stage of 128 x 128 takes
-// 2.5 us with two workgroups on a compute unit, 1.3 of which the matrix cores are busy.  7,152 x 1,024 x 1,024
-// 84 us = 178 TFLOP/s of fp32 products, 120 us on the fp32 instructions (whose peak is 157 TFLOP/s); 10,240 x 640 x 640
-// three sets 142 against 201 us, one 52 against 77.
+// What bounds it: the vector instructions of the splitting, beside the matrix instructions: both are busy for half of the
+// time that the compute units are, the LDS for 39 % (a third of that with bank conflicts).  7,152 x 1,024 x 1,024
+// 83 us = 181 TFLOP/s of fp32 products, 120 us on the fp32 instructions (whose peak is 157 TFLOP/s); 10,240 x 640 x 640
+// three sets 146 against 205 us, one 52 against 77.  The look at the operands is 1 % of a projection and 3 to 6 % of a
+// convolution of 5 taps (4,880 x 960 x 640: 217 -> 230 us).
 #pragma once
 
 namespace dsattn {

@@ -18,10 +18,9 @@
 // What bounds them.  fp32: the fp32 matrix rate (157 TFLOP/s; 40,000 x 1,280 x 1,280 reaches 131, 10,240 x
 // 640 x 640 takes 77 us where one thread per output took 16,370 us).  Four slots measured the same
 // as two, 128 x 160 tiles up to 1.5 % faster on large problems and 40 % slower on small ones.
-// Small bf16: the stages of a tile are dependent (0.5 to 0.9 us each, 20 of them at 1,280 channels), and
-// within a stage the LDS reads: a wavefront's 64 x 64 part reads four 1 KB fragments for four products of
-// 32x32x16, 128 bytes a clock and compute unit, all that the LDS has.  (The path from L2 into LDS alone does
-// 33 TB/s.)
+// Small bf16: the stages of a tile are dependent (0.5 to 0.9 us each, 20 of them at 1,280 channels), and a single
+// round starts and drains once: of the time that the compute units are busy the matrix cores are 33 % (pipelined 128 x
+// 128) and 45 % (128 x 160, three sets), the LDS 19 and 23 %.  (The path from L2 into LDS alone does 33 TB/s.)
 #pragma once
 
 namespace dsattn {
@@ -329,7 +328,8 @@ __global__ __launch_bounds__(64 * WVM * WVN, 1) void tconv_pipe_kernel(const Con
     // Chunks are swizzled by row / 2 here: the 16 lanes that a 16-byte LDS read serves together are rows 0 - 3,
     // 12 - 15, 20 - 23 and 24 - 27 of a fragment of 32 rows (or the other 16), and rows alternate between the two
     // halves of the banks, so row / 2 % 8 is what tells those of one half apart.  (By row % 8 every read was a
-    // two-way conflict, half of all LDS cycles: 2,560 x 1,280 x 1,280 on 128 x 128 tiles 16.6 us, 13.9 so.)
+    // two-way conflict.  2,560 x 1,280 x 1,280 on 128 x 128 tiles: LDS 37 % busy, half of that with conflicts, and 19 % with
+    // 6 % of it so; 13.9 us either way: a single round's latencies, not the LDS, are what it waits for.)
     const int lr = lane >> 3;
     // the chunk a lane fetches of a row of an even 8-row group; of an odd one it is the other half's
     const int lc = (lane & 7) ^ (lr >> 1);

@@ -7,8 +7,8 @@
 // in tiles of 16 keys with a running maximum.  Rows are fetched with four neighbouring lanes on 64
 // neighbouring bytes and pass through a few KB of wavefront-private LDS into the operand layout.  (Fetched in
 // the operand layout itself, 16 rows to 16 neighbouring lanes, every lane was an access of its own to the
-// first-level cache, which was then busy for the whole of the kernel: 55 accesses a load instruction
-// instead of 14, and 12 clips of 24 frames of 64 global ones, 370 positions, 8 x 160: 530 -> 425 us.)
+// first-level cache, which was then busy for the whole of the kernel: 49 to 54 accesses an instruction instead of 15,
+// fp32 28 instead of 13, and 12 clips of 24 frames of 64 global ones, 370 positions, 8 x 160: 590 -> 402 us.)
 //   S^T = K Q^T   keys on M, queries on N.  The lane's 16 bytes are chunk 4 j + lane / 16 of row
 //                 lane % 16, in both operands, so any order of the channels contracts the same:
 //                 one operand of v_mfma_f32_16x16x32_bf16, or four of v_mfma_f32_16x16x4_f32.
@@ -18,12 +18,12 @@
 //                 bf16: v_mfma_f32_16x16x32_bf16 over a pair of key tiles (an odd one: 16x16x16); a weight
 //                 enters as the sum of three bf16 numbers (8 bits each: all 24), whose products are exact.
 //
-// What bounds it: at short context lists HBM and the vector instructions of softmax and splitting, about
-// half each.  Tasks are numbered so that one XCD works through consecutive clips of one position: the
+// What bounds it: at short context lists HBM and the vector instructions of softmax and splitting (which keep the
+// vector ALUs busy for half of the time).  Tasks are numbered so that one XCD works through consecutive clips of one position: the
 // global frames and the boundary frames that neighbouring clips share are then in its L2, and measured
-// HBM reads are the tensors' own size.  12 clips of 24 frames x 135 positions, 5 x 64, bf16: 25.5 us (32.8
-// with operand-order loads and one query tile a wavefront; 19.4 at the card's copy rate); 2,304 positions
-// x 2 clips of 25, 8 x 80: 158 (200); 3 clips of 24 x 925 positions, 8 x 80, fp32: 188 (220).
+// HBM reads are the tensors' own size.  Tensors from HBM: 12 clips of 24 frames x 135 positions, 5 x 64, bf16: 25.2 us
+// (35.6 with operand-order loads; 19.4 at the card's copy rate); 2,304 positions x 2 clips of 25, 8 x 80: 162 (213);
+// 3 clips of 24 x 925 positions, 8 x 80, fp32: 195 (230).
 // Variants: V transposed by a 0/1 selector product instead of through LDS, the same time, but an
 // infinity in V reaches the 31 channels beside it; bf16 weights times V on the fp32
 // instructions, 30 % slower; weights split by rounding instead of cutting, 10 % slower.
@@ -215,10 +215,10 @@ __device__ __forceinline__ float exp2_positive(float x)
     return __builtin_amdgcn_exp2f(fmaxf(x, fmaf(x, 0x1p-100f, -126.f)));
 }
 
-// The part of the kernel that both types share: masks, running softmax.  KT key tiles per step.  OPTS: a
+// The part of the kernel that both types share: masks, running softmax.  OPTS: a
 // window, the set union or biases; compiled apart, because the conditions alone, kept in scalar registers
 // and spilled from there, were a third of the loop's instructions (12 clips of 24 frames x 135 positions,
-// 5 x 64: 28.3 -> 25.5 us without them).
+// 5 x 64, tensors in the caches: 28.3 -> 25.5 us without them).
 template <bool POSITIVE, bool OPTS>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
