@@ -324,15 +324,21 @@ def test_groupnorm_affine_factors_meet_the_normalised_value(dtype):
     (97, 2064, 8),
     (1228, 2560, 320),    # the most pieces of rows that one launch takes, and a row more
     (1229, 2560, 320),
-    (768, 2048, 512),     # fp32: four channels a group, where it takes fewer
-    (513, 2048, 512),
-    (512, 2048, 512),
 ])
 def test_groupnorm_small_tensors_in_one_launch(rows, C, groups, dtype):
     """Sizes around the limits of the single-launch kernel, held to the bars of test_groupnorm_matches_oracle;
     half of the tensor is shifted, so that no part has the whole's mean."""
-    if C // groups < 8 and dtype == "bf16":
-        pytest.skip("bf16 takes eight channels a group and more")
+    check_small(rows, C, groups, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [512, 513, 768])
+def test_groupnorm_small_groups_of_four_channels(rows):
+    """fp32 only: the most pieces of rows that one launch takes of groups of less than eight channels, and more."""
+    check_small(rows, 2048, 512, "f32")
+
+
+def check_small(rows, C, groups, dtype):
     print(f"[case] groupnorm small {rows} {C} {groups} {dtype}", flush=True)
     x = synth.make_tensor(rows, 1, C, 41, "iid", dtype)
     x = (x.float() + (torch.arange(rows) % 2 * 3.0)[:, None, None]).to(x.dtype).to(DEV)
