@@ -71,6 +71,7 @@ struct ConvArgs {
     int32_t tiles_m, tiles_n;  // row tiles, column tiles per group
     int32_t tiles;             // all tiles = groups x row tiles x column tiles
     int32_t per_xcd;           // ceil(tiles / 8)
+    int32_t panel;             // persistent kernels: column tiles that are numbered together
     int32_t w_bytes;           // taps * c_out * c_in * 2
 };
 
@@ -106,24 +107,49 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
 
     // workgroup -> tiles: XCD x (= blockIdx % 8) owns tiles [x * per_xcd, (x + 1) * per_xcd); its
     // gridDim / 8 workgroups take them in turn, so the tiles in flight on an XCD at any time are
-    // neighbours.  Tiles are numbered group outermost, then row tile, column tile fastest: the
-    // tiles in flight on an XCD are all column tiles of a few neighbouring row tiles of one
-    // group, about as many X slabs as W slabs (with the groups side by side they would be 2 row
-    // tiles against 3 x 5 column tiles and fetch W three times as often: measured 15 GB instead
-    // of 6 GB from HBM).
+    // neighbours.  The column tiles of all groups stand side by side and are numbered in panels of
+    // a.panel of them, row tile by row tile: see conv_panel().
     const int xcd = (int)(blockIdx.x % kXcds);
     const int nper = (int)(gridDim.x / kXcds);  // workgroups per XCD
     const int t_end = min((xcd + 1) * a.per_xcd, a.tiles);
     int tile_c = xcd * a.per_xcd + (int)(blockIdx.x / kXcds);  // the tile being multiplied out
     if (tile_c >= t_end) return;  // whole workgroup: no barrier has been reached yet
-    const int tiles_grp = a.tiles_m * a.tiles_n;
-    auto decode = [&](int tile, int &grp, int64_t &m0, int &n0) __attribute__((always_inline)) {
-        grp = tile / tiles_grp;
-        const int rem = tile - grp * tiles_grp;
-        const int mt = rem / a.tiles_n, nt = rem - mt * a.tiles_n;
-        m0 = (int64_t)mt * BM;
+    // A tile's place: column tile `first + c` of all groups' (`first` is the panel's first one), row tile mt.  The
+    // load side and the multiplies each step theirs along, nper tiles at a time: divided out, the
+    // divisors' reciprocals cost the main loop its registers.
+    struct Place {
+        int first, c, mt;
+    };
+    const int dmt = nper / a.panel, dc = nper - dmt * a.panel;
+    auto step = [&](Place &p) __attribute__((always_inline)) {
+        p.c += dc;
+        p.mt += dmt;
+        if (p.c >= a.panel) {
+            p.c -= a.panel;
+            ++p.mt;
+        }
+        while (p.mt >= a.tiles_m) {
+            p.mt -= a.tiles_m;
+            p.first += a.panel;
+        }
+    };
+    auto locate = [&](const Place &p, int &grp, int64_t &m0, int &n0) __attribute__((always_inline)) {
+        int nt = p.first + p.c;
+        grp = 0;
+#pragma unroll
+        for (int g = 1; g < kMaxGroups; ++g)
+            if (nt >= a.tiles_n) {
+                nt -= a.tiles_n;
+                ++grp;
+            }
+        m0 = (int64_t)p.mt * BM;
         n0 = nt * BN;
     };
+    Place place;  // of the tile being multiplied out
+    {
+        const int row = tile_c / a.panel, pn = row / a.tiles_m;
+        place = {pn * a.panel, tile_c - row * a.panel, row - pn * a.tiles_m};
+    }
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -145,36 +171,36 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
     const int lc = (lane & 7) ^ lr;
     const int rowbytes = a.Cin * 2;
     constexpr uint32_t kOob = 0xfffffff0u;
-    int xoff[GA], woff[GB];  // byte offset of this lane's row and chunk within the tile's rows
+    // Byte offset of this lane's row and chunk within the tile's rows: of X's first group, the others
+    // follow in a scalar register; of every group of W (all groups of both are four registers too many,
+    // and W counted along as well is half a percent slower).
     // (the empty asm keeps each offset in a register: recomputing it inside the loop would put a
     // multiply and several adds between the matrix instructions, per load)
-#pragma unroll
-    for (int l = 0; l < GA; ++l) {
-        xoff[l] = (wv * (8 * GA) + lr + 8 * l) * rowbytes + lc * 16;
-        asm volatile("" : "+v"(xoff[l]));
-    }
+    int xoff = (wv * (8 * GA) + lr) * rowbytes + lc * 16;
+    asm volatile("" : "+v"(xoff));
+    int woff[GB];
 #pragma unroll
     for (int l = 0; l < GB; ++l) {
         woff[l] = (wv * (8 * GB) + lr + 8 * l) * rowbytes + lc * 16;
         asm volatile("" : "+v"(woff[l]));
     }
+    const int group_bytes = 8 * rowbytes;
 
     // ---- the load side: the tile whose stages are being fetched (it runs ahead of the tile being
     // multiplied out by up to two stages), its descriptors, and the per-stage load state
-    int ld_tile = tile_c - nper;  // ld_open() advances before use
-    bool ld_has = false;          // there is such a tile
+    int ld_tile = tile_c;
+    Place ld_place = place;
+    bool ld_has = true;  // there is such a tile
     int ld_n0 = 0;
     int64_t ld_m0 = 0, ld_rb = 0;
     __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, 0, 0x00020000);
     __amdgpu_buffer_rsrc_t wres = xres;
     const int taps = 2 * a.n + 1;
-    int su_kc = 0, su_t = 0, su_ks = a.KS;  // channel block, tap and stage number within the load tile
+    int su_kc = 0, su_t = 0, su_ks = 0;  // channel block, tap and stage number within the load tile
     int ld_gs = 0;                          // stages set up so far: the ring slot is ld_gs % 2
     auto ld_open = [&]() __attribute__((always_inline)) {
-        ld_tile += nper;
-        ld_has = ld_tile < t_end;
-        int grp = 0;
-        decode(ld_has ? ld_tile : tile_c, grp, ld_m0, ld_n0);
+        int grp;
+        locate(ld_place, grp, ld_m0, ld_n0);
         ld_rb = max((int64_t)0, ld_m0 - (int64_t)a.n * a.P);  // first row the tile can touch
         xres = __builtin_amdgcn_make_buffer_rsrc(
             (void *)((const __bf16 *)a.X + ld_rb * a.Cin), 0,
@@ -193,7 +219,12 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
     // out-of-range one: no traffic, the same number of loads in flight, and no branch inside the
     // multiply schedule.
     auto stage_setup = [&]() __attribute__((always_inline)) {
-        if (su_ks == a.KS) ld_open();
+        if (su_ks == a.KS) {
+            ld_tile += nper;
+            ld_has = ld_tile < t_end;
+            if (ld_has) step(ld_place);
+            ld_open();
+        }
         const int kc = su_kc, t = su_t;
         ++su_ks;
         if (++su_t == taps) {
@@ -210,15 +241,18 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
         ld_bs = smem + slot * SLOT + ABYTES + wv * (GB * 1024);
     };
     constexpr int NL = GA + GB;  // loads per wavefront and stage
+    // (a stage's loads are issued in order)
     auto issue_one = [&](int l) __attribute__((always_inline)) {
-        if (l < GA)
+        if (l < GA) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 xres, (__attribute__((address_space(3))) void *)(ld_as + l * 1024), 16,
-                ld_live ? (uint32_t)xoff[l] + ld_xstep : kOob, 0, 0, 0);
-        else
+                ld_live ? (uint32_t)xoff + ld_xstep : kOob, 0, 0, 0);
+            ld_xstep += group_bytes;
+        } else {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 wres, (__attribute__((address_space(3))) void *)(ld_bs + (l - GA) * 1024), 16,
                 ld_live ? (uint32_t)woff[l - GA] + ld_wstep : kOob, 0, 0, 0);
+        }
     };
 
     // The wavefront's (32 MI) x (32 NJ) part is MB x NB blocks of 16 x 16, one
@@ -338,6 +372,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
     // ---- start of the stream: the first tile's first stage landed, the first loads of its
     // second stage issued as the loop's tail would have.  (Bare barriers: the wait before them is
     // the only ordering needed.)
+    ld_open();
     stage_setup();
 #pragma unroll
     for (int l = 0; l < NL; ++l) issue_one(l);
@@ -356,7 +391,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
         int grp;
         int64_t m0;
         int n0;
-        decode(tile_c, grp, m0, n0);
+        locate(place, grp, m0, n0);
         const float *gbias = a.bias[grp];
         void *gY = a.Y[grp];
         const int cbase = n0 + wn * 32 * NJ;      // first channel of this wavefront's part
@@ -510,6 +545,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
         // left the staging area
         tile_c += nper;
         if (tile_c >= t_end) break;
+        step(place);
         clear_acc();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -810,6 +846,28 @@ int linear_as_conv(const dsattn_linear_desc *l, dsattn_conv_desc &d, int64_t &M,
     return conv_validate(&d, who);
 }
 
+// Column tiles, of the groups' side by side, that the persistent kernels number together.  An XCD's 32 tiles in flight
+// are this many wide and 32 / width row tiles high, and what its L2 fetches of X and W is the sum of the two: the
+// width for which that is least, in panels of one size.  (Taps innermost: the rows of X serve all of them.)  Under the
+// chip's power limit what is not fetched is time.  us of three sets with the groups one after the other and so:
+// 600,000 x 320 x 320 547 and 491, 245,760 x 640 x 640 632 and 603, 100,000 x 1,024 x 1,024 621 and 578, 368,640 x
+// 1,280 x 1,280 3,033 and 2,937 (six of twelve column tiles; four 3,033, all twelve 3,030).
+int conv_panel(int cols, int taps, int bm, int bn)
+{
+    int best = 1;
+    double least = 1e300;
+    for (int panels = 1; panels <= std::min(cols, 64); ++panels) {
+        if (cols % panels != 0) continue;
+        const int width = cols / panels;
+        const double rows = (double)taps * width * bn + 32.0 / std::min(width, 32) * bm;
+        if (rows < least) {
+            least = rows;
+            best = width;
+        }
+    }
+    return best;
+}
+
 // Launches the implicit-GEMM kernel (when `v`) or the vector kernel for `groups` weight sets
 // applied to the same X.  `d` describes one set; M = rows of X and of every Y.
 hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *v, int groups,
@@ -855,6 +913,7 @@ hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *
         a.tiles_m = (int32_t)((M + bm - 1) / bm);
         a.tiles = a.tiles_m * a.tiles_n * groups;
         a.per_xcd = (a.tiles + kXcds - 1) / kXcds;
+        a.panel = v->resident ? conv_panel(a.tiles_n * groups, 2 * d.reach + 1, v->bm, v->bn) : 0;
         a.w_bytes = (int32_t)((2 * (int64_t)d.reach + 1) * d.c_out * d.c_in * es);
         void *params[] = {&a};
         // persistent workgroups: one per compute unit at most, the same number on every XCD

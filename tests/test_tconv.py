@@ -582,6 +582,25 @@ def test_linear_tiles_for_few_tiles_and_few_channels(rows, c_in, c_out, n_out, t
         assert (info["kernel"], info["tile_m"], info["tile_n"], info["block_threads"]) == (1,) + tile
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", [
+    (33100, 64, 312, 3, (256, 320, 512)),     # three sets' column tiles in one panel; a stage a tile: loads run two tiles ahead
+    (10113, 72, 1270, 3, (256, 320, 512)),    # twelve column tiles in two panels of six: the second set is cut
+    (25100, 64, 250, 4, (256, 256, 512)),
+])
+def test_linear_panels_of_column_tiles(rows, c_in, c_out, n_out, tile):
+    for out_dtype in ("f32", "bf16"):
+        info = linear_case(rows, c_in, c_out, n_out, dtype="bf16", out_dtype=out_dtype)
+        assert (info["kernel"], info["tile_m"], info["tile_n"], info["block_threads"]) == (1,) + tile
+
+
+@pytest.mark.gpu
+def test_conv_panels_of_column_tiles():
+    """Six column tiles of a convolution of five taps: three panels of two."""
+    info = conv_case(16, 41, 25, 8, 1920, 2)
+    assert (info["tile_m"], info["tile_n"]) == (256, 320)
+
+
 @pytest.mark.parametrize("shape,tile", [
     # clip_len, n_clips, P, c_in, c_out, n: the fastest of the eight kernels where they were timed, by 5 % and more
     ((16, 1, 500, 320, 320, 1), (64, 64)),      # three 64 x 64 tiles on a compute unit, 11.0 us; 11.6 on 128 x 128
