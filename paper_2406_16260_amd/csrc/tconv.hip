@@ -328,7 +328,8 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
                     read_a(base, kk, HB + r);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-            const int j = m / HB, i = m - j * HB;
+            // (back and forth: one operand stays the same from one multiply to the next)
+            const int j = m / HB, i0 = m - j * HB, i = j & 1 ? HB - 1 - i0 : i0;
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -340,12 +341,12 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
 #pragma unroll
         for (int m = 0; m < NMH; ++m) {
             loads_at(g0 + m, do_loads);
-            const int j = m / HB, i = m - j * HB;
-            if (i == 0 && j > 0) {
+            const int j = m / HB, i0 = m - j * HB, i = j & 1 ? HB - 1 - i0 : i0;
+            if (i0 == 0 && j > 0) {
                 read_b(nbase, nkk, j - 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (i == HB - 1 && j < HB) {  // one X fragment per column, behind the column's first multiplies
+            if (i0 == HB - 1 && j < HB) {  // one X fragment per column, behind the column's first multiplies
                 read_a(nbase, nkk, j);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -408,8 +409,17 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
         for (int ks = 0; ks < a.KS; ++ks, ++cs) {
             const unsigned char *bufc = smem + (cs & 1) * SLOT;
             const unsigned char *bufn = smem + ((cs + 1) & 1) * SLOT;
+            // Wavefronts w and w + 4 share a SIMD and leave a barrier together.  Of equals the older one goes first
+            // throughout, and both then wait for their operands and loads at the same time; with the younger one first in
+            // this sub-step they draw apart, and one multiplies while the other waits.  us, without and with:
+            // convolution of 368,640 rows, 1,280 channels 2,619 and 2,550, of 245,760 rows, 640 channels 485 and 476,
+            // 100,000 x 1,024 x 1,024 223 and 218, three sets of 368,640 x 1,280 x 1,280 2,953 and 2,914.  (Every wavefront
+            // raised in half of the sub-step, or the two by turns in both sub-steps: within half a percent; raised in the
+            // other halves, throughout, or by stages: nothing.)
+            if (wv >= NW / 2) __builtin_amdgcn_s_setprio(1);
             half1(bufc, 0, TAIL);
             half2(bufc, 1, TAIL + NMH, true);
+            __builtin_amdgcn_s_setprio(0);
             // last sub-step: its first half, then the barrier (this wavefront's loads of the
             // next stage have landed; after the barrier everybody's have, and every wavefront
             // has left the current slot), then its second half with the first fragments of the
