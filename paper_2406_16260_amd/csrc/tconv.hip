@@ -297,9 +297,12 @@ __global__ __launch_bounds__(64 * WVM * WVN, WVM * WVN / 4) void tconv_mfma_kern
     // must have landed by the next barrier; they are spread over the first kSpread multiplies
     // after the barrier (three of the four halves between two barriers), so that the memory
     // pipeline's queue never fills (a wavefront that cannot issue a load cannot issue multiplies
-    // either), and the last one still has the fourth half to land.
+    // either), and the last one still has the fourth half to land.  The smaller tiles' stages are shorter and
+    // their loads take as long: two and a half halves.  100,000 x 1,024 x 1,024 on 256 x 256, us over one, two, two and
+    // a half and three halves: 230, 211, 209, 213; 368,640 x 1,280 x 1,280 on 256 x 320 over two, two and a half and
+    // three: 1,023, 1,036, 1,027, three taps 2,568, 2,562, 2,540.
     constexpr int TAIL = NMH;  // multiplies of a stage's last half, which follow the barrier
-    constexpr int kSpread = 3 * NMH;
+    constexpr int kSpread = NB >= 10 ? 3 * NMH : 5 * NMH / 2;
     auto read_a = [&](const unsigned char *base, int kk, int i) __attribute__((always_inline)) {
         af[i] = *(const bf16x8 *)(base + abase + i * (16 * kRow) + koff[kk]);
     };
@@ -628,8 +631,10 @@ constexpr int conv_lds_bytes(int bm, int bn, int nj, int waves)
      {(const void *)&tconv_split_kernel<MB>, (const void *)&tconv_split_kernel<MB>}}
 // Eight wavefronts (two per SIMD) in the persistent kernels: one wavefront per SIMD cannot keep the
 // matrix cores busy with 16x16x32 instructions (measured: 1.46 against 2.4 PFLOP/s on idle data).
+// A part of 64 x 128 of the 256 x 256 tile, not of 128 x 64: 100,000 x 1,024 x 1,024 215 -> 212 us, 368,640 x 1,280 x 1,280
+// 1,089 -> 1,076.
 const ConvVariant kConvVariants[] = {
-    DSATTN_CONV_VARIANT(4, 2, 2, 4),     // 256 x 256
+    DSATTN_CONV_VARIANT(2, 4, 4, 2),     // 256 x 256
     DSATTN_CONV_VARIANT(2, 5, 4, 2),     // 256 x 320
     DSATTN_CONV_VARIANT(2, 3, 4, 2),     // 256 x 192
     DSATTN_TILE_VARIANT(4, 5, 2, 2),     // 128 x 160
