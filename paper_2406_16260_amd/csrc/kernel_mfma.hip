@@ -44,34 +44,25 @@ int env_int(const char *name, int dflt)
     return e && *e ? atoi(e) : dflt;
 }
 
-}  // namespace
+// What a launch is made of: the variant, wavefronts per workgroup, query tiles per chunk.
+struct Geometry {
+    const MfmaVariant *var = nullptr;
+    int id = -1, hpw = 0, wpb = 1, m = 1, lds = 0;
+    int64_t tasks = 0;  // wavefronts
+};
 
-bool mfma_plan(dsattn_plan_t &pl)
+// A plan's shape as the kernel sees it.
+struct Shape {
+    int n_tiles, wr, R, NLT, NGT, G;
+    bool out_f32;
+};
+
+// spread: narrower rows and smaller workgroups, see mfma_plan().
+bool mfma_geometry(const dsattn_plan_t &pl, const Shape &sh, bool spread, Geometry &geo)
 {
     const dsattn_desc &d = pl.desc;
-    // The kernel works on query tiles of 16 frames; a clip is a whole number of them.
-    if (d.io_dtype != DSATTN_BF16 || d.clip_len % 16 != 0) return false;
-    if (pl.C % 8 != 0) return false;
-    // the kernel addresses the 16 frame rows of a tile with 32-bit byte offsets
-    if ((int64_t)d.spatial * pl.C * 2 * 16 >= ((int64_t)1 << 32)) return false;
-    const int G = (int)pl.global_idx.size();
-    // global key tiles: variants exist for 0, 1, 4 and (where a wavefront's registers hold
-    // them) 8 tiles; a partly used tile is masked
-    if (G > 128) return false;
-    const int NGT = G == 0 ? 0 : (G <= 16 ? 1 : (G <= 64 ? 4 : 8));
-    // Frames a tile's local scope can reach beyond the tile on each side: up to the end of the
-    // clip's local range (the rest of the clip plus the neighbour's context frames), or the
-    // sliding window's radius when that is shorter.  With 16-frame clips and no window this is
-    // the clip's local context width.
-    const int64_t reach = (int64_t)d.clip_len - 16 + d.local_ctx;
-    const int64_t wr64 = pl.window >= 0 ? std::min<int64_t>(pl.window, reach) : reach;
-    if (wr64 > 16) return false;  // local key tiles: variants exist for 1 to 3
-    const int wr = (int)wr64;
-    const int n_tiles = pl.F / 16;
-    const int R = 16 + 2 * wr;
-    const int NLT = (R + 15) / 16;
-    const bool out_f32 = d.out_dtype == DSATTN_F32;
-
+    const int n_tiles = sh.n_tiles, wr = sh.wr, R = sh.R, NLT = sh.NLT, NGT = sh.NGT, G = sh.G;
+    const bool out_f32 = sh.out_f32;
     // heads per wavefront: prefer the variant that keeps two wavefronts per SIMD (more loads in
     // flight, compute of one wavefront hidden behind the other), then the widest rows; a
     // wavefront never straddles two positions
@@ -100,6 +91,21 @@ bool mfma_plan(dsattn_plan_t &pl)
         if (var) break;
     }
     if (!var) return false;
+    // Narrower rows: up to 96 channels (one head, or two of 40 and of 32), and one head where there are fewer than
+    // 1,024 query tiles of those.
+    const int wide = var->HPW;
+    if (spread && !force_hpw) {
+        for (int cand : {2, 1}) {
+            if (cand >= var->HPW || d.heads % cand != 0) continue;
+            if (var->HPW * d.head_dim <= 96 && (int64_t)d.spatial * (d.heads / var->HPW) * n_tiles >= 1024) break;
+            int id = -1;
+            const MfmaVariant *v = find_variant(d.head_dim, cand, NLT, NGT, out_f32, &id);
+            if (v && v->WPE == var->WPE) {
+                var = v;
+                var_id = id;
+            }
+        }
+    }
     const int hpw = var->HPW;
     const int lds_wave = (2 * R + 16) * row_stride_bytes(d.head_dim * hpw);
     if (lds_wave > kLdsPerCu) return false;
@@ -111,7 +117,10 @@ bool mfma_plan(dsattn_plan_t &pl)
     // unit are better than one: while one starts or drains a chunk the other keeps streaming.
     const int max_waves_cu = std::min(4 * var->WPE, kLdsPerCu / lds_wave);
     const int waves_per_pos = d.heads / hpw;
-    const int want = std::min(max_waves_cu, std::max(waves_per_pos, max_waves_cu / 2));
+    // Where the rows are spread: about 640 bytes of a frame (1 clip of 1,398 positions, 8 x 128, 50.6 us with eight
+    // wavefronts, 41.4 with two; 9 of 271 71.9 and 62.4), and 512 workgroups if there are as many wavefronts.
+    const int want = spread ? std::min(max_waves_cu, std::max(1, 640 / (2 * hpw * d.head_dim)))
+                            : std::min(max_waves_cu, std::max(waves_per_pos, max_waves_cu / 2));
     int wpb = 1;
     for (int cand : {8, 4, 2, 1})
         if (cand <= want && RG % cand == 0) {
@@ -150,8 +159,9 @@ bool mfma_plan(dsattn_plan_t &pl)
                                                 : 0.0);
         const double fill = rounds_eff / rounds;
         const double kv = (16.0 * m + (nc > 1 ? 2.0 * wr : 0.0) + G) / (16.0 * m);
-        // a chunk's start (two memory round trips before its first tile) costs about one tile
-        const double cost = (2.0 + 2.0 * kv) / 4.0 * fill * (1.0 + 1.0 / m);
+        // a chunk's start (two memory round trips before its first tile) costs about one tile, less where
+        // narrower wavefronts than the widest leave more of them to fill it
+        const double cost = (2.0 + 2.0 * kv) / 4.0 * fill * (1.0 + (hpw < wide ? 0.5 : 1.0) / m);
         if (cost < best_cost - 1e-12) {
             best_cost = cost;
             best_nc = nc;
@@ -167,26 +177,92 @@ bool mfma_plan(dsattn_plan_t &pl)
     // 9.7, 160 x 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  From 24 clips on
     // (35.5 / 36.1), and with four wavefronts and a single clip (8.0 / 8.3), the shared lines of neighbouring
     // rows count for more.
-    if ((int64_t)RG * NC <= (int64_t)kCus * max_waves_cu && n_tiles <= 16 && wpb > (n_tiles == 1 ? 4 : 2) &&
-        RG % 2 == 0 && !env_int("DSATTN_WAVES_PER_BLOCK", 0))
+    if (env_int("DSATTN_WAVES_PER_BLOCK", 0)) {
+    } else if (spread) {
+        while (wpb > 1 && (int64_t)(RG / wpb) * NC < 512) wpb /= 2;
+    } else if ((int64_t)RG * NC <= (int64_t)kCus * max_waves_cu && n_tiles <= 16 && wpb > (n_tiles == 1 ? 4 : 2) &&
+               RG % 2 == 0) {
         wpb = 2;
+    }
+    geo.var = var;
+    geo.id = var_id;
+    geo.hpw = hpw;
+    geo.wpb = wpb;
+    geo.m = m;
+    geo.lds = lds_wave * wpb;
+    geo.tasks = (int64_t)RG * NC;
+    return true;
+}
+
+}  // namespace
+
+bool mfma_plan(dsattn_plan_t &pl)
+{
+    const dsattn_desc &d = pl.desc;
+    // The kernel works on query tiles of 16 frames; a clip is a whole number of them.
+    if (d.io_dtype != DSATTN_BF16 || d.clip_len % 16 != 0) return false;
+    if (pl.C % 8 != 0) return false;
+    // the kernel addresses the 16 frame rows of a tile with 32-bit byte offsets
+    if ((int64_t)d.spatial * pl.C * 2 * 16 >= ((int64_t)1 << 32)) return false;
+    const int G = (int)pl.global_idx.size();
+    // global key tiles: variants exist for 0, 1, 4 and (where a wavefront's registers hold
+    // them) 8 tiles; a partly used tile is masked
+    if (G > 128) return false;
+    const int NGT = G == 0 ? 0 : (G <= 16 ? 1 : (G <= 64 ? 4 : 8));
+    // Frames a tile's local scope can reach beyond the tile on each side: up to the end of the
+    // clip's local range (the rest of the clip plus the neighbour's context frames), or the
+    // sliding window's radius when that is shorter.  With 16-frame clips and no window this is
+    // the clip's local context width.
+    const int64_t reach = (int64_t)d.clip_len - 16 + d.local_ctx;
+    const int64_t wr64 = pl.window >= 0 ? std::min<int64_t>(pl.window, reach) : reach;
+    if (wr64 > 16) return false;  // local key tiles: variants exist for 1 to 3
+    const int wr = (int)wr64;
+    const int n_tiles = pl.F / 16;
+    const int R = 16 + 2 * wr;
+    const int NLT = (R + 15) / 16;
+    const bool out_f32 = d.out_dtype == DSATTN_F32;
+
+    const Shape sh = {n_tiles, wr, R, NLT, NGT, G, out_f32};
+    Geometry geo, ctx;
+    if (!mfma_geometry(pl, sh, false, ctx)) return false;
+    // More and narrower wavefronts, each with less to do between its loads, in smaller workgroups: where the tensors are
+    // no larger than the 256 MB cache, so that how the rows lie in HBM does not decide, and with three local
+    // key tiles, whose ring leaves a compute unit less than a full set of wide wavefronts.  us, wide and narrow: 1 clip of
+    // 600 positions, 8 x 80, 22.9 and 15.7; 3 clips of 168, 8 x 40, 12.7 and 9.2; 8 clips of 111, 8 x 40, 16.0 and 12.5;
+    // three key tiles: 64 frames x 728, 10 x 64, 90 and 65, 2,112 x 696, 8 x 40, 1,054 and 817, 2,432 x 93, 6 x 96, 263
+    // and 219 (head_dim 32, 5,184 x 97, 123 and 131: not there; from head_dim 128 on there is nothing narrower).  Larger
+    // tensors: 2,304 frames of 160 positions, 20 x 64, 728 and 752, under a window, 640, 8 x 80, 1,489 and 1,574.  Over 143
+    // drawn shapes of 16 to 2,560 positions the calls take 0.937 of the time, and the best of all swept choices (heads,
+    // wavefronts, chunks) would take 0.965 of that.  Fewer than 16 positions, less than a level has, keep the widest
+    // rows.  A materialised context, whose chunks are clips, keeps them too: 9 clips of 52, 8 x 80, with the gather 26.5
+    // and 28.3.
+    const int64_t bytes = (int64_t)pl.F * d.spatial * pl.C * (out_f32 ? 10 : 8);
+    const bool spread = d.spatial >= 16 && (bytes <= (int64_t)256 << 20 ||
+                                            (NLT == 3 && d.head_dim != 32 && d.head_dim < 128));
+    // (a launch has less than 2^32 threads)
+    if (!spread || !mfma_geometry(pl, sh, true, geo) || geo.tasks > ((int64_t)1 << 32) / 64 - 8) geo = ctx;
+    const MfmaVariant *var = geo.var;
+    const int m = geo.m;
 
     dsattn_launch_info &li = pl.launch;
     li.kernel = 1;
-    li.heads_per_wave = hpw;
+    li.heads_per_wave = geo.hpw;
     li.local_tiles = NLT;
     li.global_tiles = NGT;
     li.clips_per_task = m;
-    li.n_tasks = RG * NC;
-    li.block_threads = 64 * wpb;
-    li.lds_bytes = lds_wave * wpb;
-    li.variant = var_id;
+    li.n_tasks = (int32_t)geo.tasks;
+    li.block_threads = 64 * geo.wpb;
+    li.lds_bytes = geo.lds;
+    li.variant = geo.id;
     li.ring_reach = wr;
+    pl.ctx_hpw = ctx.hpw;
+    pl.ctx_wpb = ctx.wpb;
+    pl.ctx_lds = ctx.lds;
 
     // everything a launch needs that does not depend on the tensors
     // (24 tiles: the shortest chunk of the long videos; a clip of a materialised context is a chunk)
     pl.mfma_fn = m >= 24 && var->fn_sel ? var->fn_sel : var->fn;
-    pl.mfma_ctx_fn = d.clip_len / 16 >= 24 && var->fn_sel ? var->fn_sel : var->fn;
+    pl.mfma_ctx_fn = d.clip_len / 16 >= 24 && ctx.var->fn_sel ? ctx.var->fn_sel : ctx.var->fn;
     pl.gdup = 0;  // entries that repeat an earlier one (the kernel takes at most 64 entries)
     for (size_t j = 0; j < pl.global_idx.size() && j < 64; ++j)
         for (size_t jj = 0; jj < j; ++jj)
@@ -218,7 +294,7 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
     const dsattn_launch_info &li = pl.launch;
     const void *fn = ctx_mode ? pl.mfma_ctx_fn : pl.mfma_fn;
     if (!fn) return hipErrorInvalidValue;
-    const int wpb = li.block_threads / 64;
+    const int wpb = ctx_mode ? pl.ctx_wpb : li.block_threads / 64;
 
     MfmaArgs a;
     a.Q = (const __bf16 *)Q;
@@ -238,7 +314,7 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
     a.window = pl.window;
     a.M = ctx_mode ? d.clip_len / 16 : li.clips_per_task;
     a.cstride = ctx_mode ? (int64_t)pl.lk_max * d.spatial * pl.C : 0;
-    a.RG = d.spatial * (d.heads / li.heads_per_wave);
+    a.RG = d.spatial * (d.heads / (ctx_mode ? pl.ctx_hpw : li.heads_per_wave));
     a.BPC = a.RG / wpb;
     a.C = pl.C;
     a.FS = (int64_t)d.spatial * pl.C;
@@ -257,8 +333,8 @@ hipError_t launch_mfma(const dsattn_plan_t &pl, const void *Q, const void *K, co
         return hipErrorInvalidValue;
 
     void *params[] = {&a};
-    return hipLaunchKernel(fn, dim3((unsigned)(a.BPC * NC)), dim3((unsigned)li.block_threads),
-                           params, (size_t)li.lds_bytes, st);
+    return hipLaunchKernel(fn, dim3((unsigned)(a.BPC * NC)), dim3((unsigned)(64 * wpb)),
+                           params, (size_t)(ctx_mode ? pl.ctx_lds : li.lds_bytes), st);
 }
 
 }  // namespace dsattn

@@ -31,7 +31,9 @@ struct dsattn_plan_s {
 
     // resolved once by the planner for the matrix-core kernel, so that a launch searches nothing
     const void *mfma_fn = nullptr;      // the variant's kernel
-    const void *mfma_ctx_fn = nullptr;  // the same on a materialised context
+    // on a materialised context: the variant's kernel, its heads per wavefront, wavefronts and LDS bytes per workgroup
+    const void *mfma_ctx_fn = nullptr;
+    int ctx_hpw = 0, ctx_wpb = 0, ctx_lds = 0;
     uint64_t gdup = 0;              // bit j: global entry j (< 64) repeats an earlier entry
 
     const void *tile_fn = nullptr;  // the tile kernel, where the streaming kernel has no variant

@@ -322,6 +322,29 @@ def test_mfma_interior_clips_every_local_width(w, D, h, G):
                   what=f"interior w={w} D={D} G={G}")
 
 
+@pytest.mark.parametrize("D,h,P,n_clips,w,G,hpw,widest", [
+    (40, 8, 17, 30, 2, 16, 2, 4),    # 1,024 query tiles of two heads and more
+    (40, 8, 17, 3, 2, 16, 1, 4),     # fewer: one head
+    (40, 8, 16, 5, 11, 4, 1, 4),     # three local key tiles
+    (80, 8, 19, 4, 3, 0, 1, 2),
+    (64, 10, 23, 3, 2, 12, 1, 2),
+    (96, 6, 16, 2, 8, 16, 1, 2),
+    (32, 4, 16, 2, 2, 40, 1, 2),
+])
+def test_mfma_small_launches_take_narrow_rows(D, h, P, n_clips, w, G, hpw, widest, monkeypatch):
+    """Fewer heads a wavefront are the same arithmetic: equal to the widest rows to the bit, and both to the oracle."""
+    g = synth.stride_global_idx(16 * n_clips, G)
+    kw = dict(gen="iid", out_dtypes=("f32", "bf16"))
+    info = run_mfma_case(n_clips, w, P, h, D, g, what=f"narrow D={D}", **kw)
+    assert info["heads_per_wave"] == hpw
+    q, k, v = make(16 * n_clips, P, h * D, 41, "iid", "bf16")
+    o, _ = U.library_forward(q, k, v, 16, n_clips, w, h, g)
+    monkeypatch.setenv("DSATTN_HEADS_PER_WAVE", str(widest))
+    o2, info = U.library_forward(q, k, v, 16, n_clips, w, h, g)
+    assert info["heads_per_wave"] == widest
+    assert torch.equal(o, o2)
+
+
 def test_mfma_odd_row_group_count():
     # 3 positions x 2 heads = 6 row groups: workgroups of 2 wavefronts, not 8
     info = run_mfma_case(3, 2, 3, 2, 160, [0, 9], what="odd rows")
