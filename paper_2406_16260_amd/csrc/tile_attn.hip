@@ -215,11 +215,37 @@ __device__ __forceinline__ float exp2_positive(float x)
     return __builtin_amdgcn_exp2f(fmaxf(x, fmaf(x, 0x1p-100f, -126.f)));
 }
 
-// The part of the kernel that both types share: masks, running softmax.  OPTS: a
-// window, the set union or biases; compiled apart, because the conditions alone, kept in scalar registers
-// and spilled from there, were a third of the loop's instructions (12 clips of 24 frames x 135 positions,
-// 5 x 64, tensors in the caches: 28.3 -> 25.5 us without them).
-template <bool POSITIVE, bool OPTS>
+// What a kernel is compiled for: no option, biases of the scopes, the set union without a window over up to 63
+// global frames (and biases), any.  Apart, because the conditions alone, kept in scalar registers and spilled from
+// there, were a third of the plain loop's instructions (12 clips of 24 frames x 135 positions, 5 x 64, tensors in the
+// caches: 28.3 -> 25.5 us without them).  What an option costs is instructions per score and registers: in the kernel
+// for all of them a bias alone takes the union's and the window's conditions along, and the union looks every global
+// key up in LDS and compares its frame for every query tile and key tile, though the answer is a task's, not a query's.
+// Against that kernel, 16 global frames, us, bias of the global scope; union; both (no option):
+//   91 clips of 24 frames x 246 positions, 4 x 32   188.3 -> 174.9  196.7 -> 174.2  208.9 -> 177.1  (162)
+//   40 clips of 24 frames x 100 positions, 10 x 64  123.8 -> 115.0  129.3 -> 121.5  132.4 -> 124.3  (113)
+//   40 clips of 25 frames x 100 positions, 8 x 160  265.6 -> 260.4  274.9 -> 260.4  277.3 -> 264.4  (258)
+//   90 clips of 8 frames x 135 positions, 6 x 96    135.8 -> 118.1  148.0 -> 133.5  152.7 -> 136.2  (117)
+//   40 clips of 24 frames x 100 positions, 5 x 64, fp32  133.0 -> 132.0  136.2 -> 132.2  137.3 -> 133.9  (126)
+// A window makes what is hidden a query's own, and more than 63 global frames do not fit one word: these stay with it.
+enum { kPlain, kBiases, kUnion, kAll };
+constexpr int kUnionGlobals = 63;
+
+// The global entries, bit i the i-th, that the set union hides from every query of a task: the ones whose frame is a
+// local one or an earlier entry's; and those past the list.  (Up to 63: bit 63 says so of what lies beyond.)
+__device__ __forceinline__ uint64_t hidden_entries(const TileArgs &a, const Context &c, const Globals &g)
+{
+    const int i = threadIdx.x & 63;
+    bool hidden = i >= a.G;
+    if (a.dedup && a.G > 0) {
+        const int ki = g[i], frame = ki & 0x3fffffff;
+        hidden = hidden || (ki >> 30 & 1) || (frame >= c.lo && frame < c.lo + c.nl);
+    }
+    return __ballot(hidden);
+}
+
+// The part of the kernel that both types share: masks, running softmax.
+template <bool POSITIVE, int OPTS>
 struct Softmax {
     float m = -INFINITY, l = 0.f;  // running maximum of the query's column; this lane's part of the sum
     // A shift of the local scores holds from the query's first visible global key on: the set union may
@@ -229,11 +255,21 @@ struct Softmax {
     // scores of key tiles t0 .. t0 + KT - 1 -> weights (unnormalised; those of keys past the list are zero);
     // returns the factor for what has been accumulated so far
     template <int KT>
-    __device__ __forceinline__ float step(const TileArgs &a, const Context &c, const Globals &g, int aq,
+    __device__ __forceinline__ float step(const TileArgs &a, const Context &c, const Globals &g, uint64_t hide, int aq,
                                           f32x4 (&s)[KT], int t0, int lane)
     {
         const int lg = lane >> 4, j0 = 16 * t0 + 4 * lg;
-        if (OPTS && (a.window >= 0 || a.dedup)) {
+        if (OPTS == kUnion) {
+            // (a lane's four keys are four bits in a row; local ones are never hidden)
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                if (16 * (t0 + t) + 16 <= c.nl) continue;
+                const int at = j0 + 16 * t - c.nl;  // -15 and up
+                const uint32_t bits = (uint32_t)(at < 0 ? hide << -at : (uint64_t)((int64_t)hide >> min(at, 63)));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[t][e] = bits >> e & 1 ? -INFINITY : s[t][e];
+            }
+        } else if (OPTS == kAll && (a.window >= 0 || a.dedup)) {
             const Visible vis = visible_to(a, c, aq);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
@@ -259,7 +295,7 @@ struct Softmax {
                 for (int e = 0; e < 4; ++e) s[t][e] = 16 * t + e >= left ? -INFINITY : s[t][e];
         }
         if (OPTS && (a.lb != 0.f || a.gb != 0.f)) {
-            if (a.dedup && a.lb != 0.f) {
+            if (OPTS != kBiases && a.dedup && a.lb != 0.f) {
                 float mg = -INFINITY;
 #pragma unroll
                 for (int t = 0; t < KT; ++t)
@@ -270,13 +306,22 @@ struct Softmax {
                 m += first ? a.lb * a.sc : 0.f;
                 shifted = shifted || first;
             }
-            const float ls = shifted || !a.dedup ? a.lb : 0.f;
+            const float ls = OPTS == kBiases || shifted || !a.dedup ? a.lb : 0.f;
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const bool globals = 16 * (t0 + t) + 16 > c.nl;
-                if (!globals && ls == 0.f) continue;
+                const int from = 16 * (t0 + t);
+                if (OPTS == kAll) {  // (a branch more costs the windowed kernel 1 %)
+                    if (from + 16 <= c.nl && ls == 0.f) continue;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s[t][e] += !globals || j0 + 16 * t + e < c.nl ? ls : a.gb;
+                    for (int e = 0; e < 4; ++e) s[t][e] += from + 16 <= c.nl || j0 + 16 * t + e < c.nl ? ls : a.gb;
+                } else if (from + 16 <= c.nl) {  // one of lb and gb is zero
+                    if (a.lb != 0.f) s[t] += ls;
+                } else if (from >= c.nl) {
+                    if (a.gb != 0.f) s[t] += a.gb;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[t][e] += j0 + 16 * t + e < c.nl ? ls : a.gb;
+                }
             }
         }
         float mx = -INFINITY;
@@ -397,13 +442,13 @@ constexpr int kBf16Tiles = 2;  // key tiles per step
 
 // Wavefronts per SIMD that the kernel's registers have to leave room for: as many as the loop over pairs alone leaves.
 // (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80.)
-constexpr int bf16_waves(int NKB, bool FULL, int QT, bool OPTS)
+constexpr int bf16_waves(int NKB, bool FULL, int QT, int OPTS)
 {
-    return QT == 2 ? 2 : NKB == 1 ? 6 : NKB == 2 && FULL && !OPTS ? 5 : NKB == 3 && !OPTS ? 4 : 2;
+    return QT == 2 ? 2 : NKB == 1 ? 6 : OPTS > kBiases ? 2 : NKB == 2 && FULL ? 5 : NKB == 3 ? 4 : 2;
 }
 
 // NKB = ceil(D / 32); FULL: D = 32 NKB.  QT query tiles share every key row that is fetched.
-template <int NKB, bool FULL, int QT, bool OPTS, bool OUT_F32>
+template <int NKB, bool FULL, int QT, int OPTS, bool OUT_F32>
 __global__ __launch_bounds__(256, bf16_waves(NKB, FULL, QT, OPTS)) void tile_attn_bf16_kernel(const TileArgs a)
 {
     constexpr int KT = kBf16Tiles;
@@ -487,6 +532,7 @@ __global__ __launch_bounds__(256, bf16_waves(NKB, FULL, QT, OPTS)) void tile_att
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) o[u][kb][0] = o[u][kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     Softmax<false, OPTS> sm[QT];
+    const uint64_t hide = OPTS == kUnion ? hidden_entries(a, cx, gl) : 0;
 
     auto key_tiles = [&](auto n, int t0) __attribute__((always_inline)) {
         constexpr int KT = decltype(n)::value;  // of them in this step
@@ -527,7 +573,7 @@ __global__ __launch_bounds__(256, bf16_waves(NKB, FULL, QT, OPTS)) void tile_att
 #pragma unroll
         for (int u = 0; u < QT; ++u) {
             if (u > 0 && 16 * u >= tk.nq) break;
-            const float alpha = sm[u].step(a, cx, gl, tk.q0 + min(16 * u + l16, tk.nq - 1), s[u], t0, lane);
+            const float alpha = sm[u].step(a, cx, gl, hide, tk.q0 + min(16 * u + l16, tk.nq - 1), s[u], t0, lane);
             if (__any(alpha != 1.f)) {
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb)
@@ -643,7 +689,7 @@ constexpr int krow_bytes(int NC) { return 64 * NC + 16; }
 
 // NC = ceil(D / 16): 16-byte chunks per lane of a Q or K row, 16-channel tiles of O^T; FULL: D = 16 NC.  QT
 // query tiles share every key row that is fetched.
-template <int NC, bool FULL, int QT, bool OPTS>
+template <int NC, bool FULL, int QT, int OPTS>
 __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
 {
     // A row of V, and of O, is NF blocks of 64 channels, then one of 32, then one of 16: lane m has W consecutive
@@ -750,6 +796,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
 #pragma unroll
         for (int j = 0; j < NC; ++j) o[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     Softmax<true, OPTS> sm[QT];
+    const uint64_t hide = OPTS == kUnion ? hidden_entries(a, cx, gl) : 0;
 
     for (int t = 0; t < tiles; ++t) {
         wave_lds_sync();
@@ -783,7 +830,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(const TileArgs a)
         for (int u = 0; u < QT; ++u) {
             if (u > 0 && 16 * u >= tk.nq) break;
             f32x4 s[1] = {s2[u][0] + s2[u][1]};
-            const float alpha = sm[u].step(a, cx, gl, tk.q0 + min(16 * u + l16, tk.nq - 1), s, t, lane);
+            const float alpha = sm[u].step(a, cx, gl, hide, tk.q0 + min(16 * u + l16, tk.nq - 1), s, t, lane);
             if (__any(alpha != 1.f)) {
 #pragma unroll
                 for (int j = 0; j < NC; ++j) o[u][j] *= alpha;
@@ -845,34 +892,42 @@ constexpr bool two_query_tiles(bool f32, int blocks)
 }
 
 template <int NKB, bool FULL, bool OUT_F32>
-const void *bf16_fn(int qt, bool opts)
+const void *bf16_fn(int qt, int opts)
 {
     if constexpr (two_query_tiles(false, NKB))
-        if (qt == 2) return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 2, false, OUT_F32>;
-    return opts ? (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, true, OUT_F32>
-                : (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, false, OUT_F32>;
+        if (qt == 2) return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 2, kPlain, OUT_F32>;
+    switch (opts) {
+    case kPlain: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kPlain, OUT_F32>;
+    case kBiases: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kBiases, OUT_F32>;
+    case kUnion: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kUnion, OUT_F32>;
+    default: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kAll, OUT_F32>;
+    }
 }
 template <int NKB>
-const void *bf16_fn(int D, int qt, bool opts, bool out_f32)
+const void *bf16_fn(int D, int qt, int opts, bool out_f32)
 {
     if (D == 32 * NKB) return out_f32 ? bf16_fn<NKB, true, true>(qt, opts) : bf16_fn<NKB, true, false>(qt, opts);
     return out_f32 ? bf16_fn<NKB, false, true>(qt, opts) : bf16_fn<NKB, false, false>(qt, opts);
 }
 template <int NC, bool FULL>
-const void *f32_fn(int qt, bool opts)
+const void *f32_fn(int qt, int opts)
 {
     if constexpr (two_query_tiles(true, NC))
-        if (qt == 2) return (const void *)&tile_attn_f32_kernel<NC, FULL, 2, false>;
-    return opts ? (const void *)&tile_attn_f32_kernel<NC, FULL, 1, true>
-                : (const void *)&tile_attn_f32_kernel<NC, FULL, 1, false>;
+        if (qt == 2) return (const void *)&tile_attn_f32_kernel<NC, FULL, 2, kPlain>;
+    switch (opts) {
+    case kPlain: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kPlain>;
+    case kBiases: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kBiases>;
+    case kUnion: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kUnion>;
+    default: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kAll>;
+    }
 }
 template <int NC>
-const void *f32_fn(int D, int qt, bool opts)
+const void *f32_fn(int D, int qt, int opts)
 {
     return D == 16 * NC ? f32_fn<NC, true>(qt, opts) : f32_fn<NC, false>(qt, opts);
 }
 
-const void *tile_fn(const dsattn_desc &d, int qt, bool opts)
+const void *tile_fn(const dsattn_desc &d, int qt, int opts)
 {
     const bool out_f32 = d.out_dtype == DSATTN_F32;
     const int D = d.head_dim;
@@ -911,7 +966,7 @@ const void *tile_fn(const dsattn_desc &d, int qt, bool opts)
 //    125,000 and up  1.06, 1.12  1.18, 1.18  1.08, 1.11  1.09, 1.13    1.08, 1.19  1.09, 1.10  1.05, 1.05  1.03, 1.04
 // Clips of three query tiles leave the second wavefront one: 48 frames 0.85 to 1.00, but 40 from 37,000 tiles on 1.01 to
 // 1.04.  Options cost registers too: 157 us with one, 183 with two at 128 with the set union.
-int query_tiles(const dsattn_desc &d, bool opts)
+int query_tiles(const dsattn_desc &d, int opts)
 {
     const bool f32 = d.io_dtype == DSATTN_F32;
     const int nqt = (d.clip_len + 15) / 16, blocks = f32 ? (d.head_dim + 15) / 16 : (d.head_dim + 31) / 32;
@@ -944,12 +999,14 @@ float bias_shifts(const dsattn_plan_t &pl, float &lb, float &gb)
     return sc;
 }
 
-// Whether a plan needs the kernels with options.
-bool has_opts(const dsattn_plan_t &pl)
+// Which options the kernel of a plan is compiled for.
+int opts_of(const dsattn_plan_t &pl)
 {
+    if (pl.window >= 0) return kAll;
+    if (pl.desc.flags & DSATTN_FLAG_DEDUP_GLOBAL) return pl.global_idx.size() <= kUnionGlobals ? kUnion : kAll;
     float lb, gb;
     bias_shifts(pl, lb, gb);
-    return pl.window >= 0 || (pl.desc.flags & DSATTN_FLAG_DEDUP_GLOBAL) || lb != 0.f || gb != 0.f;
+    return lb != 0.f || gb != 0.f ? kBiases : kPlain;
 }
 
 }  // namespace
@@ -969,8 +1026,8 @@ void tile_attn_plan(dsattn_plan_t &pl)
     if (d.head_dim % (f32 ? 4 : 8) != 0) return;
     // a frame's 16-byte pieces are counted in 32 bits
     if ((int64_t)d.spatial * pl.C * (f32 ? 4 : 2) / 16 > 0xffffffffLL) return;
-    const int qt = query_tiles(d, has_opts(pl));
-    pl.tile_fn = tile_fn(d, qt, has_opts(pl));
+    const int qt = query_tiles(d, opts_of(pl));
+    pl.tile_fn = tile_fn(d, qt, opts_of(pl));
     if (!pl.tile_fn) return;
     pl.launch.n_tasks = (int32_t)(units * ((nqt + qt - 1) / qt));
     pl.launch.block_threads = 256;
@@ -997,7 +1054,7 @@ hipError_t launch_tile_attn(const dsattn_plan_t &pl, const void *Q, const void *
     a.D = d.head_dim;
     a.clip_len = d.clip_len;
     a.lk_max = pl.lk_max;
-    const int per_wave = 16 * query_tiles(d, has_opts(pl));
+    const int per_wave = 16 * query_tiles(d, opts_of(pl));
     a.nqg = (d.clip_len + per_wave - 1) / per_wave;
     a.ctx_mode = ctx_mode ? 1 : 0;
     a.G = (int32_t)pl.global_idx.size();

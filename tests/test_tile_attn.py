@@ -77,6 +77,30 @@ def test_tile_kernels_match_oracle_and_generic_kernel(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("clip_len,w,G", [
+    (24, 3, 0), (8, 0, 1), (25, 2, 16),   # 24 to 30, 8 and 27 to 29 local keys; the last bit of a tile
+    (8, 4, 62), (24, 4, 63), (13, 1, 63),  # the most entries that one word of bits holds, and padding behind them
+    (24, 4, 64), (8, 2, 70),               # more: key by key
+])
+@pytest.mark.parametrize("biases", [{}, {"bias_global": 1.5}, {"bias_local": 2.0}])
+def test_set_union_without_a_window(clip_len, w, G, biases, dtype):
+    """Hidden entries are a word of bits a task, from 64 on looked up key by key: the first and last entries, entries
+    on both sides of a key tile's edge and of the local keys' end, repeats, and every entry local."""
+    n_clips, P, h, D = 6, 2, 2, 40
+    F = clip_len * n_clips
+    rng = np.random.default_rng(G + clip_len)
+    lists = [rng.integers(0, F, size=G).tolist(), [(F // 2 + i) % F for i in range(G)]] if G else [[]]
+    for g in lists:
+        print(f"[case] union clip_len={clip_len} w={w} G={G} {biases} {dtype}", flush=True)
+        q, k, v = make(F, P, h * D, dtype)
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, dedup=True, **biases)
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32",
+                                    flags=B.DSATTN_FLAG_DEDUP_GLOBAL, **biases)
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        U.assert_parity(o, ref, "f32_strict", what=f"union G={G}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_peaked_softmax_with_growing_maximum(dtype):
     """Scores that grow along the list (the running maximum moves at every key tile) and scores that
     shrink (it never moves again), 100 in size: the accumulated sums are rescaled, not lost."""
