@@ -215,20 +215,21 @@ __device__ __forceinline__ float exp2_positive(float x)
     return __builtin_amdgcn_exp2f(fmaxf(x, fmaf(x, 0x1p-100f, -126.f)));
 }
 
-// What a kernel is compiled for: no option, biases of the scopes, the set union without a window over up to 63
-// global frames (and biases), any.  Apart, because the conditions alone, kept in scalar registers and spilled from
+// What a kernel is compiled for: no option; biases of the scopes; a window (and biases); the set union without a
+// window over up to 63 global frames (and biases); any.  Apart, because the conditions alone, kept in scalar registers and spilled from
 // there, were a third of the plain loop's instructions (12 clips of 24 frames x 135 positions, 5 x 64, tensors in the
 // caches: 28.3 -> 25.5 us without them).  What an option costs is instructions per score and registers: in the kernel
 // for all of them a bias alone takes the union's and the window's conditions along, and the union looks every global
 // key up in LDS and compares its frame for every query tile and key tile, though the answer is a task's, not a query's.
-// Against that kernel, 16 global frames, us, bias of the global scope; union; both (no option):
-//   91 clips of 24 frames x 246 positions, 4 x 32   188.3 -> 174.9  196.7 -> 174.2  208.9 -> 177.1  (162)
-//   40 clips of 24 frames x 100 positions, 10 x 64  123.8 -> 115.0  129.3 -> 121.5  132.4 -> 124.3  (113)
-//   40 clips of 25 frames x 100 positions, 8 x 160  265.6 -> 260.4  274.9 -> 260.4  277.3 -> 264.4  (258)
-//   90 clips of 8 frames x 135 positions, 6 x 96    135.8 -> 118.1  148.0 -> 133.5  152.7 -> 136.2  (117)
-//   40 clips of 24 frames x 100 positions, 5 x 64, fp32  133.0 -> 132.0  136.2 -> 132.2  137.3 -> 133.9  (126)
-// A window makes what is hidden a query's own, and more than 63 global frames do not fit one word: these stay with it.
-enum { kPlain, kBiases, kUnion, kAll };
+// Against that kernel, 16 global frames, us, bias of the global scope; union; both; window of 8 (no option):
+//   91 clips of 24 frames x 246 positions, 4 x 32   188.3 -> 174.9  196.7 -> 174.2  208.9 -> 177.1  (as before)      (162)
+//   40 clips of 24 frames x 100 positions, 10 x 64  123.8 -> 115.0  129.3 -> 121.5  132.4 -> 124.3  127.7 -> 127.4  (113)
+//   40 clips of 25 frames x 100 positions, 8 x 160  265.6 -> 260.4  274.9 -> 260.4  277.3 -> 264.4  256.1 -> 252.5  (257)
+//   90 clips of 8 frames x 135 positions, 6 x 96    135.8 -> 118.1  148.2 -> 118.0  152.7 -> 118.8  139.0 -> 119.0  (117)
+//   40 clips of 24 frames x 100 positions, 5 x 64, fp32  133.0 -> 132.0  136.2 -> 132.2  137.3 -> 133.9  146 -> 146  (126)
+// With the set union a window makes what is hidden a query's own, and more than 63 global frames do not fit one word:
+// these stay with it.
+enum { kPlain, kBiases, kWindow, kUnion, kAll };
 constexpr int kUnionGlobals = 63;
 
 // The global entries, bit i the i-th, that the set union hides from every query of a task: the ones whose frame is a
@@ -269,6 +270,21 @@ struct Softmax {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) s[t][e] = bits >> e & 1 ? -INFINITY : s[t][e];
             }
+        } else if (OPTS == kWindow) {
+            const Visible vis = visible_to(a, c, aq);
+            const int from = j0 + c.lo - vis.lo;
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                const int first = 16 * (t0 + t);
+                if (first >= c.nl && first + 16 <= c.L) continue;  // global keys only, and no padding
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int j = j0 + 16 * t + e;
+                    bool hidden = (uint32_t)(from + 16 * t + e) >= vis.span;
+                    if (first + 16 > c.nl) hidden = j < c.nl ? hidden : j >= c.L;
+                    s[t][e] = hidden ? -INFINITY : s[t][e];
+                }
+            }
         } else if (OPTS == kAll && (a.window >= 0 || a.dedup)) {
             const Visible vis = visible_to(a, c, aq);
 #pragma unroll
@@ -295,7 +311,7 @@ struct Softmax {
                 for (int e = 0; e < 4; ++e) s[t][e] = 16 * t + e >= left ? -INFINITY : s[t][e];
         }
         if (OPTS && (a.lb != 0.f || a.gb != 0.f)) {
-            if (OPTS != kBiases && a.dedup && a.lb != 0.f) {
+            if (OPTS > kWindow && a.dedup && a.lb != 0.f) {
                 float mg = -INFINITY;
 #pragma unroll
                 for (int t = 0; t < KT; ++t)
@@ -306,7 +322,7 @@ struct Softmax {
                 m += first ? a.lb * a.sc : 0.f;
                 shifted = shifted || first;
             }
-            const float ls = OPTS == kBiases || shifted || !a.dedup ? a.lb : 0.f;
+            const float ls = OPTS <= kWindow || shifted || !a.dedup ? a.lb : 0.f;
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 const int from = 16 * (t0 + t);
@@ -441,10 +457,11 @@ constexpr int vrow_bytes(int NKB) { return 64 * NKB + 16; }
 constexpr int kBf16Tiles = 2;  // key tiles per step
 
 // Wavefronts per SIMD that the kernel's registers have to leave room for: as many as the loop over pairs alone leaves.
-// (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80.)
+// (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80; with the
+// set union at 96: 118 -> 133.)  One less where a window or the set union would spill.
 constexpr int bf16_waves(int NKB, bool FULL, int QT, int OPTS)
 {
-    return QT == 2 ? 2 : NKB == 1 ? 6 : OPTS > kBiases ? 2 : NKB == 2 && FULL ? 5 : NKB == 3 ? 4 : 2;
+    return QT == 2 ? 2 : NKB == 1 ? 6 : OPTS > kBiases ? (NKB == 3 && FULL && OPTS < kAll ? 4 : 2) : NKB == 2 && FULL ? 5 : NKB == 3 ? 4 : 2;
 }
 
 // NKB = ceil(D / 32); FULL: D = 32 NKB.  QT query tiles share every key row that is fetched.
@@ -899,6 +916,7 @@ const void *bf16_fn(int qt, int opts)
     switch (opts) {
     case kPlain: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kPlain, OUT_F32>;
     case kBiases: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kBiases, OUT_F32>;
+    case kWindow: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kWindow, OUT_F32>;
     case kUnion: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kUnion, OUT_F32>;
     default: return (const void *)&tile_attn_bf16_kernel<NKB, FULL, 1, kAll, OUT_F32>;
     }
@@ -917,6 +935,7 @@ const void *f32_fn(int qt, int opts)
     switch (opts) {
     case kPlain: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kPlain>;
     case kBiases: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kBiases>;
+    case kWindow: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kWindow>;
     case kUnion: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kUnion>;
     default: return (const void *)&tile_attn_f32_kernel<NC, FULL, 1, kAll>;
     }
@@ -999,14 +1018,17 @@ float bias_shifts(const dsattn_plan_t &pl, float &lb, float &gb)
     return sc;
 }
 
-// Which options the kernel of a plan is compiled for.
+// Which options the kernel of a plan is compiled for.  (bf16 rows of 32 channels under a window alone are 1 to 3 %
+// faster in the kernel for any: 60 clips of 24 frames x 200 positions, 5 heads, 109 and 112 us; with a bias 181 and 177.)
 int opts_of(const dsattn_plan_t &pl)
 {
-    if (pl.window >= 0) return kAll;
-    if (pl.desc.flags & DSATTN_FLAG_DEDUP_GLOBAL) return pl.global_idx.size() <= kUnionGlobals ? kUnion : kAll;
     float lb, gb;
     bias_shifts(pl, lb, gb);
-    return lb != 0.f || gb != 0.f ? kBiases : kPlain;
+    const bool biases = lb != 0.f || gb != 0.f, windowed = pl.window >= 0;
+    const size_t G = pl.global_idx.size();
+    if ((pl.desc.flags & DSATTN_FLAG_DEDUP_GLOBAL) && G > 0) return windowed || G > kUnionGlobals ? kAll : kUnion;
+    if (windowed) return pl.desc.io_dtype == DSATTN_BF16 && pl.desc.head_dim == 32 && !biases ? kAll : kWindow;
+    return biases ? kBiases : kPlain;
 }
 
 }  // namespace

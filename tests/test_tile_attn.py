@@ -101,6 +101,28 @@ def test_set_union_without_a_window(clip_len, w, G, biases, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("clip_len,w,G,window", [
+    (24, 3, 0, 0), (8, 8, 1, 2), (25, 2, 16, 7),     # nothing but itself; across clips; local and global in one tile
+    (40, 8, 9, 3), (48, 0, 70, 200),                 # whole key tiles out of a query's sight; wider than the clip
+])
+@pytest.mark.parametrize("opts", [{}, {"bias_global": 1.5}, {"bias_local": 2.0}, {"dedup": True}])
+def test_window_with_and_without_the_set_union(clip_len, w, G, window, opts, dtype):
+    n_clips, P, h = 5, 2, 2
+    F = clip_len * n_clips
+    rng = np.random.default_rng(G + clip_len)
+    g = rng.integers(0, F, size=G).tolist()
+    for D in (40, 96):
+        print(f"[case] window clip_len={clip_len} w={w} G={G} r={window} {opts} {dtype} D={D}", flush=True)
+        q, k, v = make(F, P, h * D, dtype)
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, window=window, **opts)
+        biases = {x: y for x, y in opts.items() if x != "dedup"}
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype="f32", window=window,
+                                    flags=B.DSATTN_FLAG_DEDUP_GLOBAL if "dedup" in opts else 0, **biases)
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        U.assert_parity(o, ref, "f32_strict", what=f"window {window}, G={G}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_peaked_softmax_with_growing_maximum(dtype):
     """Scores that grow along the list (the running maximum moves at every key tile) and scores that
     shrink (it never moves again), 100 in size: the accumulated sums are rescaled, not lost."""
