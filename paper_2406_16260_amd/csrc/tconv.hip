@@ -23,8 +23,9 @@
 // range check, not by code.  The workgroups are persistent: at most one per compute unit, the
 // same number on every XCD, each walking its share of the output tiles as one continuous stream
 // of stages (the next tile's first stage is loading while the finished tile is stored).  An XCD
-// walks a contiguous run of tiles (all column tiles of a few neighbouring row tiles): the W
-// slabs, and the X rows shared between taps and column tiles, are then served by that XCD's L2.
+// walks a contiguous run of tiles (a panel of column tiles, of all weight sets', of a few
+// neighbouring row tiles): the W slabs, and the X rows shared between taps and column tiles, are
+// then served by that XCD's L2.
 // Problems that do not fill the chip with such tiles, and fp32 tensors, run on the kernels of
 // tconv_tile.h; conv_pick() says which.
 #include <hip/hip_runtime.h>
@@ -862,11 +863,14 @@ int linear_as_conv(const dsattn_linear_desc *l, dsattn_conv_desc &d, int64_t &M,
 }
 
 // Column tiles, of the groups' side by side, that the persistent kernels number together.  An XCD's 32 tiles in flight
-// are this many wide and 32 / width row tiles high, and what its L2 fetches of X and W is the sum of the two: the
-// width for which that is least, in panels of one size.  (Taps innermost: the rows of X serve all of them.)  Under the
-// chip's power limit what is not fetched is time.  us of three sets with the groups one after the other and so:
-// 600,000 x 320 x 320 547 and 491, 245,760 x 640 x 640 632 and 603, 100,000 x 1,024 x 1,024 621 and 578, 368,640 x
-// 1,280 x 1,280 3,033 and 2,937 (six of twelve column tiles; four 3,033, all twelve 3,030).
+// are this many wide and 32 / width row tiles high, and read as many rows of X and of W as the sum of the two: the
+// width for which that is least, in panels of one size.  (Taps innermost: the rows of X serve all of them.)
+// us of three sets with the groups one after the other and so: 600,000 x 320 x 320 547 and 491, 245,760 x 640 x 640 632
+// and 603, 100,000 x 1,024 x 1,024 621 and 578, 368,640 x 1,280 x 1,280 3,033 and 2,937.  What the L2s miss (FETCH_SIZE,
+// GB) goes with it only while the panel's W stays there: 163,840 x 640 x 640, 2, 3, 6 of six column tiles, 397, 384, 381
+// us, 0.73, 0.61, 0.57; but 100,000 x 1,024 x 1,024, 4, 6, 12 of twelve, 569, 540, 554 us, 0.97, 1.18, 1.95; 368,640 x
+// 1,280 x 1,280 2,961, 2,906, 2,965 us, 4.7, 8.5, 14.1: four wide is slowest with the fewest misses, which the 256 MB cache
+// serves.  Three wide, 2,860 to 2,900 at 1,280 channels, is 0.5 to 1.5 % slower at 1,152, 1,536 and 2,048.
 int conv_panel(int cols, int taps, int bm, int bn)
 {
     int best = 1;
