@@ -230,14 +230,16 @@ bool mfma_plan(dsattn_plan_t &pl)
     // key tiles, whose ring leaves a compute unit less than a full set of wide wavefronts.  us, wide and narrow: 1 clip of
     // 600 positions, 8 x 80, 22.9 and 15.7; 3 clips of 168, 8 x 40, 12.7 and 9.2; 8 clips of 111, 8 x 40, 16.0 and 12.5;
     // three key tiles: 64 frames x 728, 10 x 64, 90 and 65, 2,112 x 696, 8 x 40, 1,054 and 817, 2,432 x 93, 6 x 96, 263
-    // and 219 (head_dim 32, 5,184 x 97, 123 and 131: not there; from head_dim 128 on there is nothing narrower).  Larger
+    // and 219 (head_dim 32, 5,184 x 97, 123 and 131: not there, and of
+    // smaller tensors up to 12 MB only: 128 frames x 80, 4 heads, 8.3 and 6.4, 160 x 43 5.6 and 5.1, but 32 x 599 10.4 and
+    // 10.8, the layer of 576 x 92 42.0 and 43.8; from head_dim 128 on there is nothing narrower).  Larger
     // tensors: 2,304 frames of 160 positions, 20 x 64, 728 and 752, under a window, 640, 8 x 80, 1,489 and 1,574.  Over 143
     // drawn shapes of 16 to 2,560 positions the calls take 0.937 of the time, and the best of all swept choices (heads,
     // wavefronts, chunks) would take 0.965 of that.  Fewer than 16 positions, less than a level has, keep the widest
     // rows.  A materialised context, whose chunks are clips, keeps them too: 9 clips of 52, 8 x 80, with the gather 26.5
     // and 28.3.
     const int64_t bytes = (int64_t)pl.F * d.spatial * pl.C * (out_f32 ? 10 : 8);
-    const bool spread = d.spatial >= 16 && (bytes <= (int64_t)256 << 20 ||
+    const bool spread = d.spatial >= 16 && (bytes <= (int64_t)(d.head_dim == 32 ? 12 : 256) << 20 ||
                                             (NLT == 3 && d.head_dim != 32 && d.head_dim < 128));
     // (a launch has less than 2^32 threads)
     if (!spread || !mfma_geometry(pl, sh, true, geo) || geo.tasks > ((int64_t)1 << 32) / 64 - 8) geo = ctx;
