@@ -326,10 +326,16 @@ struct Softmax {
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 const int from = 16 * (t0 + t);
-                if (OPTS == kAll) {  // (a branch more costs the windowed kernel 1 %)
-                    if (from + 16 <= c.nl && ls == 0.f) continue;
+                // A branch less here is registers less: the others' three ways, or the same test worded as
+                // `from + 16 <= c.nl`, cost the fp32 kernels 2 to 10 and with them a wavefront a SIMD at head_dim 24, 32, 48, 72 and 80.
+                // us, 40 clips of 24 frames, window and union of 16 / union of 70 global frames, with that and so: 246
+                // positions, 4 x 32, 173.4 and 165.1 / 376 and 349; 100, 6 x 48, 147.7 and 141.8 / 311 and 284; 100, 8 x 80, 308 and
+                // 287 / 623 and 557; union of 16 alone (fp32), 100, 6 x 48, 149.3 and 136.7.
+                if (OPTS == kAll || (POSITIVE && OPTS == kUnion)) {
+                    const bool globals = from + 16 > c.nl;
+                    if (!globals && ls == 0.f) continue;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) s[t][e] += from + 16 <= c.nl || j0 + 16 * t + e < c.nl ? ls : a.gb;
+                    for (int e = 0; e < 4; ++e) s[t][e] += !globals || j0 + 16 * t + e < c.nl ? ls : a.gb;
                 } else if (from + 16 <= c.nl) {  // one of lb and gb is zero
                     if (a.lb != 0.f) s[t] += ls;
                 } else if (from >= c.nl) {

@@ -3,6 +3,7 @@ host-only plans and bit-exact context tables against the oracle.  No kernel is l
 import ctypes
 import os
 import re
+import struct
 
 import numpy as np
 import pytest
@@ -500,3 +501,43 @@ def test_layer_entry_point_checks_its_arguments_on_the_host():
     plan = B.dsattn_plan(16, 4, 2, 5, 8, 40, [0, 9], out_dtype=B.DSATTN_F32, device=-1)
     assert lib.dsattn_temporal_layer(*args(plan=plan.handle)) == B.DSATTN_ENODEVICE
     plan.close()
+
+
+def _device_kernels():
+    """Every kernel of the built library with what its code object says of it (registers, scratch memory)."""
+    msgpack = pytest.importorskip("msgpack")
+    blob = open(B.LIB_PATH, "rb").read()
+    kernels, at = {}, 0
+    while (at := blob.find(b"\x7fELF\x02\x01\x01\x40", at)) >= 0:  # an AMDGPU code object
+        sections, = struct.unpack_from("<Q", blob, at + 40)
+        size, count = struct.unpack_from("<HH", blob, at + 58)
+        for i in range(count):
+            _, kind, _, _, off, length = struct.unpack_from("<IIQQQQ", blob, at + sections + i * size)
+            p, end = at + off, at + off + length
+            while kind == 7 and p < end:  # notes
+                name, desc, note = struct.unpack_from("<III", blob, p)
+                p += 12 + (name + 3) // 4 * 4
+                if note == 32:  # metadata
+                    for k in msgpack.unpackb(blob[p:p + desc])["amdhsa.kernels"]:
+                        kernels[k[".name"]] = k
+                p += (desc + 3) // 4 * 4
+        at += 8
+    return kernels
+
+
+def test_no_kernel_uses_scratch_memory_and_option_kernels_keep_their_wavefronts():
+    """512 registers a SIMD, in steps of 8 a wavefront.  The fp32 tile kernels for the set union and for any option:
+    wavefronts by head_dim / 16, whole multiples of 16 and the rest."""
+    kernels = _device_kernels()
+    spills = [n for n, k in kernels.items() if k[".private_segment_fixed_size"]]
+    assert kernels and not spills, spills[:5]
+    least = {1: (8, 8), 2: (6, 6), 3: (5, 4), 4: (4, 4), 5: (4, 4), 6: (3, 3), 7: (3, 3), 8: (2, 2), 9: (2, 2), 10: (2, 2)}
+    seen = 0
+    for name, k in kernels.items():
+        m = re.search(r"tile_attn_f32_kernelILi(\d+)ELb([01])ELi1ELi([34])E", name)
+        if not m:
+            continue
+        seen += 1
+        waves = min(8, 512 // (-(-k[".vgpr_count"] // 8) * 8))
+        assert waves >= least[int(m[1])][m[2] == "0"], (name, k[".vgpr_count"])
+    assert seen == 40
