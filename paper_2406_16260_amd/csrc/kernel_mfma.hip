@@ -55,6 +55,7 @@ struct Geometry {
 struct Shape {
     int n_tiles, wr, R, NLT, NGT, G;
     bool out_f32;
+    int64_t bytes;  // of Q, K, V and O
 };
 
 // spread: narrower rows and smaller workgroups, see mfma_plan().
@@ -174,10 +175,26 @@ bool mfma_geometry(const dsattn_plan_t &pl, const Shape &sh, bool spread, Geomet
     // A short video whose wavefronts all run at once has nothing to pace: two wavefronts per workgroup
     // spread over more compute units and start independently.  Measured, one position's heads per
     // workgroup / two wavefronts: 1 clip, 40 positions, 8 heads of 160 9.1 / 6.6 us; 4 clips, 40 x 8 x 160 10.6 /
-    // 9.7, 160 x 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  From 24 clips on
-    // (35.5 / 36.1), and with four wavefronts and a single clip (8.0 / 8.3), the shared lines of neighbouring
-    // rows count for more.
+    // 9.7, 160 x 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  Four
+    // wavefronts and a single clip stay (8.0 / 8.3).  (Launches that are spread make these choices by their own two rules: here
+    // are left fewer than 16 positions, materialised contexts, and head_dim 32 above 12 MB.)
     if (env_int("DSATTN_WAVES_PER_BLOCK", 0)) {
+    } else if (spread && (int64_t)RG * NC * 4 >= (int64_t)kCus * max_waves_cu * 3 &&
+               (hpw * d.head_dim % 32 != 0 || (n_tiles > 8 && sh.bytes >= (int64_t)128 << 20))) {
+        // From three quarters of the chip's wavefronts on there is little left to spread over, and what a frame's
+        // neighbouring rows share counts: rows of 80 and 160 bytes share 128-byte lines, tensors that leave the cache
+        // are read in order.  Half a compute unit's wavefronts then stay together.  Time with them over time with one or two:
+        //   rows of 80 and 160 bytes (head_dim 40 and 80), by the share of the chip: 0.5 to 0.65 1.04, 0.7 1.01, 0.75 0.96, 0.8
+        //   and up 0.945; by query tiles, 1 to 4 0.96, 33 and more 0.94
+        //   others, tensors of 128 MB and more, from HBM and from the caches: up to 8 tiles 1.00 and 1.01 (head_dim 128 1.02 and 1.04),
+        //   more 0.97 and 0.99; less than 64 MB 1.01 and 1.03, 64 to 128 MB 0.98 and 1.01
+        // us from HBM, two and four: 39 clips of 48 positions, 8 x 80, 32 global frames, 41.2 and 37.1, 93 of 24, 8 x 80, 48.6 and 42.8, 24
+        // of 60, 8 x 128, 40.8 and 39.0, 24 of 40, 8 x 160, 36.5 and 35.0 (35.6 with eight).
+        for (int cand : {4, 2, 1})
+            if (cand <= std::max(1, max_waves_cu / 2) && RG % cand == 0) {
+                wpb = cand;
+                break;
+            }
     } else if (spread) {
         while (wpb > 1 && (int64_t)(RG / wpb) * NC < 512) wpb /= 2;
     } else if ((int64_t)RG * NC <= (int64_t)kCus * max_waves_cu && n_tiles <= 16 && wpb > (n_tiles == 1 ? 4 : 2) &&
@@ -222,7 +239,8 @@ bool mfma_plan(dsattn_plan_t &pl)
     const int NLT = (R + 15) / 16;
     const bool out_f32 = d.out_dtype == DSATTN_F32;
 
-    const Shape sh = {n_tiles, wr, R, NLT, NGT, G, out_f32};
+    const int64_t bytes = (int64_t)pl.F * d.spatial * pl.C * (out_f32 ? 10 : 8);
+    const Shape sh = {n_tiles, wr, R, NLT, NGT, G, out_f32, bytes};
     Geometry geo, ctx;
     if (!mfma_geometry(pl, sh, false, ctx)) return false;
     // More and narrower wavefronts, each with less to do between its loads, in smaller workgroups: where the tensors are
@@ -238,7 +256,6 @@ bool mfma_plan(dsattn_plan_t &pl)
     // wavefronts, chunks) would take 0.965 of that.  Fewer than 16 positions, less than a level has, keep the widest
     // rows.  A materialised context, whose chunks are clips, keeps them too: 9 clips of 52, 8 x 80, with the gather 26.5
     // and 28.3.
-    const int64_t bytes = (int64_t)pl.F * d.spatial * pl.C * (out_f32 ? 10 : 8);
     const bool spread = d.spatial >= 16 && (bytes <= (int64_t)(d.head_dim == 32 ? 12 : 256) << 20 ||
                                             (NLT == 3 && d.head_dim != 32 && d.head_dim < 128));
     // (a launch has less than 2^32 threads)

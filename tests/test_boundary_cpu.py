@@ -293,6 +293,23 @@ def test_planner_head_dims_and_heads_per_wave(D, h, G, hpw):
     assert i["lds_bytes"] <= 160 * 1024
 
 
+@pytest.mark.parametrize("n_clips,P,h,D,w,G,hpw,waves", [
+    (39, 48, 8, 80, 0, 32, 1, 4),    # 1,920 of 2,048 wavefronts, rows of 160 bytes; wide rows had eight to a workgroup
+    (118, 20, 5, 40, 3, 64, 1, 4),   # rows of 80 bytes
+    (12, 32, 8, 80, 2, 16, 1, 4),    # exactly three quarters of them
+    (12, 28, 8, 80, 2, 16, 1, 2),    # 1,344
+    (40, 64, 8, 40, 2, 16, 2, 4),    # two heads of 80 bytes
+    (24, 60, 8, 128, 2, 16, 1, 4),   # whole 64 bytes, 180 MB of tensors
+    (24, 40, 8, 128, 2, 16, 1, 2),   # 120 MB
+    (8, 192, 8, 128, 2, 16, 1, 2),   # 192 MB, but eight query tiles
+])
+def test_streaming_launches_that_fill_the_chip_keep_half_a_compute_unit_together(n_clips, P, h, D, w, G, hpw, waves):
+    plan = B.dsattn_plan(16, n_clips, w, P, h, D, list(range(G)), device=-1)
+    i = B.dsattn_plan_launch_info(plan)
+    plan.close()
+    assert (i["kernel"], i["heads_per_wave"], i["block_threads"]) == (1, hpw, 64 * waves), i
+
+
 def test_header_is_plain_c_and_usable_from_c(tmp_path):
     """include/dsattn.h compiles as C99 with warnings as errors, and a C program linked against
     libdsattn.so drives the host-side entry points."""
