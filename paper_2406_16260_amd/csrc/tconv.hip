@@ -871,8 +871,14 @@ int linear_as_conv(const dsattn_linear_desc *l, dsattn_conv_desc &d, int64_t &M,
 // us, 0.73, 0.61, 0.57; but 100,000 x 1,024 x 1,024, 4, 6, 12 of twelve, 569, 540, 554 us, 0.97, 1.18, 1.95; 368,640 x
 // 1,280 x 1,280 2,961, 2,906, 2,965 us, 4.7, 8.5, 14.1: four wide is slowest with the fewest misses, which the 256 MB cache
 // serves.  Three wide, 2,860 to 2,900 at 1,280 channels, is 0.5 to 1.5 % slower at 1,152, 1,536 and 2,048.
-int conv_panel(int cols, int taps, int bm, int bn)
+// Of three sets a panel across them is a multiple of three wide, and 32 tiles are no whole number of its rows.  That pays
+// where it saves reads of X from HBM.  Time of such a panel over that of one set's, two column tiles a set and more, by
+// bytes of X and Y (525 shapes): less than 64 MB 1.00, to 384 MB 1.03 (0.88 to 1.12), to 448 1.015, to 576 0.98, above 0.95;
+// one column tile a set 0.97 to 1.00 below 384 MB, 0.91 above.  (us: 25,821 x 320 x 1,280 83.4 and 76.7, 300,000 x 320 x
+// 1,280 878 and 943.)  Two sets 0.99 and four 0.97 at all sizes.
+int conv_panel(int groups, int tiles_n, int taps, int bm, int bn, int64_t bytes)
 {
+    const int cols = groups == 3 && tiles_n > 1 && bytes < 448000000 ? tiles_n : groups * tiles_n;
     int best = 1;
     double least = 1e300;
     for (int panels = 1; panels <= std::min(cols, 64); ++panels) {
@@ -932,7 +938,10 @@ hipError_t conv_launch(const dsattn_conv_desc &d, int64_t M, const ConvVariant *
         a.tiles_m = (int32_t)((M + bm - 1) / bm);
         a.tiles = a.tiles_m * a.tiles_n * groups;
         a.per_xcd = (a.tiles + kXcds - 1) / kXcds;
-        a.panel = v->resident ? conv_panel(a.tiles_n * groups, 2 * d.reach + 1, v->bm, v->bn) : 0;
+        const int64_t oes = d.out_dtype == DSATTN_F32 ? 4 : 2;
+        a.panel = v->resident ? conv_panel(groups, a.tiles_n, 2 * d.reach + 1, v->bm, v->bn,
+                                           M * (d.c_in * es + (int64_t)groups * d.c_out * oes))
+                              : 0;
         a.w_bytes = (int32_t)((2 * (int64_t)d.reach + 1) * d.c_out * d.c_in * es);
         void *params[] = {&a};
         // persistent workgroups: one per compute unit at most, the same number on every XCD

@@ -585,7 +585,8 @@ def test_linear_tiles_for_few_tiles_and_few_channels(rows, c_in, c_out, n_out, t
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,c_in,c_out,n_out,tile", [
     (33100, 64, 312, 3, (256, 320, 512)),     # three sets' column tiles in one panel; a stage a tile: loads run two tiles ahead
-    (10113, 72, 1270, 3, (256, 320, 512)),    # twelve column tiles in two panels of six: the second set is cut
+    (10113, 72, 1270, 3, (256, 320, 512)),    # less than 448 MB of X and Y: a panel of four column tiles a set
+    (29600, 72, 1270, 3, (256, 320, 512)),    # fp32 Y of 451 MB: twelve in two panels of six, the second set is cut; bf16 not
     (25100, 64, 250, 4, (256, 256, 512)),
 ])
 def test_linear_panels_of_column_tiles(rows, c_in, c_out, n_out, tile):
