@@ -310,6 +310,35 @@ def test_streaming_launches_that_fill_the_chip_keep_half_a_compute_unit_together
     assert (i["kernel"], i["heads_per_wave"], i["block_threads"]) == (1, hpw, 64 * waves), i
 
 
+@pytest.mark.parametrize("n_clips,P,h,D,w,out,hpw,waves", [
+    (3, 15, 8, 40, 2, B.DSATTN_BF16, 4, 2),      # fewer than 16 positions: the widest rows
+    (3, 16, 8, 40, 2, B.DSATTN_BF16, 1, 1),
+    (16, 16, 8, 40, 2, B.DSATTN_BF16, 2, 2),     # 1,024 query tiles of two heads
+    (15, 17, 8, 40, 2, B.DSATTN_BF16, 1, 4),     # 1,020
+    (16, 48, 4, 32, 2, B.DSATTN_BF16, 2, 2),     # head_dim 32: tensors of exactly 12 MB
+    (16, 49, 4, 32, 2, B.DSATTN_BF16, 4, 1),
+    (16, 38, 4, 32, 2, B.DSATTN_F32, 2, 2),      # fp32 output: 10 bytes an element
+    (16, 39, 4, 32, 2, B.DSATTN_F32, 4, 1),
+    (16, 256, 8, 64, 2, B.DSATTN_BF16, 1, 4),    # exactly 256 MB
+    (16, 257, 8, 64, 2, B.DSATTN_BF16, 2, 4),
+    (16, 204, 8, 64, 2, B.DSATTN_F32, 1, 4),
+    (16, 205, 8, 64, 2, B.DSATTN_F32, 2, 2),
+    (16, 257, 8, 64, 12, B.DSATTN_BF16, 1, 4),   # three local key tiles: above it too,
+    (16, 520, 8, 32, 12, B.DSATTN_BF16, 4, 2),   # but not at head_dim 32
+    (16, 140, 8, 128, 12, B.DSATTN_BF16, 1, 4),  # nor from 128 on
+    (16, 120, 8, 128, 12, B.DSATTN_BF16, 1, 2),
+    (1, 256, 8, 64, 2, B.DSATTN_BF16, 1, 4),     # 640 bytes of a frame and 512 workgroups
+    (1, 255, 8, 64, 2, B.DSATTN_BF16, 1, 2),
+    (1, 128, 8, 128, 2, B.DSATTN_BF16, 1, 2),
+    (1, 127, 8, 128, 2, B.DSATTN_BF16, 1, 1),
+])
+def test_bounds_of_narrow_streaming_launches(n_clips, P, h, D, w, out, hpw, waves):
+    plan = B.dsattn_plan(16, n_clips, w, P, h, D, list(range(16)), out_dtype=out, device=-1)
+    i = B.dsattn_plan_launch_info(plan)
+    plan.close()
+    assert (i["kernel"], i["heads_per_wave"], i["block_threads"]) == (1, hpw, 64 * waves), i
+
+
 def test_header_is_plain_c_and_usable_from_c(tmp_path):
     """include/dsattn.h compiles as C99 with warnings as errors, and a C program linked against
     libdsattn.so drives the host-side entry points."""

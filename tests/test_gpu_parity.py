@@ -148,6 +148,76 @@ def test_forward_ctx_on_matrix_cores(D, h, P, w, G, opts):
     U.assert_parity(o2, ref, "bf16", what="forward_ctx mfma")
 
 
+@pytest.mark.parametrize("D,h,P,clip_len,n_clips,w,G,hpw,waves,opts", [
+    (40, 8, 17, 16, 5, 2, 16, 1, 1, {}),                                    # wide: four heads
+    (40, 8, 19, 16, 30, 2, 16, 2, 2, {}),                                   # two of four
+    (80, 8, 16, 16, 4, 11, 4, 1, 1, {"bias_global": 0.5}),                  # three local key tiles
+    (96, 6, 16, 32, 3, 3, 16, 1, 1, {"window": 6}),                         # clips of two query tiles
+    (64, 10, 18, 16, 6, 2, 9, 1, 2, {"flags": B.DSATTN_FLAG_DEDUP_GLOBAL}),
+    (32, 4, 16, 16, 4, 2, 40, 1, 1, {"bias_local": 1.0}),                   # four global key tiles
+    (160, 8, 16, 16, 18, 2, 16, 1, 2, {}),                                  # as wide, smaller workgroups
+])
+def test_forward_ctx_with_a_launch_of_its_own(D, h, P, clip_len, n_clips, w, G, hpw, waves, opts):
+    """Narrow rows are for the fused path; a materialised context keeps the widest.  Equal to the bit, and both to the
+    oracle."""
+    F = clip_len * n_clips
+    g = np.random.default_rng(78 + G).integers(0, F, size=G).tolist()
+    q, k, v = make(F, P, h * D, 37, "iid", "bf16")
+    for od in ("f32", "bf16"):
+        announce(f"forward_ctx narrow D={D} h={h} P={P} w={w} G={G} {opts} out={od}")
+        kw = dict(io_dtype=B.DSATTN_BF16, out_dtype=U.dt_code(od), **opts)
+        plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, device=0, **kw)
+        i = B.dsattn_plan_launch_info(plan)
+        assert (i["kernel"], i["heads_per_wave"], i["block_threads"]) == (1, hpw, 64 * waves), i
+        # what the wide launch of these heads is: a plan of fewer positions has it
+        few = B.dsattn_plan(clip_len, n_clips, w, 15, h, D, g, device=-1, **kw)
+        wide = B.dsattn_plan_launch_info(few)
+        few.close()
+        assert (wide["heads_per_wave"], wide["block_threads"]) != (hpw, 64 * waves)
+        kc = torch.empty((n_clips, plan.lk_max, P, h * D), dtype=k.dtype, device=DEV)
+        vc = torch.empty_like(kc)
+        B.dsattn_gather_context(plan, k, v, kc, vc)
+        o1 = torch.full((F, P, h * D), float("nan"), dtype=synth.torch_dtype(od), device=DEV)
+        o2 = torch.full_like(o1, float("nan"))
+        B.dsattn_forward(plan, q, k, v, o1)
+        B.dsattn_forward_ctx(plan, q, kc, vc, o2)
+        torch.cuda.synchronize()
+        assert torch.equal(o1, o2)
+        plan.close()
+    ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, window=opts.get("window"), dedup="flags" in opts,
+                           bias_global=opts.get("bias_global", 0.0), bias_local=opts.get("bias_local", 0.0))
+    U.assert_parity(o2, ref, "bf16", what="forward_ctx narrow")
+
+
+def test_randomised_narrow_launches_with_options_against_oracle():
+    """Sixteen positions and more take narrow rows: every head size with windows, biases, the set union and clips of
+    several query tiles, against the oracle."""
+    rng = np.random.default_rng(77)
+    narrow = 0
+    for case in range(28):
+        D, h, widest = [(40, 8, 4), (80, 4, 2), (96, 2, 2), (64, 6, 2), (32, 4, 4), (160, 2, 1), (128, 3, 1)][case % 7]
+        clip_len = int(rng.choice([16, 16, 32, 48]))
+        n_clips, P = int(rng.integers(1, 5)), int(rng.integers(16, 26))
+        w, G = int(rng.integers(0, 13)), int(rng.choice([0, 3, 16, 16, 33]))
+        window = int(rng.integers(0, 13)) if clip_len > 16 or rng.random() < 0.3 else None
+        bl, bg = (float(rng.normal()) if rng.random() < 0.4 else 0.0 for _ in range(2))
+        dedup = bool(G <= 16 and rng.random() < 0.4)
+        F = clip_len * n_clips
+        g = rng.integers(0, F, size=G).tolist()
+        announce(f"narrow random {case}: D={D} h={h} Fc={clip_len} N={n_clips} P={P} w={w} G={G} r={window} {bl:.2f} "
+                 f"{bg:.2f} dedup={dedup}")
+        q, k, v = make(F, P, h * D, 300 + case, "iid", "bf16")
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, window=window, bias_local=bl, bias_global=bg,
+                               dedup=dedup)
+        for od in ("f32", "bf16"):
+            o, i = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=od, window=window, bias_local=bl,
+                                     bias_global=bg, flags=B.DSATTN_FLAG_DEDUP_GLOBAL if dedup else 0)
+            assert i["kernel"] == 1, i
+            U.assert_parity(o, ref, od, what=f"narrow random {case}")
+        narrow += i["heads_per_wave"] < widest
+    assert narrow >= 16, narrow
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_forward_ctx_equals_forward(dtype):
     clip_len, n_clips, w, P, h, D = 8, 4, 3, 11, 2, 16
