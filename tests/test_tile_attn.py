@@ -101,6 +101,35 @@ def test_set_union_without_a_window(clip_len, w, G, biases, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [8, 24, 32, 64, 72, 80, 96, 112, 128, 144, 160])
+def test_set_union_and_biases_at_every_head_size(D, dtype):
+    """The kernels for the set union and for biases alone, on the tensors and on a materialised context, in both output
+    types: lists on both sides of a key tile's edge, repeats, local entries."""
+    clip_len, n_clips, w, P, h, G = 24, 5, 3, 2, 2, 19
+    F = clip_len * n_clips
+    g = np.random.default_rng(D).integers(0, F, size=G).tolist()
+    q, k, v = make(F, P, h * D, dtype)
+    for opts in ({"dedup": True}, {"dedup": True, "bias_local": 1.5}, {"bias_global": 1.5}):
+        print(f"[case] union D={D} {opts} {dtype}", flush=True)
+        ref = U.oracle_forward(q, k, v, clip_len, n_clips, w, h, g, **opts)
+        kw = {x: y for x, y in opts.items() if x != "dedup"}
+        kw["flags"] = B.DSATTN_FLAG_DEDUP_GLOBAL if "dedup" in opts else 0
+        for out in (["f32"] if dtype == "f32" else ["f32", "bf16"]):
+            o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, **kw)
+            assert_tile_kernel(info, clip_len, n_clips, P, h)
+            U.assert_parity(o, ref, "f32_strict" if out == "f32" else "bf16", what=f"{opts}")
+            plan = B.dsattn_plan(clip_len, n_clips, w, P, h, D, g, io_dtype=U.dt_code(dtype), out_dtype=U.dt_code(out),
+                                 **kw)
+            ctx = [torch.empty(n_clips, plan.lk_max, P, h * D, dtype=q.dtype, device=DEV) for _ in range(2)]
+            o2 = torch.full_like(o, float("nan"))
+            B.dsattn_gather_context(plan, k, v, *ctx)
+            B.dsattn_forward_ctx(plan, q, *ctx, o2)
+            torch.cuda.synchronize()
+            plan.close()
+            assert torch.equal(o, o2)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("clip_len,w,G,window", [
     (24, 3, 0, 0), (8, 8, 1, 2), (25, 2, 16, 7),     # nothing but itself; across clips; local and global in one tile
     (40, 8, 9, 3), (48, 0, 70, 200),                 # whole key tiles out of a query's sight; wider than the clip
@@ -298,6 +327,30 @@ def test_tasks_with_infinities_are_done_again_with_every_option(opts, D, h):
     torch.cuda.synchronize()
     plan.close()
     assert torch.equal(o2[:, :, keep], o[:, :, keep])
+
+
+@pytest.mark.parametrize("D,h", [(40, 2), (160, 1), (96, 2), (32, 2)])
+@pytest.mark.parametrize("opts", [{"dedup": True}, {"dedup": True, "bias_local": 2.0}, {"bias_global": 2.0}, {"window": 4}])
+def test_tasks_with_infinities_are_done_again_by_the_kernels_of_one_option(opts, D, h):
+    """The same with 19 global frames: the kernels for the set union, for biases and for a window alone."""
+    clip_len, n_clips, w, P = 24, 4, 5, 2
+    F = clip_len * n_clips
+    g = np.random.default_rng(9).integers(0, F, size=19).tolist()
+    opts = dict(opts)
+    flags = B.DSATTN_FLAG_DEDUP_GLOBAL if opts.pop("dedup", False) else 0
+    q, k, v = make(F, P, h * D, "bf16")
+    v[0::2, :, D - 1], v[1::2, :, D - 1] = float("inf"), float("-inf")
+    keep = [c for c in range(h * D) if c != D - 1]
+    for out in ("f32", "bf16"):
+        print(f"[case] infinities D={D} {opts} flags={flags} out={out}", flush=True)
+        o, info = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out, flags=flags, **opts)
+        assert_tile_kernel(info, clip_len, n_clips, P, h)
+        og, _ = U.library_forward(q, k, v, clip_len, n_clips, w, h, g, out_dtype=out,
+                                  flags=flags | B.DSATTN_FLAG_FORCE_GENERIC, **opts)
+        assert o[:, :, D - 1].isnan().all() and og[:, :, D - 1].isnan().all()
+        a, b = o[:, :, keep].double(), og[:, :, keep].double()
+        bar = 2e-5 + (0 if out == "f32" else 2 * U.bf16_half_ulp(b.cpu().numpy()).max())
+        assert float((a - b).abs().max()) <= bar
 
 
 BRANCHES = [
