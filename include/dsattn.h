@@ -157,9 +157,10 @@ int dsattn_forward(const dsattn_plan_t *plan, const void *Q, const void *K, cons
 
 /*
  * Same attention, consuming the materialised context of dsattn_gather_context:
- * clip i attends over Kctx[i][0 .. ctx_len[i]).  Runs the kernel the plan chose for
- * dsattn_forward (the matrix-core kernel takes one clip per work item here, reading the clip's
- * slab of Kctx / Vctx); the result is identical to dsattn_forward's.
+ * clip i attends over Kctx[i][0 .. ctx_len[i]).  Runs the family of kernels the plan chose for
+ * dsattn_forward; the matrix-core streaming kernel takes one clip per work item here, reading the
+ * clip's slab of Kctx / Vctx, and launches with heads per wavefront, workgroup and LDS sizes of its
+ * own (dsattn_launch_info reports dsattn_forward's).  The result is identical to dsattn_forward's.
  */
 int dsattn_forward_ctx(const dsattn_plan_t *plan, const void *Q, const void *Kctx, const void *Vctx,
                        void *O, void *stream);

@@ -172,12 +172,13 @@ bool mfma_geometry(const dsattn_plan_t &pl, const Shape &sh, bool spread, Geomet
     m = std::max(1, std::min(n_tiles, env_int("DSATTN_CLIPS_PER_TASK", m)));
     const int NC = (n_tiles + m - 1) / m;
     if ((int64_t)RG * NC > 0x7fffffffLL) return false;
-    // A short video whose wavefronts all run at once has nothing to pace: two wavefronts per workgroup
-    // spread over more compute units and start independently.  Measured, one position's heads per
-    // workgroup / two wavefronts: 1 clip, 40 positions, 8 heads of 160 9.1 / 6.6 us; 4 clips, 40 x 8 x 160 10.6 /
-    // 9.7, 160 x 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  Four
-    // wavefronts and a single clip stay (8.0 / 8.3).  (Launches that are spread make these choices by their own two rules: here
-    // are left fewer than 16 positions, materialised contexts, and head_dim 32 above 12 MB.)
+    // A short video whose wavefronts all run at once has nothing to pace: two wavefronts per workgroup spread
+    // over more compute units and start independently.  Measured, one position's heads per workgroup / two
+    // wavefronts: 1 clip, 40 positions, 8 heads of 160 9.1 / 6.6 us; 4 clips, 40 x 8 x 160 10.6 / 9.7, 160 x
+    // 8 x 160 28.7 / 24.4, 640 x 8 x 40 31.9 / 29.8; 16 clips, 40 x 8 x 160 24.9 / 23.7.  From 24 clips on
+    // (35.5 / 36.1), and with four wavefronts and a single clip (8.0 / 8.3), the shared lines of neighbouring
+    // rows count for more.  (Launches that are spread decide by the two rules before it; this one is left to
+    // fewer than 16 positions, materialised contexts, and head_dim 32 above 12 MB.)
     if (env_int("DSATTN_WAVES_PER_BLOCK", 0)) {
     } else if (spread && (int64_t)RG * NC * 4 >= (int64_t)kCus * max_waves_cu * 3 &&
                (hpw * d.head_dim % 32 != 0 || (n_tiles > 8 && sh.bytes >= (int64_t)128 << 20))) {
@@ -243,18 +244,22 @@ bool mfma_plan(dsattn_plan_t &pl)
     const Shape sh = {n_tiles, wr, R, NLT, NGT, G, out_f32, bytes};
     Geometry geo, ctx;
     if (!mfma_geometry(pl, sh, false, ctx)) return false;
-    // More and narrower wavefronts, each with less to do between its loads, in smaller workgroups: where the tensors are
-    // no larger than the 256 MB cache, so that how the rows lie in HBM does not decide, and with three local
-    // key tiles, whose ring leaves a compute unit less than a full set of wide wavefronts.  us, wide and narrow: 1 clip of
-    // 600 positions, 8 x 80, 22.9 and 15.7; 3 clips of 168, 8 x 40, 12.7 and 9.2; 8 clips of 111, 8 x 40, 16.0 and 12.5;
-    // three key tiles: 64 frames x 728, 10 x 64, 90 and 65, 2,112 x 696, 8 x 40, 1,054 and 817, 2,432 x 93, 6 x 96, 263
-    // and 219 (head_dim 32, 5,184 x 97, 123 and 131: not there, and of
-    // smaller tensors up to 12 MB only: 128 frames x 80, 4 heads, 8.3 and 6.4, 160 x 43 5.6 and 5.1, but 32 x 599 10.4 and
-    // 10.8, the layer of 576 x 92 42.0 and 43.8; from head_dim 128 on there is nothing narrower).  Larger
-    // tensors: 2,304 frames of 160 positions, 20 x 64, 728 and 752, under a window, 640, 8 x 80, 1,489 and 1,574.  Over 143
-    // drawn shapes of 16 to 2,560 positions the calls take 0.937 of the time, and the best of all swept choices (heads,
-    // wavefronts, chunks) would take 0.965 of that.  Fewer than 16 positions, less than a level has, keep the widest
-    // rows.  A materialised context, whose chunks are clips, keeps them too: 9 clips of 52, 8 x 80, with the gather 26.5
+    // More and narrower wavefronts, each with less to do between its loads, in smaller workgroups: where the tensors
+    // are no larger than the 256 MB cache, so that how the rows lie in HBM does not decide, and with three local key
+    // tiles, whose ring leaves a compute unit less than a full set of wide wavefronts.  us, wide and narrow: 1 clip of
+    // 600 positions, 8 x 80, 22.9 and 15.7; 3 clips of 168, 8 x 40, 12.7 and 9.2; 8 clips of 111, 8 x 40, 16.0 and
+    // 12.5; three key tiles: 64 frames x 728, 10 x 64, 90 and 65, 2,112 x 696, 8 x 40, 1,054 and 817, 2,432 x 93, 6 x
+    // 96, 263 and 219 (from head_dim 128 on there is nothing narrower).  Larger tensors: 2,304 frames of 160 positions,
+    // 20 x 64, 728 and 752, under a window, 640, 8 x 80, 1,489 and 1,574.  Time of the launches below over that of the
+    // wide ones, two and three key tiles, from HBM and from the caches: 800 drawn shapes up to 256 MB 0.95 and 0.945
+    // (1.17 at most), 870 with three key tiles above 0.93 (0.55 to 1.18).
+    // Two lines are drawn short of where narrow rows end to be faster, and not moved yet.  Fewer than 16 positions keep
+    // the widest rows: 566 drawn shapes of 1 to 15 positions would take 0.90 of the time (0.52 to 1.10; 3 clips of 15,
+    // 8 x 40, 10.2 and 5.5 us, of 16 10.2 and 5.4; 40 clips of 15, 8 x 80, 15.8 and 13.2, 144 31.4 and 34.3).  Head_dim
+    // 32 has them up to 12 MB only: above, 0.93 to 64 MB and 0.96 to 256 (0.74 to 1.12; 128 frames x 80, 4 heads, 8.3
+    // and 6.5, 128 x 160 8.7 and 8.4, 32 x 599 8.9 and 9.4, 1,152 x 160 34.4 and 34.0), with three key tiles above 256
+    // MB 0.925 (0.68 to 1.09; 5,184 x 97 123 and 131).
+    // A materialised context, whose chunks are clips, keeps the widest rows: 9 clips of 52, 8 x 80, with the gather 26.5
     // and 28.3.
     const bool spread = d.spatial >= 16 && (bytes <= (int64_t)(d.head_dim == 32 ? 12 : 256) << 20 ||
                                             (NLT == 3 && d.head_dim != 32 && d.head_dim < 128));

@@ -864,18 +864,24 @@ int linear_as_conv(const dsattn_linear_desc *l, dsattn_conv_desc &d, int64_t &M,
 
 // Column tiles, of the groups' side by side, that the persistent kernels number together.  An XCD's 32 tiles in flight
 // are this many wide and 32 / width row tiles high, and read as many rows of X and of W as the sum of the two: the
-// width for which that is least, in panels of one size.  (Taps innermost: the rows of X serve all of them.)
-// us of three sets with the groups one after the other and so: 600,000 x 320 x 320 547 and 491, 245,760 x 640 x 640 632
-// and 603, 100,000 x 1,024 x 1,024 621 and 578, 368,640 x 1,280 x 1,280 3,033 and 2,937.  What the L2s miss (FETCH_SIZE,
-// GB) goes with it only while the panel's W stays there: 163,840 x 640 x 640, 2, 3, 6 of six column tiles, 397, 384, 381
+// width for which that is least, in panels of one size.  (Taps innermost: the rows of X serve all of them.) us of three
+// sets with the groups one after the other and so: 600,000 x 320 x 320 547 and 491, 245,760 x 640 x 640 632 and 603,
+// 100,000 x 1,024 x 1,024 621 and 578, 368,640 x 1,280 x 1,280 3,033 and 2,937.  What the L2s miss (FETCH_SIZE, GB)
+// goes with it only while the panel's W stays there: 163,840 x 640 x 640, 2, 3, 6 of six column tiles, 397, 384, 381
 // us, 0.73, 0.61, 0.57; but 100,000 x 1,024 x 1,024, 4, 6, 12 of twelve, 569, 540, 554 us, 0.97, 1.18, 1.95; 368,640 x
-// 1,280 x 1,280 2,961, 2,906, 2,965 us, 4.7, 8.5, 14.1: four wide is slowest with the fewest misses, which the 256 MB cache
-// serves.  Three wide, 2,860 to 2,900 at 1,280 channels, is 0.5 to 1.5 % slower at 1,152, 1,536 and 2,048.
-// Of three sets a panel across them is a multiple of three wide, and 32 tiles are no whole number of its rows.  That pays
-// where it saves reads of X from HBM.  Time of such a panel over that of one set's, two column tiles a set and more, by
-// bytes of X and Y (525 shapes): less than 64 MB 1.00, to 384 MB 1.03 (0.88 to 1.12), to 448 1.015, to 576 0.98, above 0.95;
-// one column tile a set 0.97 to 1.00 below 384 MB, 0.91 above.  (us: 25,821 x 320 x 1,280 83.4 and 76.7, 300,000 x 320 x
-// 1,280 878 and 943.)  Two sets 0.99 and four 0.97 at all sizes.
+// 1,280 x 1,280 2,961, 2,906, 2,965 us, 4.7, 8.5, 14.1: four wide is slowest with the fewest misses, which the 256 MB
+// cache serves.  So the rows in flight order the widths only roughly.  Three wide, 2,860 to 2,900 at 1,280 channels, is
+// 0.5 to 1.5 % slower at 1,152, 1,536 and 2,048.  Convolutions, by width: 153,600 rows, five taps, 1,280 channels, 1,
+// 2, 4, 1,737, 1,734, 1,734 us, 1,024 1,168, 1,158, 1,172, 102,400 rows of 960 to 1,280 887, 890, 891; three taps,
+// 153,600 rows of 1,280 to 1,920, 1, 2, 3, 6, 1,652, 1,644, 1,612, 1,618, 1,920 to 1,920 2,451, 2,422, 2,393, 2,389;
+// 368,640 rows of 1,280, 1, 2, 4, 2,567, 2,535, 2,558: 0.2 to 2.6 % between the best and the worst, the width taken
+// within 1 % of the best.
+// Of three sets a panel across them is a multiple of three wide, and 32 tiles are no whole number of its rows.  That
+// pays where it saves reads of X from HBM.  Time of such a panel over that of
+// one set's, two column tiles a set and more, by bytes of X and Y (525 shapes): less than 64 MB 1.00, to 384 MB 1.03
+// (0.88 to 1.12), to 448 1.015, to 576 0.98, above 0.95; one column tile a set 0.97 to 1.00 below 384 MB, 0.91 above.
+// (us: 25,821 x 320 x 1,280 83.4 and 76.7, 300,000 x 320 x 1,280 878 and 943.)  Two sets 0.99 and four 0.97 at all
+// sizes.
 int conv_panel(int groups, int tiles_n, int taps, int bm, int bn, int64_t bytes)
 {
     const int cols = groups == 3 && tiles_n > 1 && bytes < 448000000 ? tiles_n : groups * tiles_n;

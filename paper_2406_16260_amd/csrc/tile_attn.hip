@@ -227,8 +227,12 @@ __device__ __forceinline__ float exp2_positive(float x)
 //   40 clips of 25 frames x 100 positions, 8 x 160  265.6 -> 260.4  274.9 -> 260.4  277.3 -> 264.4  256.1 -> 252.5  (257)
 //   90 clips of 8 frames x 135 positions, 6 x 96    135.8 -> 118.1  148.2 -> 118.0  152.7 -> 118.8  139.0 -> 119.0  (117)
 //   40 clips of 24 frames x 100 positions, 5 x 64, fp32  133.0 -> 132.0  136.2 -> 132.2  137.3 -> 133.9  146 -> 146  (126)
+// fp32 under a window of 8, 40 clips of 24 frames, the kernel for any option and its own: head_dim 16 215.5 and 214.3,
+// 32 157.4 and 156.4, 48 137.0 and 136.0, 80 281.9 and 281.6, 96 207.3 and 206.6, 128 297 and 260, 144 235.4 and 228.8,
+// 160 322.7 and 313.2; 10 clips of 96 frames, 32 132.1 and 127.7, 64 129.9 and 128.5, 80 251.8 and 250.0, 96 183.5 and
+// 179.6, 128 271 and 228.
 // With the set union a window makes what is hidden a query's own, and more than 63 global frames do not fit one word:
-// these stay with it.
+// these stay with the kernel for any option.
 enum { kPlain, kBiases, kWindow, kUnion, kAll };
 constexpr int kUnionGlobals = 63;
 
@@ -463,8 +467,10 @@ constexpr int vrow_bytes(int NKB) { return 64 * NKB + 16; }
 constexpr int kBf16Tiles = 2;  // key tiles per step
 
 // Wavefronts per SIMD that the kernel's registers have to leave room for: as many as the loop over pairs alone leaves.
-// (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80; with the
-// set union at 96: 118 -> 133.)  One less where a window or the set union would spill.
+// (With one less, clips of 8 frames, two key tiles: 42.4 -> 45.7 us at head_dim 64, 52.8 -> 59.5 at 80; with the set
+// union at 96: 118 -> 133.)  Two under a window or the set union elsewhere, where more would spill with bf16 output
+// (under a window with fp32 output five at 64 and four at 72 to 88 fit, and are not asked for): the compiler then
+// reaches one wavefront less than the plain kernel.
 constexpr int bf16_waves(int NKB, bool FULL, int QT, int OPTS)
 {
     return QT == 2 ? 2 : NKB == 1 ? 6 : OPTS > kBiases ? (NKB == 3 && FULL && OPTS < kAll ? 4 : 2) : NKB == 2 && FULL ? 5 : NKB == 3 ? 4 : 2;
@@ -1024,8 +1030,11 @@ float bias_shifts(const dsattn_plan_t &pl, float &lb, float &gb)
     return sc;
 }
 
-// Which options the kernel of a plan is compiled for.  (bf16 rows of 32 channels under a window alone are 1 to 3 %
-// faster in the kernel for any: 60 clips of 24 frames x 200 positions, 5 heads, 109 and 112 us; with a bias 181 and 177.)
+// Which options the kernel of a plan is compiled for.  (bf16 rows of 32 channels under a window alone take the kernel
+// for any: window of 8, 60 clips of 24 frames x 200 positions, 4, 5, 8 heads, 93.0, 116.9, 180.3 us and 94.8, 119.2,
+// 188.4 in the window's; shorter clips and windows within 1.5 % either way; with a bias 196.6 and 191.8.  Rows of 8 to
+// 24 channels: 172.9 and 172.0, 178.4 and 177.5, 186.5 and 186.9, with a window of 4 168.5 and 161.7, 172.5 and 166.9,
+// 178.9 and 176.6.)
 int opts_of(const dsattn_plan_t &pl)
 {
     float lb, gb;
