@@ -415,6 +415,31 @@ def test_mfma_small_launches_take_narrow_rows(D, h, P, n_clips, w, G, hpw, wides
     assert torch.equal(o, o2)
 
 
+@pytest.mark.parametrize("D,h,P,n_clips,w,G,hpw", [
+    (80, 8, 32, 12, 2, 16, 1),     # exactly three quarters of the chip's wavefronts, rows of 160 bytes
+    (40, 5, 20, 16, 3, 16, 1),     # 80 bytes
+    (40, 8, 44, 20, 11, 16, 2),    # two heads of 80, three local key tiles
+    (128, 8, 60, 24, 2, 16, 1),    # 180 MB of tensors
+])
+def test_mfma_narrow_launches_that_fill_the_chip(D, h, P, n_clips, w, G, hpw, monkeypatch):
+    """Four wavefronts a workgroup are the same arithmetic as one: equal to the bit, and to the oracle at three
+    positions."""
+    F = 16 * n_clips
+    g = synth.stride_global_idx(F, G)
+    q, k, v = make(F, P, h * D, 43, "iid", "bf16")
+    positions = [0, P // 2, P - 1]
+    ref = U.oracle_forward(q, k, v, 16, n_clips, w, h, g, positions=positions)
+    for od in ("f32", "bf16"):
+        announce(f"narrow and full D={D} h={h} P={P} N={n_clips} w={w} out={od}")
+        o, info = U.library_forward(q, k, v, 16, n_clips, w, h, g, out_dtype=od)
+        assert (info["kernel"], info["heads_per_wave"], info["block_threads"]) == (1, hpw, 256), info
+        U.assert_parity(o, ref, od, positions=positions, what=f"narrow and full D={D}")
+    monkeypatch.setenv("DSATTN_WAVES_PER_BLOCK", "1")
+    o1, info = U.library_forward(q, k, v, 16, n_clips, w, h, g)
+    assert info["block_threads"] == 64
+    assert torch.equal(o, o1)
+
+
 def test_mfma_odd_row_group_count():
     # 3 positions x 2 heads = 6 row groups: workgroups of 2 wavefronts, not 8
     info = run_mfma_case(3, 2, 3, 2, 160, [0, 9], what="odd rows")
